@@ -97,6 +97,27 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
     return best;
 }
 
+// The fp32 kernel: a wave multiplies one 64 x 64 tile on the MFMA pipe of its SIMD (0.15e12 FLOP/s; alone there it keeps
+// the pipe about 87 % busy, two waves about 95 %), `waves` of them make a workgroup, up to eight waves share a compute unit.
+// A group of `pu` units therefore takes as long as the busiest pipe: ceil(workgroups / 256) workgroups of pu units on four
+// pipes, at least one wave's own work.  Exchange of partial sums as above.
+static double cheapest_split_f32(int64_t tiles, int64_t units, double rows_per_unit, int waves, double s_bytes, int max_split, int64_t* nsplit,
+                                 int64_t* per)
+{
+    double best = 0.0;
+    const double wave_unit = 2.0 * rows_per_unit * 64.0 * 64.0 / 0.15e12;
+    const int64_t lim = units < max_split ? units : max_split;
+    for (int64_t ns = 1; ns <= lim; ++ns) {
+        const int64_t pu = (units + ns - 1) / ns;
+        const int64_t ns_eff = (units + pu - 1) / pu;
+        const double per_pipe = (double)((tiles * ns_eff + 255) / 256) * waves / 4.0;
+        double cost = (double)pu * wave_unit * (per_pipe > 1.0 ? per_pipe * 1.05 : 1.15);
+        if (ns_eff > 1 && s_bytes > 0.0) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 2.5e-6;
+        if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
+    }
+    return best;
+}
+
 // Sustained rate of one compute unit on the bf16 blocks, FLOP/s (measured on Gaussian operands, 1B-scale layers):
 // the larger the block, the fewer bytes go from L2 into LDS and from LDS into registers per FLOP.
 // chip-wide rates of the two routes to the per-example norms, FLOP/s (measured)
@@ -113,7 +134,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     StatPlan p{};
     const bool per_example = (mode == MODE_SQUARE || mode == MODE_SIGN || mode == MODE_NORMS || mode == MODE_WEIGHTED || mode == MODE_POWER);
     p.kernel = (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) ? 1 : 0;
-    if (dt == PEX_F32 && f32_mfma_supports(B, T, din, dout, mode)) p.kernel = 2;
+    if (dt == PEX_F32 && f32_mfma_supports(B, T, din, dout)) p.kernel = 2;
 
     // The unit the batch axis is split in: whole examples when phi is applied per example (the sum over
     // the sequence must be complete before phi), slabs of 64 rows of the flattened [B*T] axis otherwise.
@@ -123,8 +144,8 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
         bf16_tile_shape(mode, B, &bm, &bn);
         target = 256;    // one workgroup per compute unit
     } else if (p.kernel == 2) {
-        f32_tile_shape(&bm, &bn);
-        target = 768;    // three workgroups of four waves per compute unit, so that loads and MFMAs overlap
+        f32_tile_shape(din, dout, &bm, &bn);
+        target = 0;      // by cost model
     } else {
         target = 1024;   // four small workgroups per compute unit
     }
@@ -135,7 +156,14 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     int64_t nsplit = 1, per = units;
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
     bool sign_bytes = false, mem_fold = false;
-    if (p.kernel != 1) {
+    if (p.kernel == 2) {
+        // partial sums of at most PEX_NOALLOC_SCRATCH_BYTES, so that every plan fits the library's own scratch (512 workgroups
+        // need more only beyond 2048 x 2048, where two groups are enough)
+        const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
+        cheapest_split_f32(tiles, units, per_example ? (double)T : (double)slab, (bm / 64) * (bn / 64),
+                           mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0,
+                           mode == MODE_NORMS || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit), &nsplit, &per);
+    } else if (p.kernel != 1) {
         nsplit = (target + tiles - 1) / tiles;
         if (nsplit > max_split) nsplit = max_split;
         if (nsplit > units) nsplit = units;
@@ -240,7 +268,8 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
                  ((nsplit > 1 && dout > wide_cols) ? (size_t)nsplit * (size_t)din * (size_t)(dout - wide_cols) * sizeof(float) : 0);
     if (p.sign_bytes) p.ws_bytes = (size_t)nsplit * sign_byte_partial_bytes(din, dout);
     if (mode == MODE_NORMS) {   // no S at all: one partial of ||M_b||^2 per tile (and wave) and example
-        p.ws_bytes = (size_t)(p.kernel == 1 ? bf16_norm_partials(din, dout) : generic_norm_partials(din, dout)) * (size_t)B * sizeof(float);
+        const int64_t nparts = p.kernel == 1 ? bf16_norm_partials(din, dout) : p.kernel == 2 ? f32_norm_partials(din, dout) : generic_norm_partials(din, dout);
+        p.ws_bytes = (size_t)nparts * (size_t)B * sizeof(float);
         // Through the Gram matrices instead: 2 T^2 (din + dout) FLOP per example (a little over half of it with the
         // symmetry, in 128 x 128 blocks) against 2 T din dout, on a kernel of lower rate but with one workgroup per block
         // and example -- no batch split, however few tiles the layer has.
@@ -291,9 +320,11 @@ static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64
     const int64_t lim = (int64_t)1 << 31;
     if (din >= lim || dout >= lim || B >= lim || T >= lim || B * T >= lim) return PEX_ERR_SHAPE;
     if (((uintptr_t)X | (uintptr_t)G | (uintptr_t)S) & 15u) return PEX_ERR_ALIGN;
-    // The fp32 and the SIMT kernels put the tiles of din (128 and 64 rows) in the second grid dimension.
-    const StatPlan plan = plan_stat(B, T, din, dout, dt, MODE_IDENTITY);
-    if (plan.kernel != 1 && din > 65535 * (int64_t)(plan.kernel == 2 ? 128 : 64)) return PEX_ERR_SHAPE;
+    // Largest din of the layers that are not whole 16-byte chunks of a row or too small for the MFMA kernels (the SIMT kernel
+    // puts the tiles of din, 64 rows, in the second grid dimension), and of the other fp32 layers.
+    const int64_t chunk = dt == PEX_BF16 ? 8 : 4;
+    const bool chunked = din % chunk == 0 && dout % chunk == 0 && din >= 32 && dout >= 32 && B * T >= 16;
+    if (!(dt == PEX_BF16 && bf16_supports(B, T, din, dout)) && din > 65535 * (int64_t)(dt == PEX_F32 && chunked ? 128 : 64)) return PEX_ERR_SHAPE;
     return PEX_OK;
 }
 
@@ -318,7 +349,7 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
         if (e == hipSuccess) e = launch_square_bf16(G, g2, B * T * dout, stream);
         if (e == hipSuccess) e = launch_stat_bf16(x2, g2, B, T, din, dout, MODE_IDENTITY, plan, S, partials, stream);
     } else if (plan.kernel == 2) {
-        e = launch_stat_f32(X, G, B, T, din, dout, mode, plan, out, stream, weight, alpha);
+        e = launch_stat_f32(X, G, B, T, din, dout, mode, plan, out, stream, weight, nullptr, alpha);
     } else if (mode == MODE_POWER) {
         e = plan.kernel == 1 ? launch_power_bf16(X, G, alpha, B, T, din, dout, plan, S, partials, stream)
                              : launch_stat_generic(X, G, B, T, din, dout, dt, mode, plan, out, stream, nullptr, nullptr, alpha);
@@ -345,6 +376,24 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
         if (e != hipSuccess) return PEX_ERR_HIP;
     }
     return PEX_OK;
+}
+
+// What pex_stat_noalloc charges a call against its scratch.  bf16 layers of whole 16-byte chunks: what their plan needs.
+// The others: the partial sums of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every
+// compute unit -- a figure of the shape alone, so that which calls are too large does not move with their plans.
+static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
+{
+    if (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) return plan_stat(B, T, din, dout, dt, mode).ws_bytes;
+    const bool chunked = dt == PEX_F32 && din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
+    const int64_t edge = chunked ? 128 : 64, target = chunked ? 768 : 1024;
+    const int64_t tiles = ((din + edge - 1) / edge) * ((dout + edge - 1) / edge);
+    const int64_t units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
+    int64_t ns = (target + tiles - 1) / tiles;
+    if (ns > option(PEX_OPT_MAX_SPLIT)) ns = option(PEX_OPT_MAX_SPLIT);
+    if (ns > units) ns = units;
+    const int64_t per = (units + ns - 1) / ns;
+    ns = (units + per - 1) / per;
+    return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
 }
 
 // How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (bf16
@@ -443,8 +492,10 @@ pex_status pex_stat_noalloc(const void* X, const void* G, int64_t B, int64_t T, 
     const pex_status st = check_stat_args(X, G, B, T, din, dout, dt, S);
     if (st != PEX_OK) return st;
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return PEX_ERR_PHI;
+    const size_t limit = (size_t)PEX_NOALLOC_SCRATCH_BYTES;
+    if (scratch_charge(B, T, din, dout, dt, (Mode)phi) > limit) return PEX_ERR_TOO_LARGE;
     const size_t need = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
-    if (need > (size_t)PEX_NOALLOC_SCRATCH_BYTES) return PEX_ERR_TOO_LARGE;
+    if (need > limit) return PEX_ERR_TOO_LARGE;
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return PEX_ERR_HIP;
     // Every partial sum the reduction reads is written by the contraction of the same call, so nothing in the
@@ -565,6 +616,9 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
     } else if (plan.kernel == 1) {
         nparts = bf16_norm_partials(din, dout);
         e = launch_norms_bf16(X, G, B, T, din, dout, plan, partial, hs);
+    } else if (plan.kernel == 2) {
+        nparts = f32_norm_partials(din, dout);
+        e = launch_stat_f32(X, G, B, T, din, dout, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
     } else {
         nparts = generic_norm_partials(din, dout);
         e = launch_stat_generic(X, G, B, T, din, dout, dt, MODE_NORMS, plan, nullptr, hs, nullptr, partial);

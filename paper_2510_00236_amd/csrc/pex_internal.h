@@ -82,10 +82,12 @@ bool bf16_triple_supported(const StatPlan& plan);
 hipError_t launch_stat_bf16_triple(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
                                    const StatPlan& plan, float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
 bool bf16_supports(int64_t B, int64_t T, int64_t din, int64_t dout);
-bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode);
-void f32_tile_shape(int* bm, int* bn);
+bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout);
+void f32_tile_shape(int64_t din, int64_t dout, int* bm, int* bn);
+int64_t f32_norm_partials(int64_t din, int64_t dout);
 hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode,
-                           const StatPlan& plan, float* out, hipStream_t stream, const float* weight, float alpha);
+                           const StatPlan& plan, float* out, hipStream_t stream, const float* weight = nullptr,
+                           float* norm_partial = nullptr, float alpha = 0.f);
 // out[i] = bf16(in[i]^2) (square in fp32, round to nearest even) for n bf16 values, n a multiple of 8
 hipError_t launch_square_bf16(const void* in, void* out, int64_t n, hipStream_t stream);
 void bf16_tile_shape(Mode mode, int64_t B, int* bm, int* bn);

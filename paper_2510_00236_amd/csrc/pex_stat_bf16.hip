@@ -67,6 +67,7 @@
 
 #include "pex_internal.h"
 #include "pex_lds_dma.h"
+#include "pex_tile_map.h"
 
 namespace pex {
 namespace {
@@ -166,28 +167,6 @@ __device__ __forceinline__ void fold_tile(float4_t& acc, float4_t& acc_id, float
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[r] = 0.f;
-}
-
-// Workgroup id -> (split, tile_m, tile_n): undo the round-robin assignment of consecutive ids to the 8 XCDs,
-// then walk tiles in groups of GROUP_M tile rows so the workgroups resident on one XCD form a compact patch
-// that shares X and G panels in that XCD's L2.
-__device__ __forceinline__ void map_workgroup(int tiles_m, int tiles_n, int& split, int& tm, int& tn)
-{
-    const int n = gridDim.x, id = blockIdx.x;
-    const int xcd = id % 8, local = id / 8;
-    const int base = n / 8, rem = n % 8;
-    const int nid = xcd * base + (xcd < rem ? xcd : rem) + local;
-    const int tiles = tiles_m * tiles_n;
-    split = nid / tiles;
-    const int q = nid - split * tiles;
-    constexpr int GROUP_M = 4;
-    const int per_group = GROUP_M * tiles_n;
-    const int group = q / per_group;
-    const int first_m = group * GROUP_M;
-    const int gm = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
-    const int r = q - group * per_group;
-    tm = first_m + r % gm;
-    tn = r / gm;
 }
 
 // Tile geometry.  RC_ = fragments of a slab's last k-step that are read in the multiply phase (the rest of the

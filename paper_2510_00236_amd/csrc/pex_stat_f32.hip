@@ -2,193 +2,295 @@
 //
 // Same mathematics as the bf16 kernel (Sec. 2.3): M_b = X_b^T G_b accumulates in registers, phi is applied to the
 // finished per-example tile, the per-example gradient never leaves the register file.  fp32 inputs keep true fp32
-// products (the 1e-4 tolerance of fp32 inputs forbids rounding them to bf16): v_mfma_f32_32x32x2_f32, 157 TFLOP/s at
+// products (the 1e-4 tolerance of fp32 inputs forbids rounding them to bf16): v_mfma_f32_16x16x4_f32, 157 TFLOP/s at
 // the datasheet clock -- the same as the vector FMA rate with packed operations, which this library is built without,
 // so the matrix pipe is the only way past ~79 TFLOP/s.
 //
-// The fp32 pipe is 16 times slower than the bf16 one per byte of operand, so this kernel is bound by its MFMAs and
-// needs none of the bf16 kernel's machinery: a workgroup of 4 waves owns a 128 x 128 tile (64 x 64 per wave, 2 x 2
-// accumulators), slabs of 16 (or 8) tokens go global -> registers -> LDS through two buffers (the loads of slab s+1 are in
-// flight while slab s is multiplied), one barrier per slab.  The t-major layout is what the MFMA wants as it is: the
-// operand of 32x32x2 is one float per lane, row (lane % 32) of token (lane / 32), i.e. a plain ds_read_b32 of 32
-// consecutive floats of one token and 32 of the next; LDS rows are padded by 32 floats so that the two tokens sit in
-// different halves of the banks.  Three workgroups share a compute unit (at most 40 KB of LDS each), which is where
-// the overlap of loads, LDS reads and MFMAs comes from.
+// Bound: the fp32 MFMA pipe, 16 times slower per byte of operand than the bf16 one.  At that ratio the operands need
+// no LDS at all: a wave owns a 64 x 64 tile and loads its fragments straight from global memory, so waves share
+// nothing, wait for nobody and the kernel has no barrier.  Measured on B=16, T=1024, 1024x4096: phi = square 0.97 ms =
+// 142 TFLOP/s, pipes busy 94 % of the cycles.  (Before: 128 x 128 blocks staged through LDS, one barrier per 16 tokens, three
+// workgroups per compute unit: 1.18 ms, 76 % -- four waves on four SIMDs that have to meet leave gaps that the other two
+// workgroups do not fill.)
+//   * The t-major layout is what the MFMA wants: its operand is one float per lane, row (lane % 16) of token
+//     (lane / 16).  Rows of the tile may be numbered freely, so operand row p of fragment m is feature 4p + m: the four
+//     fragments of a 64-feature panel and four tokens are ONE 16-byte load per lane (16 lanes read 256 contiguous
+//     bytes of a token).  Two loads feed 16 MFMAs = 512 cycles.  fp32 rows start at 4-byte boundaries whatever their
+//     length, which is all a dwordx4 load asks for, so widths need not be multiples of anything.
+//   * The last tile of a width that is no multiple of 64 starts at (width - 64) instead: it overlaps its neighbour and
+//     stores only what is its own, so no lane ever reads past the end of a row.
+//   * Groups of 4 tokens run through a ring of register sets: the loads of group g + RING - 1 are issued behind the first
+//     MFMAs of group g (about RING x 512 cycles of latency covered per wave, times the two waves of a SIMD).  Rows past
+//     the end of an example lie outside the buffer descriptor and arrive as zeros; the ring runs on across examples, so
+//     an example's first groups are in flight while the previous one is folded.
 #include "pex_internal.h"
+#include "pex_tile_map.h"
 
 namespace pex {
 namespace {
 
-typedef __attribute__((ext_vector_type(16))) float float16_t;
+typedef __attribute__((ext_vector_type(4))) float float4_t;
+typedef __attribute__((ext_vector_type(4))) unsigned int uint4_t;
+typedef float4_t __attribute__((aligned(4))) float4_u;      // four floats at any float's address
 
-constexpr int F_BM = 128, F_BN = 128, F_LD = 128 + 32, F_THREADS = 256;
+constexpr int F_T = 64;                    // edge of a wave's tile
+constexpr int F_ROWS = 4;                  // tokens per group
+constexpr int F_CHUNK = 1024;              // rows after which a plain contraction is folded into its sum
+constexpr uint32_t F_OUTSIDE = 0x80000000u; // lane offset beyond every descriptor (windows stay below 2^30 bytes)
+constexpr int F_THREADS = 256;             // up to four waves: 2 x 2 tiles of 64 x 64
+
+// What one launch produces (bit set); none of the per-example ones: a plain contraction over all rows, written to out_id
+constexpr int F_ID = 1, F_SQ = 2, F_SG = 4, F_IDW = 16, F_POW = 32, F_NORM = 64, F_TOKEN = 128;
+constexpr int F_PLAIN = 0;
 
 __device__ __forceinline__ float sign_of(float m) { return (float)((m > 0.f) - (m < 0.f)); }
 
-// F_BK = tokens per slab.  Three workgroups per compute unit (three waves per SIMD) is where loads, LDS reads and
-// MFMAs overlap best (measured against two and four), which caps a wave at 168 registers: two 64-register tiles plus
-// the staging registers of a 16-token slab fit, except with the extra temporaries of sign and the powers, which take
-// slabs of 8.
-template <int MODE, int F_BK>
-__global__ __launch_bounds__(F_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void stat_f32_kernel(const float* __restrict__ X, const float* __restrict__ G, int64_t rows_total,
-                                                            int seg_len, int din, int dout, int64_t rows_per_split,
-                                                            float* __restrict__ out, const float* __restrict__ weight, float alpha)
+template <int OUTS, int RING>
+__global__ __launch_bounds__(F_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void stat_f32_kernel(
+    const float* __restrict__ X, const float* __restrict__ G, int64_t rows_total, int seg_len, int din, int dout, int64_t rows_per_split,
+    int window_rows, int waves_n, int blocks_m, int blocks_n, int64_t out_stride, float* __restrict__ out_id, float* __restrict__ out_sq,
+    float* __restrict__ out_sg, const float* __restrict__ weight, float* __restrict__ norm_partial, int examples_total, float alpha)
 {
-    constexpr bool PER_EXAMPLE = !(MODE == MODE_IDENTITY || MODE == MODE_TOKEN_SQ);
-    constexpr int F_LOADS = F_BK * F_BM / 4 / F_THREADS;   // float4 loads per thread, operand and slab
-    __shared__ __attribute__((aligned(16))) float Xs[2][F_BK][F_LD];
-    __shared__ __attribute__((aligned(16))) float Gs[2][F_BK][F_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int i0 = blockIdx.y * F_BM, j0 = blockIdx.x * F_BN;
-    const int64_t row_begin = (int64_t)blockIdx.z * rows_per_split;
+    constexpr bool PER_EXAMPLE = !(OUTS == F_PLAIN || OUTS == F_TOKEN);
+    constexpr bool HAS_ID = !PER_EXAMPLE || (OUTS & (F_ID | F_IDW)) != 0, HAS_SQ = (OUTS & (F_SQ | F_POW)) != 0, HAS_SG = (OUTS & F_SG) != 0;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves_m = (int)(blockDim.x >> 6) / waves_n;
+    int split, bm, bn;
+    map_workgroup(blocks_m, blocks_n, split, bm, bn);
+    const int own_i = (bm * waves_m + wave / waves_n) * F_T, own_j = (bn * waves_n + wave % waves_n) * F_T;   // first entry that is this tile's own
+    if (own_i >= din || own_j >= dout) return;
+    const int i0 = own_i + F_T <= din ? own_i : (din > F_T ? din - F_T : 0);
+    const int j0 = own_j + F_T <= dout ? own_j : (dout > F_T ? dout - F_T : 0);
+
+    const int64_t row_begin = (int64_t)split * rows_per_split;
     int64_t row_end = row_begin + rows_per_split;
     if (row_end > rows_total) row_end = rows_total;
-    const int slen = PER_EXAMPLE ? seg_len : (int)(row_end - row_begin);   // segment: one example, or the whole range
-    const int nseg = PER_EXAMPLE ? (int)((row_end - row_begin) / seg_len) : (row_end > row_begin ? 1 : 0);
-    const int nst = (slen + F_BK - 1) / F_BK;
-    const int total = nseg * nst;
+    const int64_t rows = row_end - row_begin;
+    // segment: one example; a plain contraction is folded into its sum every F_CHUNK rows (shorter chains of additions)
+    const int slen = PER_EXAMPLE ? seg_len : F_CHUNK;
+    const int nst = (slen + F_ROWS - 1) / F_ROWS;
+    const int64_t total = PER_EXAMPLE ? rows / seg_len * nst : (rows + F_ROWS - 1) / F_ROWS;
 
-    float16_t acc[2][2], acc2[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[a][c][r] = 0.f; acc2[a][c][r] = 0.f; }
+    // operand lane (k, p) = (lane / 16, lane % 16): token k of the group, features 4p .. 4p+3 of the panel (whole chunks: a
+    // panel of fewer than 64 features has a multiple of 4 of them)
+    const int k = lane >> 4, p = lane & 15;
+    const uint32_t xoff = i0 + 4 * p < din ? (uint32_t)(k * din + i0 + 4 * p) * 4u : F_OUTSIDE;
+    const uint32_t goff = j0 + 4 * p < dout ? (uint32_t)(k * dout + j0 + 4 * p) * 4u : F_OUTSIDE;
 
-    // loader: float4 number q = tid + 256*u of a slab is row q / 32, columns 4*(q % 32) ..
-    float4 xr[F_LOADS], gr[F_LOADS];
-    auto gload = [&](int s) {
-        const int seg = s / nst, st = s - seg * nst;
-        const int64_t row0 = row_begin + (int64_t)seg * slen + (int64_t)st * F_BK;
-        const int valid = (slen - st * F_BK) < F_BK ? (slen - st * F_BK) : F_BK;
+    float4_t acc[4][4], acc_id[HAS_ID ? 4 : 1][4], acc_sq[HAS_SQ ? 4 : 1][4], acc_sg[HAS_SG ? 4 : 1][4];
 #pragma unroll
-        for (int u = 0; u < F_LOADS; ++u) {
-            const int q = tid + F_THREADS * u, r = q >> 5, c = (q & 31) * 4;
-            xr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            gr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (r < valid) {
-                if (i0 + c < din) xr[u] = *(const float4*)(X + (row0 + r) * din + i0 + c);   // din % 4 == 0: whole or nothing
-                if (j0 + c < dout) gr[u] = *(const float4*)(G + (row0 + r) * dout + j0 + c);
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            acc[m][n] = float4_t{0.f, 0.f, 0.f, 0.f};
+            if (HAS_ID) acc_id[m][n] = acc[m][n];
+            if (HAS_SQ) acc_sq[m][n] = acc[m][n];
+            if (HAS_SG) acc_sg[m][n] = acc[m][n];
+        }
+
+    // The loads walk through windows: runs of rows of one segment that one pair of descriptors covers, so that a group costs
+    // no more than moving the two lane offsets on.  A window ends with its segment (rows past it read as zeros) or where
+    // 32-bit offsets would; past the last one the descriptors are empty.
+    const float* xbase = X + row_begin * din;
+    const float* gbase = G + row_begin * dout;
+    const int win_rows = window_rows < slen ? window_rows : slen;      // a multiple of F_ROWS, or the whole segment
+    int64_t rows_left = rows;
+    int seg_left = slen, win_groups = 0;
+    uint32_t xat = xoff, gat = goff;
+    const uint32_t xstep = (uint32_t)din * (F_ROWS * 4u), gstep = (uint32_t)dout * (F_ROWS * 4u);
+    __amdgpu_buffer_rsrc_t rx, rg;
+    auto next_window = [&]() {
+        int n = win_rows < seg_left ? win_rows : seg_left;
+        if (n > rows_left) n = (int)rows_left;
+        rx = __builtin_amdgcn_make_buffer_rsrc((void*)xbase, 0, n * din * 4, 0x00020000);
+        rg = __builtin_amdgcn_make_buffer_rsrc((void*)gbase, 0, n * dout * 4, 0x00020000);
+        xat = xoff;
+        gat = goff;
+        xbase += (int64_t)n * din;
+        gbase += (int64_t)n * dout;
+        rows_left -= n;
+        seg_left -= n;
+        if (seg_left <= 0) seg_left = slen;
+        win_groups = n > 0 ? (n + F_ROWS - 1) / F_ROWS : 1 << 30;
+    };
+    uint4_t xr[RING], gr[RING];
+    auto load_x = [&](int slot) { xr[slot] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)xat, 0, 0); };
+    auto load_g = [&](int slot) { gr[slot] = __builtin_amdgcn_raw_buffer_load_b128(rg, (int)gat, 0, 0); };
+    auto move_on = [&]() {
+        xat += xstep;
+        gat += gstep;
+        if (--win_groups == 0) next_window();
+    };
+    // the 16 MFMAs of the group in ring slot `slot`; behind the first of them, the loads into slot `into` (< 0: none).  The
+    // column index runs back and forth, so that consecutive MFMAs share an operand register: an MFMA-only loop reaches 155
+    // TFLOP/s this way and 147 with two fresh operands at every fourth MFMA.  The fences pin that order.
+    auto multiply = [&](int slot, int into) {
+        float a[4], b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = __uint_as_float(xr[slot][e]);
+            b[e] = __uint_as_float(gr[slot][e]);
+            if (OUTS == F_TOKEN) { a[e] *= a[e]; b[e] *= b[e]; }     // exact fp32 squares
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int nn = 0; nn < 4; ++nn) {
+                const int n = (m & 1) ? 3 - nn : nn;
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], b[n], acc[m][n], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (into >= 0 && m == 0 && nn == 1) { load_x(into); __builtin_amdgcn_sched_barrier(0); }
+                if (into >= 0 && m == 0 && nn == 3) { load_g(into); __builtin_amdgcn_sched_barrier(0); }
+                if (into >= 0 && m == 1 && nn == 1) { move_on(); __builtin_amdgcn_sched_barrier(0); }
             }
-        }
     };
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int u = 0; u < F_LOADS; ++u) {
-            const int q = tid + F_THREADS * u, r = q >> 5, c = (q & 31) * 4;
-            float4 x = xr[u], g = gr[u];
-            if (MODE == MODE_TOKEN_SQ) {   // exact fp32 squares
-                x = make_float4(x.x * x.x, x.y * x.y, x.z * x.z, x.w * x.w);
-                g = make_float4(g.x * g.x, g.y * g.y, g.z * g.z, g.w * g.w);
-            }
-            *(float4*)&Xs[buf][r][c] = x;
-            *(float4*)&Gs[buf][r][c] = g;
-        }
-    };
-    auto multiply = [&](int buf) {
-        const int kk = lane >> 5, col = lane & 31;
-#pragma unroll
-        for (int ks = 0; ks < F_BK / 2; ++ks) {
-            float a[2], b[2];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) a[m] = Xs[buf][2 * ks + kk][wm * 64 + m * 32 + col];
-#pragma unroll
-            for (int n = 0; n < 2; ++n) b[n] = Gs[buf][2 * ks + kk][wn * 64 + n * 32 + col];
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m], b[n], acc[m][n], 0, 0, 0);
-        }
-    };
-    int example = (int)(row_begin / (seg_len > 0 ? seg_len : 1));
+    int example = (int)(row_begin / seg_len);
+    const int ib = i0 + 16 * k, jb = j0 + 4 * p;      // row of (m, r): ib + 4r + m; column of n: jb + n
     auto fold = [&]() {
-        float w = 1.f;
-        if (MODE == MODE_WEIGHTED) w = weight[example];
+        float w = 1.f, norm = 0.f;
+        if (OUTS & F_IDW) w = weight[example];
+        // a norm counts what is this tile's own: not its neighbour's part of an overlapping tile, nothing beyond a narrow panel
+        const bool whole = own_i + F_T <= din && own_j + F_T <= dout;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int n = 0; n < 4; ++n) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float m = acc[a][c][r];
-                    if (MODE == MODE_SQUARE) acc2[a][c][r] = fmaf(m, m, acc2[a][c][r]);
-                    if (MODE == MODE_SIGN) acc2[a][c][r] += sign_of(m);
-                    if (MODE == MODE_WEIGHTED) acc2[a][c][r] = fmaf(w, m, acc2[a][c][r]);
-                    if (MODE == MODE_POWER) acc2[a][c][r] += __builtin_amdgcn_exp2f(alpha * __builtin_amdgcn_logf(__builtin_fabsf(m)));
-                    acc[a][c][r] = 0.f;
+                for (int r = 0; r < 4; ++r) {
+                    const float v = acc[m][n][r];
+                    if (!PER_EXAMPLE || (OUTS & F_ID)) acc_id[m][n][r] += v;
+                    if (OUTS & F_IDW) acc_id[m][n][r] = fmaf(w, v, acc_id[m][n][r]);
+                    if (OUTS & F_SQ) acc_sq[m][n][r] = fmaf(v, v, acc_sq[m][n][r]);
+                    if (OUTS & F_POW) acc_sq[m][n][r] += __builtin_amdgcn_exp2f(alpha * __builtin_amdgcn_logf(__builtin_fabsf(v)));
+                    if (OUTS & F_SG) acc_sg[m][n][r] += sign_of(v);
+                    if (OUTS & F_NORM) {
+                        const int i = ib + 4 * r + m, j = jb + n;
+                        const bool mine = whole || (i >= own_i && i < din && j >= own_j && j < dout);
+                        norm = fmaf(v, mine ? v : 0.f, norm);
+                    }
                 }
+                acc[m][n] = float4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        if (OUTS & F_NORM) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) norm += __shfl_xor(norm, off);
+            const int tiles_n = (dout + F_T - 1) / F_T;
+            if (lane == 0) norm_partial[((int64_t)(own_i / F_T) * tiles_n + own_j / F_T) * examples_total + example] = norm;
+        }
         ++example;
     };
 
-    if (total > 0) {
-        gload(0);
-        sstore(0);
-        __syncthreads();
-        int st_in_seg = 0;
-        for (int s = 0; s < total; ++s) {
-            if (s + 1 < total) gload(s + 1);     // in flight during the MFMAs of slab s
-            multiply(s & 1);
-            if (s + 1 < total) sstore((s + 1) & 1);
-            __syncthreads();
-            if (PER_EXAMPLE && ++st_in_seg == nst) { st_in_seg = 0; fold(); }
+    // Whole periods of the ring run without a branch around any load or multiply, so that the compiler can wait for exactly
+    // the group it needs (guarded steps made it wait for every load once per period); what is left of a period is
+    // already in flight when the loop ends.  Step s refills the slot of step s - 1.
+    next_window();
+#pragma unroll
+    for (int s = 0; s < RING - 1; ++s) {
+        load_x(s);
+        load_g(s);
+        move_on();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int st_in_seg = 0;
+    auto end_of_step = [&]() {
+        if (++st_in_seg == nst) { st_in_seg = 0; fold(); }
+    };
+    const int64_t periods = total / RING;
+    for (int64_t g = 0; g < periods; ++g) {
+#pragma unroll
+        for (int s = 0; s < RING; ++s) {
+            multiply(s, (s + RING - 1) % RING);
+            end_of_step();
         }
     }
-
-    // epilogue: lane holds column (lane % 32), rows 8*(r/4) + 4*(lane/32) + r%4 of each 32 x 32 tile
-    float* dst = out + (int64_t)blockIdx.z * din * dout;
-    const int jn = lane & 31, ib = 4 * (lane >> 5);
+    const int rest = (int)(total - periods * RING);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int j = j0 + wn * 64 + c * 32 + jn;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i0 + wm * 64 + a * 32 + 8 * (r / 4) + ib + (r % 4);
-                if (i < din && j < dout) dst[(int64_t)i * dout + j] = PER_EXAMPLE ? acc2[a][c][r] : acc[a][c][r];
-            }
+    for (int s = 0; s < RING - 1; ++s)
+        if (s < rest) {
+            multiply(s, -1);
+            end_of_step();
         }
+    if (!PER_EXAMPLE && st_in_seg > 0) fold();
+    if (OUTS & F_NORM) return;
+
+    // epilogue: the four column fragments of a lane are four neighbouring columns
+    auto store = [&](float* __restrict__ out, auto value) {
+        out += (int64_t)split * out_stride;
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = ib + 4 * r + m;
+                if (i < own_i || i >= din) continue;
+                float* row = out + (int64_t)i * dout;
+                const float4_t v = {value(m, 0, r), value(m, 1, r), value(m, 2, r), value(m, 3, r)};
+                if (jb >= own_j && jb + 4 <= dout) *(float4_u*)(row + jb) = v;
+                else {
+#pragma unroll
+                    for (int n = 0; n < 4; ++n)
+                        if (jb + n >= own_j && jb + n < dout) row[jb + n] = v[n];
+                }
+            }
+    };
+    if constexpr (HAS_ID) store(out_id, [&](int m, int n, int r) { return acc_id[m][n][r]; });
+    if constexpr (HAS_SQ) store(out_sq, [&](int m, int n, int r) { return acc_sq[m][n][r]; });
+    if constexpr (HAS_SG) store(out_sg, [&](int m, int n, int r) { return acc_sg[m][n][r]; });
+}
+
+template <int OUTS, int RING>
+hipError_t launch_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan, float* out_id,
+                      float* out_sq, float* out_sg, hipStream_t stream, const float* weight = nullptr, float* norm_partial = nullptr,
+                      float alpha = 0.f)
+{
+    constexpr bool PER_EXAMPLE = !(OUTS == F_PLAIN || OUTS == F_TOKEN);
+    int bm, bn;
+    f32_tile_shape(din, dout, &bm, &bn);
+    const int waves_m = bm / F_T, waves_n = bn / F_T;
+    const int blocks_m = (int)((din + bm - 1) / bm), blocks_n = (int)((dout + bn - 1) / bn);
+    const int64_t rows_per_split = PER_EXAMPLE ? plan.per_split * T : plan.per_split;
+    // rows one descriptor covers: below 2^30 bytes of either operand, whole groups
+    int64_t window = ((int64_t)1 << 28) / (din > dout ? din : dout) / F_ROWS * F_ROWS;
+    const int window_rows = (int)(window < ((int64_t)1 << 30) ? window : (int64_t)1 << 30);
+    const dim3 grid((unsigned)((int64_t)blocks_m * blocks_n * plan.nsplit)), block((unsigned)(waves_m * waves_n * 64));
+    stat_f32_kernel<OUTS, RING><<<grid, block, 0, stream>>>((const float*)X, (const float*)G, B * T, (int)T, (int)din, (int)dout, rows_per_split, window_rows, waves_n,
+                                                            blocks_m, blocks_n, din * dout, out_id, out_sq, out_sg, weight,
+                                                            norm_partial, (int)B, alpha);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-void f32_tile_shape(int* bm, int* bn)
+// a workgroup of up to 2 x 2 waves; layers of at most 64 rows or columns have no use for the second wave
+void f32_tile_shape(int64_t din, int64_t dout, int* bm, int* bn)
 {
-    *bm = F_BM;
-    *bn = F_BN;
+    *bm = din > F_T ? 2 * F_T : F_T;
+    *bn = dout > F_T ? 2 * F_T : F_T;
 }
 
-bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode)
+bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout)
 {
-    // rows of 16-byte multiples, at least a quarter of a tile, and every mode but the norms (which write no S)
-    if (mode == MODE_NORMS) return false;
-    return din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
+    // a panel narrower than a tile must consist of whole 16-byte chunks; the narrowest layers stay on the SIMT kernel
+    if (B * T < 16 || din < 32 || dout < 32) return false;
+    if ((din < F_T && din % 4 != 0) || (dout < F_T && dout % 4 != 0)) return false;
+    // 32-bit byte offsets inside a window of at least four rows
+    if (din > ((int64_t)1 << 26) || dout > ((int64_t)1 << 26)) return false;
 }
 
-hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode,
-                           const StatPlan& plan, float* out, hipStream_t stream, const float* weight, float alpha)
+int64_t f32_norm_partials(int64_t din, int64_t dout) { return ((din + F_T - 1) / F_T) * ((dout + F_T - 1) / F_T); }
+
+hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, const StatPlan& plan,
+                           float* out, hipStream_t stream, const float* weight, float* norm_partial, float alpha)
 {
-    const dim3 grid((unsigned)((dout + F_BN - 1) / F_BN), (unsigned)((din + F_BM - 1) / F_BM), (unsigned)plan.nsplit);
-    const dim3 block(F_THREADS);
-    const int64_t rows_total = B * T;
-    const bool per_example = !(mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ);
-    const int64_t rows_per_split = per_example ? plan.per_split * T : plan.per_split;
-    const float* x = (const float*)X;
-    const float* g = (const float*)G;
-#define PEX_F32_LAUNCH(M) stat_f32_kernel<M, (M == MODE_SIGN || M == MODE_POWER) ? 8 : 16><<<grid, block, 0, stream>>>(x, g, rows_total, (int)T, (int)din, (int)dout, rows_per_split, out, weight, alpha)
     switch (mode) {
-    case MODE_IDENTITY: PEX_F32_LAUNCH(MODE_IDENTITY); break;
-    case MODE_SQUARE: PEX_F32_LAUNCH(MODE_SQUARE); break;
-    case MODE_SIGN: PEX_F32_LAUNCH(MODE_SIGN); break;
-    case MODE_TOKEN_SQ: PEX_F32_LAUNCH(MODE_TOKEN_SQ); break;
-    case MODE_WEIGHTED: PEX_F32_LAUNCH(MODE_WEIGHTED); break;
-    case MODE_POWER: PEX_F32_LAUNCH(MODE_POWER); break;
-    default: return hipErrorInvalidValue;
+    case MODE_IDENTITY: return launch_f32<F_PLAIN, 6>(X, G, B, T, din, dout, plan, out, nullptr, nullptr, stream);
+    case MODE_SQUARE: return launch_f32<F_SQ, 6>(X, G, B, T, din, dout, plan, nullptr, out, nullptr, stream);
+    case MODE_SIGN: return launch_f32<F_SG, 6>(X, G, B, T, din, dout, plan, nullptr, nullptr, out, stream);
+    case MODE_TOKEN_SQ: return launch_f32<F_TOKEN, 6>(X, G, B, T, din, dout, plan, out, nullptr, nullptr, stream);
+    case MODE_WEIGHTED: return launch_f32<F_IDW, 6>(X, G, B, T, din, dout, plan, out, nullptr, nullptr, stream, weight);
+    case MODE_POWER: return launch_f32<F_POW, 6>(X, G, B, T, din, dout, plan, nullptr, out, nullptr, stream, nullptr, nullptr, alpha);
+    case MODE_NORMS: return launch_f32<F_NORM, 6>(X, G, B, T, din, dout, plan, nullptr, nullptr, nullptr, stream, nullptr, norm_partial);
     }
-#undef PEX_F32_LAUNCH
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 }  // namespace pex

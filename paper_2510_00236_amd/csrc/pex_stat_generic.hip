@@ -1,7 +1,6 @@
 // pex_stat_generic.hip -- shape-agnostic SIMT kernel for S = sum_b phi(X_b^T G_b) and the per-token
 // square.  Handles any B, T, din, dout >= 1 and both storage types with true fp32 products; it is the
-// path for fp32 inputs and for bf16 shapes the MFMA kernel does not take.  Latency/ALU bound by design:
-// the tuned path lives in pex_stat_bf16.hip.
+// path of the shapes the MFMA kernels (pex_stat_bf16.hip, pex_stat_f32.hip) do not take.  Latency/ALU bound.
 //
 // One workgroup (16 x 16 lanes) owns a 64 x 64 tile of S for one group of examples.  For each example it
 // walks the sequence in slabs of 16 tokens staged through LDS, keeps the running tile of M_b in registers
