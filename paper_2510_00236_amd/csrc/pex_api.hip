@@ -396,8 +396,8 @@ static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pe
     return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
 }
 
-// How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (bf16
-// layers), the rest one at a time.
+// How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (on the layers the
+// MFMA kernels take), the rest one at a time.
 struct MultiPlan {
     bool pair;            // a fused launch is used
     uint32_t pair_want;   // for which statistics
@@ -411,16 +411,19 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
     MultiPlan m{};
     const int n = __builtin_popcount(want);
     const StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false);
-    m.pair = (n >= 2 && sq.kernel == 1);
+    // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
+    // contraction and sign keeps its own.  On fp32 layers sign shares one only as bytes.
+    m.pair_want = want;
+    if (sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
+    if (sq.kernel == 2 && !f32_bytes_suffice(sq)) m.pair_want = want & (PEX_WANT_IDENTITY | PEX_WANT_SQUARE);
+    m.pair = (__builtin_popcount(m.pair_want) >= 2 && sq.kernel != 0);
     if (m.pair) {
-        // three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square
-        // share a contraction and sign keeps its own (packed counts, large tile)
-        m.pair_want = (n == 3 && !bf16_triple_supported(sq)) ? (PEX_WANT_IDENTITY | PEX_WANT_SQUARE) : want;
         m.single_want = want & ~m.pair_want;
         m.pair_plan = sq;
         m.pair_plan.ws_bytes = sq.nsplit > 1 ? __builtin_popcount(m.pair_want) * sq.ws_bytes : 0;
         m.ws_bytes = m.pair_plan.ws_bytes;
     } else {
+        m.pair_want = 0;
         m.single_want = want;
     }
     for (int phi = 0; phi < 3; ++phi)
@@ -536,7 +539,8 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         int k = 0;
         for (int phi = 0; phi < 3; ++phi)
             if (m.pair_want & (1u << phi)) po[phi] = p.nsplit > 1 ? (float*)workspace + (int64_t)(k++) * p.nsplit * n : outs[phi];
-        const hipError_t e = (__builtin_popcount(m.pair_want) == 3)
+        const hipError_t e = p.kernel == 2 ? launch_stat_f32_multi(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs)
+                             : (__builtin_popcount(m.pair_want) == 3)
                                  ? launch_stat_bf16_triple(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs)
                                  : launch_stat_bf16_pair(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs);
         if (e != hipSuccess) return PEX_ERR_HIP;

@@ -88,6 +88,10 @@ int64_t f32_norm_partials(int64_t din, int64_t dout);
 hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode,
                            const StatPlan& plan, float* out, hipStream_t stream, const float* weight = nullptr,
                            float* norm_partial = nullptr, float alpha = 0.f);
+// byte-wide sign counters hold a group of the plan
+bool f32_bytes_suffice(const StatPlan& plan);
+hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
+                                 float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
 // out[i] = bf16(in[i]^2) (square in fp32, round to nearest even) for n bf16 values, n a multiple of 8
 hipError_t launch_square_bf16(const void* in, void* out, int64_t n, hipStream_t stream);
 void bf16_tile_shape(Mode mode, int64_t B, int* bm, int* bn);

@@ -56,3 +56,22 @@ def test_integer_inputs_are_bit_exact():
     for phi, ref in (("identity", st.S_id), ("square", st.S_sq), ("sign", st.S_sign)):
         got = pex.pex_stat(X.to(DEV), G.to(DEV), phi).cpu().numpy().astype(np.float64)
         assert np.array_equal(got, ref) if phi != "square" else np.abs(got - ref).max() <= 1e-6 * ref.max(), phi
+
+
+@pytest.mark.parametrize("B,T,din,dout", [(3, 23, 127, 200), (19, 4, 100, 333), (140, 5, 70, 64)])
+@pytest.mark.parametrize("want", [("identity", "square"), ("identity", "sign"), ("square", "sign"), ("identity", "square", "sign")])
+def test_statistics_sharing_a_contraction(pex_option, B, T, din, dout, want):
+    """Every combination against the oracle; with the batch in one group, 140 examples are more than a byte counter holds, so
+    sign runs alone there."""
+    pex_option("max_split", 1 if B > 127 else 32)
+    X, G = si.custom(B, T, din, dout, dtype="f32", seed=B + T)
+    st = oracle.stat(si.widen(X), si.widen(G))
+    out = {k: torch.full((din, dout), float("nan"), device=DEV) for k in want}
+    pex.pex_stat_multi(X.to(DEV), G.to(DEV), want, out=out)
+    got = {k: v.cpu().numpy().astype(np.float64) for k, v in out.items()}
+    if "identity" in got:
+        assert_real_stat(got["identity"], st.S_id, "f32", "identity", elementwise=False)
+    if "square" in got:
+        assert_real_stat(got["square"], st.S_sq, "f32", "square", elementwise=True)
+    if "sign" in got:
+        assert_sign_stat(got["sign"], st.S_sign, st.amb, "sign")
