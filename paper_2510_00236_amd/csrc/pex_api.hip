@@ -362,17 +362,18 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
     if (plan.wide_cols > 0) {
         // the wide part's partial sums come first in the workspace, then those of the columns beyond it
         if (plan.wide_nsplit > 1) {
-            e = launch_reduce_partials_cols(partials, plan.wide_nsplit, din, plan.wide_cols, S, dout, stream);
+            e = launch_reduce_partials({{partials}, {S}}, 1, plan.wide_nsplit, din * plan.wide_cols, din, plan.wide_cols, plan.wide_cols, dout, stream);
             if (e != hipSuccess) return PEX_ERR_HIP;
         }
-        if (plan.nsplit > 1 && dout > plan.wide_cols) {
+        const int64_t rest = dout - plan.wide_cols;
+        if (plan.nsplit > 1 && rest > 0) {
             const float* rest_partials = (const float*)((const char*)partials + plan.wide_ws_bytes);
-            e = launch_reduce_partials_cols(rest_partials, plan.nsplit, din, dout - plan.wide_cols, S + plan.wide_cols, dout, stream);
+            e = launch_reduce_partials({{rest_partials}, {S + plan.wide_cols}}, 1, plan.nsplit, din * rest, din, rest, rest, dout, stream);
             if (e != hipSuccess) return PEX_ERR_HIP;
         }
     } else if (plan.nsplit > 1) {
         e = plan.sign_bytes ? launch_reduce_sign_bytes(partials, plan.nsplit, din, dout, S, stream)
-                            : launch_reduce_partials(partials, plan.nsplit, din * dout, S, stream);
+                            : launch_reduce_partials({{partials}, {S}}, 1, plan.nsplit, din * dout, 1, din * dout, 0, 0, stream);
         if (e != hipSuccess) return PEX_ERR_HIP;
     }
     return PEX_OK;
@@ -544,9 +545,13 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
                                  ? launch_stat_bf16_triple(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs)
                                  : launch_stat_bf16_pair(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs);
         if (e != hipSuccess) return PEX_ERR_HIP;
-        if (p.nsplit > 1)
+        if (p.nsplit > 1) {
+            ReduceOutputs io{};
+            int count = 0;
             for (int phi = 0; phi < 3; ++phi)
-                if (po[phi] && launch_reduce_partials(po[phi], p.nsplit, n, outs[phi], hs) != hipSuccess) return PEX_ERR_HIP;
+                if (po[phi]) { io.partial[count] = po[phi]; io.S[count++] = outs[phi]; }
+            if (launch_reduce_partials(io, count, p.nsplit, n, 1, n, 0, 0, hs) != hipSuccess) return PEX_ERR_HIP;
+        }
     }
     for (int phi = 0; phi < 3; ++phi) {
         if (!(m.single_want & (1u << phi))) continue;

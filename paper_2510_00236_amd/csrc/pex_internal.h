@@ -114,11 +114,14 @@ VecPlan plan_vec_stat(int64_t B, int64_t T, int64_t d, pex_dtype dt);
 hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, const VecPlan& plan,
                            float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream);
 
-// S[e] = sum_{s < nsplit} partial[s][e], s ascending (fixed order => deterministic).
-hipError_t launch_reduce_partials(const float* partial, int nsplit, int64_t n, float* S, hipStream_t stream);
-// the same for a range of columns: S[i * lds + j] = sum_s partial[s][i][j], i < rows, j < cols (cols a multiple of 4)
-hipError_t launch_reduce_partials_cols(const float* partial, int nsplit, int64_t rows, int64_t cols, float* S, int64_t lds,
-                                       hipStream_t stream);
+// For the first `count` entries: S[i * ld + j] = sum_{k < nsplit} partial[k * group_stride + i * pitch + j], k ascending (fixed
+// order => deterministic), i < rows, j < cols.
+struct ReduceOutputs {
+    const float* partial[3];
+    float* S[3];
+};
+hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
+                                  int64_t ld, hipStream_t stream);
 
 hipError_t launch_adam_update(float* theta, float* m, float* v, const float* S_id, const float* S_sq, int64_t n,
                               pex_adam_variant variant, const pex_adam_params& p, hipStream_t stream,

@@ -160,30 +160,43 @@ hipError_t launch_typed(const TIn* X, const TIn* G, int64_t B, int64_t T, int64_
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial, int nsplit, int64_t n,
-                                                              float* __restrict__ S)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        float s = partial[e];
-        for (int k = 1; k < nsplit; ++k) s += partial[(int64_t)k * n + e];
-        S[e] = s;
-    }
-}
+// S[i * ld + j] = sum over the groups k, ascending, of partial[k * group_stride + i * pitch + j]: 16 bytes per lane and
+// group (rows of any length: a dwordx4 access needs no more than a float's alignment), four groups in flight; the second
+// grid dimension is the statistic, so that those of one call share a launch.  Bound by the memory-side cache the partial sums
+// were just written to.  Measured against one float per lane and one launch per statistic: 28 groups of 768 x 768 17.9 ->
+// 13 us, identity and square of 512 x 2048 in 8 groups 16 -> 13 us.
+typedef __attribute__((ext_vector_type(4))) float float4_v;
+typedef float4_v __attribute__((aligned(4))) float4_u;
 
-// the same sum for a range of columns of S: partial rows are `cols` long, S rows `ld`; four columns per lane
-__global__ __launch_bounds__(256) void reduce_partials_cols_kernel(const float4* __restrict__ partial, int nsplit, int64_t rows, int64_t cols4,
-                                                                   float* __restrict__ S, int64_t ld)
+__global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, int nsplit, int64_t group_stride, int64_t rows, int64_t cols,
+                                                              int64_t pitch, int64_t ld)
 {
-    const int64_t n4 = rows * cols4, stride = (int64_t)gridDim.x * blockDim.x;
+    const float* __restrict__ partial = io.partial[blockIdx.y];
+    float* __restrict__ S = io.S[blockIdx.y];
+    const int64_t cols4 = (cols + 3) / 4, n4 = rows * cols4, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n4; e += stride) {
-        float4 s = partial[e];
-        for (int k = 1; k < nsplit; ++k) {
-            const float4 p = partial[(int64_t)k * n4 + e];
-            s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+        const int64_t i = rows == 1 ? 0 : e / cols4, j = (e - i * cols4) * 4;
+        const float* p = partial + i * pitch + j;
+        float* out = S + i * ld + j;
+        if (j + 4 <= cols) {
+            float4_v s = *(const float4_u*)p;
+            int k = 1;
+            for (; k + 4 <= nsplit; k += 4) {
+                float4_v v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = *(const float4_u*)(p + (k + u) * group_stride);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s += v[u];
+            }
+            for (; k < nsplit; ++k) s += *(const float4_u*)(p + k * group_stride);
+            *(float4_u*)out = s;
+        } else {
+            for (int c = 0; j + c < cols; ++c) {
+                float s = p[c];
+                for (int k = 1; k < nsplit; ++k) s += p[k * group_stride + c];
+                out[c] = s;
+            }
         }
-        const int64_t i = e / cols4, j4 = e - i * cols4;
-        *(float4*)(S + i * ld + j4 * 4) = s;
     }
 }
 
@@ -286,21 +299,12 @@ hipError_t launch_token_norms(const void* X, const void* G, int64_t rows, int64_
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_partials_cols(const float* partial, int nsplit, int64_t rows, int64_t cols, float* S, int64_t ld,
-                                       hipStream_t stream)
+hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
+                                  int64_t ld, hipStream_t stream)
 {
-    if (cols % 4 != 0 || ld % 4 != 0) return hipErrorInvalidValue;
-    int64_t blocks = (rows * (cols / 4) + 255) / 256;
+    int64_t blocks = (rows * ((cols + 3) / 4) + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    reduce_partials_cols_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>((const float4*)partial, nsplit, rows, cols / 4, S, ld);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_partials(const float* partial, int nsplit, int64_t n, float* S, hipStream_t stream)
-{
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    reduce_partials_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(partial, nsplit, n, S);
+    reduce_partials_kernel<<<dim3((unsigned)blocks, (unsigned)count), dim3(256), 0, stream>>>(io, nsplit, group_stride, rows, cols, pitch, ld);
     return hipGetLastError();
 }
 
