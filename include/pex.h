@@ -113,6 +113,9 @@ int32_t pex_get_option(pex_option opt);
  *                               and sign need none, and square splits only the columns its wider block
  *                               shape leaves over, in two groups: half the size of S).  Partial sign counts
  *                               of bf16 layers are held as bytes while a group has at most 127 examples.
+ *                               For bf16 layers whose rows are not multiples of 16 bytes it may also hold
+ *                               copies of such operands with rows padded to the next multiple (about
+ *                               2*B*T*din and 2*B*T*dout bytes); din and dout above are then the padded ones.
  *   The contraction over T of one example is never split across workgroups (phi is applied to the complete
  *   sum over the sequence), the sum over b is taken in a fixed order.
  *   Any B,T,din,dout >= 1 is accepted with B*T, din, dout each < 2^31; fp32 inputs and bf16 layers whose rows are
@@ -130,7 +133,9 @@ pex_status pex_stat(const void *X, const void *G, int64_t B, int64_t T, int64_t 
  * PEX_NOALLOC_SCRATCH_BYTES that is part of the library's device image (one copy per GPU, held until the process
  * ends) instead of a caller's workspace.  The call allocates and frees nothing.
  *   - A call whose pex_stat_workspace_bytes(...) exceeds PEX_NOALLOC_SCRATCH_BYTES returns PEX_ERR_TOO_LARGE and
- *     launches nothing (small layers with many groups: e.g. 768 x 768 in 28 groups needs 63 MiB).
+ *     launches nothing (small layers with many groups: e.g. 768 x 768 in 28 groups needs 63 MiB).  Exception: a bf16
+ *     layer of odd width whose workspace is too large because of the padded copies it holds runs on the SIMT kernel
+ *     instead (same definition and error bounds, another order of additions than pex_stat).
  *   - All calls on one GPU share that GPU's buffer: calls that overlap in time on one GPU (different streams,
  *     different host threads) race on it; calls on one stream, or otherwise ordered, are safe.  Nothing in the
  *     buffer needs to start at zero and nothing is kept in it between calls.

@@ -129,9 +129,41 @@ static double bf16_block_rate(int bm, int bn)
     return area >= 256 * 256 ? 5.5e12 : (area >= 256 * 192 ? 4.8e12 : 4.3e12);
 }
 
-StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide)
+// bf16 layers whose rows are not whole 16-byte chunks: padded copies on the MFMA kernels, or the SIMT kernel on the operands as
+// they are?  The copies cost two more launches, about 10 us on small layers, so they pay where the SIMT kernel takes longer
+// than that: about 1.35 us per slab of 16 rows in a workgroup's serial loop, 35e12 FLOP/s at best on layers near the line.
+// Measured (SIMT / copies): B=8 T=64 70x130 square 20.6 / 24.8 us, B=8 T=128 201x333 square 21.9 / 24.6, B=16 T=128 301x500
+// identity + square 60 / 28, B=16 T=256 333x1001 square 86 / 33, B=2 T=4096 100x131 square 353 / 68.
+// `passes` = statistics the SIMT kernel would make one by one.  The per-token square stays on the SIMT kernel, which keeps
+// the squares in fp32.
+static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int passes)
+{
+    if (mode == MODE_TOKEN_SQ || (din % 8 == 0 && dout % 8 == 0)) return false;
+    if (!pad_supports(B * T, din, dout) || !bf16_supports(B, T, padded_width(din), padded_width(dout))) return false;
+    const int64_t tiles = ((din + 63) / 64) * ((dout + 63) / 64), units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
+    int64_t groups = (1024 + tiles - 1) / tiles;
+    if (groups > units) groups = units;
+    if (groups > 32) groups = 32;
+    const double slabs = (double)((units + groups - 1) / groups) * (mode == MODE_IDENTITY ? 4.0 : (double)((T + 15) / 16));
+    const double flop = 2.0 * (double)B * (double)T * (double)din * (double)dout;
+    const double t = flop / 35.0e12 > slabs * 1.35e-6 ? flop / 35.0e12 : slabs * 1.35e-6;
+    return t * passes > 14.0e-6;
+}
+
+StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
 {
     StatPlan p{};
+    p.out_rows = din;
+    p.out_cols = dout;
+    // (a plan on one block shape is one of several statistics at once)
+    if (allow_pad && dt == PEX_BF16 && padding_pays(B, T, din, dout, mode, allow_wide ? 1 : 2)) {
+        p.copy_x = din % 8 != 0;
+        p.copy_g = dout % 8 != 0;
+        din = padded_width(din);
+        dout = padded_width(dout);
+    }
+    p.din = din;
+    p.dout = dout;
     const bool per_example = (mode == MODE_SQUARE || mode == MODE_SIGN || mode == MODE_NORMS || mode == MODE_WEIGHTED || mode == MODE_POWER);
     p.kernel = (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) ? 1 : 0;
     if (dt == PEX_F32 && f32_mfma_supports(B, T, din, dout)) p.kernel = 2;
@@ -249,27 +281,27 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     // of direct-to-LDS loads, plus the arithmetic) costs about +50 % time; squaring them once into bf16 copies costs one
     // pass over X and G at HBM speed (~5.5 TB/s, 4 bytes moved per element).  The copies win when din*dout/(din+dout)
     // is large.
-    p.presq_bytes = 0;
     const int presquare = option(PEX_OPT_TOKEN_PRESQUARE);
     if (mode == MODE_TOKEN_SQ && p.kernel == 1 && presquare != 0) {
         const double elems = (double)B * (double)T * (double)(din + dout);
         const double t_pre = 4.0 * elems / 5.5e12 + 6.0e-6;
         const double t_fused_extra = 0.5 * 2.0 * (double)B * (double)T * (double)din * (double)dout / 1.3e15;
-        if (t_pre < t_fused_extra || presquare == 2)
-            p.presq_bytes = (((size_t)B * (size_t)T * (size_t)(din + dout) * 2) + 255) & ~(size_t)255;
+        if (t_pre < t_fused_extra || presquare == 2) p.copy_x = p.copy_g = true;
     }
+    const size_t copied = (p.copy_x ? (size_t)din : 0) + (p.copy_g ? (size_t)dout : 0);
+    p.copy_bytes = ((size_t)B * (size_t)T * copied * 2 + 255) & ~(size_t)255;
     p.sign_bytes = sign_bytes && nsplit > 1;
     p.mem_fold = mem_fold;
     p.wide_cols = wide_cols;
     p.wide_nsplit = (int)wide_nsplit;
     p.wide_per_split = wide_per;
     p.wide_ws_bytes = (wide_cols > 0 && wide_nsplit > 1) ? (size_t)wide_nsplit * (size_t)din * (size_t)wide_cols * sizeof(float) : 0;
-    p.ws_bytes = p.presq_bytes + p.wide_ws_bytes +
+    p.ws_bytes = p.copy_bytes + p.wide_ws_bytes +
                  ((nsplit > 1 && dout > wide_cols) ? (size_t)nsplit * (size_t)din * (size_t)(dout - wide_cols) * sizeof(float) : 0);
-    if (p.sign_bytes) p.ws_bytes = (size_t)nsplit * sign_byte_partial_bytes(din, dout);
+    if (p.sign_bytes) p.ws_bytes = p.copy_bytes + (size_t)nsplit * sign_byte_partial_bytes(din, dout);
     if (mode == MODE_NORMS) {   // no S at all: one partial of ||M_b||^2 per tile (and wave) and example
         const int64_t nparts = p.kernel == 1 ? bf16_norm_partials(din, dout) : p.kernel == 2 ? f32_norm_partials(din, dout) : generic_norm_partials(din, dout);
-        p.ws_bytes = (size_t)nparts * (size_t)B * sizeof(float);
+        p.ws_bytes = p.copy_bytes + (size_t)nparts * (size_t)B * sizeof(float);
         // Through the Gram matrices instead: 2 T^2 (din + dout) FLOP per example (a little over half of it with the
         // symmetry, in 128 x 128 blocks) against 2 T din dout, on a kernel of lower rate but with one workgroup per block
         // and example -- no batch split, however few tiles the layer has.
@@ -301,10 +333,10 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
             const bool wide_ok = park <= ((size_t)256 << 20);
             if (gram_opt == 3 ? wide_ok : (gram_opt == 1 && wide_ok && t_wide < t_gram && t_wide < t_direct)) {
                 p.gram = p.gram_wide = true;
-                p.ws_bytes = (((size_t)gram_wide_partials(T) * (size_t)B * sizeof(float) + 255) & ~(size_t)255) + park;
+                p.ws_bytes = p.copy_bytes + (((size_t)gram_wide_partials(T) * (size_t)B * sizeof(float) + 255) & ~(size_t)255) + park;
             } else if (gram_opt == 2 || gram_opt == 3 || t_gram < t_direct) {
                 p.gram = true;
-                p.ws_bytes = (size_t)gram_norm_partials(T) * (size_t)B * sizeof(float);
+                p.ws_bytes = p.copy_bytes + (size_t)gram_norm_partials(T) * (size_t)B * sizeof(float);
             }
         }
     }
@@ -328,26 +360,52 @@ static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64
     return PEX_OK;
 }
 
+// the partial sums of a plan without wide columns
+static hipError_t reduce_whole(const ReduceOutputs& io, int count, const StatPlan& plan, hipStream_t stream)
+{
+    const int64_t n = plan.din * plan.dout;
+    if (plan.dout == plan.out_cols) return launch_reduce_partials(io, count, plan.nsplit, n, 1, plan.out_rows * plan.out_cols, 0, 0, stream);
+    return launch_reduce_partials(io, count, plan.nsplit, n, plan.out_rows, plan.out_cols, plan.dout, plan.out_cols, stream);
+}
+
+// The copies a plan asks for, at the front of the workspace; X and G are turned into what the kernels read.
+static hipError_t make_copies(const StatPlan& plan, const void*& X, const void*& G, int64_t rows, void* workspace, bool made,
+                              hipStream_t stream)
+{
+    if (plan.copy_bytes == 0) return hipSuccess;
+    uint16_t* x = plan.copy_x ? (uint16_t*)workspace : nullptr;
+    uint16_t* g = plan.copy_g ? (uint16_t*)workspace + (plan.copy_x ? rows * plan.din : 0) : nullptr;
+    hipError_t e = hipSuccess;
+    if (!made) {
+        if (plan.din == plan.out_rows && plan.dout == plan.out_cols) {       // squares of rows that are whole chunks
+            e = launch_square_bf16(X, x, rows * plan.din, stream);
+            if (e == hipSuccess) e = launch_square_bf16(G, g, rows * plan.dout, stream);
+        } else e = launch_pad_rows(X, x, G, g, rows, plan.out_rows, plan.out_cols, stream);
+    }
+    if (x) X = x;
+    if (g) G = g;
+    return e;
+}
+
+// copies_made: the workspace already begins with the copies of X and G the plan asks for
 static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
                            Mode mode, float* S, void* workspace, size_t workspace_bytes, hipStream_t stream,
-                           const float* weight = nullptr, float alpha = 0.f)
+                           const float* weight = nullptr, float alpha = 0.f, bool allow_pad = true, bool copies_made = false)
 {
-    const StatPlan plan = plan_stat(B, T, din, dout, dt, mode);
+    const StatPlan plan = plan_stat(B, T, din, dout, dt, mode, true, allow_pad);
     float* out = S;
     if (plan.ws_bytes > 0) {
         if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     }
-    float* partials = (float*)((char*)workspace + plan.presq_bytes);
+    float* partials = (float*)((char*)workspace + plan.copy_bytes);
     if (plan.nsplit > 1) out = partials;
-    hipError_t e;
-    if (plan.presq_bytes > 0) {
-        // squared copies of X and G at the front of the workspace, then the plain contraction on them
-        uint16_t* x2 = (uint16_t*)workspace;
-        uint16_t* g2 = x2 + B * T * din;
-        e = launch_square_bf16(X, x2, B * T * din, stream);
-        if (e == hipSuccess) e = launch_square_bf16(G, g2, B * T * dout, stream);
-        if (e == hipSuccess) e = launch_stat_bf16(x2, g2, B, T, din, dout, MODE_IDENTITY, plan, S, partials, stream);
+    hipError_t e = make_copies(plan, X, G, B * T, workspace, copies_made, stream);
+    if (e != hipSuccess) return PEX_ERR_HIP;
+    din = plan.din;
+    dout = plan.dout;
+    if (mode == MODE_TOKEN_SQ && plan.copy_bytes > 0) {
+        e = launch_stat_bf16(X, G, B, T, din, dout, MODE_IDENTITY, plan, S, partials, stream);       // the copies hold the squares
     } else if (plan.kernel == 2) {
         e = launch_stat_f32(X, G, B, T, din, dout, mode, plan, out, stream, weight, nullptr, alpha);
     } else if (mode == MODE_POWER) {
@@ -359,21 +417,25 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
     } else if (plan.kernel == 1) e = launch_stat_bf16(X, G, B, T, din, dout, mode, plan, S, partials, stream);
     else e = launch_stat_generic(X, G, B, T, din, dout, dt, mode, plan, out, stream);
     if (e != hipSuccess) return PEX_ERR_HIP;
+    // partial sums have the operands' widths, S the layer's own
+    const int64_t rows = plan.out_rows, cols = plan.out_cols;
     if (plan.wide_cols > 0) {
         // the wide part's partial sums come first in the workspace, then those of the columns beyond it
         if (plan.wide_nsplit > 1) {
-            e = launch_reduce_partials({{partials}, {S}}, 1, plan.wide_nsplit, din * plan.wide_cols, din, plan.wide_cols, plan.wide_cols, dout, stream);
+            const int64_t mine = plan.wide_cols < cols ? plan.wide_cols : cols;
+            e = launch_reduce_partials({{partials}, {S}}, 1, plan.wide_nsplit, din * plan.wide_cols, rows, mine, plan.wide_cols, cols, stream);
             if (e != hipSuccess) return PEX_ERR_HIP;
         }
         const int64_t rest = dout - plan.wide_cols;
         if (plan.nsplit > 1 && rest > 0) {
             const float* rest_partials = (const float*)((const char*)partials + plan.wide_ws_bytes);
-            e = launch_reduce_partials({{rest_partials}, {S + plan.wide_cols}}, 1, plan.nsplit, din * rest, din, rest, rest, dout, stream);
+            e = launch_reduce_partials({{rest_partials}, {S + plan.wide_cols}}, 1, plan.nsplit, din * rest, rows, cols - plan.wide_cols, rest, cols,
+                                       stream);
             if (e != hipSuccess) return PEX_ERR_HIP;
         }
     } else if (plan.nsplit > 1) {
-        e = plan.sign_bytes ? launch_reduce_sign_bytes(partials, plan.nsplit, din, dout, S, stream)
-                            : launch_reduce_partials({{partials}, {S}}, 1, plan.nsplit, din * dout, 1, din * dout, 0, 0, stream);
+        e = plan.sign_bytes ? launch_reduce_sign_bytes(partials, plan.nsplit, rows, cols, S, stream)
+                            : reduce_whole({{partials}, {S}}, 1, plan, stream);
         if (e != hipSuccess) return PEX_ERR_HIP;
     }
     return PEX_OK;
@@ -421,7 +483,7 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
     if (m.pair) {
         m.single_want = want & ~m.pair_want;
         m.pair_plan = sq;
-        m.pair_plan.ws_bytes = sq.nsplit > 1 ? __builtin_popcount(m.pair_want) * sq.ws_bytes : 0;
+        m.pair_plan.ws_bytes = sq.copy_bytes + __builtin_popcount(m.pair_want) * (sq.ws_bytes - sq.copy_bytes);
         m.ws_bytes = m.pair_plan.ws_bytes;
     } else {
         m.pair_want = 0;
@@ -498,13 +560,16 @@ pex_status pex_stat_noalloc(const void* X, const void* G, int64_t B, int64_t T, 
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return PEX_ERR_PHI;
     const size_t limit = (size_t)PEX_NOALLOC_SCRATCH_BYTES;
     if (scratch_charge(B, T, din, dout, dt, (Mode)phi) > limit) return PEX_ERR_TOO_LARGE;
-    const size_t need = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
+    // copies of a layer of odd width that do not fit: the SIMT kernel
+    size_t need = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
+    const bool allow_pad = need <= limit;
+    if (!allow_pad) need = plan_stat(B, T, din, dout, dt, (Mode)phi, true, false).ws_bytes;
     if (need > limit) return PEX_ERR_TOO_LARGE;
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return PEX_ERR_HIP;
     // Every partial sum the reduction reads is written by the contraction of the same call, so nothing in the
     // scratch has to start at zero.
-    return run_stat(X, G, B, T, din, dout, dt, (Mode)phi, S, ws, need, (hipStream_t)stream);
+    return run_stat(X, G, B, T, din, dout, dt, (Mode)phi, S, ws, need, (hipStream_t)stream, nullptr, 0.f, allow_pad);
 }
 
 size_t pex_stat_multi_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want)
@@ -533,29 +598,35 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     }
     hipStream_t hs = (hipStream_t)stream;
+    bool made = m.pair;
     if (m.pair) {
         const StatPlan& p = m.pair_plan;
-        const int64_t n = din * dout;
+        const int64_t n = p.din * p.dout;
+        const void *x = X, *g = G;
+        if (make_copies(p, x, g, B * T, workspace, false, hs) != hipSuccess) return PEX_ERR_HIP;
+        float* partials = (float*)((char*)workspace + p.copy_bytes);
         float* po[3] = {nullptr, nullptr, nullptr};
         int k = 0;
         for (int phi = 0; phi < 3; ++phi)
-            if (m.pair_want & (1u << phi)) po[phi] = p.nsplit > 1 ? (float*)workspace + (int64_t)(k++) * p.nsplit * n : outs[phi];
-        const hipError_t e = p.kernel == 2 ? launch_stat_f32_multi(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs)
+            if (m.pair_want & (1u << phi)) po[phi] = p.nsplit > 1 ? partials + (int64_t)(k++) * p.nsplit * n : outs[phi];
+        const hipError_t e = p.kernel == 2 ? launch_stat_f32_multi(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
                              : (__builtin_popcount(m.pair_want) == 3)
-                                 ? launch_stat_bf16_triple(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs)
-                                 : launch_stat_bf16_pair(X, G, B, T, din, dout, p, po[0], po[1], po[2], hs);
+                                 ? launch_stat_bf16_triple(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
+                                 : launch_stat_bf16_pair(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs);
         if (e != hipSuccess) return PEX_ERR_HIP;
         if (p.nsplit > 1) {
             ReduceOutputs io{};
             int count = 0;
             for (int phi = 0; phi < 3; ++phi)
                 if (po[phi]) { io.partial[count] = po[phi]; io.S[count++] = outs[phi]; }
-            if (launch_reduce_partials(io, count, p.nsplit, n, 1, n, 0, 0, hs) != hipSuccess) return PEX_ERR_HIP;
+            if (reduce_whole(io, count, p, hs) != hipSuccess) return PEX_ERR_HIP;
         }
     }
     for (int phi = 0; phi < 3; ++phi) {
         if (!(m.single_want & (1u << phi))) continue;
-        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs);
+        // what runs alone beside a shared contraction, or after another single one, finds the padded copies made
+        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs, nullptr, 0.f, true, made);
+        made = true;
         if (st != PEX_OK) return st;
     }
     return PEX_OK;
@@ -612,25 +683,28 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
     if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     hipStream_t hs = (hipStream_t)stream;
-    float* partial = (float*)workspace;
+    char* front = (char*)workspace + plan.copy_bytes;
+    float* partial = (float*)front;
+    if (make_copies(plan, X, G, B * T, workspace, false, hs) != hipSuccess) return PEX_ERR_HIP;
+    const int64_t kin = plan.din, kout = plan.dout;
     hipError_t e;
     int64_t nparts;
     if (plan.gram_wide) {
         nparts = gram_wide_partials(T);
-        void* park = (char*)workspace + (((size_t)nparts * (size_t)B * sizeof(float) + 255) & ~(size_t)255);
-        e = launch_gram_wide(X, G, B, T, din, dout, partial, park, hs);
+        void* park = front + (((size_t)nparts * (size_t)B * sizeof(float) + 255) & ~(size_t)255);
+        e = launch_gram_wide(X, G, B, T, kin, kout, partial, park, hs);
     } else if (plan.gram) {
         nparts = gram_norm_partials(T);
-        e = launch_gram_norms(X, G, B, T, din, dout, partial, hs);
+        e = launch_gram_norms(X, G, B, T, kin, kout, partial, hs);
     } else if (plan.kernel == 1) {
-        nparts = bf16_norm_partials(din, dout);
-        e = launch_norms_bf16(X, G, B, T, din, dout, plan, partial, hs);
+        nparts = bf16_norm_partials(kin, kout);
+        e = launch_norms_bf16(X, G, B, T, kin, kout, plan, partial, hs);
     } else if (plan.kernel == 2) {
-        nparts = f32_norm_partials(din, dout);
-        e = launch_stat_f32(X, G, B, T, din, dout, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
+        nparts = f32_norm_partials(kin, kout);
+        e = launch_stat_f32(X, G, B, T, kin, kout, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
     } else {
-        nparts = generic_norm_partials(din, dout);
-        e = launch_stat_generic(X, G, B, T, din, dout, dt, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
+        nparts = generic_norm_partials(kin, kout);
+        e = launch_stat_generic(X, G, B, T, kin, kout, dt, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
     }
     if (e != hipSuccess) return PEX_ERR_HIP;
     return launch_reduce_norms(partial, nparts, B, N, hs) == hipSuccess ? PEX_OK : PEX_ERR_HIP;

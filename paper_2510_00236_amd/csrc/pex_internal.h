@@ -22,22 +22,27 @@ struct StatPlan {
     int kernel;        // 0 = generic SIMT kernel (odd shapes), 1 = bf16 MFMA kernel, 2 = fp32 MFMA kernel
     int nsplit;        // number of groups the batch (or, for plain contractions, B*T) is split into
     int64_t per_split; // examples (or rows of B*T) per group
-    size_t presq_bytes; // per-token square through pre-squared copies of X and G: their size (256-byte multiple), else 0
+    int64_t din, dout;           // widths of the operands as the kernels see them: the layer's, or those of padded copies
+    int64_t out_rows, out_cols;  // the layer's own widths
+    bool copy_x, copy_g;         // copies of the operands at the front of the workspace (X's first): rows padded to whole 16-byte
+                                 // chunks (bf16 layers of odd width), or squares (per-token square)
+    size_t copy_bytes;           // their size (256-byte multiple)
     int64_t wide_cols; // bf16, one statistic on two register tiles: columns [0, wide_cols) of S run on 256 x 192 blocks as
                        // wide_nsplit groups of wide_per_split examples; nsplit / per_split then describe the remaining columns only
     int wide_nsplit;
     int64_t wide_per_split;
-    size_t wide_ws_bytes; // partial sums of the wide part (first in the workspace after the squared copies), 0 if unsplit
+    size_t wide_ws_bytes; // partial sums of the wide part (first in the workspace after the copies), 0 if unsplit
     bool mem_fold;     // bf16, one statistic that would need two register tiles: 256 x 256 blocks, phi(M_b) added to the output
                        // in memory at the end of every example (nsplit / per_split describe the whole layer, wide_cols = 0)
     bool sign_bytes;   // MODE_SIGN on bf16 layers, split batch: the partial counts are bytes (per tile layout), not fp32
     bool gram;         // MODE_NORMS on bf16 layers: through the T x T Gram matrices instead of the contraction
     bool gram_wide;    // ... on 256 x 256 blocks whose X X^T part waits in the workspace (after the partials, 256-byte aligned)
-    size_t ws_bytes;   // presq_bytes + wide_ws_bytes + (nsplit > 1 ? nsplit * din * (dout - wide_cols) * 4 : 0)
+    size_t ws_bytes;   // copy_bytes + wide_ws_bytes + (nsplit > 1 ? nsplit * din * (dout - wide_cols) * 4 : 0)
 };
 
-// allow_wide = false keeps the plan on one block shape (the launches that produce several statistics at once need it)
-StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide = true);
+// allow_wide = false keeps the plan on one block shape (the launches that produce several statistics at once need it);
+// allow_pad = false keeps bf16 layers of odd width on the SIMT kernel
+StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide = true, bool allow_pad = true);
 
 // Launchers.  `out` is S when plan.nsplit == 1, else the workspace holding [nsplit][din][dout] partials.
 // MODE_WEIGHTED reads one weight per example from `weight`; MODE_NORMS writes no S but one partial of ||M_b||^2 per
@@ -92,6 +97,12 @@ hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, i
 bool f32_bytes_suffice(const StatPlan& plan);
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
                                  float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
+// Copies of bf16 operands [rows, width] with rows of padded_width(width) elements, zero-filled; an operand whose output
+// is NULL is left out
+int64_t padded_width(int64_t width);
+bool pad_supports(int64_t rows, int64_t din, int64_t dout);
+hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout,
+                           hipStream_t stream);
 // out[i] = bf16(in[i]^2) (square in fp32, round to nearest even) for n bf16 values, n a multiple of 8
 hipError_t launch_square_bf16(const void* in, void* out, int64_t n, hipStream_t stream);
 void bf16_tile_shape(Mode mode, int64_t B, int* bm, int* bn);

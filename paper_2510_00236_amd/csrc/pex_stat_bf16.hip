@@ -65,6 +65,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "pex_bf16.h"
 #include "pex_internal.h"
 #include "pex_lds_dma.h"
 #include "pex_tile_map.h"
@@ -111,16 +112,6 @@ __device__ __forceinline__ void mem_add_f32(float v, uint32_t voff, uint32_t sof
 {
     uint32_t at;
     asm volatile("v_add_u32 %0, %2, %3\n\tbuffer_atomic_add_f32 %1, %0, %4, 0 offen" : "=&v"(at) : "v"(v), "v"(voff), "s"(soff), "s"(rsrc) : "memory");
-}
-
-// two bf16 values -> squares in fp32 -> two bf16 (round to nearest even, one packed conversion); zero stays zero
-__device__ __forceinline__ uint32_t square_pair_rne(uint32_t packed)
-{
-    typedef __attribute__((ext_vector_type(2))) float float2_t;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-    const float lo = __uint_as_float(packed << 16), hi = __uint_as_float(packed & 0xffff0000u);
-    const float2_t sq = {lo * lo, hi * hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(sq, bf16x2_t));
 }
 
 // sign(m) in {-1, 0, +1} as a float without compares: scaling by 2^200 sends every non-zero value (denormals
@@ -237,6 +228,7 @@ __device__ __forceinline__ int chunk_at_position(int pos, int r)
 template <typename TL, int OUTS>
 __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ G,
                                                               int64_t rows_total, int seg_len, int din, int dout, int ldg, int ldo,
+                                                              int store_rows, int store_cols,
                                                               int64_t rows_per_split, int tiles_m, int tiles_n,
                                                               float* __restrict__ out_id, float* __restrict__ out_sq,
                                                               float* __restrict__ out_sg, const float* __restrict__ weight,
@@ -413,12 +405,13 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
     [[maybe_unused]] int4_t mem_rsrc;
     if constexpr (TO_MEM) {
         float* base = (HAS_W ? out_id : out_sq) + (int64_t)split * din * ldo + (int64_t)i0 * ldo + j0;
-        const int rows_valid = din_avail < BM ? din_avail : BM, cols_valid = dout_avail < BN ? dout_avail : BN;
-        mem_rsrc = make_rsrc(base, (uint32_t)(((rows_valid - 1) * ldo + cols_valid) * 4));
+        const int rows_left = store_rows - i0, cols_left = store_cols - j0;
+        const int rows_valid = rows_left < BM ? rows_left : BM, cols_valid = cols_left < BN ? cols_left : BN;
+        mem_rsrc = make_rsrc(base, rows_valid > 0 && cols_valid > 0 ? (uint32_t)(((rows_valid - 1) * ldo + cols_valid) * 4) : 0u);
 #pragma unroll
         for (int c = 0; c < FN; ++c) {
             const int j = wn * TL::WN + c * 16 + li;
-            mem_off[c] = j < dout_avail ? (uint32_t)(((wm * TL::WM + 4 * blk) * ldo + j) * 4) : 0x80000000u;
+            mem_off[c] = j < store_cols - j0 ? (uint32_t)(((wm * TL::WM + 4 * blk) * ldo + j) * 4) : 0x80000000u;
         }
     }
 
@@ -634,7 +627,7 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
         }
     }
     // outputs have their own row pitch: S itself (pointing at the first column of the range, pitch of the whole
-    // layer) or partials [split][din][ldo]
+    // layer) or partials [split][din][ldo]; store_rows and store_cols end what is written of it
     const int64_t split_off = (int64_t)split * din * ldo;
     const int jn = lane % 16, ib = 4 * (lane / 16);
 #pragma unroll
@@ -645,7 +638,7 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = i0 + wm * TL::WM + a * 16 + ib + r;
-                if (i < din && j < dout) {
+                if (i < store_rows && j < store_cols) {
                     const int64_t e = split_off + (int64_t)i * ldo + j;
                     if constexpr (!PER_EXAMPLE) out_id[e] = acc[a][c][r];
                     if constexpr (HAS_ID) out_id[e] = acc_id[a][c][r];
@@ -698,11 +691,18 @@ hipError_t launch_one(const uint16_t* X, const uint16_t* G, int64_t B, int64_t T
 {
     constexpr bool PER_EXAMPLE = !(OUTS == OUT_ID || OUTS == OUT_TOKEN);
     const int64_t ldg = dout;
-    int64_t ldo = dout;
+    int64_t ldo = dout, store_rows = din, store_cols = dout;
     if (range.ncols >= 0) {
         G += range.col0;
         dout = range.ncols;
         ldo = range.ldo;
+        store_cols = range.ncols;
+    }
+    if (plan.nsplit == 1) {        // S itself, which has the layer's own widths
+        ldo = plan.out_cols;
+        store_rows = plan.out_rows;
+        const int64_t left = plan.out_cols - (range.ncols >= 0 ? range.col0 : 0);
+        if (store_cols > left) store_cols = left;
     }
     const int tiles_m = (int)((din + TL::BM - 1) / TL::BM), tiles_n = (int)((dout + TL::BN - 1) / TL::BN);
     const int64_t rows_per_split = PER_EXAMPLE ? plan.per_split * T : plan.per_split;
@@ -713,8 +713,8 @@ hipError_t launch_one(const uint16_t* X, const uint16_t* G, int64_t B, int64_t T
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES); });
     if (attr_err != hipSuccess) return attr_err;
     const dim3 grid((unsigned)(tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
-    kern<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)T, (int)din, (int)dout, (int)ldg, (int)ldo, rows_per_split, tiles_m,
-                                                 tiles_n, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, byte_partials ? 1 : 0);
+    kern<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)T, (int)din, (int)dout, (int)ldg, (int)ldo, (int)store_rows,
+                                                 (int)store_cols, rows_per_split, tiles_m, tiles_n, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, byte_partials ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -796,7 +796,8 @@ constexpr int quad_load_slot(int i)
 
 __global__ __launch_bounds__(QuadTile::NT, 1) void stat_bf16_quad_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ G,
                                                                          int64_t rows_total, int din, int dout, int64_t rows_per_split,
-                                                                         int tiles_m, int tiles_n, float* __restrict__ out)
+                                                                         int tiles_m, int tiles_n, int ldo, int store_rows, int store_cols,
+                                                                         float* __restrict__ out)
 {
     using TL = QuadTile;
     constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, NS = TL::NS, FM = TL::FM, FN = TL::FN;
@@ -963,7 +964,7 @@ __global__ __launch_bounds__(QuadTile::NT, 1) void stat_bf16_quad_kernel(const u
     wait_vmcnt<0>();   // drain the (empty) loads issued past the end before the LDS is released
 
     // ---- epilogue: lane holds column (lane%16), rows 4*(lane/16) + r of each 16x16 tile
-    const int64_t split_off = (int64_t)split * din * dout;
+    const int64_t split_off = (int64_t)split * din * ldo;
     const int jn = lane % 16, ib = 4 * (lane / 16);
 #pragma unroll
     for (int a = 0; a < FM; ++a)
@@ -973,7 +974,7 @@ __global__ __launch_bounds__(QuadTile::NT, 1) void stat_bf16_quad_kernel(const u
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = i0 + wm * TL::WM + a * 16 + ib + r;
-                if (i < din && j < dout) out[split_off + (int64_t)i * dout + j] = acc[a][c][r];
+                if (i < store_rows && j < store_cols) out[split_off + (int64_t)i * ldo + j] = acc[a][c][r];
             }
         }
 }
@@ -990,8 +991,11 @@ hipError_t launch_quad(const uint16_t* X, const uint16_t* G, int64_t B, int64_t 
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [] { attr_err = hipFuncSetAttribute((const void*)stat_bf16_quad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES); });
     if (attr_err != hipSuccess) return attr_err;
+    // S itself has the layer's own widths, partial sums those of the operands
+    const int64_t ldo = plan.nsplit == 1 ? plan.out_cols : dout, store_rows = plan.nsplit == 1 ? plan.out_rows : din, store_cols = ldo;
     const dim3 grid((unsigned)(tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
-    stat_bf16_quad_kernel<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)din, (int)dout, plan.per_split, tiles_m, tiles_n, out);
+    stat_bf16_quad_kernel<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)din, (int)dout, plan.per_split, tiles_m, tiles_n, (int)ldo,
+                                                             (int)store_rows, (int)store_cols, out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,118 @@
+"""bf16 layers whose rows are not whole 16-byte chunks, on padded copies: every statistic against the fp64 oracle, on every
+block shape and route the planner can choose, outputs of the layer's own widths inside a larger buffer (nothing may be
+written around them)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_00236_amd as pex
+import synth_inputs as si
+from oracle import norms as on
+from parity_util import assert_real_stat, assert_sign_stat
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+f64 = lambda t: t.cpu().numpy().astype(np.float64)
+
+# (B, T, din, dout), long enough that the planner takes the copies: X, G or both of odd width
+SHAPES = [
+    (3, 180, 65, 72),
+    (2, 177, 264, 129),
+    (4, 190, 257, 33),      # one feature beyond a 256-row block; padded to 40 columns
+    (5, 300, 193, 391),     # the last column tile holds 7 features
+    (3, 200, 250, 770),     # even widths that are no multiples of 8
+]
+
+
+class Guarded:
+    """A [rows, cols] fp32 output full of NaN between two strips of a sentinel."""
+
+    def __init__(self, rows, cols):
+        self.n = rows * cols
+        self.buf = torch.full((self.n + 128,), -7.0, device=DEV)
+        self.view = self.buf[64:64 + self.n].view(rows, cols)
+        self.view.fill_(float("nan"))
+
+    def value(self):
+        assert (self.buf[:64] == -7).all() and (self.buf[64 + self.n:] == -7).all(), "written outside the output"
+        return f64(self.view)
+
+
+def _padded(B, T, din, dout):
+    odd = (din % 8 != 0) * -(-din // 8) * 8 + (dout % 8 != 0) * -(-dout // 8) * 8
+    assert pex.pex_stat_workspace_bytes(B, T, din, dout, pex.PEX_BF16, "square") >= 2 * B * T * odd, "not on the copies"
+
+
+@pytest.mark.parametrize("options", [{}, {"wide_blocks": 2}, {"wide_blocks": 0, "memory_fold": 0}, {"memory_fold": 2}, {"max_split": 1}])
+@pytest.mark.parametrize("B,T,din,dout", SHAPES)
+def test_statistics(pex_option, B, T, din, dout, options):
+    for k, v in options.items():
+        pex_option(k, v)
+    _padded(B, T, din, dout)
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=B * 17 + T)
+    Xd, Gd = X.to(DEV), G.to(DEV)
+    Xn, Gn = si.widen(X), si.widen(G)
+    st = oracle.stat(Xn, Gn)
+    tag = f"B{B} T{T} {din}x{dout} {options}"
+    out = {phi: Guarded(din, dout) for phi in ("identity", "square", "sign")}
+    for phi, o in out.items():
+        pex.pex_stat(Xd, Gd, phi, S=o.view)
+    assert_real_stat(out["identity"].value(), st.S_id, "bf16", f"{tag} identity", elementwise=False)
+    assert_real_stat(out["square"].value(), st.S_sq, "bf16", f"{tag} square", elementwise=B >= 3)
+    assert_sign_stat(out["sign"].value(), st.S_sign, st.amb, f"{tag} sign")
+    w = torch.linspace(-1.0, 2.0, B)
+    o = Guarded(din, dout)
+    pex.pex_weighted_sum(Xd, Gd, w.to(DEV), S=o.view)
+    assert_real_stat(o.value(), on.weighted_sum(Xn, Gn, w.numpy()), "bf16", f"{tag} weighted", elementwise=False)
+    o = Guarded(din, dout)
+    pex.pex_stat_power(Xd, Gd, 1.5, S=o.view)
+    ref = on.power_stat(Xn, Gn, 1.5)
+    # as in the power tests: the contraction's rounding amplified by the exponent, plus that of log2 / exp2
+    assert (np.abs(o.value() - ref) <= 1e-4 * ref + 1e-5 * ref.max()).all(), f"{tag} power"
+
+
+@pytest.mark.parametrize("want", [("identity", "square"), ("identity", "sign"), ("square", "sign"), ("identity", "square", "sign")])
+@pytest.mark.parametrize("B,T,din,dout", SHAPES[:4] + [(300, 4, 129, 250)])
+def test_statistics_sharing_a_contraction(pex_option, B, T, din, dout, want):
+    """With 300 examples in one group sign runs alone beside identity and square, on the copies they made."""
+    if B > 127:
+        pex_option("max_split", 1)
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=B + T)
+    st = oracle.stat(si.widen(X), si.widen(G))
+    out = {k: Guarded(din, dout) for k in want}
+    pex.pex_stat_multi(X.to(DEV), G.to(DEV), want, out={k: o.view for k, o in out.items()})
+    if "identity" in want:
+        assert_real_stat(out["identity"].value(), st.S_id, "bf16", "identity", elementwise=False)
+    if "square" in want:
+        assert_real_stat(out["square"].value(), st.S_sq, "bf16", "square", elementwise=B >= 3)
+    if "sign" in want:
+        assert_sign_stat(out["sign"].value(), st.S_sign, st.amb, "sign")
+
+
+@pytest.mark.parametrize("route", [0, 1, 2, 3])
+@pytest.mark.parametrize("B,T,din,dout", SHAPES)
+def test_norms(pex_option, B, T, din, dout, route):
+    pex_option("gram_norms", route)
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=B * 7 + T)
+    ref = on.example_norms(si.widen(X), si.widen(G))
+    N = f64(pex.pex_example_norms(X.to(DEV), G.to(DEV)))
+    assert (np.abs(N - ref) <= 2e-5 * ref.max()).all() and (np.abs(N - ref) <= 1e-4 * ref).all(), (N, ref)
+
+
+def test_without_a_workspace_large_copies_stay_on_the_simt_kernel():
+    """Copies of 33 MB do not fit the library's scratch: the call still succeeds, by the other kernel."""
+    B, T, din, dout = 4, 4160, 1001, 64
+    assert pex.pex_stat_workspace_bytes(B, T, din, dout, pex.PEX_BF16, "identity") > pex.NOALLOC_SCRATCH_BYTES
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=2)
+    o = Guarded(din, dout)
+    pex.pex_stat_noalloc(X.to(DEV), G.to(DEV), "identity", o.view)
+    ref = X.reshape(-1, din).double().t() @ G.reshape(-1, dout).double()
+    assert_real_stat(o.value(), ref.numpy(), "bf16", "identity", elementwise=False)
+    # and where they fit, pex_stat's bits
+    B, T, din, dout = SHAPES[0]
+    X, G = (t.to(DEV) for t in si.custom(B, T, din, dout, dtype="bf16", seed=3))
+    o = Guarded(din, dout)
+    pex.pex_stat_noalloc(X, G, "square", o.view)
+    assert torch.equal(o.view, pex.pex_stat(X, G, "square"))
