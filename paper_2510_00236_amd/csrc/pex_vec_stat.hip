@@ -10,8 +10,8 @@
 //   vec_partial_kernel   block = 64 column lanes x 4 row lanes; a lane owns VEC consecutive columns (16 bytes) and
 //                        every 4th row of one range of tokens of one example; the four row lanes are summed
 //                        through LDS and the block writes partial[b][range][columns] in fp32;
-//   vec_finalize_kernel  per column: v_b = sum over ranges (ascending), then the requested phi, then sum over b
-//                        (examples dealt to four lanes, combined in lane order).
+//   vec_finalize_kernel  per column: v_b = sum over ranges, then the requested phi, then sum over b (both dealt to the
+//                        lanes of a block, combined in a fixed order).
 // The partial sums are B * ranges * d floats: the per-example gradients of a *vector* parameter, which is the one
 // place where holding them is cheap (B*d, not B*din*dout).
 #include "pex_internal.h"
@@ -97,43 +97,104 @@ __global__ __launch_bounds__(CW * RW) void vec_partial_kernel(const TIn* __restr
     }
 }
 
-// per column: v_b = sum over ranges (ascending); the examples are dealt to four lanes (b mod 4), each sums its
-// phi(v_b) in ascending b, and the four lanes are combined in lane order
-__global__ __launch_bounds__(CW * RW) void vec_finalize_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
-                                                               float* __restrict__ s_id, float* __restrict__ s_sq,
-                                                               float* __restrict__ s_sign)
+// Second pass: per column v_b = sum over the ranges, phi, sum over the examples.  A block is 4 column lanes of VEC columns x
+// EL example lanes x RL range lanes (256 in all); example b belongs to example lane b mod EL, its range r to range lane
+// r mod RL.  Range lanes are added in order through LDS, then phi is applied; the example lanes' sums are added pairwise,
+// always in the same order.
+// Bound by latency (the partial sums are a few MB, fresh in the caches): so a block owns few columns -- d / (4 VEC) blocks --
+// and every lane has eight loads in flight of a chain of nrange / RL * B / EL.  Measured, d = 768 / 2304 / 3072, B = 64, 16 / 6 / 5
+// ranges: 5.5 / 4.8 / 4.7 us (64 columns x 4 example lanes per block, one column per lane, before: 14 / 26 / 23 us).
+template <int VEC, int EL, int RL>
+__global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
+                                                           float* __restrict__ s_id, float* __restrict__ s_sq,
+                                                           float* __restrict__ s_sign)
 {
-    __shared__ float red[3][RW][CW];
-    const int cl = threadIdx.x % CW, bl = threadIdx.x / CW;
-    const int64_t j = (int64_t)blockIdx.x * CW + cl;
-    float a_id = 0.f, a_sq = 0.f, a_sg = 0.f;
-    if (j < d) {
-        for (int b = bl; b < B; b += RW) {
+    static_assert(4 * EL * RL == 256, "one lane per column group, example lane and range lane");
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef f4 __attribute__((aligned(4))) f4_u;
+    __shared__ float red[EL * RL][4 * VEC];
+    const int cl = threadIdx.x % 4, rl = (threadIdx.x / 4) % RL, el = threadIdx.x / (4 * RL);
+    const int64_t j = ((int64_t)blockIdx.x * 4 + cl) * VEC;
+    float a_id[VEC], a_sq[VEC], a_sg[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) a_id[e] = a_sq[e] = a_sg[e] = 0.f;
+    for (int b0 = 0; b0 < B; b0 += EL) {
+        const int b = b0 + el;
+        float v[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = 0.f;
+        if (b < B && j < d) {
             const float* p = partial + (int64_t)b * nrange * d + j;
-            float v = 0.f;
-            int r = 0;
-            for (; r + 8 <= nrange; r += 8) {
-                float x[8];
+            auto load = [&](int r, float (&x)[VEC]) {
+                if constexpr (VEC == 4) {
+                    const f4 q = *(const f4_u*)(p + (int64_t)r * d);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(r + u) * d];
+                    for (int e = 0; e < 4; ++e) x[e] = q[e];
+                } else x[0] = p[(int64_t)r * d];
+            };
+            int r = rl;
+            for (; r + 7 * RL < nrange; r += 8 * RL) {
+                float x[8][VEC];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v += x[u];
+                for (int u = 0; u < 8; ++u) load(r + u * RL, x[u]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) v[e] += x[u][e];
             }
-            for (; r < nrange; ++r) v += p[(int64_t)r * d];
-            a_id += v;
-            a_sq = fmaf(v, v, a_sq);
-            a_sg += (float)((v > 0.f) - (v < 0.f));
+            // the rest of the chain, at most seven: all in flight, those past the end as zeros
+            float x[7][VEC];
+#pragma unroll
+            for (int u = 0; u < 7; ++u) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) x[u][e] = 0.f;
+                if (r + u * RL < nrange) load(r + u * RL, x[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 7; ++u)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[e] += x[u][e];
+        }
+        if constexpr (RL > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) red[el * RL + rl][cl * VEC + e] = v[e];
+            __syncthreads();
+            if (rl == 0) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    v[e] = red[el * RL][cl * VEC + e];
+#pragma unroll
+                    for (int k = 1; k < RL; ++k) v[e] += red[el * RL + k][cl * VEC + e];
+                }
+            }
+        }
+        if (rl == 0 && b < B) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                a_id[e] += v[e];
+                a_sq[e] = fmaf(v[e], v[e], a_sq[e]);
+                a_sg[e] += (float)((v[e] > 0.f) - (v[e] < 0.f));
+            }
         }
     }
-    red[0][bl][cl] = a_id;
-    red[1][bl][cl] = a_sq;
-    red[2][bl][cl] = a_sg;
-    __syncthreads();
-    if (bl == 0 && j < d) {
-        if (s_id) s_id[j] = ((red[0][0][cl] + red[0][1][cl]) + red[0][2][cl]) + red[0][3][cl];
-        if (s_sq) s_sq[j] = ((red[1][0][cl] + red[1][1][cl]) + red[1][2][cl]) + red[1][3][cl];
-        if (s_sign) s_sign[j] = ((red[2][0][cl] + red[2][1][cl]) + red[2][2][cl]) + red[2][3][cl];
-    }
+    auto finish = [&](float* out, const float (&a)[VEC]) {
+        __syncthreads();
+        if (rl == 0) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) red[el][cl * VEC + e] = a[e];
+        }
+        for (int h = EL / 2; h >= 1; h >>= 1) {
+            __syncthreads();
+            for (int t = threadIdx.x; t < h * 4 * VEC; t += 256) red[t / (4 * VEC)][t % (4 * VEC)] += red[t / (4 * VEC) + h][t % (4 * VEC)];
+        }
+        __syncthreads();
+        const int64_t c = (int64_t)blockIdx.x * 4 * VEC + threadIdx.x;
+        if (threadIdx.x < 4 * VEC && c < d) out[c] = red[0][threadIdx.x];
+    };
+    if (s_id) finish(s_id, a_id);
+    if (s_sq) finish(s_sq, a_sq);
+    if (s_sign) finish(s_sign, a_sg);
 }
 
 template <typename TIn>
@@ -186,7 +247,13 @@ hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, i
     hipError_t e = dt == PEX_F32 ? launch_typed((const float*)A, (const float*)C, B, T, d, plan, partial, stream)
                                  : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
     if (e != hipSuccess) return e;
-    vec_finalize_kernel<<<dim3((unsigned)((d + CW - 1) / CW)), dim3(CW * RW), 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign);
+    // example lanes for the batch, the rest of the block to the ranges
+    const bool quads = d % 4 == 0;
+    const dim3 grid((unsigned)((d + (quads ? 15 : 3)) / (quads ? 16 : 4))), block(256);
+    auto go = [&](auto kern) { kern<<<grid, block, 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign); };
+    if (B > 16) quads ? go(vec_finalize_kernel<4, 64, 1>) : go(vec_finalize_kernel<1, 64, 1>);
+    else if (B > 4) quads ? go(vec_finalize_kernel<4, 16, 4>) : go(vec_finalize_kernel<1, 16, 4>);
+    else quads ? go(vec_finalize_kernel<4, 4, 16>) : go(vec_finalize_kernel<1, 4, 16>);
     return hipGetLastError();
 }
 
