@@ -23,7 +23,7 @@
 namespace pex {
 namespace {
 
-constexpr int SORT_MAX_BLOCKS = 64;   // workgroups of the sort; a workgroup's tile is a multiple of 2048 keys
+constexpr int SORT_MAX_BLOCKS = 64;   // workgroups of the sort; a workgroup's tile is a multiple of 1024 keys
 
 template <typename TId>
 __device__ __forceinline__ int load_key(const TId* __restrict__ ids, int p, int V)
@@ -35,8 +35,9 @@ __device__ __forceinline__ int load_key(const TId* __restrict__ ids, int p, int 
 // Stable least-significant-digit radix sort, 8 bits per pass.  hist[block * 256 + digit] counts the keys of that
 // block's tile *of the pass's input* with that digit (the tiles of a later pass hold other keys than those of the
 // first, so every pass counts its own input; the counting is in LDS, where many equal keys cost little).
-// A tile is a multiple of 2048 keys: 8 rounds of 256 at a time, their loads issued together.
-constexpr int SORT_BATCH = 8;
+// A tile is a multiple of 1024 keys: 4 rounds of 256 at a time, their loads issued together (8 rounds left half of the 64
+// workgroups out at 65536 positions: 4 us more over the four launches).
+constexpr int SORT_BATCH = 4;
 
 template <typename TId, bool FIRST>
 __global__ __launch_bounds__(256) void sort_hist_kernel(const TId* __restrict__ ids, const int* __restrict__ keys_in, int N, int V,
@@ -197,17 +198,26 @@ struct Chunk {
     }
 };
 
-template <int CH>
+// OUTPUT: rows of S, which nothing reads soon: past the caches (two statistics of a GPT-2 vocabulary are 309 MB; 141 -> 130 us)
+template <int CH, bool OUTPUT = true>
 __device__ __forceinline__ void store_chunk(float* p, const float (&v)[CH])
 {
     if constexpr (CH == 1) p[0] = v[0];
     else {
+        typedef __attribute__((ext_vector_type(4))) float f4;
 #pragma unroll
-        for (int e = 0; e < CH; e += 4) *(float4*)(p + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+        for (int e = 0; e < CH; e += 4) {
+            const f4 q = {v[e], v[e + 1], v[e + 2], v[e + 3]};
+            if constexpr (OUTPUT) __builtin_nontemporal_store(q, (f4*)(p + e));
+            else *(f4*)(p + e) = q;
+        }
     }
 }
 
-constexpr int EMB_WAVES = 16;    // waves of a workgroup
+// waves of a workgroup: two of 12 or three of 8 share a compute unit where 16 left the first half of a frequent token's run waiting
+// for the second (141 -> 135 us; 4 waves 6 us slower than 8); a slice of partial sums is EMB_WAVES * EMB_U positions, so fewer
+// waves cost workspace
+constexpr int EMB_WAVES = 12;
 constexpr int EMB_ZROWS = 8;     // vocabulary rows a zero-fill wave looks at
 constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent rows a lane keeps in flight
 constexpr int EMB_ALONE = 64;    // a vocabulary row with at most this many positions is done by one wave
@@ -287,7 +297,8 @@ struct RowAccumulator {
 };
 
 // WANT: bit 0 identity, bit 1 square, bit 2 sign.
-// grid.x = chunk workgroups, then zero-fill workgroups; grid.y = blocks of 64 * CH columns.
+// grid = chunk workgroups of every block of 64 * CH columns, then the zero-fill workgroups: the chunks are the long poles, the
+// zero fill runs under their tail (with the column blocks one after the other, each with its own tail, 149 against 141 us).
 //   chunk workgroup: wave i owns the sorted positions [c0, c0 + EMB_U) and with them every vocabulary row whose run
 //     starts there (a run may continue past the chunk).  It loads EMB_U cotangent rows at a time whatever rows and
 //     examples they belong to, then adds them in order.  Runs longer than EMB_ALONE are only noted; after a barrier
@@ -296,14 +307,16 @@ struct RowAccumulator {
 template <typename TIn, int CH, int WANT>
 __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* __restrict__ G, const int* __restrict__ row_start,
                                                                     const int* __restrict__ keys, const int* __restrict__ pos,
-                                                                    int N, int V, int T, int64_t d, int chunk_groups,
+                                                                    int N, int V, int T, int64_t d, int chunk_groups, int colblocks,
                                                                     float* __restrict__ partial, float* __restrict__ S_id,
                                                                     float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
     typedef Chunk<TIn, CH> Ck;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t col = ((int64_t)blockIdx.y * 64 + lane) * CH;
+    const bool zero_fill = (int)blockIdx.x >= chunk_groups * colblocks;
+    const int group = zero_fill ? (int)blockIdx.x - chunk_groups * colblocks : (int)blockIdx.x / colblocks;
+    const int64_t col = ((int64_t)(blockIdx.x % colblocks) * 64 + lane) * CH;
     const bool col_ok = col < d;
     auto store_row = [&](int v, const RowSums<CH>& sums) {
         if (!col_ok) return;
@@ -313,11 +326,10 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         if (WANT & 4) store_chunk<CH>(S_sg + o, sums.sg);
     };
 
-    if ((int)blockIdx.x >= chunk_groups) {
+    if (zero_fill) {
         // whole rows, all column blocks by the same wave: an empty row is one contiguous run of d floats, and empty
         // rows are often neighbours
-        if (blockIdx.y != 0) return;
-        const int v = (((int)blockIdx.x - chunk_groups) * EMB_WAVES + wave) * EMB_ZROWS + lane;
+        const int v = (group * EMB_WAVES + wave) * EMB_ZROWS + lane;
         const bool empty = lane < EMB_ZROWS && v < V && row_start[v] == row_start[v + 1];
         unsigned long long todo = __ballot(empty);
         RowSums<CH> zeros;
@@ -342,7 +354,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
     RowAccumulator<TIn, CH, WANT> ra;
     ra.start(T);
     {
-        const int64_t c0l = ((int64_t)blockIdx.x * EMB_WAVES + wave) * EMB_U;
+        const int64_t c0l = ((int64_t)group * EMB_WAVES + wave) * EMB_U;
         const int c0 = c0l < N ? (int)c0l : N;
         const int c1 = c0 + EMB_U < N ? c0 + EMB_U : N;
         int k0 = c0;
@@ -394,7 +406,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
     // examples that start there -- candidate -1 is the run that continues from the positions before sc0, candidate i the
     // run that starts among wave i's positions.  A run that lies inside [sc0, sc1) is finished here; of any other the
     // sums go to `partial` (slot 0: continues from before, slot 1: starts here and goes on) for embed_combine_kernel.
-    const int64_t sc0l = (int64_t)blockIdx.x * (EMB_WAVES * EMB_U);
+    const int64_t sc0l = (int64_t)group * (EMB_WAVES * EMB_U);
     const int sc0 = sc0l < N ? (int)sc0l : N;
     const int sc1 = sc0 + EMB_WAVES * EMB_U < N ? sc0 + EMB_WAVES * EMB_U : N;
     for (int c = -1; c < EMB_WAVES; ++c) {
@@ -462,10 +474,10 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
             }
             if (!from_before && !goes_on) store_row(hv, ra.sums);
             else if (col_ok) {
-                float* pr = partial + (((int64_t)blockIdx.x * 2 + (from_before ? 0 : 1)) * 3) * d + col;
-                if (WANT & 1) store_chunk<CH>(pr, ra.sums.id);
-                if (WANT & 2) store_chunk<CH>(pr + d, ra.sums.sq);
-                if (WANT & 4) store_chunk<CH>(pr + 2 * d, ra.sums.sg);
+                float* pr = partial + (((int64_t)group * 2 + (from_before ? 0 : 1)) * 3) * d + col;
+                if (WANT & 1) store_chunk<CH, false>(pr, ra.sums.id);
+                if (WANT & 2) store_chunk<CH, false>(pr + d, ra.sums.sq);
+                if (WANT & 4) store_chunk<CH, false>(pr + 2 * d, ra.sums.sg);
             }
         }
         __syncthreads();
@@ -522,7 +534,7 @@ EmbedLayout embed_layout(int64_t N, int64_t V, int64_t d)
     L.passes = (bits + 7) / 8;
     if (L.passes < 1) L.passes = 1;
     int64_t tile = (N + SORT_MAX_BLOCKS - 1) / SORT_MAX_BLOCKS;
-    tile = (tile + 2047) / 2048 * 2048;
+    tile = (tile + 1023) / 1024 * 1024;
     L.tile = (int)tile;
     L.nblocks = (int)((N + tile - 1) / tile);
     size_t o = 0;
@@ -578,8 +590,8 @@ hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, cons
     const int chunk_groups = (int)((N + per_group - 1) / per_group);
     const int zero_groups = (int)(((int64_t)V + EMB_WAVES * EMB_ZROWS - 1) / (EMB_WAVES * EMB_ZROWS));
     const unsigned colblocks = (unsigned)((d + 64 * CH - 1) / (64 * CH));
-    embed_rows_kernel<TIn, CH, WANT><<<dim3((unsigned)(chunk_groups + zero_groups), colblocks), dim3(EMB_WAVES * 64), 0, stream>>>(
-        G, row_start, keys, pos, N, V, T, d, chunk_groups, partial, S_id, S_sq, S_sg);
+    embed_rows_kernel<TIn, CH, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
+        G, row_start, keys, pos, N, V, T, d, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     embed_combine_kernel<CH, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, partial,
