@@ -7,6 +7,25 @@
 namespace pex {
 namespace {
 
+// 16-byte accesses, past the caches where STREAM: a tensor whose buffers exceed the memory-side cache evicts itself on every
+// pass (see `streams`)
+template <bool STREAM>
+__device__ __forceinline__ float4 load4(const float4* p)
+{
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    if constexpr (STREAM) {
+        const f4 q = __builtin_nontemporal_load((const f4*)p);
+        return make_float4(q[0], q[1], q[2], q[3]);
+    } else return *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void store4(float4* p, const float4& v)
+{
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    if constexpr (STREAM) __builtin_nontemporal_store(f4{v.x, v.y, v.z, v.w}, (f4*)p);
+    else *p = v;
+}
+
 struct AdamConsts {
     float beta1, one_m_beta1, beta2, one_m_beta2;
     float inv_bc1, inv_bc2;   // 1/(1-beta1^t), 1/(1-beta2^t)
@@ -40,7 +59,7 @@ __device__ __forceinline__ void adam_one(float& th, float& m, float& v, float si
 // over all parameters of the model (device memory, written by sum_squares_kernel); every per-example gradient is
 // multiplied by kappa = min(1, max_norm / (|grad_scale| * sqrt(*clip_sumsq))), i.e. the mean gradient by kappa and
 // the per-example second moment by kappa^2.
-template <int VARIANT>
+template <int VARIANT, bool STREAM>
 __global__ __launch_bounds__(256) void adam_update_kernel(float* __restrict__ theta, float* __restrict__ m,
                                                           float* __restrict__ v, const float* __restrict__ S_id,
                                                           const float* __restrict__ S_sq, int64_t n, AdamConsts k,
@@ -61,15 +80,15 @@ __global__ __launch_bounds__(256) void adam_update_kernel(float* __restrict__ th
     const float4* a4 = reinterpret_cast<const float4*>(S_id);
     const float4* q4 = reinterpret_cast<const float4*>(S_sq);
     for (int64_t e = gid; e < n4; e += stride) {
-        float4 t = th4[e], mm = m4[e], vv = v4[e];
-        const float4 a = a4[e];
+        float4 t = load4<STREAM>(th4 + e), mm = load4<STREAM>(m4 + e), vv = load4<STREAM>(v4 + e);
+        const float4 a = load4<STREAM>(a4 + e);
         float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (VARIANT != PEX_ADAM) q = q4[e];
+        if (VARIANT != PEX_ADAM) q = load4<STREAM>(q4 + e);
         adam_one<VARIANT>(t.x, mm.x, vv.x, a.x, q.x, k);
         adam_one<VARIANT>(t.y, mm.y, vv.y, a.y, q.y, k);
         adam_one<VARIANT>(t.z, mm.z, vv.z, a.z, q.z, k);
         adam_one<VARIANT>(t.w, mm.w, vv.w, a.w, q.w, k);
-        th4[e] = t; m4[e] = mm; v4[e] = vv;
+        store4<STREAM>(th4 + e, t); store4<STREAM>(m4 + e, mm); store4<STREAM>(v4 + e, vv);
     }
     for (int64_t e = n4 * 4 + gid; e < n; e += stride) {
         float t = theta[e], mm = m[e], vv = v[e];
@@ -81,7 +100,7 @@ __global__ __launch_bounds__(256) void adam_update_kernel(float* __restrict__ th
 // VARIANT: PEX_MICROSIGNSGD  m <- EMA(S/B), S = sum of per-example signs, step along m
 //          PEX_SIGNSGD       m <- EMA(sign(S)), S = sum of gradients,     step along m
 //          PEX_SIGNEMA       m <- EMA(S/B), S = sum of gradients,          step along sign(m)
-template <int VARIANT>
+template <int VARIANT, bool STREAM>
 __global__ __launch_bounds__(256) void signsgd_update_kernel(float* __restrict__ theta, float* __restrict__ m,
                                                              const float* __restrict__ S_sign, int64_t n, float lr,
                                                              float beta, float one_m_beta_over_B, float wd, float debias_mul)
@@ -100,10 +119,10 @@ __global__ __launch_bounds__(256) void signsgd_update_kernel(float* __restrict__
         t = t - lr * dir - wd * t;
     };
     for (int64_t e = gid; e < n4; e += stride) {
-        float4 t = th4[e], mm = m4[e];
-        const float4 s = s4[e];
+        float4 t = load4<STREAM>(th4 + e), mm = load4<STREAM>(m4 + e);
+        const float4 s = load4<STREAM>(s4 + e);
         one(t.x, mm.x, s.x); one(t.y, mm.y, s.y); one(t.z, mm.z, s.z); one(t.w, mm.w, s.w);
-        th4[e] = t; m4[e] = mm;
+        store4<STREAM>(th4 + e, t); store4<STREAM>(m4 + e, mm);
     }
     for (int64_t e = n4 * 4 + gid; e < n; e += stride) {
         float t = theta[e], mm = m[e];
@@ -129,7 +148,9 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-__global__ __launch_bounds__(256) void moment_track_kernel(float* __restrict__ ema_adam, float* __restrict__ ema_micro,
+// ONE: a single workgroup of 1024 does the whole tensor and writes the two sums themselves
+template <bool STREAM, bool ONE>
+__global__ __launch_bounds__(ONE ? 1024 : 256) void moment_track_kernel(float* __restrict__ ema_adam, float* __restrict__ ema_micro,
                                                            const float* __restrict__ S_id, const float* __restrict__ S_sq,
                                                            int64_t n, MomentConsts k, double* __restrict__ partial)
 {
@@ -150,37 +171,42 @@ __global__ __launch_bounds__(256) void moment_track_kernel(float* __restrict__ e
         sum_sigma2 += k.c_est * (qh - ah);
     };
     for (int64_t e = gid; e < n4; e += stride) {
-        float4 a = a4[e], q = q4[e];
-        const float4 si = i4[e], ss = s4[e];
+        float4 a = load4<STREAM>(a4 + e), q = load4<STREAM>(q4 + e);
+        const float4 si = load4<STREAM>(i4 + e), ss = load4<STREAM>(s4 + e);
         one(a.x, q.x, si.x, ss.x); one(a.y, q.y, si.y, ss.y); one(a.z, q.z, si.z, ss.z); one(a.w, q.w, si.w, ss.w);
-        a4[e] = a; q4[e] = q;
+        store4<STREAM>(a4 + e, a); store4<STREAM>(q4 + e, q);
     }
     for (int64_t e = n4 * 4 + gid; e < n; e += stride) {
         float a = ema_adam[e], q = ema_micro[e];
         one(a, q, S_id[e], S_sq[e]);
         ema_adam[e] = a; ema_micro[e] = q;
     }
-    __shared__ double red[4][2];
+    constexpr int WAVES = ONE ? 16 : 4;
+    __shared__ double red[WAVES][2];
     sum_mu2 = wave_sum(sum_mu2);
     sum_sigma2 = wave_sum(sum_sigma2);
     if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6][0] = sum_mu2; red[threadIdx.x >> 6][1] = sum_sigma2; }
     __syncthreads();
-    if (threadIdx.x < 2) partial[(int64_t)blockIdx.x * 2 + threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) t += red[w][threadIdx.x];
+        partial[(int64_t)blockIdx.x * 2 + threadIdx.x] = t;
+    }
 }
 
 __global__ __launch_bounds__(1024) void moment_finalize_kernel(const double* __restrict__ partial, int nparts, double* __restrict__ sums)
 {
-    // thread t adds partials t, t + 1024, ... (eight loads in flight), then the usual fixed-order tree
-    double s0 = 0.0, s1 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 7 * 1024 < nparts; i += 8 * 1024) {
-        double a[8], b[8];
+    // at most 8192 pairs: thread t adds t, t + 1024, ..., all in flight, then the usual fixed-order tree
+    double s0 = 0.0, s1 = 0.0, a[8], b[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) { a[u] = partial[2 * (i + u * 1024)]; b[u] = partial[2 * (i + u * 1024) + 1]; }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { s0 += a[u]; s1 += b[u]; }
+    for (int u = 0; u < 8; ++u) {
+        const int i = (int)threadIdx.x + u * 1024;
+        a[u] = i < nparts ? partial[2 * i] : 0.0;
+        b[u] = i < nparts ? partial[2 * i + 1] : 0.0;
     }
-    for (; i < nparts; i += 1024) { s0 += partial[2 * i]; s1 += partial[2 * i + 1]; }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { s0 += a[u]; s1 += b[u]; }
     __shared__ double red[16][2];
     s0 = wave_sum(s0);
     s1 = wave_sum(s1);
@@ -196,7 +222,10 @@ __global__ __launch_bounds__(1024) void moment_finalize_kernel(const double* __r
 
 // acc[0] (+)= sum of x^2, squares and sums in fp64, fixed order (per thread, wave butterfly, workgroup, then one
 // workgroup over the partials): the global gradient norm the clipping needs, reproducible bit for bit.
-__global__ __launch_bounds__(256) void sum_squares_kernel(const float* __restrict__ x, int64_t n, double* __restrict__ partial)
+// ONE: a single workgroup of 1024 does the whole tensor and writes the sum itself (partial = acc)
+template <bool ONE>
+__global__ __launch_bounds__(ONE ? 1024 : 256) void sum_squares_kernel(const float* __restrict__ x, int64_t n, double* __restrict__ partial,
+                                                                       int accumulate)
 {
     const int64_t n4 = n / 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -208,18 +237,28 @@ __global__ __launch_bounds__(256) void sum_squares_kernel(const float* __restric
         s += ((double)a.x * a.x + (double)a.y * a.y) + ((double)a.z * a.z + (double)a.w * a.w);
     }
     for (int64_t e = n4 * 4 + gid; e < n; e += stride) s += (double)x[e] * x[e];
-    __shared__ double red[4];
+    constexpr int WAVES = ONE ? 16 : 4;
+    __shared__ double red[WAVES];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) t += red[w];
+        partial[blockIdx.x] = ONE && accumulate ? partial[0] + t : t;
+    }
 }
 
 __global__ __launch_bounds__(1024) void sum_squares_finalize_kernel(const double* __restrict__ partial, int nparts, int accumulate,
                                                                     double* __restrict__ acc)
 {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += 1024) s += partial[i];
+    // at most 8192 partials: eight per lane, all in flight
+    double s = 0.0, v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = (int)threadIdx.x + u * 1024 < nparts ? partial[threadIdx.x + u * 1024] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
     __shared__ double red[16];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -239,6 +278,15 @@ inline unsigned update_grid(int64_t n)
     const int64_t cap = 256 * 32;   // 256 CUs x 32 workgroups: enough loads in flight, short tail (measured best of 8 / 16 / 32)
     return (unsigned)(blocks > cap ? cap : blocks);
 }
+static_assert(256 * 32 <= 8 * 1024, "the finalizing kernels hold eight partials per lane");
+
+// Buffers of n floats that together exceed the 256 MB memory-side cache by a quarter are accessed past the caches.  Measured (cached /
+// streamed): Adam family 24 M parameters (503 MB) 157 / 138 us, 39 M 255 / 232, but 16 M (336 MB) 83 / 91; moment tracking 24 M
+// (403 MB) 113 / 91, 39 M 190 / 165, 16 M (268 MB) 62 / 62.
+inline bool streams(int64_t n, int buffers) { return n * buffers * 4 > (int64_t)320 << 20; }
+
+// Sums over at most this many values take one workgroup and one launch instead of two (a launch is about 3 us here)
+constexpr int64_t ONE_GROUP = 32768;
 
 }  // namespace
 
@@ -256,11 +304,14 @@ hipError_t launch_adam_update(float* theta, float* m, float* v, const float* S_i
     k.inv_B = 1.f / (float)p.B;
     k.c_est = p.B > 1 ? (float)(1.0 / (1.0 - 1.0 / (double)p.B)) : 0.f;
     const dim3 grid(update_grid(n)), block(256);
+    auto go = [&](auto cached, auto streamed) {
+        (streams(n, variant == PEX_ADAM ? 4 : 5) ? streamed : cached)<<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm);
+    };
     switch (variant) {
-    case PEX_ADAM: adam_update_kernel<PEX_ADAM><<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm); break;
-    case PEX_MICROADAM: adam_update_kernel<PEX_MICROADAM><<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm); break;
-    case PEX_MICROADAM_VAR: adam_update_kernel<PEX_MICROADAM_VAR><<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm); break;
-    case PEX_MICROADAM_MSQ: adam_update_kernel<PEX_MICROADAM_MSQ><<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm); break;
+    case PEX_ADAM: go(adam_update_kernel<PEX_ADAM, false>, adam_update_kernel<PEX_ADAM, true>); break;
+    case PEX_MICROADAM: go(adam_update_kernel<PEX_MICROADAM, false>, adam_update_kernel<PEX_MICROADAM, true>); break;
+    case PEX_MICROADAM_VAR: go(adam_update_kernel<PEX_MICROADAM_VAR, false>, adam_update_kernel<PEX_MICROADAM_VAR, true>); break;
+    case PEX_MICROADAM_MSQ: go(adam_update_kernel<PEX_MICROADAM_MSQ, false>, adam_update_kernel<PEX_MICROADAM_MSQ, true>); break;
     }
     return hipGetLastError();
 }
@@ -292,8 +343,12 @@ size_t sum_squares_workspace(int64_t n) { return (size_t)update_grid(n) * sizeof
 
 hipError_t launch_sum_squares(const float* x, int64_t n, double* acc, int accumulate, double* partial, hipStream_t stream)
 {
+    if (n <= ONE_GROUP) {
+        sum_squares_kernel<true><<<dim3(1), dim3(1024), 0, stream>>>(x, n, acc, accumulate);
+        return hipGetLastError();
+    }
     const unsigned grid = update_grid(n);
-    sum_squares_kernel<<<dim3(grid), dim3(256), 0, stream>>>(x, n, partial);
+    sum_squares_kernel<false><<<dim3(grid), dim3(256), 0, stream>>>(x, n, partial, 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     sum_squares_finalize_kernel<<<dim3(1), dim3(1024), 0, stream>>>(partial, (int)grid, accumulate, acc);
@@ -311,8 +366,13 @@ hipError_t launch_moment_track(float* ema_adam, float* ema_micro, const float* S
     k.corr = p.debias ? 1.0 / (1.0 - pow((double)p.beta2, (double)p.step)) : 1.0;
     k.inv_B = 1.0 / (double)p.B;
     k.c_est = 1.0 / (1.0 - k.inv_B);
+    if (n <= ONE_GROUP) {
+        moment_track_kernel<false, true><<<dim3(1), dim3(1024), 0, stream>>>(ema_adam, ema_micro, S_id, S_sq, n, k, sums);
+        return hipGetLastError();
+    }
     const unsigned grid = update_grid(n);
-    moment_track_kernel<<<dim3(grid), dim3(256), 0, stream>>>(ema_adam, ema_micro, S_id, S_sq, n, k, partial);
+    auto kern = streams(n, 4) ? moment_track_kernel<true, false> : moment_track_kernel<false, false>;
+    kern<<<dim3(grid), dim3(256), 0, stream>>>(ema_adam, ema_micro, S_id, S_sq, n, k, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     moment_finalize_kernel<<<dim3(1), dim3(1024), 0, stream>>>(partial, (int)grid, sums);
@@ -325,10 +385,13 @@ hipError_t launch_sign_update(float* theta, float* m, const float* S, int64_t n,
     const float debias_mul = debias ? (float)(1.0 / (1.0 - pow((double)beta, (double)step))) : 1.f;
     const float w = (1.f - beta) / (float)B;
     const dim3 grid(update_grid(n)), block(256);
+    auto go = [&](auto cached, auto streamed, float weight, float mul) {
+        (streams(n, 3) ? streamed : cached)<<<grid, block, 0, stream>>>(theta, m, S, n, lr, beta, weight, weight_decay, mul);
+    };
     switch (variant) {
-    case PEX_MICROSIGNSGD: signsgd_update_kernel<PEX_MICROSIGNSGD><<<grid, block, 0, stream>>>(theta, m, S, n, lr, beta, w, weight_decay, debias_mul); break;
-    case PEX_SIGNSGD: signsgd_update_kernel<PEX_SIGNSGD><<<grid, block, 0, stream>>>(theta, m, S, n, lr, beta, 1.f - beta, weight_decay, debias_mul); break;
-    case PEX_SIGNEMA: signsgd_update_kernel<PEX_SIGNEMA><<<grid, block, 0, stream>>>(theta, m, S, n, lr, beta, w, weight_decay, 1.f); break;
+    case PEX_MICROSIGNSGD: go(signsgd_update_kernel<PEX_MICROSIGNSGD, false>, signsgd_update_kernel<PEX_MICROSIGNSGD, true>, w, debias_mul); break;
+    case PEX_SIGNSGD: go(signsgd_update_kernel<PEX_SIGNSGD, false>, signsgd_update_kernel<PEX_SIGNSGD, true>, 1.f - beta, debias_mul); break;
+    case PEX_SIGNEMA: go(signsgd_update_kernel<PEX_SIGNEMA, false>, signsgd_update_kernel<PEX_SIGNEMA, true>, w, 1.f); break;
     }
     return hipGetLastError();
 }
