@@ -16,7 +16,7 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpex.so")
 
-PEX_OK = 0
+PEX_OK, PEX_ERR_WORKSPACE = 0, 6
 PEX_F32, PEX_BF16 = 0, 1
 PEX_PHI_IDENTITY, PEX_PHI_SQUARE, PEX_PHI_SIGN = 0, 1, 2
 PEX_ADAM, PEX_MICROADAM, PEX_MICROADAM_VAR, PEX_MICROADAM_MSQ = 0, 1, 2, 3
@@ -163,30 +163,61 @@ def _check(code: int):
         raise PexError(code, status_string(code))
 
 
-def _dtype_code(t) -> int:
+# torch, looked up once at the first call that handles tensors (importing the package must not import it)
+_torch = _F32 = _F64 = _U8 = None
+_DTYPE_CODES = {}
+
+
+def _bind_torch():
+    global _torch, _F32, _F64, _U8
     import torch
-    if t.dtype == torch.float32:
-        return PEX_F32
-    if t.dtype == torch.bfloat16:
-        return PEX_BF16
-    raise TypeError(f"X and G must be float32 or bfloat16, got {t.dtype}")
+    _DTYPE_CODES.update({torch.float32: PEX_F32, torch.bfloat16: PEX_BF16})
+    _F32, _F64, _U8, _torch = torch.float32, torch.float64, torch.uint8, torch
 
 
-class _Buf:
-    """A tensor whose type and size have been checked, on its way to becoming a raw device pointer."""
-    __slots__ = ("t", "name")
+def _dtype_code(t) -> int:
+    if _torch is None:
+        _bind_torch()
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"X and G must be float32 or bfloat16, got {t.dtype}")
+    return code
 
-    def __init__(self, t, name):
-        self.t, self.name = t, name
+
+# What a checked tensor becomes on its way into a call is its address; a tensor that is not on the GPU becomes a marker that
+# no library function accepts, so that all type and size checks of the call come before the is-it-on-the-GPU check.
+class _NotOnGpu:
+    __slots__ = ("name",)
+
+    def __init__(self, name):
+        self.name = name
+
+
+class _NoStream:
+    __slots__ = ("error",)
+
+    def __init__(self, error):
+        self.error = error
+
+
+def _status(fn, args) -> int:
+    """The status of a library call; an argument without an address raises before anything is launched."""
+    try:
+        return fn(*args)
+    except ctypes.ArgumentError:
+        for a in args:
+            if isinstance(a, _NotOnGpu):
+                raise ValueError(f"{a.name} must live in GPU memory (libpex has no CPU path)") from None
+        for a in args:
+            if isinstance(a, _NoStream):
+                raise a.error
+        raise
 
 
 def _invoke(fn, *args):
-    """Call a library function: every checked tensor must live on the GPU (all type and size checks of the call
-    have passed by now), then goes in as its address; a status other than PEX_OK raises."""
-    for a in args:
-        if isinstance(a, _Buf) and not a.t.is_cuda:
-            raise ValueError(f"{a.name} must live in GPU memory (libpex has no CPU path)")
-    _check(fn(*[a.t.data_ptr() if isinstance(a, _Buf) else a.handle() if isinstance(a, _Stream) else a for a in args]))
+    code = _status(fn, args)
+    if code:
+        _check(code)
 
 
 def _dev(t, name, dtype=None, numel=None, shape=None):
@@ -195,58 +226,71 @@ def _dev(t, name, dtype=None, numel=None, shape=None):
     would make a kernel read or write past its end)."""
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if numel is not None and t.numel() != numel:
         raise ValueError(f"{name} must have {numel} elements, got {t.numel()}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return _Buf(t, name)
+    return t.data_ptr() if t.is_cuda else _NotOnGpu(name)
 
 
 def _f32(t, name, numel=None, shape=None):
-    import torch
-    return _dev(t, name, torch.float32, numel, shape)
+    if _torch is None:
+        _bind_torch()
+    return _dev(t, name, _F32, numel, shape)
 
 
 def _f64(t, name, numel=None):
-    import torch
-    return _dev(t, name, torch.float64, numel)
-
-
-class _Stream:
-    """The stream argument of a call, turned into a hipStream_t by _invoke (None = torch's current stream)."""
-    __slots__ = ("stream",)
-
-    def __init__(self, stream):
-        self.stream = stream
-
-    def handle(self):
-        import torch
-        s = torch.cuda.current_stream() if self.stream is None else self.stream
-        return ctypes.c_void_p(s.cuda_stream)
+    if _torch is None:
+        _bind_torch()
+    return _dev(t, name, _F64, numel)
 
 
 def _stream(stream):
-    return _Stream(stream)
+    """The stream argument of a call as a hipStream_t (None = torch's current stream).  The raw handle of the current stream
+    costs 0.2 us, the stream object of the public call 2.7 us, a quarter of a small call."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _torch is None:
+        _bind_torch()
+    try:
+        try:
+            c = _torch._C
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        except AttributeError:
+            return _torch.cuda.current_stream().cuda_stream
+    except Exception as e:      # no GPU: a tensor that is not on one is reported first
+        return _NoStream(e)
 
 
 def _shapes(X, G):
-    if X.dim() != 3 or G.dim() != 3 or X.shape[:2] != G.shape[:2]:
-        raise ValueError(f"expected X[B,T,din] and G[B,T,dout], got {tuple(X.shape)} and {tuple(G.shape)}")
+    sx, sg = X.shape, G.shape
+    if len(sx) != 3 or len(sg) != 3 or sx[0] != sg[0] or sx[1] != sg[1]:
+        raise ValueError(f"expected X[B,T,din] and G[B,T,dout], got {tuple(sx)} and {tuple(sg)}")
     if X.dtype != G.dtype:
         raise TypeError("X and G must share a dtype")
-    B, T, din = X.shape
-    return int(B), int(T), int(din), int(G.shape[2])
+    return sx[0], sx[1], sx[2], sg[2]
 
 
 def pex_stat_workspace_bytes(B, T, din, dout, dtype_code, phi) -> int:
     return int(lib().pex_stat_workspace_bytes(B, T, din, dout, dtype_code, PHI.get(phi, phi)))
 
 
+_MASKS = {}
+
+
 def _want_mask(want) -> int:
     if isinstance(want, int):
         return want
+    if want.__class__ is tuple:
+        mask = _MASKS.get(want)
+        if mask is None:
+            mask = 0
+            for w in want:
+                mask |= WANT[w]
+            _MASKS[want] = mask
+        return mask
     mask = 0
     for w in want:
         mask |= WANT[w]
@@ -261,36 +305,56 @@ def pex_token_sq_workspace_bytes(B, T, din, dout, dtype_code) -> int:
     return int(lib().pex_token_sq_workspace_bytes(B, T, din, dout, dtype_code))
 
 
-def _workspace(nbytes, like, workspace, stream=None):
-    """The caller's workspace (uint8, at least ``nbytes``) or a temporary one.  A temporary is allocated under the
-    stream the kernels run on, so the caching allocator does not hand its memory out again before they finish."""
-    import torch
+def _workspace(query, args, like, workspace, stream=None):
+    """(tensor to keep alive, address, size) of the caller's workspace (uint8) or of a temporary one of query(*args) bytes.  A
+    temporary is allocated under the stream the kernels run on, so the caching allocator does not hand its memory out
+    again before they finish.  Whether a caller's workspace is large enough the library checks against the plan it makes
+    anyway (see _invoke_ws); here only a call that will not reach it is checked."""
+    if _torch is None:
+        _bind_torch()
     if workspace is None:
+        nbytes = query(*args)
         if nbytes == 0:
             return None, None, 0
         if stream is None:
-            workspace = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+            workspace = _torch.empty(nbytes, dtype=_U8, device=like.device)
         else:
-            with torch.cuda.stream(stream):
-                workspace = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+            with _torch.cuda.stream(stream):
+                workspace = _torch.empty(nbytes, dtype=_U8, device=like.device)
     else:
-        if workspace.dtype != torch.uint8:
+        if workspace.dtype != _U8:
             raise TypeError(f"workspace must be uint8, got {workspace.dtype}")
-        if workspace.numel() < nbytes:
-            raise ValueError(f"workspace holds {workspace.numel()} bytes, the call needs {nbytes}")
+        if not (workspace.is_cuda and like.is_cuda):
+            _check_workspace_size(workspace, query(*args))
     return workspace, _dev(workspace, "workspace"), workspace.numel()
+
+
+def _check_workspace_size(workspace, nbytes):
+    if workspace is not None and workspace.numel() < nbytes:
+        raise ValueError(f"workspace holds {workspace.numel()} bytes, the call needs {nbytes}")
+
+
+def _invoke_ws(query, qargs, workspace, fn, *args):
+    """_invoke for a call with a workspace: one that is too small raises like the binding's other checks."""
+    code = _status(fn, args)
+    if code:
+        if code == PEX_ERR_WORKSPACE:
+            _check_workspace_size(workspace, query(*qargs))
+        _check(code)
 
 
 def pex_stat(X, G, phi, S=None, workspace=None, stream=None):
     """S[din,dout] = sum_b phi(X_b^T G_b), fp32.  ``phi`` is 'identity' | 'square' | 'sign' (or its code)."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     code = PHI.get(phi, phi)
     if S is None:
-        S = torch.empty(din, dout, dtype=torch.float32, device=X.device)
-    ws, wptr, wbytes = _workspace(pex_stat_workspace_bytes(B, T, din, dout, dt, code), X, workspace, stream)
-    _invoke(lib().pex_stat, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, code, _f32(S, "S", shape=(din, dout)), wptr, wbytes,
+        S = _torch.empty(din, dout, dtype=_torch.float32, device=X.device)
+    query, qargs = pex_stat_workspace_bytes, (B, T, din, dout, dt, code)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_stat, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, code, _f32(S, "S", shape=(din, dout)), wptr, wbytes,
                           _stream(stream))
     return S
 
@@ -310,7 +374,8 @@ def pex_stat_noalloc(X, G, phi, S, stream=None):
 def pex_stat_multi(X, G, want, out=None, workspace=None, stream=None):
     """Several statistics from one pass.  ``want`` is an iterable of 'identity' | 'square' | 'sign' (or the bit
     set); returns a dict name -> S[din,dout] fp32.  ``out`` may supply the output tensors by name."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     mask = _want_mask(want)
@@ -320,13 +385,14 @@ def pex_stat_multi(X, G, want, out=None, workspace=None, stream=None):
         if mask & bit:
             S = (out or {}).get(name)
             if S is None:
-                S = torch.empty(din, dout, dtype=torch.float32, device=X.device)
+                S = _torch.empty(din, dout, dtype=_torch.float32, device=X.device)
             res[name] = S
             ptrs.append(_f32(S, name, shape=(din, dout)))
         else:
             ptrs.append(None)
-    ws, wptr, wbytes = _workspace(pex_stat_multi_workspace_bytes(B, T, din, dout, dt, mask), X, workspace, stream)
-    _invoke(lib().pex_stat_multi, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, mask, ptrs[0], ptrs[1], ptrs[2],
+    query, qargs = pex_stat_multi_workspace_bytes, (B, T, din, dout, dt, mask)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_stat_multi, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, mask, ptrs[0], ptrs[1], ptrs[2],
                                 wptr, wbytes, _stream(stream))
     return res
 
@@ -338,7 +404,8 @@ def pex_vec_stat_workspace_bytes(B, T, d, dtype_code) -> int:
 def pex_vec_stat(A, C=None, want=("identity", "square", "sign"), out=None, workspace=None, stream=None):
     """Statistics of a vector parameter: s[d] = sum_b phi(sum_t A[b,t,:] * C[b,t,:]); ``C=None`` is an offset.
     Returns a dict name -> s[d] fp32."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     if A.dim() != 3 or (C is not None and C.shape != A.shape):
         raise ValueError("expected A[B,T,d] and C of the same shape (or None)")
     if C is not None and C.dtype != A.dtype:
@@ -351,13 +418,14 @@ def pex_vec_stat(A, C=None, want=("identity", "square", "sign"), out=None, works
         if mask & bit:
             s = (out or {}).get(name)
             if s is None:
-                s = torch.empty(d, dtype=torch.float32, device=A.device)
+                s = _torch.empty(d, dtype=_torch.float32, device=A.device)
             res[name] = s
             ptrs.append(_f32(s, name, numel=d))
         else:
             ptrs.append(None)
-    ws, wptr, wbytes = _workspace(pex_vec_stat_workspace_bytes(B, T, d, dt), A, workspace, stream)
-    _invoke(lib().pex_vec_stat, _dev(A, "A"), _dev(C, "C") if C is not None else None, B, T, d, dt, mask,
+    query, qargs = pex_vec_stat_workspace_bytes, (B, T, d, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, A, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_vec_stat, _dev(A, "A"), _dev(C, "C") if C is not None else None, B, T, d, dt, mask,
                               ptrs[0], ptrs[1], ptrs[2], wptr, wbytes, _stream(stream))
     return res
 
@@ -376,26 +444,30 @@ def pex_stat_power_workspace_bytes(B, T, din, dout, dtype_code) -> int:
 
 def pex_example_norms(X, G, N=None, workspace=None, stream=None):
     """N[B] = ||X_b^T G_b||_F^2, fp32."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     if N is None:
-        N = torch.empty(B, dtype=torch.float32, device=X.device)
-    ws, wptr, wbytes = _workspace(pex_example_norms_workspace_bytes(B, T, din, dout, dt), X, workspace, stream)
-    _invoke(lib().pex_example_norms, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, _f32(N, "N", numel=B), wptr, wbytes,
+        N = _torch.empty(B, dtype=_torch.float32, device=X.device)
+    query, qargs = pex_example_norms_workspace_bytes, (B, T, din, dout, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_example_norms, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, _f32(N, "N", numel=B), wptr, wbytes,
                                    _stream(stream))
     return N
 
 
 def pex_weighted_sum(X, G, w, S=None, workspace=None, stream=None):
     """S[din,dout] = sum_b w[b] X_b^T G_b, fp32 (``w`` fp32 [B] on the GPU)."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     if S is None:
-        S = torch.empty(din, dout, dtype=torch.float32, device=X.device)
-    ws, wptr, wbytes = _workspace(pex_weighted_sum_workspace_bytes(B, T, din, dout, dt), X, workspace, stream)
-    _invoke(lib().pex_weighted_sum, _dev(X, "X"), _dev(G, "G"), _f32(w, "w", numel=B), B, T, din, dout, dt, _f32(S, "S", shape=(din, dout)), wptr,
+        S = _torch.empty(din, dout, dtype=_torch.float32, device=X.device)
+    query, qargs = pex_weighted_sum_workspace_bytes, (B, T, din, dout, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_weighted_sum, _dev(X, "X"), _dev(G, "G"), _f32(w, "w", numel=B), B, T, din, dout, dt, _f32(S, "S", shape=(din, dout)), wptr,
                                   wbytes, _stream(stream))
     return S
 
@@ -403,49 +475,55 @@ def pex_weighted_sum(X, G, w, S=None, workspace=None, stream=None):
 def pex_clip_weights(N, max_norm, w=None, stream=None):
     """w[B] = min(1, max_norm / sqrt(sum over layers of N)), ``N`` fp32 [layers, B] (or [B]) of per-layer squared
     per-example gradient norms on the GPU."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     if N.dim() not in (1, 2):
         raise ValueError("N must be [layers, B] or [B]")
     nlayers, B = (1, N.shape[0]) if N.dim() == 1 else (int(N.shape[0]), int(N.shape[1]))
     if w is None:
-        w = torch.empty(B, dtype=torch.float32, device=N.device)
+        w = _torch.empty(B, dtype=_torch.float32, device=N.device)
     _invoke(lib().pex_clip_weights, _f32(N, "N"), B, nlayers, float(max_norm), _f32(w, "w", numel=B), _stream(stream))
     return w
 
 
 def pex_stat_power(X, G, alpha, S=None, workspace=None, stream=None):
     """S[din,dout] = sum_b |X_b^T G_b|^alpha, fp32."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     if S is None:
-        S = torch.empty(din, dout, dtype=torch.float32, device=X.device)
-    ws, wptr, wbytes = _workspace(pex_stat_power_workspace_bytes(B, T, din, dout, dt), X, workspace, stream)
-    _invoke(lib().pex_stat_power, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, float(alpha), _f32(S, "S", shape=(din, dout)), wptr,
+        S = _torch.empty(din, dout, dtype=_torch.float32, device=X.device)
+    query, qargs = pex_stat_power_workspace_bytes, (B, T, din, dout, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_stat_power, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, float(alpha), _f32(S, "S", shape=(din, dout)), wptr,
                                 wbytes, _stream(stream))
     return S
 
 
 def pex_token_norms(X, G, N_tok=None, stream=None):
     """N_tok[B,T] = ||x_bt||^2 ||g_bt||^2, fp32."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     if N_tok is None:
-        N_tok = torch.empty(B, T, dtype=torch.float32, device=X.device)
+        N_tok = _torch.empty(B, T, dtype=_torch.float32, device=X.device)
     _invoke(lib().pex_token_norms, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, _f32(N_tok, "N_tok", numel=B * T), _stream(stream))
     return N_tok
 
 
 def pex_token_sq(X, G, S=None, workspace=None, stream=None):
     """S_tok[din,dout] = (X o X)^T (G o G), fp32."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
     if S is None:
-        S = torch.empty(din, dout, dtype=torch.float32, device=X.device)
-    ws, wptr, wbytes = _workspace(pex_token_sq_workspace_bytes(B, T, din, dout, dt), X, workspace, stream)
-    _invoke(lib().pex_token_sq, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, _f32(S, "S", shape=(din, dout)), wptr, wbytes,
+        S = _torch.empty(din, dout, dtype=_torch.float32, device=X.device)
+    query, qargs = pex_token_sq_workspace_bytes, (B, T, din, dout, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, X, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_token_sq, _dev(X, "X"), _dev(G, "G"), B, T, din, dout, dt, _f32(S, "S", shape=(din, dout)), wptr, wbytes,
                               _stream(stream))
     return S
 
@@ -481,12 +559,14 @@ def pex_moment_track_workspace_bytes(n) -> int:
 def pex_moment_track(ema_adam, ema_micro, S_id, S_sq, params: MomentParams, sums=None, workspace=None, stream=None):
     """One step of the on-line mu^2 / sigma^2 measurement (Sec. 3.2.2): updates the two EMAs in place and returns a
     float64 tensor [2] = (sum of mu^2-hat, sum of sigma^2-hat) over the parameters."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     n = ema_adam.numel()
     if sums is None:
-        sums = torch.empty(2, dtype=torch.float64, device=ema_adam.device)
-    ws, wptr, wbytes = _workspace(pex_moment_track_workspace_bytes(n), ema_adam, workspace, stream)
-    _invoke(lib().pex_moment_track, _f32(ema_adam, "ema_adam"), _f32(ema_micro, "ema_micro", n), _f32(S_id, "S_id", n),
+        sums = _torch.empty(2, dtype=_torch.float64, device=ema_adam.device)
+    query, qargs = pex_moment_track_workspace_bytes, (n,)
+    ws, wptr, wbytes = _workspace(query, qargs, ema_adam, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_moment_track, _f32(ema_adam, "ema_adam"), _f32(ema_micro, "ema_micro", n), _f32(S_id, "S_id", n),
                                   _f32(S_sq, "S_sq", n), n, ctypes.byref(params), _f64(sums, "sums", 2), wptr, wbytes,
                                   _stream(stream))
     return sums
@@ -499,10 +579,11 @@ def pex_embed_stat_workspace_bytes(B, T, V, d) -> int:
 def pex_embed_stat(ids, G, V, want, out=None, workspace=None, stream=None):
     """Per-example gradient statistics of an embedding table: ``ids`` [B,T] int32/int64, ``G`` [B,T,d] cotangents of
     the looked-up vectors; returns a dict name -> S[V,d] fp32 for the names in ``want``.  Ids outside [0,V) are padding."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     if ids.dim() != 2 or G.dim() != 3 or tuple(G.shape[:2]) != tuple(ids.shape):
         raise ValueError("ids must be [B,T] and G [B,T,d]")
-    if ids.dtype not in (torch.int32, torch.int64):
+    if ids.dtype not in (_torch.int32, _torch.int64):
         raise TypeError(f"ids must be int32 or int64, got {ids.dtype}")
     B, T, d = G.shape
     mask = _want_mask(want)
@@ -511,13 +592,14 @@ def pex_embed_stat(ids, G, V, want, out=None, workspace=None, stream=None):
         if mask & bit:
             S = (out or {}).get(name)
             if S is None:
-                S = torch.empty(V, d, dtype=torch.float32, device=G.device)
+                S = _torch.empty(V, d, dtype=_torch.float32, device=G.device)
             res[name] = S
             ptrs.append(_f32(S, name, shape=(V, d)))
         else:
             ptrs.append(None)
-    ws, wptr, wbytes = _workspace(pex_embed_stat_workspace_bytes(B, T, V, d), G, workspace, stream)
-    _invoke(lib().pex_embed_stat, _dev(ids, "ids"), ids.element_size(), _dev(G, "G"), B, T, V, d, _dtype_code(G), mask,
+    query, qargs = pex_embed_stat_workspace_bytes, (B, T, V, d)
+    ws, wptr, wbytes = _workspace(query, qargs, G, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_embed_stat, _dev(ids, "ids"), ids.element_size(), _dev(G, "G"), B, T, V, d, _dtype_code(G), mask,
                                 ptrs[0], ptrs[1], ptrs[2], wptr, wbytes, _stream(stream))
     return res
 
@@ -541,12 +623,13 @@ def pex_status_string(code: int) -> str:
 def pex_mfma_probe(operands, workgroups, iters, sink=None, stream=None):
     """Measurement aid: one launch of nothing but bf16 MFMAs (see ``pex_mfma_probe`` in the header).  ``operands`` is a
     bf16 tensor of at least ``pex_mfma_probe_operand_bytes()`` bytes.  Returns (FLOP of the launch, sink tensor)."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     need = pex_mfma_probe_operand_bytes()
     if operands.numel() * operands.element_size() < need:
         raise ValueError(f"operands must hold at least {need} bytes")
     if sink is None:
-        sink = torch.empty(pex_mfma_probe_sink_floats(workgroups), dtype=torch.float32, device=operands.device)
+        sink = _torch.empty(pex_mfma_probe_sink_floats(workgroups), dtype=_torch.float32, device=operands.device)
     flop = ctypes.c_double(0.0)
     _invoke(lib().pex_mfma_probe, _dev(operands, "operands"), int(workgroups), int(iters), _f32(sink, "sink"), ctypes.byref(flop),
                                 _stream(stream))
@@ -559,12 +642,14 @@ def pex_sum_squares_workspace_bytes(n) -> int:
 
 def pex_sum_squares(x, acc=None, accumulate=False, workspace=None, stream=None):
     """acc[0] (+)= sum of x^2 in fp64 (one double on the GPU): the squared global gradient norm, layer by layer."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     n = x.numel()
     if acc is None:
-        acc = torch.zeros(1, dtype=torch.float64, device=x.device)
-    ws, wptr, wbytes = _workspace(pex_sum_squares_workspace_bytes(n), x, workspace, stream)
-    _invoke(lib().pex_sum_squares, _f32(x, "x"), n, _f64(acc, "acc", 1), int(bool(accumulate)), wptr, wbytes, _stream(stream))
+        acc = _torch.zeros(1, dtype=_torch.float64, device=x.device)
+    query, qargs = pex_sum_squares_workspace_bytes, (n,)
+    ws, wptr, wbytes = _workspace(query, qargs, x, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_sum_squares, _f32(x, "x"), n, _f64(acc, "acc", 1), int(bool(accumulate)), wptr, wbytes, _stream(stream))
     return acc
 
 
