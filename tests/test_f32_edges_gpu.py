@@ -75,3 +75,19 @@ def test_statistics_sharing_a_contraction(pex_option, B, T, din, dout, want):
         assert_real_stat(got["square"], st.S_sq, "f32", "square", elementwise=True)
     if "sign" in got:
         assert_sign_stat(got["sign"], st.S_sign, st.amb, "sign")
+
+
+@pytest.mark.parametrize("din,dout", [(152, 320), (44, 250), (250, 64), (190, 190)])
+def test_arrangements_of_waves(din, dout):
+    """Workgroups of 3 x 1, 1 x 4, 4 x 1 and 2 x 2 or 3 x 1 waves: layers whose tile counts leave 2 x 2 blocks half empty."""
+    B, T = 5, 21
+    X, G = si.custom(B, T, din, dout, dtype="f32", seed=din + dout)
+    Xn, Gn = si.widen(X), si.widen(G)
+    f = lambda t: t.cpu().numpy().astype(np.float64)
+    st = oracle.stat(Xn, Gn)
+    out = {k: torch.full((din, dout), float("nan"), device=DEV) for k in ("identity", "square")}
+    pex.pex_stat_multi(X.to(DEV), G.to(DEV), ("identity", "square"), out=out)
+    assert_real_stat(f(out["identity"]), st.S_id, "f32", "identity", elementwise=False)
+    assert_real_stat(f(out["square"]), st.S_sq, "f32", "square", elementwise=True)
+    ref = on.example_norms(Xn, Gn)
+    assert np.abs(f(pex.pex_example_norms(X.to(DEV), G.to(DEV))) - ref).max() <= 2e-5 * ref.max()
