@@ -240,6 +240,9 @@ pex_status pex_clip_weights(const float *N, int64_t B, int32_t nlayers, float ma
  *   Workspace: besides partial sums, for large bf16 layers (din*dout/(din+dout) beyond roughly 800) the
  *   workspace holds bf16 copies of the squared operands, 2*B*T*(din+dout) bytes: squaring once at HBM speed
  *   is cheaper there than squaring every slab inside the contraction.  The query returns the total.
+ *   For large bf16 layers whose rows are not multiples of 16 bytes it holds the squares exactly, as two bf16 each
+ *   (about 4*B*T*(din+dout) bytes, and four sets of partial sums); their results, like those of small ones, carry
+ *   no rounding of the squares.
  */
 size_t pex_token_sq_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt);
 pex_status pex_token_sq(const void *X, const void *G, int64_t B, int64_t T, int64_t din, int64_t dout,

@@ -134,20 +134,22 @@ static double bf16_block_rate(int bm, int bn)
 // than that: about 1.35 us per slab of 16 rows in a workgroup's serial loop, 35e12 FLOP/s at best on layers near the line.
 // Measured (SIMT / copies): B=8 T=64 70x130 square 20.6 / 24.8 us, B=8 T=128 201x333 square 21.9 / 24.6, B=16 T=128 301x500
 // identity + square 60 / 28, B=16 T=256 333x1001 square 86 / 33, B=2 T=4096 100x131 square 353 / 68.
-// `passes` = statistics the SIMT kernel would make one by one.  The per-token square stays on the SIMT kernel, which keeps
-// the squares in fp32.
+// `passes` = statistics the SIMT kernel would make one by one.  The per-token square takes four contractions and copies of
+// twice the size (see pex_pad.hip), and the SIMT kernel reaches 60e12 FLOP/s on its larger layers: from an estimate of 200 us
+// (SIMT / halves: B=16 T=256 333x1001 75 / 96 us, B=64 T=256 999x768 425 / 208, B=14 T=544 3776x1943 1735 / 451).
 static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int passes)
 {
-    if (mode == MODE_TOKEN_SQ || (din % 8 == 0 && dout % 8 == 0)) return false;
+    if (din % 8 == 0 && dout % 8 == 0) return false;
     if (!pad_supports(B * T, din, dout) || !bf16_supports(B, T, padded_width(din), padded_width(dout))) return false;
-    const int64_t tiles = ((din + 63) / 64) * ((dout + 63) / 64), units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
+    const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
+    const int64_t tiles = ((din + 63) / 64) * ((dout + 63) / 64), units = plain ? (B * T + 63) / 64 : B;
     int64_t groups = (1024 + tiles - 1) / tiles;
     if (groups > units) groups = units;
     if (groups > 32) groups = 32;
-    const double slabs = (double)((units + groups - 1) / groups) * (mode == MODE_IDENTITY ? 4.0 : (double)((T + 15) / 16));
+    const double slabs = (double)((units + groups - 1) / groups) * (plain ? 4.0 : (double)((T + 15) / 16));
     const double flop = 2.0 * (double)B * (double)T * (double)din * (double)dout;
     const double t = flop / 35.0e12 > slabs * 1.35e-6 ? flop / 35.0e12 : slabs * 1.35e-6;
-    return t * passes > 14.0e-6;
+    return t * passes > (mode == MODE_TOKEN_SQ ? 200.0e-6 : 14.0e-6);
 }
 
 static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
@@ -157,8 +159,9 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     p.out_cols = dout;
     // (a plan on one block shape is one of several statistics at once)
     if (allow_pad && dt == PEX_BF16 && padding_pays(B, T, din, dout, mode, allow_wide ? 1 : 2)) {
-        p.copy_x = din % 8 != 0;
-        p.copy_g = dout % 8 != 0;
+        p.square_halves = mode == MODE_TOKEN_SQ;
+        p.copy_x = din % 8 != 0 || p.square_halves;
+        p.copy_g = dout % 8 != 0 || p.square_halves;
         din = padded_width(din);
         dout = padded_width(dout);
     }
@@ -282,14 +285,14 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     // pass over X and G at HBM speed (~5.5 TB/s, 4 bytes moved per element).  The copies win when din*dout/(din+dout)
     // is large.
     const int presquare = option(PEX_OPT_TOKEN_PRESQUARE);
-    if (mode == MODE_TOKEN_SQ && p.kernel == 1 && presquare != 0) {
+    if (mode == MODE_TOKEN_SQ && p.kernel == 1 && presquare != 0 && !p.square_halves) {
         const double elems = (double)B * (double)T * (double)(din + dout);
         const double t_pre = 4.0 * elems / 5.5e12 + 6.0e-6;
         const double t_fused_extra = 0.5 * 2.0 * (double)B * (double)T * (double)din * (double)dout / 1.3e15;
         if (t_pre < t_fused_extra || presquare == 2) p.copy_x = p.copy_g = true;
     }
     const size_t copied = (p.copy_x ? (size_t)din : 0) + (p.copy_g ? (size_t)dout : 0);
-    p.copy_bytes = ((size_t)B * (size_t)T * copied * 2 + 255) & ~(size_t)255;
+    p.copy_bytes = ((size_t)B * (size_t)T * copied * (p.square_halves ? 4 : 2) + 255) & ~(size_t)255;
     p.sign_bytes = sign_bytes && nsplit > 1;
     p.mem_fold = mem_fold;
     p.wide_cols = wide_cols;
@@ -298,6 +301,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     p.wide_ws_bytes = (wide_cols > 0 && wide_nsplit > 1) ? (size_t)wide_nsplit * (size_t)din * (size_t)wide_cols * sizeof(float) : 0;
     p.ws_bytes = p.copy_bytes + p.wide_ws_bytes +
                  ((nsplit > 1 && dout > wide_cols) ? (size_t)nsplit * (size_t)din * (size_t)(dout - wide_cols) * sizeof(float) : 0);
+    if (p.square_halves) p.ws_bytes = p.copy_bytes + (size_t)4 * (size_t)nsplit * (size_t)din * (size_t)dout * sizeof(float);
     if (p.sign_bytes) p.ws_bytes = p.copy_bytes + (size_t)nsplit * sign_byte_partial_bytes(din, dout);
     if (mode == MODE_NORMS) {   // no S at all: one partial of ||M_b||^2 per tile (and wave) and example
         const int64_t nparts = p.kernel == 1 ? bf16_norm_partials(din, dout) : p.kernel == 2 ? f32_norm_partials(din, dout) : generic_norm_partials(din, dout);
@@ -407,13 +411,13 @@ static hipError_t make_copies(const StatPlan& plan, const void*& X, const void*&
 {
     if (plan.copy_bytes == 0) return hipSuccess;
     uint16_t* x = plan.copy_x ? (uint16_t*)workspace : nullptr;
-    uint16_t* g = plan.copy_g ? (uint16_t*)workspace + (plan.copy_x ? rows * plan.din : 0) : nullptr;
+    uint16_t* g = plan.copy_g ? (uint16_t*)workspace + (plan.copy_x ? rows * plan.din * (plan.square_halves ? 2 : 1) : 0) : nullptr;
     hipError_t e = hipSuccess;
     if (!made) {
-        if (plan.din == plan.out_rows && plan.dout == plan.out_cols) {       // squares of rows that are whole chunks
+        if (!plan.square_halves && plan.din == plan.out_rows && plan.dout == plan.out_cols) {       // squares of rows that are whole chunks
             e = launch_square_bf16(X, x, rows * plan.din, stream);
             if (e == hipSuccess) e = launch_square_bf16(G, g, rows * plan.dout, stream);
-        } else e = launch_pad_rows(X, x, G, g, rows, plan.out_rows, plan.out_cols, stream);
+        } else e = launch_pad_rows(X, x, G, g, rows, plan.out_rows, plan.out_cols, plan.square_halves, stream);
     }
     if (x) X = x;
     if (g) G = g;
@@ -437,6 +441,19 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
     if (e != hipSuccess) return PEX_ERR_HIP;
     din = plan.din;
     dout = plan.dout;
+    if (plan.square_halves) {
+        StatPlan part = plan;               // one of the four contractions: a result of the operands' widths
+        part.out_rows = din;
+        part.out_cols = dout;
+        const int64_t n = din * dout, xhalf = B * T * din, ghalf = B * T * dout;
+        for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+            float* dst = partials + (int64_t)k * plan.nsplit * n;
+            e = launch_stat_bf16((const uint16_t*)X + (k / 2) * xhalf, (const uint16_t*)G + (k % 2) * ghalf, B, T, din, dout, MODE_IDENTITY, part, dst,
+                                 dst, stream);
+        }
+        if (e == hipSuccess) e = launch_reduce_partials({{partials}, {S}}, 1, 4 * plan.nsplit, n, plan.out_rows, plan.out_cols, dout, plan.out_cols, stream);
+        return e == hipSuccess ? PEX_OK : PEX_ERR_HIP;
+    }
     if (mode == MODE_TOKEN_SQ && plan.copy_bytes > 0) {
         e = launch_stat_bf16(X, G, B, T, din, dout, MODE_IDENTITY, plan, S, partials, stream);       // the copies hold the squares
     } else if (plan.kernel == 2) {

@@ -27,6 +27,8 @@ struct StatPlan {
     bool copy_x, copy_g;         // copies of the operands at the front of the workspace (X's first): rows padded to whole 16-byte
                                  // chunks (bf16 layers of odd width), or squares (per-token square)
     size_t copy_bytes;           // their size (256-byte multiple)
+    bool square_halves;          // per-token square of odd widths: the copies hold exact squares in two halves, the four products of
+                                 // the halves are contracted into nsplit groups of partial sums each
     int64_t wide_cols; // bf16, one statistic on two register tiles: columns [0, wide_cols) of S run on 256 x 192 blocks as
                        // wide_nsplit groups of wide_per_split examples; nsplit / per_split then describe the remaining columns only
     int wide_nsplit;
@@ -98,10 +100,10 @@ bool f32_bytes_suffice(const StatPlan& plan);
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
                                  float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
 // Copies of bf16 operands [rows, width] with rows of padded_width(width) elements, zero-filled; an operand whose output
-// is NULL is left out
+// is NULL is left out.  squares: the copy holds the rounded squares and, after them, their remainders (twice the size)
 int64_t padded_width(int64_t width);
 bool pad_supports(int64_t rows, int64_t din, int64_t dout);
-hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout,
+hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout, bool squares,
                            hipStream_t stream);
 // out[i] = bf16(in[i]^2) (square in fp32, round to nearest even) for n bf16 values, n a multiple of 8
 hipError_t launch_square_bf16(const void* in, void* out, int64_t n, hipStream_t stream);

@@ -5,10 +5,16 @@
 // feature adds zero rows or columns to M_b, which are not stored) costs one pass at HBM speed and brings every statistic
 // onto those kernels.
 //
+// For the per-token square the copies hold the squares, each as a pair of bf16 that is exact (the SIMT kernel, which these
+// layers came from, keeps the squares in fp32): first the rounded squares of the whole operand, then their remainders.  The four
+// products of the halves are contracted one after the other into partial sums.  B=14 T=544 3776x1943: 1735 us on the SIMT
+// kernel, 451 so.
+//
 // Bound by HBM: 2 bytes read and 2 written per element.  A lane makes one 16-byte chunk of the copy from five dwords at
 // 4-byte addresses (a row may start in the middle of a dword: then the five are shifted by 16 bits into four), four chunks
 // in flight per lane.  Measured: 16000 rows of 2049 and 3001 elements in 54 us (6.0 TB/s); the layer's phi = square 3401 us on
 // the SIMT kernel, 279 us with the copies.  B=8 T=256 768 x 50257, identity + square: 4253 -> 351 us, 92 of them for the copy.
+#include "pex_bf16.h"
 #include "pex_internal.h"
 
 namespace pex {
@@ -52,6 +58,7 @@ struct PadOperand {
     int width, chunks;      // elements per row, 16-byte chunks per row of the copy
 };
 
+template <bool SQUARES>
 __global__ __launch_bounds__(256) void pad_rows_kernel(PadOperand a, PadOperand b, int64_t rows)
 {
     const PadOperand o = blockIdx.y == 0 ? a : b;
@@ -67,8 +74,22 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(PadOperand a, PadOperand 
         v[u] = load_chunk(o.in, (int64_t)row * o.width + 8 * c, o.width - (int)(8 * c), total);
     }
 #pragma unroll
-    for (int u = 0; u < PAD_CHUNKS; ++u)
-        if (first + 256 * u < n) o.out[first + 256 * u] = v[u];
+    for (int u = 0; u < PAD_CHUNKS; ++u) {
+        const uint32_t k = first + 256 * u;
+        if (k >= n) continue;
+        if constexpr (SQUARES) {
+            uint4_t hi, lo;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t h, l;
+                square_pair_split(v[u][d], h, l);
+                hi[d] = h;
+                lo[d] = l;
+            }
+            o.out[k] = hi;
+            o.out[(int64_t)n + k] = lo;
+        } else o.out[k] = v[u];
+    }
 }
 
 }  // namespace
@@ -81,7 +102,7 @@ bool pad_supports(int64_t rows, int64_t din, int64_t dout)
     return din < lim / 2 && dout < lim / 2 && rows * (padded_width(din) / 8) < lim && rows * (padded_width(dout) / 8) < lim;
 }
 
-hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout,
+hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout, bool squares,
                            hipStream_t stream)
 {
     PadOperand op[2];
@@ -98,7 +119,8 @@ hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_ou
     if (count == 0) return hipSuccess;
     if (count == 1) op[1] = op[0];
     const dim3 grid((unsigned)((most + 256 * PAD_CHUNKS - 1) / (256 * PAD_CHUNKS)), (unsigned)count), block(256);
-    pad_rows_kernel<<<grid, block, 0, stream>>>(op[0], op[1], rows);
+    if (squares) pad_rows_kernel<true><<<grid, block, 0, stream>>>(op[0], op[1], rows);
+    else pad_rows_kernel<false><<<grid, block, 0, stream>>>(op[0], op[1], rows);
     return hipGetLastError();
 }
 

@@ -116,3 +116,18 @@ def test_without_a_workspace_large_copies_stay_on_the_simt_kernel():
     o = Guarded(din, dout)
     pex.pex_stat_noalloc(X, G, "square", o.view)
     assert torch.equal(o.view, pex.pex_stat(X, G, "square"))
+
+
+@pytest.mark.parametrize("B,T,din,dout", [(16, 300, 1001, 770), (7, 1111, 519, 904)])
+def test_per_token_square_from_exact_halves(B, T, din, dout):
+    """The squares travel as two bf16 each that add up to them exactly: as accurate as fp32 squares (a rounded bf16 square alone
+    would be off by up to 2^-9)."""
+    halves = -(-din // 8) * 8 + -(-dout // 8) * 8
+    assert pex.pex_token_sq_workspace_bytes(B, T, din, dout, pex.PEX_BF16) >= 4 * B * T * halves, "not on the halves"
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=5, g_std=1e-2, g_token="lognormal")
+    o = Guarded(din, dout)
+    pex.pex_token_sq(X.to(DEV), G.to(DEV), S=o.view)
+    ref = (X.reshape(-1, din).to(DEV).double().square().t() @ G.reshape(-1, dout).to(DEV).double().square()).cpu().numpy()
+    got = o.value()
+    # terms >= 0 summed in fp32 (at most ~2000 rows per group, then the groups): 1e-5 of every entry
+    assert (np.abs(got - ref) <= 1e-5 * ref).all(), float((np.abs(got - ref) / ref).max())
