@@ -145,73 +145,217 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(const TId* __restrict
     }
 }
 
-// row_start[v] = first index k of the sorted keys with key[k] >= v, for v = 0 .. V (N if there is none).  Thread k
-// writes the entries between its left neighbour's key and its own, so every entry is written exactly once.
+// row_start[v] = first index k of the sorted keys with key[k] >= v, for v = 0 .. V (N if there is none).  Position k writes the
+// entries between its left neighbour's key and its own, so every entry is written exactly once: short gaps by the position's
+// lane, long ones (rare tokens, the end of the vocabulary) by the whole wave.  Called by whole waves, lane l with the
+// neighbours prev, cur of a position k (prev >= cur: nothing to write).
+__device__ __forceinline__ void fill_row_start(int* __restrict__ row_start, int k, int prev, int cur, int V)
+{
+    prev = prev < -1 ? -1 : (prev > V ? V : prev);   // keys are in [0, V]; the clamps keep the writes inside the array regardless
+    cur = cur > V ? V : cur;
+    const int lane = threadIdx.x & 63;
+    unsigned long long far = __ballot(cur - prev > 8);
+    if (cur - prev <= 8)
+        for (int v = prev + 1; v <= cur; ++v) row_start[v] = k;
+    while (far) {
+        const int l = __builtin_ctzll(far);
+        far &= far - 1;
+        const int kl = __shfl(k, l), pl = __shfl(prev, l), cl = __shfl(cur, l);
+        for (int v = pl + 1 + lane; v <= cl; v += 64) row_start[v] = kl;
+    }
+}
+
 __global__ __launch_bounds__(256) void row_start_kernel(const int* __restrict__ keys, int N, int V, int* __restrict__ row_start)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k > N) return;
-    int prev = k == 0 ? -1 : keys[k - 1];
-    int cur = k == N ? V : keys[k];
-    prev = prev < -1 ? -1 : (prev > V ? V : prev);   // keys are in [0, V]; the clamps keep the writes inside the array regardless
-    cur = cur > V ? V : cur;
-    for (int v = prev + 1; v <= cur; ++v) row_start[v] = (int)k;
+    const bool valid = k <= N;
+    fill_row_start(row_start, valid ? (int)k : 0, !valid ? 0 : (k == 0 ? -1 : keys[k - 1]), !valid ? 0 : (k == N ? V : keys[k]), V);
 }
 
-__device__ __forceinline__ float widen_el(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ __forceinline__ float widen_el(float f) { return f; }
+// Few positions: the whole sort and row_start in one launch of one workgroup, keys and positions in LDS.  Same digits, same
+// order: wave i owns a contiguous segment of the positions; counters per (wave, digit) give every key its place.  Bound by the
+// latency of its few dozen steps, 15 - 18 us for 1500 - 2040 positions, against the five or seven launches of the kernels above,
+// which take about 4.5 us each whatever they do (whole call, 345 / 630 / 2040 positions: 45 / 104 / 58 -> 27 / 45 / 38 us; at 3700
+// and 8192 positions the one workgroup is the slower one by 4 and 7 us).
+constexpr int SMALL_N = 2048, SMALL_WAVES = 16;
 
-// What a lane loads from a cotangent row: CH elements (4 fp32 = 16 bytes, 4 bf16 = 8 bytes, or one element), kept as
-// loaded until it is added: widening bf16 early would double the registers a lane holds in flight.  Four columns per
-// lane make the fp32 stores of a wave dense (16 bytes per lane, 1 KiB per instruction); eight bf16 columns per lane
-// would leave every store instruction writing half of each 32 bytes.
-template <typename TIn, int CH>
+template <typename TId>
+__global__ __launch_bounds__(SMALL_WAVES * 64) void sort_small_kernel(const TId* __restrict__ ids, int N, int V, int passes, int* __restrict__ keys_out,
+                                                                     int* __restrict__ vals_out, int* __restrict__ row_start)
+{
+    __shared__ int keys[2][SMALL_N], counts[SMALL_WAVES][256];
+    __shared__ uint16_t vals[2][SMALL_N];
+    auto key = [&](int buf, int k) -> int& { return keys[buf][k]; };
+    auto cnt = [&](int w, int digit) -> int& { return counts[w][digit]; };
+    auto val = [&](int buf, int k) -> uint16_t& { return vals[buf][k]; };
+    __shared__ int wtot[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int p = tid; p < N; p += SMALL_WAVES * 64) {
+        key(0, p) = load_key(ids, p, V);
+        val(0, p) = (uint16_t)p;
+    }
+    const int seg = (N + SMALL_WAVES * 64 - 1) / (SMALL_WAVES * 64) * 64;      // positions per wave, whole batches of 64
+    const int lo = wave * seg;
+    const int hi = lo + seg < N ? lo + seg : N;
+    int cur = 0;
+    for (int ps = 0; ps < passes; ++ps) {
+        const int shift = 8 * ps;
+        for (int t = tid; t < SMALL_WAVES * 256; t += SMALL_WAVES * 64) cnt(t >> 8, t & 255) = 0;
+        __syncthreads();
+        for (int k = lo + lane; k < hi; k += 64) atomicAdd(&cnt(wave, (key(cur, k) >> shift) & 255), 1);
+        __syncthreads();
+        // thread t < 256: digit t; its keys start after all smaller digits, wave by wave
+        int total = 0, incl = 0;
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < SMALL_WAVES; ++w) total += cnt(w, tid);
+            incl = total;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(incl, o);
+                if (lane >= o) incl += t;
+            }
+            if (lane == 63) wtot[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            int base = incl - total;
+            for (int w = 0; w < wave; ++w) base += wtot[w];
+#pragma unroll
+            for (int w = 0; w < SMALL_WAVES; ++w) {
+                const int c = cnt(w, tid);
+                cnt(w, tid) = base;
+                base += c;
+            }
+        }
+        __syncthreads();
+        // batches of 64 in order: rank among the batch's keys of the same digit from 8 ballots, place from the wave's counter,
+        // which the first of them moves on
+        for (int k0 = lo; k0 < hi; k0 += 64) {
+            const bool active = k0 + lane < hi;
+            const int kk = active ? key(cur, k0 + lane) : 0;
+            const uint16_t vv = active ? val(cur, k0 + lane) : (uint16_t)0;
+            const int dg = (kk >> shift) & 255;
+            unsigned long long same = __ballot(active);
+#pragma unroll
+            for (int bit = 0; bit < 8; ++bit) {
+                const bool one = (dg >> bit) & 1;
+                const unsigned long long bb = __ballot(one);
+                same &= one ? bb : ~bb;
+            }
+            const int rank = __popcll(same & ((1ull << lane) - 1ull));
+            const int at = active ? cnt(wave, dg) + rank : 0;
+            __builtin_amdgcn_wave_barrier();            // every lane has read its counter (LDS operations of a wave stay in order)
+            if (active && rank == 0) cnt(wave, dg) = at + __popcll(same);
+            __builtin_amdgcn_wave_barrier();
+            if (active && at < N) {
+                key(cur ^ 1, at) = kk;
+                val(cur ^ 1, at) = vv;
+            }
+        }
+        cur ^= 1;
+        __syncthreads();
+    }
+    for (int k0 = 0; k0 <= N; k0 += SMALL_WAVES * 64) {
+        const int k = k0 + tid;
+        if (k < N) {
+            keys_out[k] = key(cur, k);
+            vals_out[k] = val(cur, k);
+        }
+        const bool valid = k <= N;
+        fill_row_start(row_start, valid ? k : 0, !valid ? 0 : (k == 0 ? -1 : key(cur, k - 1)), !valid ? 0 : (k == N ? V : key(cur, k)), V);
+    }
+}
+
+// What a lane loads from a cotangent row: four columns (fp32 16 bytes, bf16 8 bytes), kept as loaded until they are added:
+// widening bf16 early would double the registers a lane holds in flight.  Four columns per lane make the fp32 stores of a
+// wave dense (16 bytes per lane, 1 KiB per instruction); eight bf16 columns per lane would leave every store instruction
+// writing half of each 32 bytes.
+// ALIGN = the largest of 4, 2, 1 that divides the row length, 0 for rows shorter than four columns.  Rows of any length from
+// four on are whole chunks: the last lane takes the row's last four columns, whoever else has some of them (the same sums in
+// the same order).  fp32 chunks are one load whatever their address (a dwordx4 asks for no more than a float's); bf16 rows of
+// even length start at dwords; in rows of odd length a chunk is the two dwords that hold its first three columns and its
+// last column by itself, told apart when they are added.  (Element by element, one column per lane, before: V=50257, d=767,
+// B=64 T=1024 288 us, 161 this way; V=40529, d=206, B=6 T=105 108 us, 43 together with the sort of one launch.)
+constexpr int CH = 4;
+
+template <typename TIn, int ALIGN>
 struct Chunk {
     typedef __attribute__((ext_vector_type(4))) unsigned int u4;
+    typedef __attribute__((ext_vector_type(3))) unsigned int u3;
     typedef __attribute__((ext_vector_type(2))) unsigned int u2;
-    typedef typename std::conditional<CH == 1, TIn, typename std::conditional<sizeof(TIn) == 2, u2, u4>::type>::type Raw;
-    static_assert(CH == 1 || CH == 4, "one element or four");
-    static __device__ __forceinline__ Raw zero()
+    typedef u4 __attribute__((aligned(4))) u4_u;
+    typedef u2 __attribute__((aligned(4))) u2_u;
+    static constexpr bool BF16 = sizeof(TIn) == 2;
+    typedef typename std::conditional<!BF16 || ALIGN == 0, u4, typename std::conditional<ALIGN == 1, u3, u2>::type>::type Raw;
+    static __device__ __forceinline__ Raw zero() { return (Raw)(0u); }
+    // columns col .. col+3 of `row` (of length d)
+    static __device__ __forceinline__ Raw load(const TIn* row, int64_t col, int64_t d)
     {
-        if constexpr (CH == 1) return (TIn)0;
-        else if constexpr (sizeof(TIn) == 2) return u2{0u, 0u};
-        else return u4{0u, 0u, 0u, 0u};
+        const TIn* p = row + col;
+        if constexpr (ALIGN == 0) {          // fewer than four columns: the last one stands in for those beyond
+            Raw z;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const TIn x = p[e < (int)d ? e : (int)d - 1];
+                z[e] = __builtin_bit_cast(typename std::conditional<BF16, unsigned short, unsigned int>::type, x);
+            }
+            return z;
+        } else if constexpr (!BF16) return *(const u4_u*)p;
+        else if constexpr (ALIGN == 4) return *(const u2*)p;
+        else if constexpr (ALIGN == 2) return *(const u2_u*)p;
+        else {
+            const u2 q = *(const u2_u*)((uintptr_t)p & ~(uintptr_t)3);
+            Raw z;
+            z[0] = q[0];
+            z[1] = q[1];
+            z[2] = p[3];
+            return z;
+        }
     }
-    static __device__ __forceinline__ Raw load(const TIn* p)
+    // odd: the chunk starts in the second half of a dword
+    static __device__ __forceinline__ void add_to(float (&acc)[CH], const Raw& raw, bool odd)
     {
-        if constexpr (CH == 1) return p[0];
-        else return *(const Raw*)p;
-    }
-    static __device__ __forceinline__ void add_to(float (&acc)[CH], const Raw& raw)
-    {
-        if constexpr (CH == 1) acc[0] += widen_el(raw);
-        else if constexpr (sizeof(TIn) == 2) {
+        if constexpr (ALIGN == 0 || !BF16) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(BF16 ? raw[e] << 16 : raw[e]);
+        } else if constexpr (ALIGN == 1) {
+            const unsigned int lo0 = raw[0] << 16, hi0 = raw[0] & 0xffff0000u, lo1 = raw[1] << 16, hi1 = raw[1] & 0xffff0000u;
+            acc[0] += __uint_as_float(odd ? hi0 : lo0);
+            acc[1] += __uint_as_float(odd ? lo1 : hi0);
+            acc[2] += __uint_as_float(odd ? hi1 : lo1);
+            acc[3] += __uint_as_float(raw[2] << 16);
+        } else {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 acc[2 * e] += __uint_as_float(raw[e] << 16);
                 acc[2 * e + 1] += __uint_as_float(raw[e] & 0xffff0000u);
             }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(raw[e]);
         }
     }
 };
 
-// OUTPUT: rows of S, which nothing reads soon: past the caches (two statistics of a GPT-2 vocabulary are 309 MB; 141 -> 130 us)
-template <int CH, bool OUTPUT = true>
-__device__ __forceinline__ void store_chunk(float* p, const float (&v)[CH])
+// Four columns, in rows shorter than that d of them.  OUTPUT: rows of S, which nothing reads soon: past the caches (two
+// statistics of a GPT-2 vocabulary are 309 MB; 141 -> 130 us)
+template <int ALIGN, bool OUTPUT = true>
+__device__ __forceinline__ void store_chunk(float* p, const float (&v)[CH], int64_t d)
 {
-    if constexpr (CH == 1) p[0] = v[0];
-    else {
-        typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef f4 __attribute__((aligned(4))) f4_u;
+    const f4 q = {v[0], v[1], v[2], v[3]};
+    if constexpr (ALIGN == 0) {
 #pragma unroll
-        for (int e = 0; e < CH; e += 4) {
-            const f4 q = {v[e], v[e + 1], v[e + 2], v[e + 3]};
-            if constexpr (OUTPUT) __builtin_nontemporal_store(q, (f4*)(p + e));
-            else *(f4*)(p + e) = q;
-        }
-    }
+        for (int e = 0; e < 3; ++e)
+            if (e < (int)d) p[e] = v[e];
+    } else if constexpr (OUTPUT) __builtin_nontemporal_store(q, (f4_u*)p);
+    else *(f4_u*)p = q;
+}
+
+// first column of the chunk at `col` (a multiple of four): the row's last chunk ends with the row
+template <int ALIGN>
+__device__ __forceinline__ int64_t chunk_start(int64_t col, int64_t d)
+{
+    return ALIGN != 0 && ALIGN != 4 && col + CH > d ? d - CH : col;
 }
 
 // waves of a workgroup: two of 12 or three of 8 share a compute unit where 16 left the first half of a frequent token's run waiting
@@ -222,7 +366,6 @@ constexpr int EMB_ZROWS = 8;     // vocabulary rows a zero-fill wave looks at
 constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent rows a lane keeps in flight
 constexpr int EMB_ALONE = 64;    // a vocabulary row with at most this many positions is done by one wave
 
-template <int CH>
 struct RowSums {
     float id[CH], sq[CH], sg[CH];
     __device__ __forceinline__ void clear()
@@ -252,9 +395,9 @@ __device__ __forceinline__ int first_at_least(const int* __restrict__ pos, int l
 
 // Accumulates the cotangent rows of one vocabulary row, example by example: acc holds the running sum of the current
 // example, phi(acc) goes to the row's sums when the example changes.
-template <typename TIn, int CH, int WANT>
+template <typename TIn, int ALIGN, int WANT>
 struct RowAccumulator {
-    RowSums<CH> sums;
+    RowSums sums;
     float acc[CH];
     int limit;     // first position of the next example
     bool open;     // acc holds something
@@ -279,14 +422,14 @@ struct RowAccumulator {
         }
     }
     // p is uniform over the wave
-    __device__ __forceinline__ void add(int p, const typename Chunk<TIn, CH>::Raw& raw)
+    __device__ __forceinline__ void add(int p, const typename Chunk<TIn, ALIGN>::Raw& raw, bool odd)
     {
         if (p >= limit) {
             if (open) fold();
             open = true;
             limit = (p / T + 1) * T;
         }
-        Chunk<TIn, CH>::add_to(acc, raw);
+        Chunk<TIn, ALIGN>::add_to(acc, raw, odd);
     }
     __device__ __forceinline__ void finish()
     {
@@ -304,26 +447,27 @@ struct RowAccumulator {
 //     examples they belong to, then adds them in order.  Runs longer than EMB_ALONE are only noted; after a barrier
 //     the whole workgroup does each of them, every wave on a contiguous run of whole examples, combined in wave order.
 //   zero-fill workgroup: wave i looks at EMB_ZROWS vocabulary rows and writes zeros to those without positions.
-template <typename TIn, int CH, int WANT>
+template <typename TIn, int ALIGN, int WANT>
 __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* __restrict__ G, const int* __restrict__ row_start,
                                                                     const int* __restrict__ keys, const int* __restrict__ pos,
                                                                     int N, int V, int T, int64_t d, int chunk_groups, int colblocks,
                                                                     float* __restrict__ partial, float* __restrict__ S_id,
                                                                     float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
-    typedef Chunk<TIn, CH> Ck;
+    typedef Chunk<TIn, ALIGN> Ck;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool zero_fill = (int)blockIdx.x >= chunk_groups * colblocks;
     const int group = zero_fill ? (int)blockIdx.x - chunk_groups * colblocks : (int)blockIdx.x / colblocks;
-    const int64_t col = ((int64_t)(blockIdx.x % colblocks) * 64 + lane) * CH;
-    const bool col_ok = col < d;
-    auto store_row = [&](int v, const RowSums<CH>& sums) {
+    const int64_t col0 = ((int64_t)(blockIdx.x % colblocks) * 64 + lane) * CH;
+    const bool col_ok = col0 < d;
+    const int64_t col = chunk_start<ALIGN>(col0, d);
+    auto store_row = [&](int v, const RowSums& sums) {
         if (!col_ok) return;
         const int64_t o = (int64_t)v * d + col;
-        if (WANT & 1) store_chunk<CH>(S_id + o, sums.id);
-        if (WANT & 2) store_chunk<CH>(S_sq + o, sums.sq);
-        if (WANT & 4) store_chunk<CH>(S_sg + o, sums.sg);
+        if (WANT & 1) store_chunk<ALIGN>(S_id + o, sums.id, d);
+        if (WANT & 2) store_chunk<ALIGN>(S_sq + o, sums.sq, d);
+        if (WANT & 4) store_chunk<ALIGN>(S_sg + o, sums.sg, d);
     };
 
     if (zero_fill) {
@@ -332,16 +476,17 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         const int v = (group * EMB_WAVES + wave) * EMB_ZROWS + lane;
         const bool empty = lane < EMB_ZROWS && v < V && row_start[v] == row_start[v + 1];
         unsigned long long todo = __ballot(empty);
-        RowSums<CH> zeros;
+        RowSums zeros;
         zeros.clear();
         while (todo) {
             const int l = __builtin_ctzll(todo);
             todo &= todo - 1;
             const int64_t o = (int64_t)(v - lane + l) * d;
-            for (int64_t c = (int64_t)lane * CH; c < d; c += 64 * CH) {
-                if (WANT & 1) store_chunk<CH>(S_id + o + c, zeros.id);
-                if (WANT & 2) store_chunk<CH>(S_sq + o + c, zeros.sq);
-                if (WANT & 4) store_chunk<CH>(S_sg + o + c, zeros.sg);
+            for (int64_t c0 = (int64_t)lane * CH; c0 < d; c0 += 64 * CH) {
+                const int64_t c = chunk_start<ALIGN>(c0, d);
+                if (WANT & 1) store_chunk<ALIGN>(S_id + o + c, zeros.id, d);
+                if (WANT & 2) store_chunk<ALIGN>(S_sq + o + c, zeros.sq, d);
+                if (WANT & 4) store_chunk<ALIGN>(S_sg + o + c, zeros.sg, d);
             }
         }
         return;
@@ -351,7 +496,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
     __shared__ float comb[3][64 * CH];
     if (lane == 0) heavy_row[wave] = -1;
 
-    RowAccumulator<TIn, CH, WANT> ra;
+    RowAccumulator<TIn, ALIGN, WANT> ra;
     ra.start(T);
     {
         const int64_t c0l = ((int64_t)group * EMB_WAVES + wave) * EMB_U;
@@ -382,7 +527,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
                 eu[u] = __builtin_amdgcn_readlane(re, u);
             }
 #pragma unroll
-            for (int u = 0; u < EMB_U; ++u) data[u] = (pu[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pu[u] * d + col) : Ck::zero();
+            for (int u = 0; u < EMB_U; ++u) data[u] = (pu[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pu[u] * d, col, d) : Ck::zero();
 #pragma unroll
             for (int u = 0; u < EMB_U; ++u) {
                 if (pu[u] < 0) continue;
@@ -391,7 +536,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
                     cur_v = ku[u];
                     open_end = eu[u];
                 }
-                ra.add(pu[u], data[u]);
+                ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
             }
             // the last position of the batch decides where the next batch starts: inside a run that is loaded the next
             // batch follows on; a run that is not (another wave's, or a long one) is skipped to its end
@@ -449,10 +594,10 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
                 if (pp[u] >= N) pp[u] = -1;   // positions are in [0, N)
             }
 #pragma unroll
-            for (int u = 0; u < EMB_U; ++u) data[u] = (pp[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pp[u] * d + col) : Ck::zero();
+            for (int u = 0; u < EMB_U; ++u) data[u] = (pp[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pp[u] * d, col, d) : Ck::zero();
 #pragma unroll
             for (int u = 0; u < EMB_U; ++u)
-                if (pp[u] >= 0) ra.add(pp[u], data[u]);
+                if (pp[u] >= 0) ra.add(pp[u], data[u], ((pp[u] + (int)col) & 1) != 0);
         }
         ra.finish();
         for (int i = 0; i < EMB_WAVES; ++i) {
@@ -475,9 +620,9 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
             if (!from_before && !goes_on) store_row(hv, ra.sums);
             else if (col_ok) {
                 float* pr = partial + (((int64_t)group * 2 + (from_before ? 0 : 1)) * 3) * d + col;
-                if (WANT & 1) store_chunk<CH, false>(pr, ra.sums.id);
-                if (WANT & 2) store_chunk<CH, false>(pr + d, ra.sums.sq);
-                if (WANT & 4) store_chunk<CH, false>(pr + 2 * d, ra.sums.sg);
+                if (WANT & 1) store_chunk<ALIGN, false>(pr, ra.sums.id, d);
+                if (WANT & 2) store_chunk<ALIGN, false>(pr + d, ra.sums.sq, d);
+                if (WANT & 4) store_chunk<ALIGN, false>(pr + 2 * d, ra.sums.sg, d);
             }
         }
         __syncthreads();
@@ -487,7 +632,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
 // Finishes the long runs that span several workgroups of embed_rows_kernel: the workgroup-sized slice s in which such a
 // run starts adds up the partial sums of the slices the run covers, in slice order, and stores the row.
 // grid = (slices, column blocks), one wave each.
-template <int CH, int WANT>
+template <int ALIGN, int WANT>
 __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict__ row_start, const int* __restrict__ keys, int N, int V,
                                                            int64_t d, const float* __restrict__ partial, float* __restrict__ S_id,
                                                            float* __restrict__ S_sq, float* __restrict__ S_sg)
@@ -499,8 +644,9 @@ __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict
     if (key < 0 || key >= V) return;
     const int rs = row_start[key], re = row_start[key + 1];
     if (!(rs >= sc0 && re > sc1 && re <= N && re - rs > EMB_ALONE)) return;
-    const int64_t col = ((int64_t)blockIdx.y * 64 + threadIdx.x) * CH;
-    if (col >= d) return;
+    const int64_t col0 = ((int64_t)blockIdx.y * 64 + threadIdx.x) * CH;
+    if (col0 >= d) return;
+    const int64_t col = chunk_start<ALIGN>(col0, d);
     float sum[3][CH];
     auto take = [&](int64_t slice, int slot, bool first) {
         const float* pr = partial + ((slice * 2 + slot) * 3) * d + col;
@@ -508,15 +654,18 @@ __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict
         for (int o = 0; o < 3; ++o) {
             if (!(WANT & (1 << o))) continue;
 #pragma unroll
-            for (int e = 0; e < CH; ++e) sum[o][e] = first ? pr[o * d + e] : sum[o][e] + pr[o * d + e];
+            for (int e = 0; e < CH; ++e) {
+                const float v = ALIGN != 0 || e < (int)d ? pr[o * d + e] : 0.f;
+                sum[o][e] = first ? v : sum[o][e] + v;
+            }
         }
     };
     take(blockIdx.x, 1, true);
     for (int64_t sl = (int64_t)blockIdx.x + 1; sl * SLICE < re; ++sl) take(sl, 0, false);
     const int64_t o = (int64_t)key * d + col;
-    if (WANT & 1) store_chunk<CH>(S_id + o, sum[0]);
-    if (WANT & 2) store_chunk<CH>(S_sq + o, sum[1]);
-    if (WANT & 4) store_chunk<CH>(S_sg + o, sum[2]);
+    if (WANT & 1) store_chunk<ALIGN>(S_id + o, sum[0], d);
+    if (WANT & 2) store_chunk<ALIGN>(S_sq + o, sum[1], d);
+    if (WANT & 4) store_chunk<ALIGN>(S_sg + o, sum[2], d);
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -560,6 +709,13 @@ hipError_t sort_positions(const TId* ids, int N, int V, const EmbedLayout& L, ch
     int* va = (int*)(ws + L.vals_a);
     int* kb = (int*)(ws + L.keys_b);
     int* vb = (int*)(ws + L.vals_b);
+    int* row_start = (int*)(ws + L.row_start);
+    if (N <= SMALL_N) {
+        sort_small_kernel<TId><<<dim3(1), dim3(SMALL_WAVES * 64), 0, stream>>>(ids, N, V, L.passes, ka, va, row_start);
+        *keys = ka;
+        *vals = va;
+        return hipGetLastError();
+    }
     const dim3 grid(L.nblocks), block(256);
     const int* kin = nullptr;
     const int* vin = nullptr;
@@ -579,10 +735,11 @@ hipError_t sort_positions(const TId* ids, int N, int V, const EmbedLayout& L, ch
     }
     *keys = kin;
     *vals = vin;
+    row_start_kernel<<<dim3((unsigned)(((int64_t)N + 1 + 255) / 256)), dim3(256), 0, stream>>>(kin, N, V, row_start);
     return hipGetLastError();
 }
 
-template <typename TIn, int CH, int WANT>
+template <typename TIn, int ALIGN, int WANT>
 hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, const int* pos, int N, int V, int T, int64_t d,
                        float* partial, float* S_id, float* S_sq, float* S_sg, hipStream_t stream)
 {
@@ -590,27 +747,27 @@ hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, cons
     const int chunk_groups = (int)((N + per_group - 1) / per_group);
     const int zero_groups = (int)(((int64_t)V + EMB_WAVES * EMB_ZROWS - 1) / (EMB_WAVES * EMB_ZROWS));
     const unsigned colblocks = (unsigned)((d + 64 * CH - 1) / (64 * CH));
-    embed_rows_kernel<TIn, CH, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
+    embed_rows_kernel<TIn, ALIGN, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
         G, row_start, keys, pos, N, V, T, d, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    embed_combine_kernel<CH, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, partial,
+    if (e != hipSuccess || chunk_groups == 1) return e;       // no run leaves a single slice
+    embed_combine_kernel<ALIGN, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, partial,
                                                                                                    S_id, S_sq, S_sg);
     return hipGetLastError();
 }
 
-template <typename TIn, int CH>
+template <typename TIn, int ALIGN>
 hipError_t launch_rows_want(uint32_t want, const TIn* G, const int* rs, const int* keys, const int* pos, int N, int V, int T, int64_t d, float* pr, float* a,
                             float* q, float* g, hipStream_t st)
 {
     switch (want) {
-    case 1: return launch_rows<TIn, CH, 1>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 2: return launch_rows<TIn, CH, 2>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 3: return launch_rows<TIn, CH, 3>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 4: return launch_rows<TIn, CH, 4>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 5: return launch_rows<TIn, CH, 5>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 6: return launch_rows<TIn, CH, 6>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    default: return launch_rows<TIn, CH, 7>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 1: return launch_rows<TIn, ALIGN, 1>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 2: return launch_rows<TIn, ALIGN, 2>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 3: return launch_rows<TIn, ALIGN, 3>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 4: return launch_rows<TIn, ALIGN, 4>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 5: return launch_rows<TIn, ALIGN, 5>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 6: return launch_rows<TIn, ALIGN, 6>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    default: return launch_rows<TIn, ALIGN, 7>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
     }
 }
 
@@ -632,15 +789,17 @@ hipError_t launch_embed_stat(const void* ids, int ids_bytes, const void* G, int6
     if (e != hipSuccess) return e;
     int* row_start = (int*)(ws + L.row_start);
     float* partial = (float*)(ws + L.partial);
-    row_start_kernel<<<dim3((unsigned)(((int64_t)N + 1 + 255) / 256)), dim3(256), 0, stream>>>(keys, N, (int)V, row_start);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (dt == PEX_BF16) {
-        if (d % 4 == 0) return launch_rows_want<uint16_t, 4>(want, (const uint16_t*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign, stream);
-        return launch_rows_want<uint16_t, 1>(want, (const uint16_t*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign, stream);
-    }
-    if (d % 4 == 0) return launch_rows_want<float, 4>(want, (const float*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign, stream);
-    return launch_rows_want<float, 1>(want, (const float*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign, stream);
+    auto rows = [&](auto zero, auto align) {
+        typedef decltype(zero) TIn;
+        return launch_rows_want<TIn, decltype(align)::value>(want, (const TIn*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign,
+                                                             stream);
+    };
+    constexpr std::integral_constant<int, 4> A4{};
+    constexpr std::integral_constant<int, 2> A2{};
+    constexpr std::integral_constant<int, 1> A1{};
+    constexpr std::integral_constant<int, 0> A0{};
+    if (dt == PEX_BF16) return d < CH ? rows(uint16_t{}, A0) : d % 4 == 0 ? rows(uint16_t{}, A4) : d % 2 == 0 ? rows(uint16_t{}, A2) : rows(uint16_t{}, A1);
+    return d < CH ? rows(float{}, A0) : d % 4 == 0 ? rows(float{}, A4) : rows(float{}, A1);
 }
 
 }  // namespace pex
