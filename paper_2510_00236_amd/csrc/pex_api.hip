@@ -200,7 +200,10 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     tiles = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn);
     const int64_t slab = 64;
     units = per_example ? B : (B * T + slab - 1) / slab;
-    const int max_split = option(PEX_OPT_MAX_SPLIT);
+    // The option bounds the workspace; the norms exchange no partial sums, so unless it is lowered they take as many groups as
+    // there are examples (B=56 T=1150 64x312, two blocks: 32 groups 71 us, 56 groups 27)
+    int max_split = option(PEX_OPT_MAX_SPLIT);
+    if (mode == MODE_NORMS && max_split == 32) max_split = B < 1024 ? (int)B : 1024;
     int64_t nsplit = 1, per = units;
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
     bool sign_bytes = false, mem_fold = false;
