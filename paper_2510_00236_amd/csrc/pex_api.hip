@@ -165,6 +165,24 @@ static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode m
     return t * passes > (mode == MODE_TOKEN_SQ ? 200.0e-6 : 14.0e-6);
 }
 
+// What pex_stat_noalloc charges a call against its scratch.  bf16 layers of whole 16-byte chunks: what their plan needs.
+// The others: the partial sums of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every
+// compute unit -- a figure of the shape alone, so that which calls are too large does not move with their plans.
+static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
+{
+    if (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) return plan_stat(B, T, din, dout, dt, mode).ws_bytes;
+    const bool chunked = dt == PEX_F32 && din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
+    const int64_t edge = chunked ? 128 : 64, target = chunked ? 768 : 1024;
+    const int64_t tiles = ((din + edge - 1) / edge) * ((dout + edge - 1) / edge);
+    const int64_t units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
+    int64_t ns = (target + tiles - 1) / tiles;
+    if (ns > option(PEX_OPT_MAX_SPLIT)) ns = option(PEX_OPT_MAX_SPLIT);
+    if (ns > units) ns = units;
+    const int64_t per = (units + ns - 1) / ns;
+    ns = (units + per - 1) / per;
+    return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
+}
+
 static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
 {
     StatPlan p{};
@@ -208,12 +226,13 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
     bool sign_bytes = false, mem_fold = false;
     if (p.kernel == 2) {
-        // partial sums of at most PEX_NOALLOC_SCRATCH_BYTES, so that every plan fits the library's own scratch (512 workgroups
-        // need more only beyond 2048 x 2048, where two groups are enough)
+        // Calls that pex_stat_noalloc takes keep their partial sums within its scratch; the others are free (B=42 T=112 704x3648
+        // sign, 10 MB of S, three groups in 32 MB: 321 us, free 311; B=16 T=512 1536x1536 square 369 and 319)
+        const bool held = mode <= MODE_SIGN && scratch_charge(B, T, din, dout, dt, mode) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
         const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
         cheapest_split_f32(tiles, units, per_example ? (double)T : (double)slab, (bm / 64) * (bn / 64),
-                           mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0,
-                           mode == MODE_NORMS || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit), &nsplit, &per);
+                           mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit),
+                           &nsplit, &per);
     } else if (p.kernel != 1) {
         nsplit = (target + tiles - 1) / tiles;
         if (nsplit > max_split) nsplit = max_split;
@@ -505,24 +524,6 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
         if (e != hipSuccess) return PEX_ERR_HIP;
     }
     return PEX_OK;
-}
-
-// What pex_stat_noalloc charges a call against its scratch.  bf16 layers of whole 16-byte chunks: what their plan needs.
-// The others: the partial sums of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every
-// compute unit -- a figure of the shape alone, so that which calls are too large does not move with their plans.
-static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
-{
-    if (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) return plan_stat(B, T, din, dout, dt, mode).ws_bytes;
-    const bool chunked = dt == PEX_F32 && din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
-    const int64_t edge = chunked ? 128 : 64, target = chunked ? 768 : 1024;
-    const int64_t tiles = ((din + edge - 1) / edge) * ((dout + edge - 1) / edge);
-    const int64_t units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
-    int64_t ns = (target + tiles - 1) / tiles;
-    if (ns > option(PEX_OPT_MAX_SPLIT)) ns = option(PEX_OPT_MAX_SPLIT);
-    if (ns > units) ns = units;
-    const int64_t per = (units + ns - 1) / ns;
-    ns = (units + per - 1) / per;
-    return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
 }
 
 // How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (on the layers the
