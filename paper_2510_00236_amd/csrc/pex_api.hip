@@ -72,7 +72,8 @@ static int option(int opt) { return options().v[opt].load(); }
 // The bf16 kernels run one workgroup per compute unit, so a launch of `tiles` blocks with the batch in `ns` groups takes
 //   rounds(ns) * ceil(units / ns)  unit-times,  rounds = ceil(tiles * ns / 256),
 // its workgroups write ns copies of the output (s_bytes each) and the fixed-order reduction reads them back and writes
-// the sum, all at ~4 TB/s.
+// the sum, all at ~4 TB/s, in a launch of its own: ~6 us on layers so small that it counts (B=2 T=192 64x288 square, an
+// example 3.7 us: one group 14 us, two groups 19).
 // fold_bytes > 0: every workgroup adds that many bytes to the output in memory after each of its units but the first
 // (which stores); the workgroups of a round do so at the same time, and what they move -- read and written back
 // across the fabric -- goes at ~5.5 TB/s while they wait (measured: 22 - 29 us for the 67 MB of a 1B-scale layer).
@@ -91,7 +92,7 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
             const int64_t at_once = tiles * ns_eff < 256 ? tiles * ns_eff : 256;
             cost += (double)rounds * (double)(pu - 1) * (2.0 * (double)at_once * fold_bytes / 5.5e12 + 2.0e-6);
         }
-        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 3.0e-6;
+        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + (s_bytes > 0.0 ? 6.0e-6 : 0.0);
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -99,8 +100,8 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
 
 // The fp32 kernel: a wave multiplies one 64 x 64 tile on the MFMA pipe of its SIMD (0.15e12 FLOP/s; alone there it keeps
 // the pipe about 87 % busy, two waves about 95 %), `waves` of them make a workgroup, up to eight waves share a compute unit.
-// A group of `pu` units therefore takes as long as the busiest pipe: ceil(workgroups / 256) workgroups of pu units on four
-// pipes, at least one wave's own work.  Exchange of partial sums as above.
+// A group of `pu` units therefore takes as long as the busiest pipe: ceil(workgroups / 256) waves of pu units (the waves of
+// workgroups of two or three meet on the same pipes, single waves spread), at least one wave's own work.  Exchange of partial sums as above.
 static double cheapest_split_f32(int64_t tiles, int64_t units, double rows_per_unit, int waves, double s_bytes, int max_split, int64_t* nsplit,
                                  int64_t* per)
 {
@@ -110,7 +111,7 @@ static double cheapest_split_f32(int64_t tiles, int64_t units, double rows_per_u
     for (int64_t ns = 1; ns <= lim; ++ns) {
         const int64_t pu = (units + ns - 1) / ns;
         const int64_t ns_eff = (units + pu - 1) / pu;
-        const double per_pipe = (double)((tiles * ns_eff + 255) / 256) * waves / 4.0;
+        const double per_pipe = (double)((tiles * ns_eff + 255) / 256) * (waves > 1 ? 1.0 : 0.25);
         double cost = (double)pu * wave_unit * (per_pipe > 1.0 ? per_pipe * 1.05 : 1.15);
         if (ns_eff > 1 && s_bytes > 0.0) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 2.5e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
@@ -147,9 +148,10 @@ static double fold_time(Mode mode, int bn, bool shared)
 // than that: about 1.35 us per slab of 16 rows in a workgroup's serial loop, 35e12 FLOP/s at best on layers near the line.
 // Measured (SIMT / copies): B=8 T=64 70x130 square 20.6 / 24.8 us, B=8 T=128 201x333 square 21.9 / 24.6, B=16 T=128 301x500
 // identity + square 60 / 28, B=16 T=256 333x1001 square 86 / 33, B=2 T=4096 100x131 square 353 / 68.
-// `passes` = statistics the SIMT kernel would make one by one.  The per-token square takes four contractions and copies of
-// twice the size (see pex_pad.hip), and the SIMT kernel reaches 60e12 FLOP/s on its larger layers: from an estimate of 200 us
-// (SIMT / halves: B=16 T=256 333x1001 75 / 96 us, B=64 T=256 999x768 425 / 208, B=14 T=544 3776x1943 1735 / 451).
+// `passes` = statistics the SIMT kernel would make one by one.  The per-token square takes four contractions (on blocks of 256 x
+// 256, at ~1.4e15 FLOP/s) and copies of twice the size (10 bytes moved per element; see pex_pad.hip), the SIMT kernel reaches
+// 60e12 FLOP/s on its larger layers (SIMT / halves: B=16 T=256 333x1001 75 / 96 us, B=64 T=256 999x768 425 / 208, B=14 T=544
+// 3776x1943 1735 / 451, but B=37 T=1744 2240x58, three quarters of whose blocks are padding, 383 / 502).
 static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int passes)
 {
     if (din % 8 == 0 && dout % 8 == 0) return false;
@@ -161,8 +163,12 @@ static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode m
     if (groups > 32) groups = 32;
     const double slabs = (double)((units + groups - 1) / groups) * (plain ? 4.0 : (double)((T + 15) / 16));
     const double flop = 2.0 * (double)B * (double)T * (double)din * (double)dout;
+    if (mode == MODE_TOKEN_SQ) {
+        const double rows = (double)B * (double)T, area = (double)((din + 255) / 256 * 256) * (double)((dout + 255) / 256 * 256);
+        return 8.0 * rows * area / 1.4e15 + 10.0 * rows * (double)(din + dout) / 5.0e12 + 60.0e-6 < (flop / 60.0e12 > slabs * 1.35e-6 ? flop / 60.0e12 : slabs * 1.35e-6);
+    }
     const double t = flop / 35.0e12 > slabs * 1.35e-6 ? flop / 35.0e12 : slabs * 1.35e-6;
-    return t * passes > (mode == MODE_TOKEN_SQ ? 200.0e-6 : 14.0e-6);
+    return t * passes > 14.0e-6;
 }
 
 // What pex_stat_noalloc charges a call against its scratch.  bf16 layers of whole 16-byte chunks: what their plan needs.

@@ -276,10 +276,11 @@ hipError_t launch_f32(const void* X, const void* G, int64_t B, int64_t T, int64_
 
 }  // namespace
 
-// Waves of a workgroup: the arrangement of at most four 64 x 64 tiles that leaves the fewest waves without a tile at the layer's
-// edges, the largest and squarest among equals (2 x 2 draws the fewest bytes).  A wave without one exits and leaves its SIMD to
-// the others' waves, which sit on theirs: 152 x 3328 in blocks of 2 x 2 kept half the SIMDs half idle (B=22 T=2889 per-token
-// square 865 us, 613 in rows of 3).
+// Waves of a workgroup: the arrangement of at most four 64 x 64 tiles that makes the fewest workgroups of the layer, among equals
+// the one with the fewest waves, then the squarest (2 x 2 draws the fewest bytes).  Workgroups are what counts: a wave without a
+// tile exits and leaves its SIMD idle beside the others', and the waves of two small workgroups meet on the same SIMDs.
+// Measured, 3 x 52 tiles (152 x 3328, B=22 T=2889 per-token square): 2 x 2 waves 865 us, 1 x 4 609; 2 x 13 tiles (128 x 828, B=32
+// T=1997 square): 2 x 1 waves 243 us, 2 x 2 136.
 void f32_tile_shape(int64_t din, int64_t dout, int* bm, int* bn)
 {
     const int64_t tm = (din + F_T - 1) / F_T, tn = (dout + F_T - 1) / F_T;
@@ -287,9 +288,9 @@ void f32_tile_shape(int64_t din, int64_t dout, int* bm, int* bn)
     int wm = 1, wn = 1;
     for (int a = 1; a <= 4; ++a)
         for (int b = 1; a * b <= 4; ++b) {
-            const int64_t slots = ((tm + a - 1) / a) * ((tn + b - 1) / b) * a * b;
-            const bool better = best == 0 || slots < best || (slots == best && (a * b > wm * wn || (a * b == wm * wn && a + b < wm + wn)));
-            if (better) { best = slots; wm = a; wn = b; }
+            const int64_t blocks = ((tm + a - 1) / a) * ((tn + b - 1) / b);
+            const bool better = best == 0 || blocks < best || (blocks == best && (a * b < wm * wn || (a * b == wm * wn && a + b < wm + wn)));
+            if (better) { best = blocks; wm = a; wn = b; }
         }
     *bm = wm * F_T;
     *bn = wn * F_T;
