@@ -72,7 +72,7 @@ static int option(int opt) { return options().v[opt].load(); }
 // The bf16 kernels run one workgroup per compute unit, so a launch of `tiles` blocks with the batch in `ns` groups takes
 //   rounds(ns) * ceil(units / ns)  unit-times,  rounds = ceil(tiles * ns / 256),
 // its workgroups write ns copies of the output (s_bytes each) and the fixed-order reduction reads them back and writes
-// the sum, all at ~4 TB/s, in a launch of its own: ~6 us on layers so small that it counts (B=2 T=192 64x288 square, an
+// the sum, all at ~4 TB/s, in a launch of its own: ~5.5 us on layers so small that it counts (B=2 T=192 64x288 square, an
 // example 3.7 us: one group 14 us, two groups 19).
 // fold_bytes > 0: every workgroup adds that many bytes to the output in memory after each of its units but the first
 // (which stores); the workgroups of a round do so at the same time, and what they move -- read and written back
@@ -92,7 +92,7 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
             const int64_t at_once = tiles * ns_eff < 256 ? tiles * ns_eff : 256;
             cost += (double)rounds * (double)(pu - 1) * (2.0 * (double)at_once * fold_bytes / 5.5e12 + 2.0e-6);
         }
-        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + (s_bytes > 0.0 ? 6.0e-6 : 0.0);
+        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + (s_bytes > 0.0 ? 5.5e-6 : 0.0);
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
