@@ -72,8 +72,7 @@ static int option(int opt) { return options().v[opt].load(); }
 // The bf16 kernels run one workgroup per compute unit, so a launch of `tiles` blocks with the batch in `ns` groups takes
 //   rounds(ns) * ceil(units / ns)  unit-times,  rounds = ceil(tiles * ns / 256),
 // its workgroups write ns copies of the output (s_bytes each) and the fixed-order reduction reads them back and writes
-// the sum, all at ~4 TB/s, in a launch of its own: ~5.5 us on layers so small that it counts (B=2 T=192 64x288 square, an
-// example 3.7 us: one group 14 us, two groups 19).
+// the sum, all at ~4 TB/s.
 // fold_bytes > 0: every workgroup adds that many bytes to the output in memory after each of its units but the first
 // (which stores); the workgroups of a round do so at the same time, and what they move -- read and written back
 // across the fabric -- goes at ~5.5 TB/s while they wait (measured: 22 - 29 us for the 67 MB of a 1B-scale layer).
@@ -92,7 +91,7 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
             const int64_t at_once = tiles * ns_eff < 256 ? tiles * ns_eff : 256;
             cost += (double)rounds * (double)(pu - 1) * (2.0 * (double)at_once * fold_bytes / 5.5e12 + 2.0e-6);
         }
-        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + (s_bytes > 0.0 ? 5.5e-6 : 0.0);
+        if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 3.0e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -128,19 +127,6 @@ static double bf16_block_rate(int bm, int bn)
 {
     const int area = bm * bn;
     return area >= 256 * 256 ? 5.5e12 : (area >= 256 * 192 ? 4.8e12 : 4.3e12);
-}
-
-// What an example costs a workgroup of the bf16 kernel besides its slabs of 32 rows: the fold, and the hand-over to the next
-// example.  Measured on layers of 256 and of 3 blocks with T = 32 .. 512 (time per example, extrapolated to no slabs): 0.8 us for
-// one statistic on 256 x 128 blocks, 1.1 for several or on 256 x 192, 1.9 for the norms and 2.4 for sign on 256 x 256.  Without it
-// the planner left layers of short sequences in one group (B=24 T=23 176x2496 weighted sum: 20 workgroups, 30 us; the
-// whole clipped sum 43.5 -> 32.4).
-static double slab_rows(int64_t T) { return (double)((T + 31) / 32 * 32); }
-static double fold_time(Mode mode, int bn, bool shared)
-{
-    if (mode == MODE_SIGN) return bn >= 256 ? 2.4e-6 : 1.1e-6;
-    if (mode == MODE_NORMS) return 1.9e-6;
-    return shared || bn > 128 ? 1.1e-6 : 0.8e-6;
 }
 
 // bf16 layers whose rows are not whole 16-byte chunks: padded copies on the MFMA kernels, or the SIMT kernel on the operands as
@@ -247,8 +233,8 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         per = (units + nsplit - 1) / nsplit;
     } else {
         // A unit-time is one example (or 64 rows) on one block.
-        const double rows_per_unit = per_example ? slab_rows(T) : (double)slab;
-        const double t_unit = 2.0 * rows_per_unit * bm * bn / bf16_block_rate(bm, bn) + (per_example ? fold_time(mode, bn, !allow_wide) : 0.0);
+        const double rows_per_unit = per_example ? (double)T : (double)slab;
+        const double t_unit = 2.0 * rows_per_unit * bm * bn / bf16_block_rate(bm, bn);
         // (the per-example norms exchange no partial sums of S, only one number per workgroup and example)
         double best = cheapest_split(tiles, units, t_unit, mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, max_split, &nsplit, &per);
         // Packed sign counts can be exchanged as bytes while a group holds at most 127 examples: a quarter of the
@@ -272,7 +258,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
             int wm, wn;
             bf16_wide_tile_shape(&wm, &wn);
             const int64_t tiles_m = (din + wm - 1) / wm, max_wide = dout / wn;
-            const double t_wide = 2.0 * slab_rows(T) * wm * wn / bf16_block_rate(wm, wn) + fold_time(mode, wn, false);
+            const double t_wide = 2.0 * (double)T * wm * wn / bf16_block_rate(wm, wn);
             auto consider = [&](int64_t na, bool forced) {
                 const int64_t rest = dout - na * wn;
                 int64_t ns_w = 1, per_w = units, ns_r = 1, per_r = units;
