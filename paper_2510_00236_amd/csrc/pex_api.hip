@@ -478,7 +478,8 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
             e = launch_stat_bf16((const uint16_t*)X + (k / 2) * xhalf, (const uint16_t*)G + (k % 2) * ghalf, B, T, din, dout, MODE_IDENTITY, part, dst,
                                  dst, stream);
         }
-        if (e == hipSuccess) e = launch_reduce_partials({{partials}, {S}}, 1, 4 * plan.nsplit, n, plan.out_rows, plan.out_cols, dout, plan.out_cols, stream);
+        if (e == hipSuccess) e = launch_reduce_partials({{partials}, {S}}, 1, 4 * plan.nsplit, n, plan.out_rows, plan.out_cols, dout, plan.out_cols, stream,
+                                       plan.nsplit);
         return e == hipSuccess ? PEX_OK : PEX_ERR_HIP;
     }
     if (mode == MODE_TOKEN_SQ && plan.copy_bytes > 0) {

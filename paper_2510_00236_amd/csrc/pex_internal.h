@@ -100,7 +100,7 @@ bool f32_bytes_suffice(const StatPlan& plan);
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
                                  float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
 // Copies of bf16 operands [rows, width] with rows of padded_width(width) elements, zero-filled; an operand whose output
-// is NULL is left out.  squares: the copy holds the rounded squares and, after them, their remainders (twice the size)
+// is NULL is left out.  squares: the copy holds the upper halves of the squares and, after them, their remainders (twice the size)
 int64_t padded_width(int64_t width);
 bool pad_supports(int64_t rows, int64_t din, int64_t dout);
 hipError_t launch_pad_rows(const void* X, void* x_out, const void* G, void* g_out, int64_t rows, int64_t din, int64_t dout, bool squares,
@@ -128,13 +128,13 @@ hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, i
                            float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream);
 
 // For the first `count` entries: S[i * ld + j] = sum_{k < nsplit} partial[k * group_stride + i * pitch + j], k ascending (fixed
-// order => deterministic), i < rows, j < cols.
+// order => deterministic), i < rows, j < cols.  leading > 0: where the sum of the first `leading` groups is not finite, it is S.
 struct ReduceOutputs {
     const float* partial[3];
     float* S[3];
 };
 hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
-                                  int64_t ld, hipStream_t stream);
+                                  int64_t ld, hipStream_t stream, int leading = 0);
 
 hipError_t launch_adam_update(float* theta, float* m, float* v, const float* S_id, const float* S_sq, int64_t n,
                               pex_adam_variant variant, const pex_adam_params& p, hipStream_t stream,

@@ -6,8 +6,9 @@
 // onto those kernels.
 //
 // For the per-token square the copies hold the squares, each as a pair of bf16 that is exact (the SIMT kernel, which these
-// layers came from, keeps the squares in fp32): first the rounded squares of the whole operand, then their remainders.  The four
-// products of the halves are contracted one after the other into partial sums.  B=14 T=544 3776x1943: 1735 us on the SIMT
+// layers came from, keeps the squares in fp32): first the upper halves of the whole operand, then the remainders.  The four
+// products of the halves are contracted one after the other into partial sums; where those of the upper halves overflow or hold an
+// infinity or a NaN, they alone are the result.  B=14 T=544 3776x1943: 1735 us on the SIMT
 // kernel, 451 so.
 //
 // Bound by HBM: 2 bytes read and 2 written per element.  A lane makes one 16-byte chunk of the copy from five dwords at

@@ -165,11 +165,13 @@ hipError_t launch_typed(const TIn* X, const TIn* G, int64_t B, int64_t T, int64_
 // grid dimension is the statistic, so that those of one call share a launch.  Bound by the memory-side cache the partial sums
 // were just written to.  Measured against one float per lane and one launch per statistic: 28 groups of 768 x 768 17.9 ->
 // 11.3 us, identity and square of 512 x 2048 in 8 groups 16 -> 12.7 us.
+// Where the sum of the first `leading` groups is not finite, it is the result (the products of exact halves: an infinity times a
+// remainder of zero is no part of the square).
 typedef __attribute__((ext_vector_type(4))) float float4_v;
 typedef float4_v __attribute__((aligned(4))) float4_u;
 
 __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, int nsplit, int64_t group_stride, int64_t rows, int64_t cols,
-                                                              int64_t pitch, int64_t ld)
+                                                              int64_t pitch, int64_t ld, int leading)
 {
     const float* __restrict__ partial = io.partial[blockIdx.y];
     float* __restrict__ S = io.S[blockIdx.y];
@@ -179,21 +181,31 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, 
         const float* p = partial + i * pitch + j;
         float* out = S + i * ld + j;
         if (j + 4 <= cols) {
-            float4_v s = *(const float4_u*)p;
-            int k = 1;
-            for (; k + 4 <= nsplit; k += 4) {
-                float4_v v[4];
+            auto add = [&](float4_v s, int k, int end) {
+                for (; k + 4 <= end; k += 4) {
+                    float4_v v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = *(const float4_u*)(p + (k + u) * group_stride);
+                    for (int u = 0; u < 4; ++u) v[u] = *(const float4_u*)(p + (k + u) * group_stride);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) s += v[u];
+                    for (int u = 0; u < 4; ++u) s += v[u];
+                }
+                for (; k < end; ++k) s += *(const float4_u*)(p + k * group_stride);
+                return s;
+            };
+            float4_v s = add(*(const float4_u*)p, 1, leading);
+            if (leading < nsplit) {
+                const float4_v all = add(s, leading, nsplit);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) s[c] = __builtin_isfinite(s[c]) ? all[c] : s[c];
             }
-            for (; k < nsplit; ++k) s += *(const float4_u*)(p + k * group_stride);
             *(float4_u*)out = s;
         } else {
             for (int c = 0; j + c < cols; ++c) {
                 float s = p[c];
-                for (int k = 1; k < nsplit; ++k) s += p[k * group_stride + c];
+                for (int k = 1; k < nsplit; ++k) {
+                    if (k == leading && !__builtin_isfinite(s)) break;
+                    s += p[k * group_stride + c];
+                }
                 out[c] = s;
             }
         }
@@ -300,11 +312,12 @@ hipError_t launch_token_norms(const void* X, const void* G, int64_t rows, int64_
 }
 
 hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
-                                  int64_t ld, hipStream_t stream)
+                                  int64_t ld, hipStream_t stream, int leading)
 {
+    if (leading <= 0) leading = nsplit;
     int64_t blocks = (rows * ((cols + 3) / 4) + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    reduce_partials_kernel<<<dim3((unsigned)blocks, (unsigned)count), dim3(256), 0, stream>>>(io, nsplit, group_stride, rows, cols, pitch, ld);
+    reduce_partials_kernel<<<dim3((unsigned)blocks, (unsigned)count), dim3(256), 0, stream>>>(io, nsplit, group_stride, rows, cols, pitch, ld, leading);
     return hipGetLastError();
 }
 

@@ -131,3 +131,29 @@ def test_per_token_square_from_exact_halves(B, T, din, dout):
     got = o.value()
     # terms >= 0 summed in fp32 (at most ~2000 rows per group, then the groups): 1e-5 of every entry
     assert (np.abs(got - ref) <= 1e-5 * ref).all(), float((np.abs(got - ref) / ref).max())
+
+
+def test_per_token_square_of_infinities_and_of_the_largest_squares():
+    """An infinite square meets remainders of zero and of every size and stays infinite; a zero makes it NaN; squares between the
+    largest bf16 and the largest fp32 value stay finite; sums beyond fp32 overflow to infinity."""
+    B, T, din, dout = 16, 300, 1001, 770
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=6)
+    X[1, 3, 999] = float("inf")
+    G[2, 7, 0] = float("-inf")
+    X[0, 0, 2] = 1.842e19          # squared 3.393e38: finite in fp32, above the largest bf16
+    G[0, 0, 769] = 1.0             # a square without a remainder
+    G[1, 3, 5] = 0.0               # inf * 0
+    X[:, :, 7] = 1e18
+    G[:, :, 9] = 1e18              # products of 1e72
+    X[4, 4, 11] = float("nan")
+    halves = -(-din // 8) * 8 + -(-dout // 8) * 8
+    assert pex.pex_token_sq_workspace_bytes(B, T, din, dout, pex.PEX_BF16) >= 4 * B * T * halves, "not on the halves"
+    o = Guarded(din, dout)
+    pex.pex_token_sq(X.to(DEV), G.to(DEV), S=o.view)
+    got = o.value()
+    x2, g2 = (t.reshape(B * T, -1).float().square().double() for t in (X, G))       # exact in fp32, or infinite
+    ref = (x2.t() @ g2).float().double().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.isinf(ref).sum() > 1000 and np.isnan(ref).sum() > 700
+    ok = np.isfinite(ref)
+    assert (np.abs(got - ref)[ok] <= 1e-5 * ref[ok]).all()      # as above
