@@ -336,8 +336,11 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // Through the Gram matrices instead: 2 T^2 (din + dout) FLOP per example (a little over half of it with the
         // symmetry, in 128 x 128 blocks) against 2 T din dout, on a kernel of lower rate but with one workgroup per block
         // and example -- no batch split, however few tiles the layer has.
+        // Not for padded copies: layers of odd width keep the contraction.  A sum of squares is exact to rounding whatever the inputs,
+        // <X X^T, G G^T> cancels where tokens are alike (X = 1 + 0.03 noise, G of zero mean over the tokens, B=4 T=190 257x40: relative
+        // error 2e-8 by the contraction, 5e-5 through the Gram matrices).
         const int gram_opt = option(PEX_OPT_GRAM_NORMS);
-        if (dt == PEX_BF16 && gram_opt != 0 && gram_supports(B, T, din, dout)) {
+        if (dt == PEX_BF16 && gram_opt != 0 && p.copy_bytes == 0 && gram_supports(B, T, din, dout)) {
             // Gram kernel: 6.0e14 FLOP/s on a full chip (its 128 x 128 blocks draw twice the bytes per FLOP from L2 that
             // the 256 x 256 blocks of the contraction do), and never faster than its serial loop over the features, one
             // 64-feature step per ~0.45 us (measured with fewer workgroups than compute units).  Contraction: the plan's

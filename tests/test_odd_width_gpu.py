@@ -101,6 +101,21 @@ def test_norms(pex_option, B, T, din, dout, route):
     assert (np.abs(N - ref) <= 2e-5 * ref.max()).all() and (np.abs(N - ref) <= 1e-4 * ref).all(), (N, ref)
 
 
+@pytest.mark.parametrize("route", [1, 2, 3])
+@pytest.mark.parametrize("B,T,din,dout", [(4, 190, 257, 40), (16, 300, 1001, 770)])
+def test_norms_of_tokens_that_are_alike(pex_option, B, T, din, dout, route):
+    """Inputs near one vector and cotangents without a mean over the sequence: N_b is small against the entries of the T x T Gram
+    matrices, whose product would cancel; a sum of squares cannot."""
+    pex_option("gram_norms", route)
+    X, G = si.custom(B, T, din, dout, dtype="f32", seed=B + 1)
+    X = (1 + 0.03 * X).bfloat16()
+    G = (G - G.mean(1, keepdim=True)).bfloat16()
+    ref = on.example_norms(si.widen(X), si.widen(G))
+    N = f64(pex.pex_example_norms(X.to(DEV), G.to(DEV)))
+    # sums of T products of size |X||G| ~ 1 in fp32 against entries ~ 0.03 sqrt(T): 2e-5 as for the other sums of squares
+    assert (np.abs(N - ref) <= 2e-5 * ref).all(), np.abs(N - ref) / ref
+
+
 def test_without_a_workspace_large_copies_stay_on_the_simt_kernel():
     """Copies of 33 MB do not fit the library's scratch: the call still succeeds, by the other kernel."""
     B, T, din, dout = 4, 4160, 1001, 64
