@@ -214,6 +214,13 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     // there are examples (B=56 T=1150 64x312, two blocks: 32 groups 71 us, 56 groups 27)
     int max_split = option(PEX_OPT_MAX_SPLIT);
     if (mode == MODE_NORMS && max_split == 32) max_split = B < 1024 ? (int)B : 1024;
+    if (p.kernel != 0) {
+        // the MFMA kernels put blocks and groups in one grid dimension, which holds fewer than 2^32 threads (the SIMT kernel has
+        // a dimension for each)
+        const int64_t threads = p.kernel == 2 ? (int64_t)(bm / 64) * (bn / 64) * 64 : 512;
+        const int64_t fit = (((int64_t)1 << 32) - 1) / (tiles * threads);
+        if (max_split > fit) max_split = fit < 1 ? 1 : (int)fit;
+    }
     int64_t nsplit = 1, per = units;
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
     bool sign_bytes = false, mem_fold = false;

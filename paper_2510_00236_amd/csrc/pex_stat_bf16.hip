@@ -712,7 +712,7 @@ hipError_t launch_one(const uint16_t* X, const uint16_t* G, int64_t B, int64_t T
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES); });
     if (attr_err != hipSuccess) return attr_err;
-    const dim3 grid((unsigned)(tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
+    const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
     kern<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)T, (int)din, (int)dout, (int)ldg, (int)ldo, (int)store_rows,
                                                  (int)store_cols, rows_per_split, tiles_m, tiles_n, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, byte_partials ? 1 : 0);
     return hipGetLastError();
@@ -993,7 +993,7 @@ hipError_t launch_quad(const uint16_t* X, const uint16_t* G, int64_t B, int64_t 
     if (attr_err != hipSuccess) return attr_err;
     // S itself has the layer's own widths, partial sums those of the operands
     const int64_t ldo = plan.nsplit == 1 ? plan.out_cols : dout, store_rows = plan.nsplit == 1 ? plan.out_rows : din, store_cols = ldo;
-    const dim3 grid((unsigned)(tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
+    const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * plan.nsplit)), block(TL::NT);
     stat_bf16_quad_kernel<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)din, (int)dout, plan.per_split, tiles_m, tiles_n, (int)ldo,
                                                              (int)store_rows, (int)store_cols, out);
     return hipGetLastError();

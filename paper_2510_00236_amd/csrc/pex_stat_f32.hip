@@ -303,7 +303,7 @@ bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout)
     if ((din < F_T && din % 4 != 0) || (dout < F_T && dout % 4 != 0)) return false;
     // 32-bit byte offsets inside a window of at least four rows
     if (din > ((int64_t)1 << 26) || dout > ((int64_t)1 << 26)) return false;
-    // the one-dimensional grid: below 2^31 threads
+    // one group of the batch: below 2^31 threads (the planner bounds the groups)
     return ((din + F_T - 1) / F_T) * ((dout + F_T - 1) / F_T) < ((int64_t)1 << 25);
 }
 

@@ -1,5 +1,47 @@
-"""Planner choices that can be seen in the workspace a call asks for (host only)."""
+"""Planner choices (host only): those seen in the workspace a call asks for, others through a small program linked to the
+library (plan_probe.cpp)."""
+import os
+import subprocess
+
+import pytest
+
 import paper_2510_00236_amd as pex
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+MODE = {"identity": 0, "square": 1, "sign": 2, "token_sq": 3, "norms": 4, "weighted": 5, "power": 6}
+
+
+def _compile(source, exe):
+    package = os.path.dirname(pex.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + os.path.join(package, "csrc"), os.path.join(HERE, source), pex.LIB_PATH, "-Wl,-rpath," + package, "-Wl,--allow-shlib-undefined",
+                    "-pthread", "-o", exe], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = _compile("plan_probe.cpp", str(tmp_path_factory.mktemp("plan") / "probe"))
+
+    def ask(shapes):
+        """[(B, T, din, dout, dtype code, statistic)] -> [(kernel, nsplit, per_split, blocks, threads)]"""
+        text = "".join(f"{B} {T} {i} {o} {dt} {MODE[m]}\n" for B, T, i, o, dt, m in shapes)
+        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        return [tuple(int(v) for v in l.split()) for l in out.splitlines()]
+
+    return ask
+
+
+def test_launches_stay_below_the_grid_limit(plans):
+    """gridDim.x * blockDim.x of a launch is below 2^32, however many groups of examples would pay."""
+    shapes = [(1021, 16, 8192, 50257, pex.PEX_F32, "norms"), (1021, 16, 16448, 16448, pex.PEX_F32, "norms"), (997, 8, 4096, 128256, pex.PEX_F32, "norms"),
+              (16, 1, 131136, 131136, pex.PEX_F32, "norms"), (1021, 16, 32768, 32776, pex.PEX_BF16, "norms"), (1021, 16, 16384, 131080, pex.PEX_BF16, "norms"),
+              (1021, 16, 8192, 50257, pex.PEX_F32, "square")]
+    for shape, (kernel, nsplit, per_split, blocks, threads) in zip(shapes, plans(shapes)):
+        assert kernel in (1, 2), shape
+        assert blocks * nsplit * threads < 2**32, (shape, nsplit, blocks, threads)
+        assert (nsplit - 1) * per_split < shape[0] <= nsplit * per_split, shape      # every example in a group, none empty
 
 
 def test_fp32_plans_fit_the_librarys_scratch_where_the_call_without_a_workspace_takes_them():
