@@ -97,13 +97,56 @@ __global__ __launch_bounds__(CW * RW) void vec_partial_kernel(const TIn* __restr
     }
 }
 
-// Second pass: per column v_b = sum over the ranges, phi, sum over the examples.  A block is 4 column lanes of VEC columns x
-// EL example lanes x RL range lanes (256 in all); example b belongs to example lane b mod EL, its range r to range lane
-// r mod RL.  Range lanes are added in order through LDS, then phi is applied; the example lanes' sums are added pairwise,
-// always in the same order.
-// Bound by latency (the partial sums are a few MB, fresh in the caches): so a block owns few columns -- d / (4 VEC) blocks --
-// and every lane has eight loads in flight of a chain of nrange / RL * B / EL.  Measured, d = 768 / 2304 / 3072, B = 64, 16 / 6 / 5
-// ranges: 5.5 / 4.8 / 4.7 us (64 columns x 4 example lanes per block, one column per lane, before: 14 / 26 / 23 us).
+// Second pass: per column v_b = sum over the ranges, phi, sum over the examples, the partial sums fresh in the caches.
+//
+// Wide blocks: 64 columns, the examples dealt to four lanes (b mod 4), each sums its phi(v_b) in ascending b with eight ranges in
+// flight, the four lanes are combined in lane order.  256 contiguous bytes of a row per wave: for vectors of many columns, and
+// for chains of a few loads (ceil(B / 4) * ceil(nrange / 8), about half a microsecond each).
+__global__ __launch_bounds__(CW * RW) void vec_finalize_wide_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
+                                                               float* __restrict__ s_id, float* __restrict__ s_sq,
+                                                               float* __restrict__ s_sign)
+{
+    __shared__ float red[3][RW][CW];
+    const int cl = threadIdx.x % CW, bl = threadIdx.x / CW;
+    const int64_t j = (int64_t)blockIdx.x * CW + cl;
+    float a_id = 0.f, a_sq = 0.f, a_sg = 0.f;
+    if (j < d) {
+        for (int b = bl; b < B; b += RW) {
+            const float* p = partial + (int64_t)b * nrange * d + j;
+            float v = 0.f;
+            int r = 0;
+            for (; r + 8 <= nrange; r += 8) {
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(r + u) * d];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v += x[u];
+            }
+            for (; r < nrange; ++r) v += p[(int64_t)r * d];
+            a_id += v;
+            a_sq = fmaf(v, v, a_sq);
+            a_sg += (float)((v > 0.f) - (v < 0.f));
+        }
+    }
+    red[0][bl][cl] = a_id;
+    red[1][bl][cl] = a_sq;
+    red[2][bl][cl] = a_sg;
+    __syncthreads();
+    if (bl == 0 && j < d) {
+        if (s_id) s_id[j] = ((red[0][0][cl] + red[0][1][cl]) + red[0][2][cl]) + red[0][3][cl];
+        if (s_sq) s_sq[j] = ((red[1][0][cl] + red[1][1][cl]) + red[1][2][cl]) + red[1][3][cl];
+        if (s_sign) s_sign[j] = ((red[2][0][cl] + red[2][1][cl]) + red[2][2][cl]) + red[2][3][cl];
+    }
+}
+
+// Narrow blocks, for long chains over few columns: a block is 4 column lanes of VEC columns x EL example lanes x RL range lanes
+// (256 in all); example b belongs to example lane b mod EL, its range r to range lane r mod RL.  Range lanes are added in
+// order through LDS, then phi is applied; the example lanes' sums are added pairwise, always in the same order.  A block owns few
+// columns -- d / (4 VEC) blocks -- and every lane has eight loads in flight of a chain of nrange / RL * B / EL.  VEC = 4 reads
+// rows of any length 16 bytes at a time (a dwordx4 access needs no more than a float's alignment).
+// Measured, the second pass alone, wide / narrow (us): B=64 in 2 ranges d=768 11.2 / 4.4, 8192 11.0 / 4.4; B=16 in 2 ranges
+// d=768 4.4 / 3.8, 32768 4.0 / 5.4; B=2 d=768 2.6 / 3.9, 50256 2.6 / 6.8; B=1 in 128 ranges d=768 7.5 / 4.1; B=3000 d=768 241 / 28;
+// B=2 d=4000001 28 / 810 (VEC = 1).
 template <int VEC, int EL, int RL>
 __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
                                                            float* __restrict__ s_id, float* __restrict__ s_sq,
@@ -114,7 +157,13 @@ __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restri
     typedef f4 __attribute__((aligned(4))) f4_u;
     __shared__ float red[EL * RL][4 * VEC];
     const int cl = threadIdx.x % 4, rl = (threadIdx.x / 4) % RL, el = threadIdx.x / (4 * RL);
-    const int64_t j = ((int64_t)blockIdx.x * 4 + cl) * VEC;
+    // first column of a column lane: the row's last chunk ends with the row (the columns it shares with its neighbour come out
+    // the same twice)
+    auto first_column = [&](int lane) {
+        const int64_t c = ((int64_t)blockIdx.x * 4 + lane) * VEC;
+        return c < d && c + VEC > d ? d - VEC : c;
+    };
+    const int64_t j = first_column(cl);
     float a_id[VEC], a_sq[VEC], a_sg[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a_id[e] = a_sq[e] = a_sg[e] = 0.f;
@@ -189,7 +238,7 @@ __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restri
             for (int t = threadIdx.x; t < h * 4 * VEC; t += 256) red[t / (4 * VEC)][t % (4 * VEC)] += red[t / (4 * VEC) + h][t % (4 * VEC)];
         }
         __syncthreads();
-        const int64_t c = (int64_t)blockIdx.x * 4 * VEC + threadIdx.x;
+        const int64_t c = first_column(threadIdx.x / VEC) + threadIdx.x % VEC;
         if (threadIdx.x < 4 * VEC && c < d) out[c] = red[0][threadIdx.x];
     };
     if (s_id) finish(s_id, a_id);
@@ -247,9 +296,16 @@ hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, i
     hipError_t e = dt == PEX_F32 ? launch_typed((const float*)A, (const float*)C, B, T, d, plan, partial, stream)
                                  : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
     if (e != hipSuccess) return e;
+    // The narrow blocks' two-stage sum costs about three chain steps of the wide ones; beyond one block per compute unit, every 450
+    // blocks of sixteen columns cost another (measurements above the kernels).
+    const int64_t narrow = (d + 15) / 16, chain = ((B + RW - 1) / RW) * ((plan.nrange + 7) / 8);
+    if (chain < 3 + (narrow > 256 ? (narrow - 256) / 450 : 0)) {
+        vec_finalize_wide_kernel<<<dim3((unsigned)((d + CW - 1) / CW)), dim3(CW * RW), 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign);
+        return hipGetLastError();
+    }
     // example lanes for the batch, the rest of the block to the ranges
-    const bool quads = d % 4 == 0;
-    const dim3 grid((unsigned)((d + (quads ? 15 : 3)) / (quads ? 16 : 4))), block(256);
+    const bool quads = d % 4 == 0 || d >= 512;      // (short rows of odd length: more blocks; B=3000 d=77 22 against 27 us)
+    const dim3 grid((unsigned)(quads ? narrow : (d + 3) / 4)), block(256);
     auto go = [&](auto kern) { kern<<<grid, block, 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign); };
     if (B > 16) quads ? go(vec_finalize_kernel<4, 64, 1>) : go(vec_finalize_kernel<1, 64, 1>);
     else if (B > 4) quads ? go(vec_finalize_kernel<4, 16, 4>) : go(vec_finalize_kernel<1, 16, 4>);
