@@ -177,7 +177,8 @@ __global__ __launch_bounds__(F_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)
                     if (OUTS & F_NORM) {
                         const int i = ib + 4 * r + m, j = jb + n;
                         const bool mine = whole || (i >= own_i && i < din && j >= own_j && j < dout);
-                        norm = fmaf(v, mine ? v : 0.f, norm);
+                        const float u = mine ? v : 0.f;      // (on both factors: an infinity that is not ours times zero is NaN)
+                        norm = fmaf(u, u, norm);
                     }
                 }
                 if (HAS_SG8) cnt[m][n] += bytes;
