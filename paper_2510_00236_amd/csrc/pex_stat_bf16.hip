@@ -515,6 +515,19 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
             ++example;
             return;
         }
+        if constexpr (HAS_NORM) {
+            // rows and columns beyond the layer are zeros times what the other operand holds: NaN beside an infinity
+            if (i0 + BM > store_rows || j0 + BN > store_cols) {
+#pragma unroll
+                for (int a = 0; a < FM; ++a)
+#pragma unroll
+                    for (int c = 0; c < FN; ++c)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (i0 + wm * TL::WM + a * 16 + 4 * (lane / 16) + r >= store_rows || j0 + wn * TL::WN + c * 16 + lane % 16 >= store_cols)
+                                acc[a][c][r] = 0.f;
+            }
+        }
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
@@ -698,7 +711,7 @@ hipError_t launch_one(const uint16_t* X, const uint16_t* G, int64_t B, int64_t T
         ldo = range.ldo;
         store_cols = range.ncols;
     }
-    if (plan.nsplit == 1) {        // S itself, which has the layer's own widths
+    if (plan.nsplit == 1 || OUTS == OUT_NORM) {        // S itself (or the entries a norm counts), which has the layer's own widths
         ldo = plan.out_cols;
         store_rows = plan.out_rows;
         const int64_t left = plan.out_cols - (range.ncols >= 0 ? range.col0 : 0);

@@ -1,5 +1,5 @@
 """Per-example norms beside infinities: an entry of M_b that is infinite makes that example's norm infinite, at tile edges too (the
-fp32 kernel's overlapping and narrow tiles), and leaves the others alone."""
+fp32 kernel's overlapping and narrow tiles, rows and columns of zeros beyond the layer), and leaves the others alone."""
 import numpy as np
 import pytest
 import torch
@@ -12,9 +12,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("B,T,din,dout,dtype", [(5, 26, 68, 36, "f32"), (3, 23, 127, 200, "f32"), (4, 50, 130, 66, "f32")])
+@pytest.mark.parametrize("B,T,din,dout,dtype", [(5, 26, 68, 36, "f32"), (3, 23, 127, 200, "f32"), (4, 50, 130, 66, "f32"), (5, 300, 192, 391, "bf16"),
+                                                (4, 190, 257, 40, "bf16"), (8, 256, 768, 1001, "bf16"), (6, 80, 328, 200, "bf16")])
 @pytest.mark.parametrize("where", ["X", "G", "sum"])
-def test_infinities(B, T, din, dout, dtype, where):
+def test_infinities(pex_option, B, T, din, dout, dtype, where):
+    pex_option("gram_norms", 0)
     X, G = si.custom(B, T, din, dout, dtype=dtype, seed=B + T)
     ref = on.example_norms(si.widen(X), si.widen(G))
     # one column of X or of G that the last tile shares with, or has next to, its neighbour
