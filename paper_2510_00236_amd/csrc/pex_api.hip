@@ -157,9 +157,9 @@ static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode m
     return t * passes > 14.0e-6;
 }
 
-// What pex_stat_noalloc charges a call against its scratch.  bf16 layers of whole 16-byte chunks: what their plan needs.
-// The others: the partial sums of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every
-// compute unit -- a figure of the shape alone, so that which calls are too large does not move with their plans.
+// The partial sums pex_stat_noalloc has always had room for, by the shape alone.  bf16 layers of whole 16-byte chunks: what their
+// plan needs.  The others: those of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every compute
+// unit.  A layer within the scratch by this figure keeps a plan that fits it.
 static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
 {
     if (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) return plan_stat(B, T, din, dout, dt, mode).ws_bytes;
@@ -225,7 +225,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
     bool sign_bytes = false, mem_fold = false;
     if (p.kernel == 2) {
-        // Calls that pex_stat_noalloc takes keep their partial sums within its scratch; the others are free (B=42 T=112 704x3648
+        // Calls that pex_stat_noalloc has always taken keep their partial sums within its scratch; the others are free (B=42 T=112 704x3648
         // sign, 10 MB of S, three groups in 32 MB: 321 us, free 311; B=16 T=512 1536x1536 square 369 and 319)
         const bool held = mode <= MODE_SIGN && scratch_charge(B, T, din, dout, dt, mode) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
         const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
@@ -629,7 +629,6 @@ pex_status pex_stat_noalloc(const void* X, const void* G, int64_t B, int64_t T, 
     if (st != PEX_OK) return st;
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return PEX_ERR_PHI;
     const size_t limit = (size_t)PEX_NOALLOC_SCRATCH_BYTES;
-    if (scratch_charge(B, T, din, dout, dt, (Mode)phi) > limit) return PEX_ERR_TOO_LARGE;
     // copies of a layer of odd width that do not fit: the SIMT kernel
     size_t need = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
     const bool allow_pad = need <= limit;

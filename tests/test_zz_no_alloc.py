@@ -84,3 +84,21 @@ def test_noalloc_without_scratch_need_and_over_the_limit():
     assert ei.value.code == 8
     torch.cuda.synchronize()
     assert bool((Sb == 7.0).all())                                  # nothing was launched
+
+
+@pytest.mark.parametrize("B,T,din,dout,dtype", [(8, 128, 2048, 2048, "f32"), (16, 256, 1024, 4096, "f32"), (16, 96, 1024, 4096, "f32"), (64, 128, 512, 512, "f32"),
+                                                (16, 512, 1536, 1536, "f32"), (4, 60, 768, 50257, "bf16")])
+def test_noalloc_takes_what_the_query_says_fits(B, T, din, dout, dtype):
+    """Refused where pex_stat_workspace_bytes exceeds the scratch, and only there: fp32 layers of many tiles need none of it."""
+    dt, code = (torch.bfloat16, pex.PEX_BF16) if dtype == "bf16" else (torch.float32, pex.PEX_F32)
+    g = torch.Generator(device=DEV).manual_seed(B)
+    X, G = (torch.randn(B, T, w, device=DEV, generator=g).to(dt) for w in (din, dout))
+    for phi in PHI:
+        S = torch.full((din, dout), 7.0, device=DEV)
+        if pex.pex_stat_workspace_bytes(B, T, din, dout, code, phi) <= pex.NOALLOC_SCRATCH_BYTES:
+            _noalloc(X, G, phi, S)
+            assert torch.equal(S, pex.pex_stat(X, G, phi))
+        else:
+            with pytest.raises(pex.PexError) as ei:
+                pex.pex_stat_noalloc(X, G, phi, S)
+            assert ei.value.code == 8 and bool((S == 7.0).all())
