@@ -461,6 +461,12 @@ static hipError_t make_copies(const StatPlan& plan, const void*& X, const void*&
     return e;
 }
 
+static bool same_copies(const StatPlan& a, const StatPlan& b)
+{
+    return a.copy_bytes > 0 && a.copy_bytes == b.copy_bytes && a.copy_x == b.copy_x && a.copy_g == b.copy_g && a.din == b.din && a.dout == b.dout &&
+           a.square_halves == b.square_halves;
+}
+
 // copies_made: the workspace already begins with the copies of X and G the plan asks for
 static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
                            Mode mode, float* S, void* workspace, size_t workspace_bytes, hipStream_t stream,
@@ -667,9 +673,9 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     }
     hipStream_t hs = (hipStream_t)stream;
-    bool made = m.pair;
+    StatPlan front{};       // whose copies the workspace begins with
     if (m.pair) {
-        const StatPlan& p = m.pair_plan;
+        const StatPlan& p = front = m.pair_plan;
         const int64_t n = p.din * p.dout;
         const void *x = X, *g = G;
         if (make_copies(p, x, g, B * T, workspace, false, hs) != hipSuccess) return PEX_ERR_HIP;
@@ -693,9 +699,11 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
     }
     for (int phi = 0; phi < 3; ++phi) {
         if (!(m.single_want & (1u << phi))) continue;
-        // what runs alone beside a shared contraction, or after another single one, finds the padded copies made
-        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs, nullptr, 0.f, true, made);
-        made = true;
+        // what runs alone beside a shared contraction finds the padded copies made, if it reads the same ones
+        const StatPlan p = plan_stat(B, T, din, dout, dt, (Mode)phi);
+        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs, nullptr, 0.f, true,
+                                       same_copies(p, front));
+        front = p;
         if (st != PEX_OK) return st;
     }
     return PEX_OK;

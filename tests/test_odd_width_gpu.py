@@ -74,11 +74,14 @@ def test_statistics(pex_option, B, T, din, dout, options):
 
 
 @pytest.mark.parametrize("want", [("identity", "square"), ("identity", "sign"), ("square", "sign"), ("identity", "square", "sign")])
-@pytest.mark.parametrize("B,T,din,dout", SHAPES[:4] + [(300, 4, 129, 250)])
+@pytest.mark.parametrize("B,T,din,dout", SHAPES[:4] + [(300, 4, 129, 250), (300, 40, 129, 250)])
 def test_statistics_sharing_a_contraction(pex_option, B, T, din, dout, want):
-    """With 300 examples in one group sign runs alone beside identity and square, on the copies they made."""
+    """With 300 examples in one group sign runs alone beside identity and square: on the SIMT kernel where the sequences are
+    short, on the copies the others made where they are long."""
     if B > 127:
         pex_option("max_split", 1)
+        alone, copies = pex.pex_stat_workspace_bytes(B, T, din, dout, pex.PEX_BF16, "sign"), 2 * B * T * (136 + 256)
+        assert (alone == 0) if T == 4 else (copies <= alone < copies + 256)
     X, G = si.custom(B, T, din, dout, dtype="bf16", seed=B + T)
     st = oracle.stat(si.widen(X), si.widen(G))
     out = {k: Guarded(din, dout) for k in want}
