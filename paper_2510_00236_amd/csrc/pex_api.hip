@@ -69,6 +69,12 @@ static Options& options()
 
 static int option(int opt) { return options().v[opt].load(); }
 
+// The options one plan is made with: read once, so that a plan is never a mixture.
+struct OptionValues {
+    int v[NUM_OPTIONS];
+    int operator[](int opt) const { return v[opt]; }
+};
+
 // The bf16 kernels run one workgroup per compute unit, so a launch of `tiles` blocks with the batch in `ns` groups takes
 //   rounds(ns) * ceil(units / ns)  unit-times,  rounds = ceil(tiles * ns / 256),
 // its workgroups write ns copies of the output (s_bytes each) and the fixed-order reduction reads them back and writes
@@ -157,25 +163,25 @@ static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode m
     return t * passes > 14.0e-6;
 }
 
-// The partial sums pex_stat_noalloc has always had room for, by the shape alone.  bf16 layers of whole 16-byte chunks: what their
-// plan needs.  The others: those of as many groups as put three workgroups of 128 x 128 (fp32) or four of 64 x 64 on every compute
-// unit.  A layer within the scratch by this figure keeps a plan that fits it.
-static size_t scratch_charge(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
+// The partial sums of an fp32 call that pex_stat_noalloc has always had room for, by the shape alone: those of as many groups as
+// put three workgroups of 128 x 128 on every compute unit, or four of 64 x 64 where rows are not whole 16-byte chunks.  A layer
+// within the scratch by this figure keeps a plan that fits it.
+static size_t scratch_charge_f32(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int max_split)
 {
-    if (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) return plan_stat(B, T, din, dout, dt, mode).ws_bytes;
-    const bool chunked = dt == PEX_F32 && din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
+    const bool chunked = din % 4 == 0 && dout % 4 == 0 && din >= 32 && dout >= 32 && B * T >= 16;
     const int64_t edge = chunked ? 128 : 64, target = chunked ? 768 : 1024;
     const int64_t tiles = ((din + edge - 1) / edge) * ((dout + edge - 1) / edge);
     const int64_t units = mode == MODE_IDENTITY ? (B * T + 63) / 64 : B;
     int64_t ns = (target + tiles - 1) / tiles;
-    if (ns > option(PEX_OPT_MAX_SPLIT)) ns = option(PEX_OPT_MAX_SPLIT);
+    if (ns > max_split) ns = max_split;
     if (ns > units) ns = units;
     const int64_t per = (units + ns - 1) / ns;
     ns = (units + per - 1) / per;
     return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
 }
 
-static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
+static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad,
+                          const OptionValues& options)
 {
     StatPlan p{};
     p.out_rows = din;
@@ -212,7 +218,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     units = per_example ? B : (B * T + slab - 1) / slab;
     // The option bounds the workspace; the norms exchange no partial sums, so unless it is lowered they take as many groups as
     // there are examples (B=56 T=1150 64x312, two blocks: 32 groups 71 us, 56 groups 27)
-    int max_split = option(PEX_OPT_MAX_SPLIT);
+    int max_split = options[PEX_OPT_MAX_SPLIT];
     if (mode == MODE_NORMS && max_split == 32) max_split = B < 1024 ? (int)B : 1024;
     if (p.kernel != 0) {
         // the MFMA kernels put blocks and groups in one grid dimension, which holds fewer than 2^32 threads (the SIMT kernel has
@@ -227,7 +233,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     if (p.kernel == 2) {
         // Calls that pex_stat_noalloc has always taken keep their partial sums within its scratch; the others are free (B=42 T=112 704x3648
         // sign, 10 MB of S, three groups in 32 MB: 321 us, free 311; B=16 T=512 1536x1536 square 369 and 319)
-        const bool held = mode <= MODE_SIGN && scratch_charge(B, T, din, dout, dt, mode) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
+        const bool held = mode <= MODE_SIGN && scratch_charge_f32(B, T, din, dout, mode, max_split) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
         const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
         cheapest_split_f32(tiles, units, per_example ? (double)T : (double)slab, (bm / 64) * (bn / 64),
                            mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit),
@@ -260,7 +266,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // remaining columns on the 256 x 128 block, each part with a split of the batch of its own.  Candidates: every
         // number of wide block columns up to 64, beyond that the largest number that fits k rounds of 256 workgroups,
         // and all columns wide.
-        const int wide_opt = option(PEX_OPT_WIDE_BLOCKS);
+        const int wide_opt = options[PEX_OPT_WIDE_BLOCKS];
         if (allow_wide && wide_opt != 0 && (mode == MODE_SQUARE || mode == MODE_WEIGHTED || mode == MODE_POWER) && bm == 256 && bn == 128) {
             int wm, wn;
             bf16_wide_tile_shape(&wm, &wn);
@@ -292,7 +298,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         }
         // ... or keep no second register tile at all: 256 x 256 blocks (eight waves: 5.2e12 FLOP/s per compute unit) that
         // add phi(M_b) to the output in memory at the end of every example
-        const int fold_opt = option(PEX_OPT_MEMORY_FOLD);
+        const int fold_opt = options[PEX_OPT_MEMORY_FOLD];
         if (allow_wide && fold_opt != 0 && (mode == MODE_SQUARE || mode == MODE_WEIGHTED || mode == MODE_POWER) && bm == 256 && bn == 128 &&
             dout < ((int64_t)1 << 20)) {      // 32-bit byte offsets inside a tile of the output
             int fm, fn;
@@ -318,7 +324,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     // of direct-to-LDS loads, plus the arithmetic) costs about +50 % time; squaring them once into bf16 copies costs one
     // pass over X and G at HBM speed (~5.5 TB/s, 4 bytes moved per element).  The copies win when din*dout/(din+dout)
     // is large.
-    const int presquare = option(PEX_OPT_TOKEN_PRESQUARE);
+    const int presquare = options[PEX_OPT_TOKEN_PRESQUARE];
     if (mode == MODE_TOKEN_SQ && p.kernel == 1 && presquare != 0 && !p.square_halves) {
         const double elems = (double)B * (double)T * (double)(din + dout);
         const double t_pre = 4.0 * elems / 5.5e12 + 6.0e-6;
@@ -346,7 +352,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // Not for padded copies: layers of odd width keep the contraction.  A sum of squares is exact to rounding whatever the inputs,
         // <X X^T, G G^T> cancels where tokens are alike (X = 1 + 0.03 noise, G of zero mean over the tokens, B=4 T=190 257x40: relative
         // error 2e-8 by the contraction, 5e-5 through the Gram matrices).
-        const int gram_opt = option(PEX_OPT_GRAM_NORMS);
+        const int gram_opt = options[PEX_OPT_GRAM_NORMS];
         if (dt == PEX_BF16 && gram_opt != 0 && p.copy_bytes == 0 && gram_supports(B, T, din, dout)) {
             // Gram kernel: 6.0e14 FLOP/s on a full chip (its 128 x 128 blocks draw twice the bytes per FLOP from L2 that
             // the 256 x 256 blocks of the contraction do), and never faster than its serial loop over the features, one
@@ -390,7 +396,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
 {
     struct Kept {
         int64_t key[5];
-        int options[NUM_OPTIONS];
+        OptionValues options;
         bool valid;
         StatPlan plan;
     };
@@ -406,12 +412,12 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     bool same = true;
     Kept& at = kept[h >> 60];
     for (int k = 0; k < NUM_OPTIONS; ++k) {
-        now.options[k] = option(k);
+        now.options.v[k] = option(k);
         same = same && now.options[k] == at.options[k];
     }
     for (int k = 0; k < 5; ++k) same = same && now.key[k] == at.key[k];
     if (at.valid && same) return at.plan;
-    now.plan = make_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad);
+    now.plan = make_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, now.options);
     now.valid = true;
     at = now;
     return now.plan;

@@ -1,5 +1,5 @@
 """Planner choices (host only): those seen in the workspace a call asks for, others through a small program linked to the
-library (plan_probe.cpp)."""
+library (plan_probe.cpp); plans made while another thread sets an option (plan_race.cpp)."""
 import os
 import subprocess
 
@@ -49,3 +49,9 @@ def test_fp32_plans_fit_the_librarys_scratch_where_the_call_without_a_workspace_
     assert pex.pex_stat_workspace_bytes(64, 128, 512, 512, pex.PEX_F32, "square") <= pex.NOALLOC_SCRATCH_BYTES
     # charged more than the scratch: as many groups as pay
     assert pex.pex_stat_workspace_bytes(16, 512, 1536, 1536, pex.PEX_F32, "square") > pex.NOALLOC_SCRATCH_BYTES
+
+
+def test_kept_plans_are_those_of_their_options(tmp_path):
+    exe = _compile("plan_race.cpp", str(tmp_path / "race"))
+    out = subprocess.run([exe], stdout=subprocess.PIPE, text=True, check=True, timeout=100).stdout
+    assert int(out) == 0, f"{out.strip()} plans kept under an option they were not made with"
