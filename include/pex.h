@@ -63,7 +63,9 @@ int pex_version(void);
  *                            chip; it bounds the workspace at max_split * din*dout*4 bytes.
  *   PEX_OPT_TOKEN_PRESQUARE  0 = pex_token_sq always squares inside the contraction, 1 = chosen by a cost model
  *                            (default), 2 = always through bf16 copies of the squares (environment
- *                            PEX_TOKEN_PRESQUARE).  Both routes round alike and give the same bits.
+ *                            PEX_TOKEN_PRESQUARE).  Both routes round alike and give the same bits.  On layers whose rows
+ *                            are not multiples of 16 bytes no square is rounded: 0 = fp32 squares, 1 and 2 = by a cost
+ *                            model fp32 squares or copies that hold each square exactly; the two agree to fp32 rounding.
  *   PEX_OPT_WIDE_BLOCKS      pex_stat(square), pex_weighted_sum and pex_stat_power on bf16 layers keep two fp32
  *                            register tiles and have two block shapes, 256 x 128 and 256 x 192.  0 = the narrow one
  *                            only, 1 = the first columns of S on the wide shape where a cost model says so

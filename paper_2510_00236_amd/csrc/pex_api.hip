@@ -186,7 +186,9 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     StatPlan p{};
     p.out_rows = din;
     p.out_cols = dout;
-    // (a plan on one block shape is one of several statistics at once)
+    // (a plan on one block shape is one of several statistics at once; option 0: squares inside the contraction, of odd widths the
+    // SIMT kernel's)
+    if (mode == MODE_TOKEN_SQ && options[PEX_OPT_TOKEN_PRESQUARE] == 0) allow_pad = false;
     if (allow_pad && dt == PEX_BF16 && padding_pays(B, T, din, dout, mode, allow_wide ? 1 : 2)) {
         p.square_halves = mode == MODE_TOKEN_SQ;
         p.copy_x = din % 8 != 0 || p.square_halves;

@@ -137,7 +137,7 @@ def test_without_a_workspace_large_copies_stay_on_the_simt_kernel():
 
 
 @pytest.mark.parametrize("B,T,din,dout", [(16, 300, 1001, 770), (7, 1111, 519, 904)])
-def test_per_token_square_from_exact_halves(B, T, din, dout):
+def test_per_token_square_from_exact_halves(pex_option, B, T, din, dout):
     """The squares travel as two bf16 each that add up to them exactly: as accurate as fp32 squares (a rounded bf16 square alone
     would be off by up to 2^-9)."""
     halves = -(-din // 8) * 8 + -(-dout // 8) * 8
@@ -149,6 +149,10 @@ def test_per_token_square_from_exact_halves(B, T, din, dout):
     got = o.value()
     # terms >= 0 summed in fp32 (at most ~2000 rows per group, then the groups): 1e-5 of every entry
     assert (np.abs(got - ref) <= 1e-5 * ref).all(), float((np.abs(got - ref) / ref).max())
+    pex_option("token_presquare", 0)        # fp32 squares in the SIMT kernel
+    o = Guarded(din, dout)
+    pex.pex_token_sq(X.to(DEV), G.to(DEV), S=o.view)
+    assert (np.abs(o.value() - ref) <= 1e-5 * ref).all()
 
 
 def test_per_token_square_of_infinities_and_of_the_largest_squares():

@@ -55,3 +55,12 @@ def test_kept_plans_are_those_of_their_options(tmp_path):
     exe = _compile("plan_race.cpp", str(tmp_path / "race"))
     out = subprocess.run([exe], stdout=subprocess.PIPE, text=True, check=True, timeout=100).stdout
     assert int(out) == 0, f"{out.strip()} plans kept under an option they were not made with"
+
+
+def test_squares_inside_the_contraction_where_the_option_asks_for_it(pex_option):
+    """No copies of squares under value 0, of layers of odd width either."""
+    odd, even = (16, 300, 1001, 770, pex.PEX_BF16), (16, 2048, 2048, 8192, pex.PEX_BF16)
+    copies = [2 * 2 * 16 * 300 * (1008 + 776), 2 * 16 * 2048 * (2048 + 8192)]
+    assert [pex.pex_token_sq_workspace_bytes(*s) >= c for s, c in zip((odd, even), copies)] == [True, True]
+    pex_option("token_presquare", 0)
+    assert [pex.pex_token_sq_workspace_bytes(*s) >= c for s, c in zip((odd, even), copies)] == [False, False]
