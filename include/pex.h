@@ -60,7 +60,9 @@ int pex_version(void);
  * plans anything) and is changed afterwards only by pex_set_option; both calls are safe from any host thread.
  *   PEX_OPT_MAX_SPLIT        1 .. 32 (default 32; environment PEX_MAX_SPLIT, clamped to that range): the largest
  *                            number of groups the batch is split into when a layer has too few tiles to fill the
- *                            chip; it bounds the workspace at max_split * din*dout*4 bytes.
+ *                            chip; it bounds the workspace at max_split * din*dout*4 bytes.  Per-example norms, which
+ *                            keep no such partial sums, are bounded by it below 32 only: at 32 they take up to as many
+ *                            groups as examples (at most 1024).  Their results are the same bits under every value.
  *   PEX_OPT_TOKEN_PRESQUARE  0 = pex_token_sq always squares inside the contraction, 1 = chosen by a cost model
  *                            (default), 2 = always through bf16 copies of the squares (environment
  *                            PEX_TOKEN_PRESQUARE).  Both routes round alike and give the same bits.  On layers whose rows
@@ -117,7 +119,10 @@ int32_t pex_get_option(pex_option opt);
  *                               of bf16 layers are held as bytes while a group has at most 127 examples.
  *                               For bf16 layers whose rows are not multiples of 16 bytes it may also hold
  *                               copies of such operands with rows padded to the next multiple (about
- *                               2*B*T*din and 2*B*T*dout bytes); din and dout above are then the padded ones.
+ *                               2*B*T*din and 2*B*T*dout bytes); din and dout above are then the padded ones.  A
+ *                               call with less workspace than the query says, but enough for its partial sums alone,
+ *                               makes no copies and runs on the SIMT kernel (same definition and error bounds, another
+ *                               order of additions); so do the other calls on X and G.
  *   The contraction over T of one example is never split across workgroups (phi is applied to the complete
  *   sum over the sequence), the sum over b is taken in a fixed order.
  *   Any B,T,din,dout >= 1 is accepted with B*T, din, dout each < 2^31; fp32 inputs and bf16 layers whose rows are

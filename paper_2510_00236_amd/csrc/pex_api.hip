@@ -425,6 +425,16 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     return now.plan;
 }
 
+// The plan of a call that has `bytes` of workspace: a layer of odd width whose padded copies do not fit runs on the SIMT kernel if
+// that plan does.
+static StatPlan plan_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, size_t bytes)
+{
+    const StatPlan plan = plan_stat(B, T, din, dout, dt, mode);
+    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout)) return plan;
+    const StatPlan simt = plan_stat(B, T, din, dout, dt, mode, true, false);
+    return simt.ws_bytes <= bytes ? simt : plan;
+}
+
 static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
                                   pex_dtype dt, const float* S)
 {
@@ -475,12 +485,12 @@ static bool same_copies(const StatPlan& a, const StatPlan& b)
            a.square_halves == b.square_halves;
 }
 
-// copies_made: the workspace already begins with the copies of X and G the plan asks for
+// front: a plan whose copies the workspace already begins with
 static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
                            Mode mode, float* S, void* workspace, size_t workspace_bytes, hipStream_t stream,
-                           const float* weight = nullptr, float alpha = 0.f, bool allow_pad = true, bool copies_made = false)
+                           const float* weight = nullptr, float alpha = 0.f, const StatPlan* front = nullptr)
 {
-    const StatPlan plan = plan_stat(B, T, din, dout, dt, mode, true, allow_pad);
+    const StatPlan plan = plan_within(B, T, din, dout, dt, mode, workspace ? workspace_bytes : 0);
     float* out = S;
     if (plan.ws_bytes > 0) {
         if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
@@ -488,7 +498,7 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
     }
     float* partials = (float*)((char*)workspace + plan.copy_bytes);
     if (plan.nsplit > 1) out = partials;
-    hipError_t e = make_copies(plan, X, G, B * T, workspace, copies_made, stream);
+    hipError_t e = make_copies(plan, X, G, B * T, workspace, front && same_copies(plan, *front), stream);
     if (e != hipSuccess) return PEX_ERR_HIP;
     din = plan.din;
     dout = plan.dout;
@@ -553,11 +563,11 @@ struct MultiPlan {
     size_t ws_bytes;
 };
 
-static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want)
+static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true)
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
-    const StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false);
+    const StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad);
     // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
     // contraction and sign keeps its own.  On fp32 layers sign shares one only as bytes.
     m.pair_want = want;
@@ -575,7 +585,7 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
     }
     for (int phi = 0; phi < 3; ++phi)
         if (m.single_want & (1u << phi)) {
-            const size_t w = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
+            const size_t w = plan_stat(B, T, din, dout, dt, (Mode)phi, true, allow_pad).ws_bytes;
             if (w > m.ws_bytes) m.ws_bytes = w;     // passes run one after the other on the stream and reuse it
         }
     return m;
@@ -643,16 +653,13 @@ pex_status pex_stat_noalloc(const void* X, const void* G, int64_t B, int64_t T, 
     if (st != PEX_OK) return st;
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return PEX_ERR_PHI;
     const size_t limit = (size_t)PEX_NOALLOC_SCRATCH_BYTES;
-    // copies of a layer of odd width that do not fit: the SIMT kernel
-    size_t need = plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
-    const bool allow_pad = need <= limit;
-    if (!allow_pad) need = plan_stat(B, T, din, dout, dt, (Mode)phi, true, false).ws_bytes;
+    const size_t need = plan_within(B, T, din, dout, dt, (Mode)phi, limit).ws_bytes;
     if (need > limit) return PEX_ERR_TOO_LARGE;
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return PEX_ERR_HIP;
     // Every partial sum the reduction reads is written by the contraction of the same call, so nothing in the
     // scratch has to start at zero.
-    return run_stat(X, G, B, T, din, dout, dt, (Mode)phi, S, ws, need, (hipStream_t)stream, nullptr, 0.f, allow_pad);
+    return run_stat(X, G, B, T, din, dout, dt, (Mode)phi, S, ws, limit, (hipStream_t)stream);
 }
 
 size_t pex_stat_multi_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want)
@@ -675,7 +682,12 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         const pex_status st = check_stat_args(X, G, B, T, din, dout, dt, outs[phi]);
         if (st != PEX_OK) return st;
     }
-    const MultiPlan m = plan_multi(B, T, din, dout, dt, want);
+    const size_t given = workspace ? workspace_bytes : 0;
+    MultiPlan m = plan_multi(B, T, din, dout, dt, want);
+    if (m.ws_bytes > given) {        // without padded copies?
+        const MultiPlan simt = plan_multi(B, T, din, dout, dt, want, false);
+        if (simt.ws_bytes <= given) m = simt;
+    }
     if (m.ws_bytes > 0) {
         if (!workspace || workspace_bytes < m.ws_bytes) return PEX_ERR_WORKSPACE;
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
@@ -708,10 +720,8 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
     for (int phi = 0; phi < 3; ++phi) {
         if (!(m.single_want & (1u << phi))) continue;
         // what runs alone beside a shared contraction finds the padded copies made, if it reads the same ones
-        const StatPlan p = plan_stat(B, T, din, dout, dt, (Mode)phi);
-        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs, nullptr, 0.f, true,
-                                       same_copies(p, front));
-        front = p;
+        const pex_status st = run_stat(X, G, B, T, din, dout, dt, (Mode)phi, outs[phi], workspace, workspace_bytes, hs, nullptr, 0.f, &front);
+        front = plan_within(B, T, din, dout, dt, (Mode)phi, given);
         if (st != PEX_OK) return st;
     }
     return PEX_OK;
@@ -764,7 +774,7 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
     if (st != PEX_OK) return st;
     if (!N) return PEX_ERR_NULL;
     if ((uintptr_t)N & 3u) return PEX_ERR_ALIGN;
-    const StatPlan plan = plan_stat(B, T, din, dout, dt, MODE_NORMS);
+    const StatPlan plan = plan_within(B, T, din, dout, dt, MODE_NORMS, workspace ? workspace_bytes : 0);
     if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     hipStream_t hs = (hipStream_t)stream;

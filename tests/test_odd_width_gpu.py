@@ -179,3 +179,36 @@ def test_per_token_square_of_infinities_and_of_the_largest_squares():
     assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.isinf(ref).sum() > 1000 and np.isnan(ref).sum() > 700
     ok = np.isfinite(ref)
     assert (np.abs(got - ref)[ok] <= 1e-5 * ref[ok]).all()      # as above
+
+
+def test_less_workspace_than_the_copies_take():
+    """A call with enough for its partial sums alone (none, on these layers of many tiles) runs without the copies, on the SIMT
+    kernel; with less than that it is refused."""
+    B, T, din, dout = 8, 512, 768, 6001
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=8)
+    Xd, Gd = X.to(DEV), G.to(DEV)
+    Xf, Gf = Xd.double(), Gd.double()
+    M = torch.stack([Xf[b].t() @ Gf[b] for b in range(B)])
+    ref = {"identity": M.sum(0), "square": M.square().sum(0)}
+    token = Xf.flatten(0, 1).square().t() @ Gf.flatten(0, 1).square()
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)
+    close = lambda got, want, what: assert_real_stat(f64(got), f64(want), "bf16", what, elementwise=False)
+    for phi in ref:
+        assert pex.pex_stat_workspace_bytes(B, T, din, dout, pex.PEX_BF16, phi) > 0
+        close(pex.pex_stat(Xd, Gd, phi, workspace=none), ref[phi], phi)
+    both = pex.pex_stat_multi(Xd, Gd, ("identity", "square"), workspace=none)
+    for phi in ref:
+        close(both[phi], ref[phi], f"{phi} of both")
+    assert pex.pex_token_sq_workspace_bytes(B, T, din, dout, pex.PEX_BF16) > 0
+    close(pex.pex_token_sq(Xd, Gd, workspace=none), token, "token square")
+    w = torch.linspace(-1.0, 2.0, B, device=DEV)
+    close(pex.pex_weighted_sum(Xd, Gd, w, workspace=none), (w.double()[:, None, None] * M).sum(0), "weighted")
+    need = -(-din // 64) * -(-dout // 64) * B * 4        # norms: a partial of every 64 x 64 tile and example
+    N = pex.pex_example_norms(Xd, Gd, workspace=torch.empty(need, dtype=torch.uint8, device=DEV))
+    close(N, M.square().sum((1, 2)), "norms")
+    with pytest.raises(ValueError, match="workspace holds"):
+        pex.pex_example_norms(Xd, Gd, workspace=torch.empty(need - 4, dtype=torch.uint8, device=DEV))
+    few = (8, 256, 768, 1001)       # six groups of examples: less than their partial sums
+    Xd, Gd = (t.to(DEV) for t in si.custom(*few, dtype="bf16", seed=9))
+    with pytest.raises(ValueError, match="workspace holds"):
+        pex.pex_stat(Xd, Gd, "square", workspace=torch.empty(768 * 1001 * 4, dtype=torch.uint8, device=DEV))
