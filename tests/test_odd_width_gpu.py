@@ -212,3 +212,20 @@ def test_less_workspace_than_the_copies_take():
     Xd, Gd = (t.to(DEV) for t in si.custom(*few, dtype="bf16", seed=9))
     with pytest.raises(ValueError, match="workspace holds"):
         pex.pex_stat(Xd, Gd, "square", workspace=torch.empty(768 * 1001 * 4, dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.parametrize("B,T,din,dout", [(4, 190, 257, 40), (300, 40, 129, 250), (2100, 8, 129, 250)])
+def test_sign_of_a_nan_counts_as_zero(pex_option, B, T, din, dout):
+    """Entries of M_b that are NaN (a NaN in X or G, infinities of both signs) add nothing to the count, whatever represents it."""
+    _padded(B, T, din, dout)
+    X, G = si.custom(B, T, din, dout, dtype="bf16", seed=B)
+    X[1, 3, din - 2] = float("nan")
+    G[0, 5, 0] = float("nan")
+    X[2, 0, 7], X[2, 1, 7], G[2, 0, :], G[2, 1, :] = float("inf"), float("-inf"), 1.0, 1.0
+    M = [X[b].double().t() @ G[b].double() for b in range(B)]
+    ref = sum(torch.nan_to_num(torch.sign(m), nan=0.0) for m in M).numpy()
+    # the fp32 sum of an entry next to zero may have either sign
+    amb = sum((m.abs() <= 1e-5 * torch.nan_to_num(m, nan=0.0, posinf=0.0, neginf=0.0).abs().max()).double() for m in M).numpy()
+    for want in (("sign",), ("identity", "sign"), ("square", "sign"), ("identity", "square", "sign")):
+        got = f64(pex.pex_stat_multi(X.to(DEV), G.to(DEV), want)["sign"])
+        assert (np.abs(got - ref) <= 2 * amb).all(), want
