@@ -138,14 +138,13 @@ __device__ __forceinline__ float abs_power(float m, float alpha)
 // four biased byte counters.
 template <int OUTS>
 __device__ __forceinline__ void fold_tile(float4_t& acc, float4_t& acc_id, float4_t& acc_sq, float4_t& acc_sg, half2_t (&cnt)[2],
-                                          uint32_t& cnt8, float weight, float& norm)
+                                          uint32_t& cnt8, float weight)
 {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const float m = acc[r];
         if (OUTS & OUT_ID) acc_id[r] += m;
         if (OUTS & OUT_IDW) acc_id[r] = fmaf(weight, m, acc_id[r]);
-        if (OUTS & OUT_NORM) norm = fmaf(m, m, norm);
         if (OUTS & OUT_SQ) acc_sq[r] = fmaf(m, m, acc_sq[r]);
         if (OUTS & OUT_POW) acc_sq[r] += abs_power(m, weight);        // the exponent travels in the weight slot
         if (OUTS & OUT_SIGN_F32) acc_sg[r] += sign_as_float<OUTS>(m);
@@ -521,16 +520,31 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
             return;
         }
         if constexpr (HAS_NORM) {
-            // rows and columns beyond the layer are zeros times what the other operand holds: NaN beside an infinity
-            if (i0 + BM > store_rows || j0 + BN > store_cols) {
+            // (four chains of additions, which keep the pipeline busy: one chain waits for itself)
+            float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int c = 0; c < FN; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part[r] = fmaf(acc[a][c][r], acc[a][c][r], part[r]);
+            norm = (part[0] + part[1]) + (part[2] + part[3]);
+            // rows and columns beyond the layer are zeros times what the other operand holds: NaN beside an infinity, and then left
+            // out (not before: telling the entries apart costs as much as the rest of the fold)
+            if ((i0 + BM > store_rows || j0 + BN > store_cols) && __any(__builtin_isnan(norm))) {
+                norm = 0.f;
+                // rows and columns of this lane's first entry up to the layer's end, hidden from the compiler: it would form all the
+                // masks at the start of the kernel (2 us)
+                int rows_left = store_rows - (i0 + wm * TL::WM + 4 * (lane / 16)), cols_left = store_cols - (j0 + wn * TL::WN + lane % 16);
+                asm volatile("" : "+v"(rows_left), "+v"(cols_left));
 #pragma unroll
                 for (int a = 0; a < FM; ++a)
 #pragma unroll
                     for (int c = 0; c < FN; ++c)
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            if (i0 + wm * TL::WM + a * 16 + 4 * (lane / 16) + r >= store_rows || j0 + wn * TL::WN + c * 16 + lane % 16 >= store_cols)
-                                acc[a][c][r] = 0.f;
+                            if (a * 16 + r < rows_left && c * 16 < cols_left)
+                                norm = fmaf(acc[a][c][r], acc[a][c][r], norm);
             }
         }
 #pragma unroll
@@ -540,7 +554,7 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
                 if constexpr (PER_EXAMPLE)
                     fold_tile<OUTS>(acc[a][c], acc_id[HAS_ID ? a : 0][HAS_ID ? c : 0], acc_sq[HAS_SQ ? a : 0][HAS_SQ ? c : 0],
                                     acc_sg[HAS_SF ? a : 0][HAS_SF ? c : 0], cnt[HAS_PK ? a : 0][HAS_PK ? c : 0],
-                                    cnt8[HAS_U8 ? a : 0][HAS_U8 ? c : 0], w, norm);
+                                    cnt8[HAS_U8 ? a : 0][HAS_U8 ? c : 0], w);
         if constexpr (HAS_NORM) {
             // this wave's part of ||M_b||^2 for this tile: lanes summed in a fixed butterfly order
 #pragma unroll
