@@ -164,7 +164,8 @@ hipError_t launch_typed(const TIn* X, const TIn* G, int64_t B, int64_t T, int64_
 // group (rows of any length: a dwordx4 access needs no more than a float's alignment), four groups in flight; the second
 // grid dimension is the statistic, so that those of one call share a launch.  Bound by the memory-side cache the partial sums
 // were just written to.  Measured against one float per lane and one launch per statistic: 28 groups of 768 x 768 17.9 ->
-// 11.3 us, identity and square of 512 x 2048 in 8 groups 16 -> 12.7 us.
+// 11.3 us, identity and square of 512 x 2048 in 8 groups 16 -> 12.7 us.  (Columns left over by themselves made one lane add them one
+// after the other: 9 x 1215 in 32 groups 11.5 - 15 us, 4.4 so.)
 // Where the sum of the first `leading` groups is not finite, it is the result (the products of exact halves: an infinity times a
 // remainder of zero is no part of the square).
 typedef __attribute__((ext_vector_type(4))) float float4_v;
@@ -177,10 +178,11 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, 
     float* __restrict__ S = io.S[blockIdx.y];
     const int64_t cols4 = (cols + 3) / 4, n4 = rows * cols4, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n4; e += stride) {
-        const int64_t i = rows == 1 ? 0 : e / cols4, j = (e - i * cols4) * 4;
+        const int64_t i = rows == 1 ? 0 : e / cols4, at = (e - i * cols4) * 4;
+        const int64_t j = cols >= 4 && at + 4 > cols ? cols - 4 : at;       // the last four columns end with the row (some are written twice)
         const float* p = partial + i * pitch + j;
         float* out = S + i * ld + j;
-        if (j + 4 <= cols) {
+        if (cols >= 4) {
             auto add = [&](float4_v s, int k, int end) {
                 for (; k + 4 <= end; k += 4) {
                     float4_v v[4];
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, 
             }
             *(float4_u*)out = s;
         } else {
-            for (int c = 0; j + c < cols; ++c) {
+            for (int c = 0; c < cols; ++c) {
                 float s = p[c];
                 for (int k = 1; k < nsplit; ++k) {
                     if (k == leading && !__builtin_isfinite(s)) break;
