@@ -280,10 +280,11 @@ inline unsigned update_grid(int64_t n)
 }
 static_assert(256 * 32 <= 8 * 1024, "the finalizing kernels hold eight partials per lane");
 
-// Buffers of n floats that together exceed the 256 MB memory-side cache by a quarter are accessed past the caches.  Measured (cached /
-// streamed): Adam family 24 M parameters (503 MB) 157 / 138 us, 39 M 255 / 232, but 16 M (336 MB) 83 / 91; moment tracking 24 M
-// (403 MB) 113 / 91, 39 M 190 / 165, 16 M (268 MB) 62 / 62.
-inline bool streams(int64_t n, int buffers) { return n * buffers * 4 > (int64_t)320 << 20; }
+// Buffers of n floats that together exceed the 256 MB memory-side cache by so much that a pass evicts what the next one would have
+// found are accessed past the caches.  Measured on repeated passes (cached / streamed, us), Adam family on five buffers: 320 MiB
+// 84 / 93, 340 91 / 96, 360 104 / 104, 380 114 / 108, 500 159 / 144; on four buffers 360 118 / 113; sign updates 340 100 / 99; moment
+// tracking 340 86 / 92, 360 98 / 98, 400 117 / 108.
+inline bool streams(int64_t n, int buffers) { return n * buffers * 4 > (int64_t)360 << 20; }
 
 // Sums over at most this many values take one workgroup and one launch instead of two (a launch is about 3 us here)
 constexpr int64_t ONE_GROUP = 32768;

@@ -8,7 +8,7 @@ import paper_2510_00236_amd as pex
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-N = 28_311_555          # three buffers of this many floats exceed 320 MiB; no multiple of 4
+N = 31_500_003          # three buffers of this many floats exceed 360 MiB; no multiple of 4
 
 
 def _rand(seed, n=N):
