@@ -97,6 +97,13 @@ __global__ __launch_bounds__(NTHREADS) void stat_generic_kernel(const TIn* __res
         if (PER_EXAMPLE) {
             const int example = (int)(seg / T);
             float norm = 0.f;
+            if (MODE == MODE_NORMS) {       // the layer's entries only: beyond them zeros times what the other operand holds, NaN beside an infinity
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (i0 + ty * 4 + a >= din || j0 + tx * 4 + c >= dout) acc[a][c] = 0.f;
+            }
             fold<MODE>(acc2, acc, MODE == MODE_WEIGHTED ? weight[example] : (MODE == MODE_POWER ? alpha : 1.0f), norm);
             if (MODE == MODE_NORMS) {
                 // this tile's part of ||M_b||^2: fixed-order tree over the 256 lanes

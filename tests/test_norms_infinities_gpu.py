@@ -13,7 +13,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("B,T,din,dout,dtype", [(5, 26, 68, 36, "f32"), (3, 23, 127, 200, "f32"), (4, 50, 130, 66, "f32"), (5, 300, 192, 391, "bf16"),
-                                                (4, 190, 257, 40, "bf16"), (8, 256, 768, 1001, "bf16"), (6, 80, 328, 200, "bf16")])
+                                                (4, 190, 257, 40, "bf16"), (8, 256, 768, 1001, "bf16"), (6, 80, 328, 200, "bf16"), (3, 20, 70, 66, "bf16"), (3, 20, 30, 75, "f32")])
 @pytest.mark.parametrize("where", ["X", "G", "sum"])
 def test_infinities(pex_option, B, T, din, dout, dtype, where):
     pex_option("gram_norms", 0)
