@@ -16,9 +16,9 @@ constexpr int TM = 64, TN = 64, TK = 16, NTHREADS = 256;
 __device__ __forceinline__ float load_as_float(const float* p) { return *p; }
 __device__ __forceinline__ float load_as_float(const uint16_t* p) { return __uint_as_float(((uint32_t)*p) << 16); }
 
-// end of an example: acc2 += phi(M_b) (weighted identity for MODE_WEIGHTED), norm += ||M_b||^2 of this lane's part
+// end of an example: acc2 += phi(M_b) (weighted identity for MODE_WEIGHTED)
 template <int MODE>
-__device__ __forceinline__ void fold(float (&acc2)[4][4], float (&acc)[4][4], float w, float& norm)
+__device__ __forceinline__ void fold(float (&acc2)[4][4], float (&acc)[4][4], float w)
 {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -29,7 +29,6 @@ __device__ __forceinline__ void fold(float (&acc2)[4][4], float (&acc)[4][4], fl
             else if (MODE == MODE_SIGN) acc2[a][c] += (float)((m > 0.f) - (m < 0.f));
             else if (MODE == MODE_WEIGHTED) acc2[a][c] = fmaf(w, m, acc2[a][c]);
             else if (MODE == MODE_POWER) acc2[a][c] += __builtin_amdgcn_exp2f(w * __builtin_amdgcn_logf(__builtin_fabsf(m)));
-            else if (MODE == MODE_NORMS) norm = fmaf(m, m, norm);
             acc[a][c] = 0.f;
         }
 }
@@ -97,14 +96,24 @@ __global__ __launch_bounds__(NTHREADS) void stat_generic_kernel(const TIn* __res
         if (PER_EXAMPLE) {
             const int example = (int)(seg / T);
             float norm = 0.f;
-            if (MODE == MODE_NORMS) {       // the layer's entries only: beyond them zeros times what the other operand holds, NaN beside an infinity
+            if (MODE == MODE_NORMS) {
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (i0 + ty * 4 + a >= din || j0 + tx * 4 + c >= dout) acc[a][c] = 0.f;
+                    for (int c = 0; c < 4; ++c) norm = fmaf(acc[a][c], acc[a][c], norm);
+                // beyond the layer there are zeros times what the other operand holds: NaN beside an infinity, and then left out
+                if ((i0 + TM > din || j0 + TN > dout) && __any(__builtin_isnan(norm))) {
+                    int rows_left = din - (i0 + ty * 4), cols_left = dout - (j0 + tx * 4);
+                    asm volatile("" : "+v"(rows_left), "+v"(cols_left));      // (keeps the masks out of the loop's start)
+                    norm = 0.f;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (a < rows_left && c < cols_left) norm = fmaf(acc[a][c], acc[a][c], norm);
+                }
             }
-            fold<MODE>(acc2, acc, MODE == MODE_WEIGHTED ? weight[example] : (MODE == MODE_POWER ? alpha : 1.0f), norm);
+            fold<MODE>(acc2, acc, MODE == MODE_WEIGHTED ? weight[example] : (MODE == MODE_POWER ? alpha : 1.0f));
             if (MODE == MODE_NORMS) {
                 // this tile's part of ||M_b||^2: fixed-order tree over the 256 lanes
                 sN[tid] = norm;
