@@ -82,9 +82,10 @@ struct OptionValues {
 // fold_bytes > 0: every workgroup adds that many bytes to the output in memory after each of its units but the first
 // (which stores); the workgroups of a round do so at the same time, and what they move -- read and written back
 // across the fabric -- goes at ~5.5 TB/s while they wait (measured: 22 - 29 us for the 67 MB of a 1B-scale layer).
+// t_round > 0: what a round costs besides its units (the start of a workgroup).
 // Returns the cheapest cost over ns <= max_split and the split that reaches it.
 static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double s_bytes, int max_split, int64_t* nsplit, int64_t* per,
-                             double fold_bytes = 0.0)
+                             double fold_bytes = 0.0, double t_round = 0.0)
 {
     double best = 0.0;
     const int64_t lim = units < max_split ? units : max_split;
@@ -92,7 +93,7 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
         const int64_t pu = (units + ns - 1) / ns;
         const int64_t ns_eff = (units + pu - 1) / pu;
         const int64_t rounds = (tiles * ns_eff + 255) / 256;
-        double cost = (double)rounds * (double)pu * t_unit;
+        double cost = (double)rounds * ((double)pu * t_unit + t_round);
         if (fold_bytes > 0.0) {
             const int64_t at_once = tiles * ns_eff < 256 ? tiles * ns_eff : 256;
             cost += (double)rounds * (double)(pu - 1) * (2.0 * (double)at_once * fold_bytes / 5.5e12 + 2.0e-6);
@@ -135,32 +136,70 @@ static double bf16_block_rate(int bm, int bn)
     return area >= 256 * 256 ? 5.5e12 : (area >= 256 * 192 ? 4.8e12 : 4.3e12);
 }
 
-// bf16 layers whose rows are not whole 16-byte chunks: padded copies on the MFMA kernels, or the SIMT kernel on the operands as
-// they are?  The copies cost two more launches, about 10 us on small layers, so they pay where the SIMT kernel takes longer
-// than that: about 1.35 us per slab of 16 rows in a workgroup's serial loop, 35e12 FLOP/s at best on layers near the line.
-// Measured (SIMT / copies): B=8 T=64 70x130 square 20.6 / 24.8 us, B=8 T=128 201x333 square 21.9 / 24.6, B=16 T=128 301x500
-// identity + square 60 / 28, B=16 T=256 333x1001 square 86 / 33, B=2 T=4096 100x131 square 353 / 68.
-// `passes` = statistics the SIMT kernel would make one by one.  The per-token square takes four contractions (on blocks of 256 x
-// 256, at ~1.4e15 FLOP/s) and copies of twice the size (10 bytes moved per element; see pex_pad.hip), the SIMT kernel reaches
-// 60e12 FLOP/s on its larger layers (SIMT / halves: B=16 T=256 333x1001 75 / 96 us, B=64 T=256 999x768 425 / 208, B=14 T=544
-// 3776x1943 1735 / 451, but B=37 T=1744 2240x58, three quarters of whose blocks are padding, 383 / 502).
-static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int passes)
+// A unit on a bf16 block, seconds: its slabs of 32 rows and, at the end of an example, the fold into the statistics.  Measured with
+// T <= 32 (one slab: 0.45 us on 256 x 128, 0.53 us on 256 x 256), per example: square and weighted sum 1.0 us, power 2.05, identity +
+// square 1.2, with signs 1.9, all three 2.3 (256 x 128 blocks); signs 2.95, norms 2.15 (256 x 256).
+// Used for the norms and for layers of odd width.  The other plans count the contraction alone: with the fold some layers of few
+// examples got up to a fifth slower (and others, of many short ones, a quarter faster).
+static double bf16_unit_with_fold(Mode mode, bool shared, int64_t T, int bm, int bn)
 {
-    if (din % 8 == 0 && dout % 8 == 0) return false;
-    if (!pad_supports(B * T, din, dout) || !bf16_supports(B, T, padded_width(din), padded_width(dout))) return false;
+    const double slabs = 2.0 * (double)((T + 31) / 32 * 32) * bm * bn / bf16_block_rate(bm, bn);
+    const double fold = shared ? 1.3e-6 : mode == MODE_SIGN ? 1.2e-6 : mode == MODE_NORMS ? 0.8e-6 : mode == MODE_POWER ? 1.6e-6 : 0.55e-6;
+    return slabs + fold * (bm * bn / 32768.0);
+}
+
+// bf16 layers whose rows are not whole 16-byte chunks: padded copies on the MFMA kernels, or the SIMT kernel on the operands as
+// they are?  Whichever these estimates say is faster (2500 drawn calls of 8 to 12000 columns, 1 to 600 examples and tokens: chosen
+// right but for 2 % of the time; the estimates' own spread is about 10 %).
+//
+// The SIMT kernel: serial loops of 16 rows on 64 x 64 tiles, 1.4 us a slab plus 0.3 for each workgroup per compute unit, 2.3 us from four on.
+static double simt_seconds(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode)
+{
     const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
     const int64_t tiles = ((din + 63) / 64) * ((dout + 63) / 64), units = plain ? (B * T + 63) / 64 : B;
     int64_t groups = (1024 + tiles - 1) / tiles;
     if (groups > units) groups = units;
     if (groups > 32) groups = 32;
-    const double slabs = (double)((units + groups - 1) / groups) * (plain ? 4.0 : (double)((T + 15) / 16));
-    const double flop = 2.0 * (double)B * (double)T * (double)din * (double)dout;
-    if (mode == MODE_TOKEN_SQ) {
-        const double rows = (double)B * (double)T, area = (double)((din + 255) / 256 * 256) * (double)((dout + 255) / 256 * 256);
-        return 8.0 * rows * area / 1.4e15 + 10.0 * rows * (double)(din + dout) / 5.0e12 + 60.0e-6 < (flop / 60.0e12 > slabs * 1.35e-6 ? flop / 60.0e12 : slabs * 1.35e-6);
+    const int64_t per = (units + groups - 1) / groups;
+    groups = (units + per - 1) / per;
+    int64_t steps = per * (plain ? 4 : (T + 15) / 16);
+    if (plain && steps > (B * T + 15) / 16) steps = (B * T + 15) / 16;
+    const double slabs = (double)steps, density = (double)(tiles * groups) / 256.0;
+    double t = slabs * (density < 4.0 ? 1.4e-6 + 0.3e-6 * density : 0.575e-6 * density) + 3.0e-6;
+    if (groups > 1 && mode != MODE_NORMS) t += (double)(2 * groups + 1) * (double)din * (double)dout * 4.0 / 4.0e12 + 3.0e-6;
+    return t;
+}
+
+// The copies: one pass over the operands, the MFMA plan, and about 10 us for two more launches and the start and end of the blocks
+// (12: where the two come out alike the SIMT kernel does, which needs no copies).
+static double padded_seconds(int64_t B, int64_t T, int64_t width_in, int64_t width_out, Mode mode, bool shared)
+{
+    const int64_t din = padded_width(width_in), dout = padded_width(width_out);
+    const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ, norms = mode == MODE_NORMS;
+    int bm, bn;
+    bf16_tile_shape(mode, B, &bm, &bn);
+    const int64_t tiles = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn), units = plain ? (B * T + 63) / 64 : B;
+    const double s_bytes = (double)din * (double)dout * 4.0, rows = (double)B * (double)T;
+    const double unit = plain ? 2.0 * 64.0 * bm * bn / bf16_block_rate(bm, bn) : bf16_unit_with_fold(mode, shared, T, bm, bn);
+    int64_t ns, per;
+    double t = cheapest_split(tiles, units, unit, norms ? 0.0 : s_bytes * (shared ? 2.0 : 1.0), norms ? (B < 1024 ? (int)B : 1024) : 32, &ns, &per, 0.0,
+                              norms ? 2.0e-6 : 0.0);
+    // per-token square: four such contractions into partial sums of their own, copies of twice the size, seven launches
+    if (mode == MODE_TOKEN_SQ)
+        return 3.1 * (double)((tiles * ns + 255) / 256) * (double)per * unit + (double)(8 * ns + 1) * s_bytes / 5.0e12 + 10.0 * rows * (double)(din + dout) / 15.0e12 + 36.0e-6;
+    if (mode == MODE_SIGN && bm == 256 && bn == 256) {       // partial counts as bytes
+        const double bytes = cheapest_split(tiles, units, unit, (double)sign_byte_partial_bytes(din, dout), 32, &ns, &per);
+        if (bytes < t) t = bytes;
     }
-    const double t = flop / 35.0e12 > slabs * 1.35e-6 ? flop / 35.0e12 : slabs * 1.35e-6;
-    return t * passes > 14.0e-6;
+    return t + 4.0 * rows * (double)((width_in % 8 != 0 ? din : 0) + (width_out % 8 != 0 ? dout : 0)) / 5.0e12 + 12.0e-6;
+}
+
+// `passes` = statistics the SIMT kernel would make one by one
+static bool padding_pays(int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, int passes)
+{
+    if (din % 8 == 0 && dout % 8 == 0) return false;
+    if (!pad_supports(B * T, din, dout) || !bf16_supports(B, T, padded_width(din), padded_width(dout))) return false;
+    return padded_seconds(B, T, din, dout, mode, passes > 1) < simt_seconds(B, T, din, dout, mode) * passes;
 }
 
 // The partial sums of an fp32 call that pex_stat_noalloc has always had room for, by the shape alone: those of as many groups as
@@ -198,6 +237,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     }
     p.din = din;
     p.dout = dout;
+    const bool padded = din != p.out_rows || dout != p.out_cols;
     const bool per_example = (mode == MODE_SQUARE || mode == MODE_SIGN || mode == MODE_NORMS || mode == MODE_WEIGHTED || mode == MODE_POWER);
     p.kernel = (dt == PEX_BF16 && bf16_supports(B, T, din, dout)) ? 1 : 0;
     if (dt == PEX_F32 && f32_mfma_supports(B, T, din, dout)) p.kernel = 2;
@@ -249,9 +289,12 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     } else {
         // A unit-time is one example (or 64 rows) on one block.
         const double rows_per_unit = per_example ? (double)T : (double)slab;
-        const double t_unit = 2.0 * rows_per_unit * bm * bn / bf16_block_rate(bm, bn);
-        // (the per-example norms exchange no partial sums of S, only one number per workgroup and example)
-        double best = cheapest_split(tiles, units, t_unit, mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, max_split, &nsplit, &per);
+        const bool folds = per_example && (padded || mode == MODE_NORMS);
+        const double t_unit = folds ? bf16_unit_with_fold(mode, !allow_wide, T, bm, bn) : 2.0 * rows_per_unit * bm * bn / bf16_block_rate(bm, bn);
+        // (the per-example norms exchange no partial sums of S, only one number per workgroup and example: without the cost of a round
+        // they would take every group there is to save a fraction of one; B=131 T=67 10304x64, 41 blocks: 6 groups 77 us, 131 125)
+        double best = cheapest_split(tiles, units, t_unit, mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, max_split, &nsplit, &per, 0.0,
+                                     mode == MODE_NORMS ? 2.0e-6 : 0.0);
         // Packed sign counts can be exchanged as bytes while a group holds at most 127 examples: a quarter of the
         // traffic, so more groups pay.  Planned with that cost; kept if the groups it gives are small enough.
         if (mode == MODE_SIGN && bm == 256 && bn == 256) {
@@ -273,7 +316,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
             int wm, wn;
             bf16_wide_tile_shape(&wm, &wn);
             const int64_t tiles_m = (din + wm - 1) / wm, max_wide = dout / wn;
-            const double t_wide = 2.0 * (double)T * wm * wn / bf16_block_rate(wm, wn);
+            const double t_wide = folds ? bf16_unit_with_fold(mode, false, T, wm, wn) : 2.0 * (double)T * wm * wn / bf16_block_rate(wm, wn);
             auto consider = [&](int64_t na, bool forced) {
                 const int64_t rest = dout - na * wn;
                 int64_t ns_w = 1, per_w = units, ns_r = 1, per_r = units;
