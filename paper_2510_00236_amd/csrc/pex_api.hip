@@ -107,19 +107,21 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
 // The fp32 kernel: a wave multiplies one 64 x 64 tile on the MFMA pipe of its SIMD (0.15e12 FLOP/s; alone there it keeps
 // the pipe about 87 % busy, two waves about 95 %), `waves` of them make a workgroup, up to eight waves share a compute unit.
 // A group of `pu` units therefore takes as long as the busiest pipe: ceil(workgroups / 256) waves of pu units (the waves of
-// workgroups of two or three meet on the same pipes, single waves spread), at least one wave's own work.  Exchange of partial sums as above.
-static double cheapest_split_f32(int64_t tiles, int64_t units, double rows_per_unit, int waves, double s_bytes, int max_split, int64_t* nsplit,
-                                 int64_t* per)
+// workgroups of two or three meet on the same pipes, single waves spread), at least one wave's own work.  Exchange of partial sums as above;
+// without any (norms), a round of workgroups costs 1 us.  A unit is whole groups of four rows and, of an example, the fold (`t_fold`).
+static double cheapest_split_f32(int64_t tiles, int64_t units, int64_t rows_per_unit, double t_fold, int waves, double s_bytes, int max_split,
+                                 int64_t* nsplit, int64_t* per)
 {
     double best = 0.0;
-    const double wave_unit = 2.0 * rows_per_unit * 64.0 * 64.0 / 0.15e12;
+    const double wave_unit = 2.0 * (double)((rows_per_unit + 3) / 4 * 4) * 64.0 * 64.0 / 0.15e12 + t_fold;
     const int64_t lim = units < max_split ? units : max_split;
     for (int64_t ns = 1; ns <= lim; ++ns) {
         const int64_t pu = (units + ns - 1) / ns;
         const int64_t ns_eff = (units + pu - 1) / pu;
         const double per_pipe = (double)((tiles * ns_eff + 255) / 256) * (waves > 1 ? 1.0 : 0.25);
         double cost = (double)pu * wave_unit * (per_pipe > 1.0 ? per_pipe * 1.05 : 1.15);
-        if (ns_eff > 1 && s_bytes > 0.0) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 2.5e-6;
+        if (s_bytes == 0.0) cost += (double)((tiles * ns_eff + 255) / 256) * 1.0e-6;
+        else if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 2.5e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -277,7 +279,11 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // sign, 10 MB of S, three groups in 32 MB: 321 us, free 311; B=16 T=512 1536x1536 square 369 and 319)
         const bool held = mode <= MODE_SIGN && scratch_charge_f32(B, T, din, dout, mode, max_split) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
         const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
-        cheapest_split_f32(tiles, units, per_example ? (double)T : (double)slab, (bm / 64) * (bn / 64),
+        // folds as measured on one wave per SIMD (T=1 .. 128, 2048 x 2048), seconds per example: three groups of examples became one with
+        // them left out (B=72 T=1 880x128 power 83 us, with them 12; B=26 T=1 118x384 sign 39 and 7)
+        const double t_fold = !per_example ? 0.0 : !allow_wide ? 1.0e-6 : mode == MODE_SIGN ? 1.07e-6 : mode == MODE_NORMS ? 1.15e-6 :
+                              mode == MODE_POWER ? 0.88e-6 : 0.3e-6;
+        cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64),
                            mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit),
                            &nsplit, &per);
     } else if (p.kernel != 1) {

@@ -68,11 +68,12 @@ def test_squares_inside_the_contraction_where_the_option_asks_for_it(pex_option)
 
 def test_short_examples(plans):
     """What an example costs besides its tokens is part of the plan: layers of odd width whose examples are a few tokens take more
-    groups or stay on the SIMT kernel, long ones leave it; the norms take no more groups than
+    groups or stay on the SIMT kernel, long ones leave it; fp32 examples of one token spread over many groups; the norms take no more groups than
     save a round of workgroups."""
-    BF = pex.PEX_BF16
+    BF, F = pex.PEX_BF16, pex.PEX_F32
     kernels = lambda shapes: [p[0] for p in plans(shapes)]
     assert kernels([(592, 2, 2139, 64, BF, "power"), (72, 45, 43, 5632, BF, "power"), (67, 1, 9093, 4664, BF, "token_sq")]) == [0] * 3
     assert plans([(79, 3, 4984, 259, BF, "sign")])[0][:2] == (1, 6)      # (one group of 79 examples before: 241 us, 87 on the SIMT kernel)
     assert kernels([(79, 300, 4984, 259, BF, "sign"), (592, 200, 2139, 64, BF, "power"), (8, 256, 768, 50257, BF, "square"), (14, 544, 3776, 1943, BF, "token_sq")]) == [1] * 4
+    assert all(p[0] == 2 and p[1] >= 8 for p in plans([(72, 1, 880, 128, F, "power"), (26, 1, 118, 384, F, "sign"), (36, 1, 694, 64, F, "power")]))
     assert plans([(131, 67, 10304, 64, BF, "norms")])[0][1] == 6 and plans([(56, 1150, 64, 312, BF, "norms")])[0][1] == 56
