@@ -279,8 +279,8 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // sign, 10 MB of S, three groups in 32 MB: 321 us, free 311; B=16 T=512 1536x1536 square 369 and 319)
         const bool held = mode <= MODE_SIGN && scratch_charge_f32(B, T, din, dout, mode, max_split) <= (size_t)PEX_NOALLOC_SCRATCH_BYTES;
         const int64_t fit = (int64_t)PEX_NOALLOC_SCRATCH_BYTES / (din * dout * 4);
-        // folds as measured on one wave per SIMD (T=1 .. 128, 2048 x 2048), seconds per example: three groups of examples became one with
-        // them left out (B=72 T=1 880x128 power 83 us, with them 12; B=26 T=1 118x384 sign 39 and 7)
+        // folds as measured on one wave per SIMD (T=1 .. 128, 2048 x 2048), seconds per example: with them left out, layers of a few
+        // tokens per example were planned in one group (B=72 T=1 880x128 power 83 us, 17 with them; B=26 T=1 118x384 sign 39 and 12)
         const double t_fold = !per_example ? 0.0 : !allow_wide ? 1.0e-6 : mode == MODE_SIGN ? 1.07e-6 : mode == MODE_NORMS ? 1.15e-6 :
                               mode == MODE_POWER ? 0.88e-6 : 0.3e-6;
         cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64),

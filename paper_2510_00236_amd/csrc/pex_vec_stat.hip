@@ -297,9 +297,10 @@ hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, i
                                  : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
     if (e != hipSuccess) return e;
     // The narrow blocks' two-stage sum costs about three chain steps of the wide ones; beyond one block per compute unit, every 450
-    // blocks of sixteen columns cost another (measurements above the kernels).
+    // blocks of sixteen columns cost another, every 300 where a step is a single load (measurements above the kernels; B=84 d=119314
+    // in one range, whole call: wide 72 us, narrow 84).
     const int64_t narrow = (d + 15) / 16, chain = ((B + RW - 1) / RW) * ((plan.nrange + 7) / 8);
-    if (chain < 3 + (narrow > 256 ? (narrow - 256) / 450 : 0)) {
+    if (chain < 3 + (narrow > 256 ? (narrow - 256) / (plan.nrange == 1 ? 300 : 450) : 0)) {
         vec_finalize_wide_kernel<<<dim3((unsigned)((d + CW - 1) / CW)), dim3(CW * RW), 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign);
         return hipGetLastError();
     }
