@@ -411,7 +411,7 @@ def main() -> int:
                                                "the contraction inside pex_token_sq)", "identity")
     square_roofline = contraction_roofline(sq_events, "pex_stat phi=square as a whole: stat_bf16_kernel<256x192 tile, square> on the columns that fill one "
                                                       "round of 256 workgroups, stat_bf16_kernel<256x128 tile, square> on the rest in two groups of "
-                                                      "examples, reduce_partials_cols_kernel", "square")
+                                                      "examples, reduce_partials_kernel", "square")
     sign_roofline = contraction_roofline(sc_events, "stat_bf16_kernel<256x256 tile, sign with packed counts> (pex_stat phi=sign)", "sign")
     token_roofline = contraction_roofline(tk_events, "pex_token_sq as a whole: square_bf16_kernel on X and on G, then stat_bf16_quad_kernel "
                                                      "on the copies; FLOP of the contraction only", "token")

@@ -34,12 +34,12 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
-    # what the four-wave kernel and the Gram kernel assume about their own machine code, checked while the objects compile
+    # what the four-wave, Gram and fp32 kernels assume about their own machine code, checked while the objects compile
     from . import isa_check
     isa_error = None
     try:
-        isa_check.check_all(HIPCC, [*FLAGS, *extra_flags], os.path.join(CSRC, "pex_stat_bf16.hip"), os.path.join(CSRC, "pex_gram.hip"),
-                            os.path.join(CSRC, "pex_gram_wide.hip"))
+        at = lambda name: os.path.join(CSRC, name)
+        isa_check.check_all(HIPCC, [*FLAGS, *extra_flags], at("pex_stat_bf16.hip"), (at("pex_gram.hip"), at("pex_gram_wide.hip")), at("pex_stat_f32.hip"))
     except (isa_check.IsaCheckError, subprocess.CalledProcessError) as e:
         isa_error = e
     failed = False

@@ -442,7 +442,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
 }
 
 // A plan is a function of the shape, the statistic and the options; weighing the candidates takes 1 to 4 us, as long as a
-// launch.  Each host thread keeps its last few.
+// launch, and up to 12 for the norms of a thousand examples.  Each host thread keeps sixteen, one per hash of what they depend on.
 StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
 {
     struct Kept {
