@@ -75,6 +75,13 @@ struct OptionValues {
     int operator[](int opt) const { return v[opt]; }
 };
 
+// The next number of groups with a smaller largest group (the numbers between share the same plan), past every bound if there is none.
+static int64_t more_groups(int64_t units, int64_t ns)
+{
+    const int64_t per = (units + ns - 1) / ns;
+    return per > 1 ? (units + per - 2) / (per - 1) : INT64_MAX;
+}
+
 // The bf16 kernels run one workgroup per compute unit, so a launch of `tiles` blocks with the batch in `ns` groups takes
 //   rounds(ns) * ceil(units / ns)  unit-times,  rounds = ceil(tiles * ns / 256),
 // its workgroups write ns copies of the output (s_bytes each) and the fixed-order reduction reads them back and writes
@@ -89,7 +96,7 @@ static double cheapest_split(int64_t tiles, int64_t units, double t_unit, double
 {
     double best = 0.0;
     const int64_t lim = units < max_split ? units : max_split;
-    for (int64_t ns = 1; ns <= lim; ++ns) {
+    for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
         const int64_t pu = (units + ns - 1) / ns;
         const int64_t ns_eff = (units + pu - 1) / pu;
         const int64_t rounds = (tiles * ns_eff + 255) / 256;
@@ -115,13 +122,44 @@ static double cheapest_split_f32(int64_t tiles, int64_t units, int64_t rows_per_
     double best = 0.0;
     const double wave_unit = 2.0 * (double)((rows_per_unit + 3) / 4 * 4) * 64.0 * 64.0 / 0.15e12 + t_fold;
     const int64_t lim = units < max_split ? units : max_split;
-    for (int64_t ns = 1; ns <= lim; ++ns) {
+    for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
         const int64_t pu = (units + ns - 1) / ns;
         const int64_t ns_eff = (units + pu - 1) / pu;
         const double per_pipe = (double)((tiles * ns_eff + 255) / 256) * (waves > 1 ? 1.0 : 0.25);
         double cost = (double)pu * wave_unit * (per_pipe > 1.0 ? per_pipe * 1.05 : 1.15);
         if (s_bytes == 0.0) cost += (double)((tiles * ns_eff + 255) / 256) * 1.0e-6;
         else if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes / 4.0e12 + 2.5e-6;
+        if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
+    }
+    return best;
+}
+
+// fp32 layers on the bf16 matrix cores: blocks of 128 x 128, two of them on a compute unit.  A slab of 32 tokens takes 1.75 us when
+// a block has its unit to itself, two slabs 2.45 us when two blocks share one; the fold of an example 0.5 us (signs and norms 0.9);
+// a launch 5 us to start and end, norms another 2 us with every round of blocks (their partial sums leave after every example).
+// Identity and square together also add S_id up in memory: 64 KiB per block and example, read and written at 3.9 TB/s, of which a fifth of
+// the contraction's time is hidden (2048 x 2048, B=32 T=64: 21 us an example; 2048 x 4096, B=8 T=1024: 6 us).  Fitted on 150 drawn
+// layers of 8 to 700 us and eight statistics: the estimates are within 16 % for nine in ten.
+static double cheapest_split_f32_pieces(int64_t blocks, int64_t units, int64_t slabs_per_unit, Mode mode, bool pair, double s_bytes, int max_split,
+                                        int64_t* nsplit, int64_t* per)
+{
+    constexpr double SLAB_ALONE = 1.75e-6, SLABS_SHARED = 2.45e-6;
+    const double slabs = (double)slabs_per_unit;
+    const double t_fold = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ ? 0.0 : mode == MODE_SIGN || mode == MODE_NORMS ? 0.9e-6 : 0.5e-6;
+    double best = 0.0;
+    const int64_t lim = units < max_split ? units : max_split;
+    for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
+        const int64_t pu = (units + ns - 1) / ns;
+        const int64_t ns_eff = (units + pu - 1) / pu;
+        const int64_t wgs = blocks * ns_eff, per_cu = (wgs + 255) / 256;
+        double t_unit = t_fold;
+        if (pair) {
+            const double memory = 1.25 * 2.0 * 65536.0 * (double)(wgs < 512 ? wgs : 512) / 3.9e12 - 0.2 * slabs * SLABS_SHARED;
+            if (memory > 0.0) t_unit += memory;
+        }
+        double cost = (double)pu * ((double)(per_cu / 2) * (slabs * SLABS_SHARED + t_unit) + (double)(per_cu % 2) * (slabs * SLAB_ALONE + t_unit)) + 5.0e-6;
+        if (mode == MODE_NORMS) cost += (double)((per_cu + 1) / 2) * 2.0e-6;
+        else if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes * (pair ? 2.0 : 1.0) / 4.0e12 + 2.5e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -272,7 +310,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         if (max_split > fit) max_split = fit < 1 ? 1 : (int)fit;
     }
     int64_t nsplit = 1, per = units;
-    int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units;
+    int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units, direct_nsplit = 1;
     bool sign_bytes = false, mem_fold = false;
     if (p.kernel == 2) {
         // Calls that pex_stat_noalloc has always taken keep their partial sums within its scratch; the others are free (B=42 T=112 704x3648
@@ -283,9 +321,23 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         // tokens per example were planned in one group (B=72 T=1 880x128 power 83 us, 17 with them; B=26 T=1 118x384 sign 39 and 12)
         const double t_fold = !per_example ? 0.0 : !allow_wide ? 1.0e-6 : mode == MODE_SIGN ? 1.07e-6 : mode == MODE_NORMS ? 1.15e-6 :
                               mode == MODE_POWER ? 0.88e-6 : 0.3e-6;
-        cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64),
-                           mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0, !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit),
-                           &nsplit, &per);
+        const double s_bytes = mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0;
+        const int most = !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit);
+        const double direct = cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64), s_bytes, most, &nsplit, &per);
+        // ... or split into bf16 pieces, where that is faster (never for examples of fewer than 48 tokens: there its sums of 32 tokens
+        // are no more exact than the fp32 ones, 1.39e-7 against 1.38e-7 of the 2-norm at T = 32, 1.51e-7 against 1.60e-7 at T = 48)
+        if (allow_pad && f32_split_supports(B, T, din, dout) && (per_example ? T : B * T) >= 48) {
+            int64_t ns_p = 1, per_p = units;
+            const int64_t blocks = f32_split_blocks(din, dout), fit_p = (((int64_t)1 << 32) - 1) / (blocks * 256);
+            const double pieces = cheapest_split_f32_pieces(blocks, units, ((per_example ? T : slab) + 31) / 32, mode, !allow_wide, s_bytes,
+                                                            most > fit_p ? (int)fit_p : most, &ns_p, &per_p);
+            if (pieces < direct) {
+                p.f32_split = true;
+                direct_nsplit = nsplit;
+                nsplit = ns_p;
+                per = per_p;
+            }
+        }
     } else if (p.kernel != 1) {
         nsplit = (target + tiles - 1) / tiles;
         if (nsplit > max_split) nsplit = max_split;
@@ -392,10 +444,12 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     p.wide_ws_bytes = (wide_cols > 0 && wide_nsplit > 1) ? (size_t)wide_nsplit * (size_t)din * (size_t)wide_cols * sizeof(float) : 0;
     p.ws_bytes = p.copy_bytes + p.wide_ws_bytes +
                  ((nsplit > 1 && dout > wide_cols) ? (size_t)nsplit * (size_t)din * (size_t)(dout - wide_cols) * sizeof(float) : 0);
+    // (a layer that fits a bound on the workspace, or does not, is the same layer whichever way it is multiplied)
+    if (p.f32_split && direct_nsplit > nsplit) p.ws_bytes = (size_t)direct_nsplit * (size_t)din * (size_t)dout * sizeof(float);
     if (p.square_halves) p.ws_bytes = p.copy_bytes + (size_t)4 * (size_t)nsplit * (size_t)din * (size_t)dout * sizeof(float);
     if (p.sign_bytes) p.ws_bytes = p.copy_bytes + (size_t)nsplit * sign_byte_partial_bytes(din, dout);
     if (mode == MODE_NORMS) {   // no S at all: one partial of ||M_b||^2 per tile (and wave) and example
-        const int64_t nparts = p.kernel == 1 ? bf16_norm_partials(din, dout) : p.kernel == 2 ? f32_norm_partials(din, dout) : generic_norm_partials(din, dout);
+        const int64_t nparts = p.kernel == 1 ? bf16_norm_partials(din, dout) : p.kernel == 2 ? (p.f32_split ? 4 * f32_split_blocks(din, dout) : f32_norm_partials(din, dout)) : generic_norm_partials(din, dout);
         p.ws_bytes = p.copy_bytes + (size_t)nparts * (size_t)B * sizeof(float);
         // Through the Gram matrices instead: 2 T^2 (din + dout) FLOP per example (a little over half of it with the
         // symmetry, in 128 x 128 blocks) against 2 T din dout, on a kernel of lower rate but with one workgroup per block
@@ -479,9 +533,9 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
 static StatPlan plan_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, size_t bytes)
 {
     const StatPlan plan = plan_stat(B, T, din, dout, dt, mode);
-    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout)) return plan;
-    const StatPlan simt = plan_stat(B, T, din, dout, dt, mode, true, false);
-    return simt.ws_bytes <= bytes ? simt : plan;
+    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout && !plan.f32_split)) return plan;
+    const StatPlan direct = plan_stat(B, T, din, dout, dt, mode, true, false);
+    return direct.ws_bytes <= bytes ? direct : plan;
 }
 
 static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
@@ -616,12 +670,14 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
-    const StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad);
+    // (what shares a contraction on the bf16 matrix cores is identity and square only)
+    constexpr uint32_t BOTH = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
+    StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH));
     // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
     // contraction and sign keeps its own.  On fp32 layers sign shares one only as bytes.
     m.pair_want = want;
-    if (sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
-    if (sq.kernel == 2 && !f32_bytes_suffice(sq)) m.pair_want = want & (PEX_WANT_IDENTITY | PEX_WANT_SQUARE);
+    if (sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = BOTH;
+    if (sq.kernel == 2 && !f32_bytes_suffice(sq)) m.pair_want = want & BOTH;
     m.pair = (__builtin_popcount(m.pair_want) >= 2 && sq.kernel != 0);
     if (m.pair) {
         m.single_want = want & ~m.pair_want;
@@ -844,7 +900,7 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
         nparts = bf16_norm_partials(kin, kout);
         e = launch_norms_bf16(X, G, B, T, kin, kout, plan, partial, hs);
     } else if (plan.kernel == 2) {
-        nparts = f32_norm_partials(kin, kout);
+        nparts = plan.f32_split ? 4 * f32_split_blocks(kin, kout) : f32_norm_partials(kin, kout);
         e = launch_stat_f32(X, G, B, T, kin, kout, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
     } else {
         nparts = generic_norm_partials(kin, kout);

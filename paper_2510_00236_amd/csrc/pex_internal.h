@@ -20,6 +20,7 @@ enum Mode : int { MODE_IDENTITY = 0, MODE_SQUARE = 1, MODE_SIGN = 2, MODE_TOKEN_
 // the launch always agree.
 struct StatPlan {
     int kernel;        // 0 = generic SIMT kernel (odd shapes), 1 = bf16 MFMA kernel, 2 = fp32 MFMA kernel
+    bool f32_split;    // kernel 2: the operands as three bf16 pieces each on the bf16 matrix cores (128 x 128 blocks)
     int nsplit;        // number of groups the batch (or, for plain contractions, B*T) is split into
     int64_t per_split; // examples (or rows of B*T) per group
     int64_t din, dout;           // widths of the operands as the kernels see them: the layer's, or those of padded copies
@@ -95,6 +96,13 @@ int64_t f32_norm_partials(int64_t din, int64_t dout);
 hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode,
                            const StatPlan& plan, float* out, hipStream_t stream, const float* weight = nullptr,
                            float* norm_partial = nullptr, float alpha = 0.f);
+// fp32 layers on the bf16 matrix cores
+bool f32_split_supports(int64_t B, int64_t T, int64_t din, int64_t dout);
+int64_t f32_split_blocks(int64_t din, int64_t dout);
+hipError_t launch_stat_f32_split(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, const StatPlan& plan,
+                                 float* out, hipStream_t stream, const float* weight, float* norm_partial, float alpha);
+hipError_t launch_stat_f32_split_pair(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
+                                      float* out_id, float* out_sq, hipStream_t stream);
 // byte-wide sign counters hold a group of the plan
 bool f32_bytes_suffice(const StatPlan& plan);
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,

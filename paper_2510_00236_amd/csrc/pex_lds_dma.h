@@ -1,5 +1,5 @@
-// pex_lds_dma.h -- device helpers shared by the kernels that fill their LDS with direct-to-LDS buffer loads and
-// track completion by hand (gfx950).  Device code only; every function is inlined into its caller.
+// pex_lds_dma.h -- device helpers shared by the kernels that fill their LDS with direct-to-LDS buffer loads, add to their
+// output in memory or track completion by hand (gfx950).  Device code only; every function is inlined into its caller.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,6 +41,21 @@ __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// One dword per lane to (descriptor base + voff + soff): plain store, or fp32 add performed by the L2 (no value
+// returned).  Lanes whose offset is outside the descriptor's range do nothing.  Both count in vmcnt like the loads.
+// The sum of the offsets is formed inside the statement (the range check does not see the instruction's own scalar
+// offset), so that the compiler cannot keep one precomputed address per accumulator register alive across the main loop.
+__device__ __forceinline__ void mem_store_f32(float v, uint32_t voff, uint32_t soff, int4_t rsrc)
+{
+    uint32_t at;
+    asm volatile("v_add_u32 %0, %2, %3\n\tbuffer_store_dword %1, %0, %4, 0 offen" : "=&v"(at) : "v"(v), "v"(voff), "s"(soff), "s"(rsrc) : "memory");
+}
+__device__ __forceinline__ void mem_add_f32(float v, uint32_t voff, uint32_t soff, int4_t rsrc)
+{
+    uint32_t at;
+    asm volatile("v_add_u32 %0, %2, %3\n\tbuffer_atomic_add_f32 %1, %0, %4, 0 offen" : "=&v"(at) : "v"(v), "v"(voff), "s"(soff), "s"(rsrc) : "memory");
 }
 
 // this wave's LDS reads and writes are complete, then the workgroup barrier

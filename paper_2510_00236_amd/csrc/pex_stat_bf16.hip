@@ -101,21 +101,6 @@ typedef __attribute__((ext_vector_type(2))) _Float16 half2_t;
 typedef short4_t __attribute__((address_space(3)))* lds_v4;
 typedef uint4_t __attribute__((address_space(3)))* lds_u4;
 
-// One dword per lane to (descriptor base + voff + soff): plain store, or fp32 add performed by the L2 (no value
-// returned).  Lanes whose offset is outside the descriptor's range do nothing.  Both count in vmcnt like the loads.
-// The sum of the offsets is formed inside the statement (the range check does not see the instruction's own scalar
-// offset), so that the compiler cannot keep one precomputed address per accumulator register alive across the main loop.
-__device__ __forceinline__ void mem_store_f32(float v, uint32_t voff, uint32_t soff, int4_t rsrc)
-{
-    uint32_t at;
-    asm volatile("v_add_u32 %0, %2, %3\n\tbuffer_store_dword %1, %0, %4, 0 offen" : "=&v"(at) : "v"(v), "v"(voff), "s"(soff), "s"(rsrc) : "memory");
-}
-__device__ __forceinline__ void mem_add_f32(float v, uint32_t voff, uint32_t soff, int4_t rsrc)
-{
-    uint32_t at;
-    asm volatile("v_add_u32 %0, %2, %3\n\tbuffer_atomic_add_f32 %1, %0, %4, 0 offen" : "=&v"(at) : "v"(v), "v"(voff), "s"(soff), "s"(rsrc) : "memory");
-}
-
 // sign(m) in {-1, 0, +1} as a float without compares: scaling by 2^200 sends every non-zero value (denormals
 // included) beyond +-1 and keeps +-0 at 0, the median with -1 and +1 clamps it.  The median of a NaN is the lowest of the other two.
 template <int OUTS>

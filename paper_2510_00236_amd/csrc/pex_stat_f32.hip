@@ -3,8 +3,9 @@
 // Same mathematics as the bf16 kernel (Sec. 2.3): M_b = X_b^T G_b accumulates in registers, phi is applied to the
 // finished per-example tile, the per-example gradient never leaves the register file.  fp32 inputs keep true fp32
 // products (the 1e-4 tolerance of fp32 inputs forbids rounding them to bf16): v_mfma_f32_16x16x4_f32, 157 TFLOP/s at
-// the datasheet clock -- the same as the vector FMA rate with packed operations, which this library is built without,
-// so the matrix pipe is the only way past ~79 TFLOP/s.
+// the datasheet clock -- the same as the vector FMA rate with packed operations, which this library is built without.
+// Layers large enough run past that rate on the bf16 matrix cores instead (pex_stat_f32_split.hip); this kernel keeps short
+// examples, small layers and the statistics that share a contraction with sign.
 //
 // Bound: the fp32 MFMA pipe, 16 times slower per byte of operand than the bf16 one.  At that ratio the operands need
 // no LDS at all: a wave owns a 64 x 64 tile and loads its fragments straight from global memory, so waves share
@@ -29,28 +30,16 @@
 // and bytes, four with three tiles, two with all three statistics.  Measured on B=16, T=1024, 1024x4096: identity + square
 // 0.98 ms (one after the other 1.92), all three 1.08 ms; three tiles in a ring of six on one wave per SIMD take 1.38 ms, all
 // three in a ring of three spill and take 1.29 ms.
+#include "pex_f32.h"
 #include "pex_internal.h"
 #include "pex_tile_map.h"
 
 namespace pex {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) float float4_t;
-typedef __attribute__((ext_vector_type(4))) unsigned int uint4_t;
-typedef float4_t __attribute__((aligned(4))) float4_u;      // four floats at any float's address
-
-constexpr int F_T = 64;                    // edge of a wave's tile
 constexpr int F_ROWS = 4;                  // tokens per group
-constexpr int F_CHUNK = 1024;              // rows after which a plain contraction is folded into its sum
-constexpr uint32_t F_OUTSIDE = 0x80000000u; // lane offset beyond every descriptor (windows stay below 2^30 bytes)
 constexpr int F_THREADS = 256;             // up to four waves: 2 x 2 tiles of 64 x 64
-
-// What one launch produces (bit set); none of the per-example ones: a plain contraction over all rows, written to out_id
-constexpr int F_ID = 1, F_SQ = 2, F_SG = 4, F_SG8 = 8, F_IDW = 16, F_POW = 32, F_NORM = 64, F_TOKEN = 128;
-constexpr int F_PLAIN = 0;
 constexpr int F_MAX_U8 = 127;              // examples a byte counter of sign + 1 holds
-
-__device__ __forceinline__ float sign_of(float m) { return (float)((m > 0.f) - (m < 0.f)); }
 
 template <int OUTS, int RING>
 __global__ __launch_bounds__(F_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void stat_f32_kernel(
@@ -171,7 +160,7 @@ __global__ __launch_bounds__(F_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)
                     if (!PER_EXAMPLE || (OUTS & F_ID)) acc_id[m][n][r] += v;
                     if (OUTS & F_IDW) acc_id[m][n][r] = fmaf(w, v, acc_id[m][n][r]);
                     if (OUTS & F_SQ) acc_sq[m][n][r] = fmaf(v, v, acc_sq[m][n][r]);
-                    if (OUTS & F_POW) acc_sq[m][n][r] += __builtin_amdgcn_exp2f(alpha * __builtin_amdgcn_logf(__builtin_fabsf(v)));
+                    if (OUTS & F_POW) acc_sq[m][n][r] += power_of(v, alpha);
                     if (OUTS & F_SG) acc_sg[m][n][r] += sign_of(v);
                     if (OUTS & F_SG8) bytes = __builtin_amdgcn_cvt_pk_u8_f32(sign_of(v) + 1.0f, r, bytes);
                     if (OUTS & F_NORM) {
@@ -313,6 +302,7 @@ int64_t f32_norm_partials(int64_t din, int64_t dout) { return ((din + F_T - 1) /
 hipError_t launch_stat_f32(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, Mode mode, const StatPlan& plan,
                            float* out, hipStream_t stream, const float* weight, float* norm_partial, float alpha)
 {
+    if (plan.f32_split) return launch_stat_f32_split(X, G, B, T, din, dout, mode, plan, out, stream, weight, norm_partial, alpha);
     switch (mode) {
     case MODE_IDENTITY: return launch_f32<F_PLAIN, 6>(X, G, B, T, din, dout, plan, out, nullptr, nullptr, stream);
     case MODE_SQUARE: return launch_f32<F_SQ, 6>(X, G, B, T, din, dout, plan, nullptr, out, nullptr, stream);
@@ -331,7 +321,8 @@ bool f32_bytes_suffice(const StatPlan& plan) { return plan.per_split <= F_MAX_U8
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
                                  float* out_id, float* out_sq, float* out_sg, hipStream_t stream)
 {
-    if (out_sg && !f32_bytes_suffice(plan)) return hipErrorInvalidValue;
+    if (out_sg && (plan.f32_split || !f32_bytes_suffice(plan))) return hipErrorInvalidValue;
+    if (plan.f32_split) return launch_stat_f32_split_pair(X, G, B, T, din, dout, plan, out_id, out_sq, stream);
     if (out_id && out_sq && out_sg) return launch_f32<F_ID | F_SQ | F_SG8, 2>(X, G, B, T, din, dout, plan, out_id, out_sq, out_sg, stream);
     if (out_id && out_sq) return launch_f32<F_ID | F_SQ, 4>(X, G, B, T, din, dout, plan, out_id, out_sq, nullptr, stream);
     if (out_id && out_sg) return launch_f32<F_ID | F_SG8, 6>(X, G, B, T, din, dout, plan, out_id, nullptr, out_sg, stream);

@@ -98,15 +98,17 @@ def check_accumulators_in_place(text: str) -> None:
         raise IsaCheckError(f"{len(moves)} accumulator moves in the Gram kernel, e.g. {moves[0]}")
 
 
-def check_all(hipcc: str, flags, src: str, gram_srcs, f32_src: str) -> None:
+def check_all(hipcc: str, flags, src: str, gram_srcs, f32_srcs) -> None:
     with ThreadPoolExecutor(2) as pool:
-        text, f32, *grams = pool.map(lambda path: device_asm(hipcc, flags, path), (src, f32_src, *gram_srcs))
+        text, *rest = pool.map(lambda path: device_asm(hipcc, flags, path), (src, *f32_srcs, *gram_srcs))
+    f32s, grams = rest[:len(f32_srcs)], rest[len(f32_srcs):]
     check_no_scratch(text)
     body, meta = quad_kernel_asm(hipcc, flags, src, text)
     check_m0(body)
     check_registers(body, meta)
     # the fp32 kernel's ring takes what the register tiles leave of 256 registers: one set more spills (1.08 -> 1.29 ms)
-    check_no_scratch(f32)
+    for f32 in f32s:
+        check_no_scratch(f32)
     for gram in grams:
         check_no_scratch(gram)
         check_accumulators_in_place(gram)
