@@ -1015,9 +1015,10 @@ pex_status pex_embed_stat(const void* ids, int32_t ids_bytes, const void* G, int
     if (want & PEX_WANT_SQUARE) al |= (uintptr_t)S_sq;
     if (want & PEX_WANT_SIGN) al |= (uintptr_t)S_sign;
     if ((al & 15u) || ((uintptr_t)ids & (uintptr_t)(ids_bytes - 1))) return PEX_ERR_ALIGN;
-    if (!workspace || workspace_bytes < embed_workspace(B, T, V, d)) return PEX_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < embed_workspace_least(B, T, V, d)) return PEX_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
-    return launch_embed_stat(ids, ids_bytes, G, B, T, V, d, dt, want, S_id, S_sq, S_sign, workspace, (hipStream_t)stream) == hipSuccess
+    return launch_embed_stat(ids, ids_bytes, G, B, T, V, d, dt, want, S_id, S_sq, S_sign, workspace, workspace_bytes,
+                             (hipStream_t)stream) == hipSuccess
                ? PEX_OK
                : PEX_ERR_HIP;
 }

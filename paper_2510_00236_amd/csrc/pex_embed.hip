@@ -7,10 +7,12 @@
 // not occur are written as zeros), plus the ids.
 //
 // Everything is deterministic (no floating-point atomics):
-//   1. a stable least-significant-digit radix sort (8 bits per pass, a counting and a placing launch per pass) of
-//      the B*T positions by token id; positions enter in the order p = b*T + t, so inside a token's run
-//      they stay ordered by example and then by t; ids outside [0, V) (padding) get the key V and are never consumed;
-//   2. row_start[v] = first sorted index whose key is >= v;
+//   1. a stable sort of the B*T positions that brings those of a token together; positions enter in the order p = b*T + t, so
+//      inside a token's run they stay ordered by example and then by t; ids outside [0, V) (padding) get the key V and are
+//      never consumed.  One launch of 256 workgroups that each collect the tokens of one bucket (bucket_sort_kernel); batches and
+//      vocabularies too large for that: a least-significant-digit radix sort (8 bits per pass, a counting and a placing
+//      launch per pass);
+//   2. row_start: where each token's run begins and, at the next index, ends (RowIndex);
 //   3. each wave owns 16 consecutive sorted positions and every vocabulary row whose run starts among them: cotangent
 //      rows are loaded 16 at a time and added per example, phi is applied whenever the example changes, and the result
 //      is added to the row's sums.  Rows with many positions are done by all waves of the workgroup, each on a
@@ -172,8 +174,8 @@ __global__ __launch_bounds__(256) void row_start_kernel(const int* __restrict__ 
     fill_row_start(row_start, valid ? (int)k : 0, !valid ? 0 : (k == 0 ? -1 : keys[k - 1]), !valid ? 0 : (k == N ? V : keys[k]), V);
 }
 
-// Few positions: the whole sort and row_start in one launch of one workgroup, keys and positions in LDS.  Same digits, same
-// order: wave i owns a contiguous segment of the positions; counters per (wave, digit) give every key its place.  Bound by the
+// Few positions of a vocabulary too large for buckets: the whole radix sort and row_start in one launch of one workgroup, keys
+// and positions in LDS.  Same digits, same order: wave i owns a contiguous segment of the positions; counters per (wave, digit) give every key its place.  Bound by the
 // latency of its few dozen steps, 15 - 18 us for 1500 - 2040 positions, against the five or seven launches of the kernels above,
 // which take about 4.5 us each whatever they do (whole call, 345 / 630 / 2040 positions: 45 / 104 / 58 -> 27 / 45 / 38 us; at 3700
 // and 8192 positions the one workgroup is the slower one by 4 and 7 us).
@@ -265,6 +267,249 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void sort_small_kernel(const TId*
         const bool valid = k <= N;
         fill_row_start(row_start, valid ? k : 0, !valid ? 0 : (k == 0 ? -1 : key(cur, k - 1)), !valid ? 0 : (k == N ? V : key(cur, k)), V);
     }
+}
+
+// The sort by buckets.  Token v belongs to bucket v mod 256 and workgroup b does bucket b alone: it counts the tokens of its
+// bucket, places their positions and writes their part of row_start.  Order: by bucket, then by token, then by position --
+// consecutive tokens, which are alike in frequency, fall into different buckets.  A wave takes a contiguous part of the positions;
+// counters per (wave, token) give every position its place, whatever the frequencies.
+//   bucket_sort_kernel<.., false>: one launch.  Every workgroup reads all ids, twice; where its bucket begins it knows from the ids
+//     of smaller buckets it meets.  Bound by the instructions of 256 workgroups reading everything: 12 us for 8192 positions, 66
+//     for 65536, so it ends at 4096, where two launches take as long.
+//   tile_buckets_kernel, bucket_sort_kernel<.., true>: tiles of 1024 positions are first put in bucket order, each by a
+//     workgroup of its own; a bucket's workgroup then reads its segment of every tile.  4.8 + 7 us for 65536 positions; 50 where half
+//     of them are one token, which one workgroup then places alone.
+// (Before: a radix sort with five launches for two 8-bit digits, 30 us.  Whole calls, identity and square, before / now: B=64 T=1024
+// V=50257 d=768 115 / 96 us, uniform tokens 94 / 80, half of them one token 190 / 169; B=8 T=512 d=256 56 / 38; B=9 T=152 V=2515 d=384,
+// by one workgroup before, 25.7 / 19.1; B=128 T=2048 d=256 126 / 101.)
+constexpr int BUCKETS = 256, BUCKET_WAVES = 16, BUCKET_TILE = BUCKET_WAVES * 64, BUCKET_MAX_TILES = 256;
+constexpr int BUCKET_MAX_V = BUCKETS * 1024;               // 64 KiB of counters
+constexpr int BUCKET_ONE_LAUNCH_N = 4096, BUCKET_MAX_N = BUCKET_MAX_TILES * BUCKET_TILE;
+
+// Where row_start keeps token v: its run is row_start[at(v)] .. row_start[at(v) + 1].  By bucket, or (mask = shift = 0) by token.
+struct RowIndex {
+    int mask, shift, per_bucket;
+    __device__ __forceinline__ int at(int v) const { return (v & mask) * per_bucket + (v >> shift); }
+};
+
+// lanes of this wave that are active and hold the same number of `bits` bits
+__device__ __forceinline__ unsigned long long same_number(bool active, int x, int bits)
+{
+    unsigned long long same = __ballot(active);
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (x >> b) & 1;
+        const unsigned long long bb = __ballot(one);
+        same &= one ? bb : ~bb;
+    }
+    return same;
+}
+
+// inclusive sum over the lanes of a wave
+__device__ __forceinline__ int wave_scan(int x)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(x, o);
+        if (lane >= o) x += t;
+    }
+    return x;
+}
+
+// One tile in bucket order, padding left out: keys and positions at the tile's place, off[tile][b] = where bucket b begins in it
+template <typename TId>
+__global__ __launch_bounds__(BUCKET_TILE) void tile_buckets_kernel(const TId* __restrict__ ids, int N, int V, int* __restrict__ keys_out,
+                                                                   int* __restrict__ vals_out, int* __restrict__ off)
+{
+    __shared__ int counts[BUCKET_WAVES][BUCKETS];
+    __shared__ int wtot[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p = blockIdx.x * BUCKET_TILE + tid;
+    for (int t = tid; t < BUCKET_WAVES * BUCKETS; t += BUCKET_TILE) counts[t / BUCKETS][t % BUCKETS] = 0;
+    const int key = p < N ? load_key(ids, p, V) : V;
+    const bool active = key < V;
+    const int b = key & (BUCKETS - 1);
+    const unsigned long long same = same_number(active, b, 8);
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    __syncthreads();
+    if (active && rank == 0) counts[wave][b] = __popcll(same);
+    __syncthreads();
+    int total = 0, incl = 0;
+    if (tid < BUCKETS) {
+#pragma unroll
+        for (int w = 0; w < BUCKET_WAVES; ++w) total += counts[w][tid];
+        incl = wave_scan(total);
+        if (lane == 63) wtot[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < BUCKETS) {
+        int at = incl - total;
+        for (int w = 0; w < wave; ++w) at += wtot[w];
+        off[blockIdx.x * (BUCKETS + 1) + tid] = at;
+        if (tid == BUCKETS - 1) off[blockIdx.x * (BUCKETS + 1) + BUCKETS] = at + total;
+#pragma unroll
+        for (int w = 0; w < BUCKET_WAVES; ++w) {
+            const int c = counts[w][tid];
+            counts[w][tid] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    if (active) {
+        const int place = blockIdx.x * BUCKET_TILE + counts[wave][b] + rank;
+        keys_out[place] = key;
+        vals_out[place] = p;
+    }
+}
+
+// TILED: the segments of tile_buckets_kernel (tiles <= BUCKET_MAX_TILES of them) instead of the ids
+template <typename TId, bool TILED>
+__global__ __launch_bounds__(BUCKET_TILE) void bucket_sort_kernel(const TId* __restrict__ ids, const int* __restrict__ tile_keys,
+                                                                  const int* __restrict__ tile_vals, const int* __restrict__ off, int tiles, int N, int V,
+                                                                  int per_bucket, int* __restrict__ keys_out, int* __restrict__ vals_out,
+                                                                  int* __restrict__ row_start)
+{
+    extern __shared__ int counts[];       // [BUCKET_WAVES][per_bucket]
+    __shared__ int wsum[2][BUCKET_WAVES];
+    __shared__ int seg_at[TILED ? BUCKET_MAX_TILES : 1], seg_src[TILED ? BUCKET_MAX_TILES : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, bucket = blockIdx.x;
+    int* mine = counts + wave * per_bucket;
+    for (int t = tid; t < BUCKET_WAVES * per_bucket; t += BUCKET_TILE) counts[t] = 0;
+    int smaller = 0;      // positions of smaller buckets, this thread's share
+    int n = N;            // entries this workgroup reads
+    if constexpr (TILED) {
+        int len = 0;
+        if (tid < tiles) {
+            smaller = off[tid * (BUCKETS + 1) + bucket];
+            len = off[tid * (BUCKETS + 1) + bucket + 1] - smaller;
+            seg_src[tid] = tid * BUCKET_TILE + smaller;
+        }
+        const int incl = wave_scan(len);
+        if (lane == 63) wsum[1][wave] = incl;
+        __syncthreads();
+        int at = incl - len;
+        n = 0;
+#pragma unroll
+        for (int w = 0; w < BUCKET_MAX_TILES / 64; ++w) {
+            if (w < wave) at += wsum[1][w];
+            n += wsum[1][w];
+        }
+        if (tid < tiles) seg_at[tid] = at;
+    }
+    __syncthreads();
+    const int seg = (n + BUCKET_TILE - 1) / BUCKET_TILE * 64;      // entries per wave, whole batches of 64
+    const int lo = wave * seg < n ? wave * seg : n, hi = lo + seg < n ? lo + seg : n;
+    // entry e: its key and position
+    auto entry = [&](int e, int& val) {
+        if constexpr (TILED) {
+            int t = 0;
+            for (int step = BUCKET_MAX_TILES / 2; step > 0; step >>= 1)
+                if (t + step < tiles && seg_at[t + step] <= e) t += step;
+            const int src = seg_src[t] + (e - seg_at[t]);
+            val = tile_vals[src];
+            return tile_keys[src];
+        } else {
+            val = e;
+            return load_key(ids, e, V);
+        }
+    };
+    // U batches of 64 from k0 on, their loads in flight together (lanes past the end repeat the last entry)
+    auto entries = [&](int k0, auto& key, auto& val) {
+        constexpr int U = sizeof(key) / sizeof(int);
+        int k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = entry(k0 + 64 * u + lane < hi ? k0 + 64 * u + lane : hi - 1, val[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = k0 + 64 * u + lane < hi ? k[u] : V;
+    };
+    auto count = [&](int k0, auto UC) {
+        constexpr int U = decltype(UC)::value;
+        int key[U], val[U];
+        entries(k0, key, val);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = key[u] < V ? key[u] & (BUCKETS - 1) : BUCKETS;
+            if (!TILED) smaller += b < bucket;
+            // (the positions of the first lane's token are one addition: a frequent token's would wait for each other)
+            const int first = __builtin_amdgcn_readfirstlane(key[u]);
+            const unsigned long long alike = TILED ? __ballot(key[u] == first) : 0;
+            if (b == bucket && (!TILED || lane == 0 || key[u] != first)) atomicAdd(&mine[key[u] / BUCKETS], TILED && lane == 0 ? __popcll(alike) : 1);
+        }
+    };
+    constexpr std::integral_constant<int, 8> U8{};
+    constexpr std::integral_constant<int, 1> U1{};
+    int at0 = lo;
+    for (; at0 + 64 * 7 < hi; at0 += 64 * 8) count(at0, U8);
+    for (; at0 < hi; at0 += 64) count(at0, U1);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) smaller += __shfl_xor(smaller, o);
+    if (lane == 0) wsum[0][wave] = smaller;
+    __syncthreads();
+    // thread t: the bucket's token t; its run begins after all smaller ones, wave by wave
+    int total = 0;
+    if (tid < per_bucket)
+#pragma unroll
+        for (int w = 0; w < BUCKET_WAVES; ++w) total += counts[w * per_bucket + tid];
+    const int incl = wave_scan(total);
+    if (lane == 63) wsum[1][wave] = incl;
+    __syncthreads();
+    int at = incl - total, end = 0;
+#pragma unroll
+    for (int w = 0; w < BUCKET_WAVES; ++w) {
+        at += wsum[0][w] + (w < wave ? wsum[1][w] : 0);
+        end += wsum[0][w] + wsum[1][w];
+    }
+    if (tid < per_bucket) {
+        row_start[bucket * per_bucket + tid] = at;
+#pragma unroll
+        for (int w = 0; w < BUCKET_WAVES; ++w) {
+            const int c = counts[w * per_bucket + tid];
+            counts[w * per_bucket + tid] = at;
+            at += c;
+        }
+    }
+    if (bucket == BUCKETS - 1) {          // the last run's end, and the positions of padding
+        if (tid == 0) row_start[BUCKETS * per_bucket] = end;
+        for (int k = end + tid; k < N; k += BUCKET_TILE) {
+            keys_out[k] = V;
+            vals_out[k] = 0;
+        }
+    }
+    __syncthreads();
+    int bits = 0;
+    while ((per_bucket - 1) >> bits) ++bits;
+    auto place_batches = [&](int k0, auto UC) {
+        constexpr int U = decltype(UC)::value;
+        int key[U], val[U];
+        entries(k0, key, val);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool match = key[u] < V && (key[u] & (BUCKETS - 1)) == bucket;
+            unsigned long long todo = __ballot(match), same = 0;
+            if (todo == 0) continue;
+            // batches of 64 in order: rank among the batch's positions of the same token, place from the wave's counter, which the
+            // first of them moves on.  Up to four tokens (a frequent one among others) one by one, more by their bits.
+            const int token = match ? key[u] / BUCKETS : 0;
+            for (int i = 0; i < 4 && todo; ++i) {
+                const unsigned long long m = __ballot(match && key[u] == __builtin_amdgcn_readlane(key[u], __builtin_ctzll(todo)));
+                if ((m >> lane) & 1) same = m;
+                todo &= ~m;
+            }
+            if (todo) same = same_number(match, token, bits);
+            const int rank = __popcll(same & ((1ull << lane) - 1ull));
+            const int place = match ? mine[token] + rank : 0;
+            __builtin_amdgcn_wave_barrier();            // every lane has read its counter (LDS operations of a wave stay in order)
+            if (match && rank == 0) mine[token] = place + __popcll(same);
+            __builtin_amdgcn_wave_barrier();
+            if (match && place < N) {
+                keys_out[place] = key[u];
+                vals_out[place] = val[u];
+            }
+        }
+    };
+    at0 = lo;
+    for (; at0 + 64 * 7 < hi; at0 += 64 * 8) place_batches(at0, U8);
+    for (; at0 < hi; at0 += 64) place_batches(at0, U1);
 }
 
 // What a lane loads from a cotangent row: four columns (fp32 16 bytes, bf16 8 bytes), kept as loaded until they are added:
@@ -450,8 +695,8 @@ struct RowAccumulator {
 template <typename TIn, int ALIGN, int WANT>
 __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* __restrict__ G, const int* __restrict__ row_start,
                                                                     const int* __restrict__ keys, const int* __restrict__ pos,
-                                                                    int N, int V, int T, int64_t d, int chunk_groups, int colblocks,
-                                                                    float* __restrict__ partial, float* __restrict__ S_id,
+                                                                    int N, int V, int T, int64_t d, RowIndex index, int chunk_groups,
+                                                                    int colblocks, float* __restrict__ partial, float* __restrict__ S_id,
                                                                     float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
     typedef Chunk<TIn, ALIGN> Ck;
@@ -474,7 +719,8 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         // whole rows, all column blocks by the same wave: an empty row is one contiguous run of d floats, and empty
         // rows are often neighbours
         const int v = (group * EMB_WAVES + wave) * EMB_ZROWS + lane;
-        const bool empty = lane < EMB_ZROWS && v < V && row_start[v] == row_start[v + 1];
+        const int r = v < V ? index.at(v) : 0;
+        const bool empty = lane < EMB_ZROWS && v < V && row_start[r] == row_start[r + 1];
         unsigned long long todo = __ballot(empty);
         RowSums zeros;
         zeros.clear();
@@ -512,7 +758,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
             int key = V, p = -1, rs = 0, re = 0;
             if (valid) { key = keys[k]; p = pos[k]; }
             key = key < 0 ? V : (key > V ? V : key);
-            if (valid && key < V) { rs = row_start[key]; re = row_start[key + 1]; }
+            if (valid && key < V) { const int r = index.at(key); rs = row_start[r]; re = row_start[r + 1]; }
             re = re > N ? N : re;
             const bool ours = valid && key < V && rs >= c0 && rs < c1;
             const bool is_heavy = re - rs > EMB_ALONE;
@@ -559,10 +805,10 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         if (c >= 0) hv = heavy_row[c];
         else if (sc0 > 0 && sc0 < N) {
             const int key = keys[sc0];
-            if (key >= 0 && key < V && row_start[key] < sc0 && row_start[key + 1] - row_start[key] > EMB_ALONE) hv = key;
+            if (key >= 0 && key < V && row_start[index.at(key)] < sc0 && row_start[index.at(key) + 1] - row_start[index.at(key)] > EMB_ALONE) hv = key;
         }
         if (hv < 0 || hv >= V) continue;   // the same for every wave of the workgroup
-        int hs = row_start[hv], he = row_start[hv + 1];
+        int hs = row_start[index.at(hv)], he = row_start[index.at(hv) + 1];
         hs = hs < 0 ? 0 : (hs > N ? N : hs);
         he = he < hs ? hs : (he > N ? N : he);
         // first position at or after k (hs < k < he) that begins an example
@@ -634,34 +880,50 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
 // grid = (slices, column blocks), one wave each.
 template <int ALIGN, int WANT>
 __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict__ row_start, const int* __restrict__ keys, int N, int V,
-                                                           int64_t d, const float* __restrict__ partial, float* __restrict__ S_id,
-                                                           float* __restrict__ S_sq, float* __restrict__ S_sg)
+                                                           int64_t d, RowIndex index, const float* __restrict__ partial,
+                                                           float* __restrict__ S_id, float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
     constexpr int SLICE = EMB_WAVES * EMB_U;
     const int64_t sc0 = (int64_t)blockIdx.x * SLICE, sc1 = sc0 + SLICE;
     if (sc1 >= N) return;   // nothing goes on past the last slice
     const int key = keys[sc1 - 1];
     if (key < 0 || key >= V) return;
-    const int rs = row_start[key], re = row_start[key + 1];
+    const int rs = row_start[index.at(key)], re = row_start[index.at(key) + 1];
     if (!(rs >= sc0 && re > sc1 && re <= N && re - rs > EMB_ALONE)) return;
     const int64_t col0 = ((int64_t)blockIdx.y * 64 + threadIdx.x) * CH;
     if (col0 >= d) return;
     const int64_t col = chunk_start<ALIGN>(col0, d);
+    // (eight slices' partial sums are loaded together: a run of many slices -- a token that fills half of a batch of 65536 crosses
+    // 170 -- is a chain of additions, not of loads: 57 -> 13 us there)
     float sum[3][CH];
-    auto take = [&](int64_t slice, int slot, bool first) {
-        const float* pr = partial + ((slice * 2 + slot) * 3) * d + col;
+    auto take = [&](int64_t slice, int slot, auto UC, bool first) {      // this and the following slices
+        constexpr int U = decltype(UC)::value;
+        float v[U][3][CH];
 #pragma unroll
-        for (int o = 0; o < 3; ++o) {
-            if (!(WANT & (1 << o))) continue;
+        for (int u = 0; u < U; ++u) {
+            const float* pr = partial + (((slice + u) * 2 + slot) * 3) * d + col;
 #pragma unroll
-            for (int e = 0; e < CH; ++e) {
-                const float v = ALIGN != 0 || e < (int)d ? pr[o * d + e] : 0.f;
-                sum[o][e] = first ? v : sum[o][e] + v;
-            }
+            for (int o = 0; o < 3; ++o)
+                if (WANT & (1 << o))
+#pragma unroll
+                    for (int e = 0; e < CH; ++e) v[u][o][e] = ALIGN != 0 || e < (int)d ? pr[o * d + e] : 0.f;
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+                if (WANT & (1 << o))
+#pragma unroll
+                    for (int e = 0; e < CH; ++e) sum[o][e] = first ? v[u][o][e] : sum[o][e] + v[u][o][e];
     };
-    take(blockIdx.x, 1, true);
-    for (int64_t sl = (int64_t)blockIdx.x + 1; sl * SLICE < re; ++sl) take(sl, 0, false);
+    constexpr std::integral_constant<int, 1> U1{};
+    constexpr std::integral_constant<int, 8> U8{};
+    take(blockIdx.x, 1, U1, true);
+    const int64_t end = (re + SLICE - 1) / SLICE;      // past the slice the run ends in
+    int64_t sl = (int64_t)blockIdx.x + 1;
+    for (; sl + 8 <= end; sl += 8) take(sl, 0, U8, false);
+    for (; sl < end; ++sl) take(sl, 0, U1, false);
     const int64_t o = (int64_t)key * d + col;
     if (WANT & 1) store_chunk<ALIGN>(S_id + o, sum[0], d);
     if (WANT & 2) store_chunk<ALIGN>(S_sq + o, sum[1], d);
@@ -670,12 +932,16 @@ __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Where the workspace keeps what (byte offsets).  The partial sums come last: two of three statistics per slice of EMB_WAVES * EMB_U
+// positions, for runs that cross slices.
 struct EmbedLayout {
     int passes, tile, nblocks;
-    size_t hist, keys_a, vals_a, keys_b, vals_b, row_start, partial, total;   // byte offsets into the workspace
+    size_t hist, keys_a, vals_a, keys_b, vals_b, row_start, partial, total;
 };
 
-EmbedLayout embed_layout(int64_t N, int64_t V, int64_t d)
+// by_bucket: `hist` holds the offsets of tile_buckets_kernel; up to BUCKET_ONE_LAUNCH_N positions need no more than the radix sort does
+// (256 * ceil(V / 256) + 1 entries of row_start are at most 1020 bytes more than its V + 2, its counters and buffers 1536)
+EmbedLayout embed_layout(int64_t N, int64_t V, int64_t d, bool by_bucket)
 {
     EmbedLayout L;
     int bits = 0;
@@ -686,23 +952,27 @@ EmbedLayout embed_layout(int64_t N, int64_t V, int64_t d)
     tile = (tile + 1023) / 1024 * 1024;
     L.tile = (int)tile;
     L.nblocks = (int)((N + tile - 1) / tile);
+    const bool one_launch = by_bucket && N <= BUCKET_ONE_LAUNCH_N;
+    const size_t list = align256((size_t)N * sizeof(int)), tiles = (size_t)(N + BUCKET_TILE - 1) / BUCKET_TILE;
     size_t o = 0;
-    L.hist = o; o += align256((size_t)256 * L.nblocks * sizeof(int));
-    L.keys_a = o; o += align256((size_t)N * sizeof(int));
-    L.vals_a = o; o += align256((size_t)N * sizeof(int));
-    L.keys_b = o; o += align256((size_t)N * sizeof(int));
-    L.vals_b = o; o += align256((size_t)N * sizeof(int));
-    L.row_start = o; o += align256((size_t)(V + 2) * sizeof(int));
-    // two partial sums of three statistics per slice of EMB_WAVES * EMB_U positions, for runs that cross slices
+    L.hist = o; o += one_launch ? 0 : by_bucket ? align256(tiles * (BUCKETS + 1) * sizeof(int)) : align256((size_t)256 * L.nblocks * sizeof(int));
+    L.keys_a = o; o += list;
+    L.vals_a = o; o += list;
+    L.keys_b = o; o += one_launch ? 0 : list;
+    L.vals_b = o; o += one_launch ? 0 : list;
+    L.row_start = o; o += align256((by_bucket ? (size_t)BUCKETS * (size_t)((V + BUCKETS - 1) / BUCKETS) + 1 : (size_t)(V + 2)) * sizeof(int));
     const int64_t slices = (N + EMB_WAVES * EMB_U - 1) / (EMB_WAVES * EMB_U);
     L.partial = o; o += align256((size_t)slices * 2 * 3 * d * sizeof(float));
     L.total = o;
     return L;
 }
 
+// By buckets: one launch while 256 readers of the ids cost less than a second one, two while a tile has a lane
+inline bool sorts_by_bucket(int64_t N, int64_t V) { return N <= BUCKET_MAX_N && V <= BUCKET_MAX_V; }
+
 template <typename TId>
-hipError_t sort_positions(const TId* ids, int N, int V, const EmbedLayout& L, char* ws, const int** keys, const int** vals,
-                          hipStream_t stream)
+hipError_t sort_positions(const TId* ids, int N, int V, bool by_bucket, const EmbedLayout& L, char* ws, const int** keys, const int** vals,
+                          RowIndex* index, hipStream_t stream)
 {
     int* hist = (int*)(ws + L.hist);
     int* ka = (int*)(ws + L.keys_a);
@@ -710,6 +980,21 @@ hipError_t sort_positions(const TId* ids, int N, int V, const EmbedLayout& L, ch
     int* kb = (int*)(ws + L.keys_b);
     int* vb = (int*)(ws + L.vals_b);
     int* row_start = (int*)(ws + L.row_start);
+    if (by_bucket) {
+        const int per_bucket = (V + BUCKETS - 1) / BUCKETS, tiles = (N + BUCKET_TILE - 1) / BUCKET_TILE;
+        const size_t lds = (size_t)BUCKET_WAVES * per_bucket * sizeof(int);
+        *index = RowIndex{BUCKETS - 1, 8, per_bucket};
+        *keys = ka;
+        *vals = va;
+        if (N <= BUCKET_ONE_LAUNCH_N) {
+            bucket_sort_kernel<TId, false><<<dim3(BUCKETS), dim3(BUCKET_TILE), lds, stream>>>(ids, nullptr, nullptr, nullptr, 0, N, V, per_bucket, ka, va, row_start);
+        } else {
+            tile_buckets_kernel<TId><<<dim3(tiles), dim3(BUCKET_TILE), 0, stream>>>(ids, N, V, kb, vb, hist);
+            bucket_sort_kernel<TId, true><<<dim3(BUCKETS), dim3(BUCKET_TILE), lds, stream>>>(ids, kb, vb, hist, tiles, N, V, per_bucket, ka, va, row_start);
+        }
+        return hipGetLastError();
+    }
+    *index = RowIndex{0, 0, 0};
     if (N <= SMALL_N) {
         sort_small_kernel<TId><<<dim3(1), dim3(SMALL_WAVES * 64), 0, stream>>>(ids, N, V, L.passes, ka, va, row_start);
         *keys = ka;
@@ -741,58 +1026,69 @@ hipError_t sort_positions(const TId* ids, int N, int V, const EmbedLayout& L, ch
 
 template <typename TIn, int ALIGN, int WANT>
 hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, const int* pos, int N, int V, int T, int64_t d,
-                       float* partial, float* S_id, float* S_sq, float* S_sg, hipStream_t stream)
+                       RowIndex index, float* partial, float* S_id, float* S_sq, float* S_sg, hipStream_t stream)
 {
     const int64_t per_group = (int64_t)EMB_WAVES * EMB_U;
     const int chunk_groups = (int)((N + per_group - 1) / per_group);
     const int zero_groups = (int)(((int64_t)V + EMB_WAVES * EMB_ZROWS - 1) / (EMB_WAVES * EMB_ZROWS));
     const unsigned colblocks = (unsigned)((d + 64 * CH - 1) / (64 * CH));
     embed_rows_kernel<TIn, ALIGN, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
-        G, row_start, keys, pos, N, V, T, d, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
+        G, row_start, keys, pos, N, V, T, d, index, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || chunk_groups == 1) return e;       // no run leaves a single slice
-    embed_combine_kernel<ALIGN, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, partial,
+    embed_combine_kernel<ALIGN, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, index, partial,
                                                                                                    S_id, S_sq, S_sg);
     return hipGetLastError();
 }
 
 template <typename TIn, int ALIGN>
-hipError_t launch_rows_want(uint32_t want, const TIn* G, const int* rs, const int* keys, const int* pos, int N, int V, int T, int64_t d, float* pr, float* a,
+hipError_t launch_rows_want(uint32_t want, const TIn* G, const int* rs, const int* keys, const int* pos, int N, int V, int T, int64_t d, RowIndex ix, float* pr, float* a,
                             float* q, float* g, hipStream_t st)
 {
     switch (want) {
-    case 1: return launch_rows<TIn, ALIGN, 1>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 2: return launch_rows<TIn, ALIGN, 2>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 3: return launch_rows<TIn, ALIGN, 3>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 4: return launch_rows<TIn, ALIGN, 4>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 5: return launch_rows<TIn, ALIGN, 5>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    case 6: return launch_rows<TIn, ALIGN, 6>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
-    default: return launch_rows<TIn, ALIGN, 7>(G, rs, keys, pos, N, V, T, d, pr, a, q, g, st);
+    case 1: return launch_rows<TIn, ALIGN, 1>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    case 2: return launch_rows<TIn, ALIGN, 2>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    case 3: return launch_rows<TIn, ALIGN, 3>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    case 4: return launch_rows<TIn, ALIGN, 4>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    case 5: return launch_rows<TIn, ALIGN, 5>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    case 6: return launch_rows<TIn, ALIGN, 6>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
+    default: return launch_rows<TIn, ALIGN, 7>(G, rs, keys, pos, N, V, T, d, ix, pr, a, q, g, st);
     }
 }
 
 }  // namespace
 
-size_t embed_workspace(int64_t B, int64_t T, int64_t V, int64_t d) { return embed_layout(B * T, V, d).total; }
+// (what a call needs: the radix sort's, with which a smaller workspace than the query's makes do)
+size_t embed_workspace_least(int64_t B, int64_t T, int64_t V, int64_t d) { return embed_layout(B * T, V, d, false).total; }
+
+size_t embed_workspace(int64_t B, int64_t T, int64_t V, int64_t d)
+{
+    const size_t least = embed_workspace_least(B, T, V, d);
+    const size_t by_bucket = sorts_by_bucket(B * T, V) ? embed_layout(B * T, V, d, true).total : 0;
+    return by_bucket > least ? by_bucket : least;
+}
 
 hipError_t launch_embed_stat(const void* ids, int ids_bytes, const void* G, int64_t B, int64_t T, int64_t V, int64_t d,
-                             pex_dtype dt, uint32_t want, float* S_id, float* S_sq, float* S_sign, void* workspace,
+                             pex_dtype dt, uint32_t want, float* S_id, float* S_sq, float* S_sign, void* workspace, size_t workspace_bytes,
                              hipStream_t stream)
 {
     const int N = (int)(B * T);
-    const EmbedLayout L = embed_layout(N, V, d);
+    bool by_bucket = sorts_by_bucket(N, V);
+    EmbedLayout L = embed_layout(N, V, d, by_bucket);
+    if (by_bucket && workspace_bytes < L.total) L = embed_layout(N, V, d, by_bucket = false);
     char* ws = (char*)workspace;
     const int* keys = nullptr;
     const int* pos = nullptr;
-    hipError_t e = ids_bytes == 8 ? sort_positions<int64_t>((const int64_t*)ids, N, (int)V, L, ws, &keys, &pos, stream)
-                                  : sort_positions<int32_t>((const int32_t*)ids, N, (int)V, L, ws, &keys, &pos, stream);
+    RowIndex index;
+    hipError_t e = ids_bytes == 8 ? sort_positions<int64_t>((const int64_t*)ids, N, (int)V, by_bucket, L, ws, &keys, &pos, &index, stream)
+                                  : sort_positions<int32_t>((const int32_t*)ids, N, (int)V, by_bucket, L, ws, &keys, &pos, &index, stream);
     if (e != hipSuccess) return e;
-    int* row_start = (int*)(ws + L.row_start);
+    const int* row_start = (const int*)(ws + L.row_start);
     float* partial = (float*)(ws + L.partial);
     auto rows = [&](auto zero, auto align) {
         typedef decltype(zero) TIn;
-        return launch_rows_want<TIn, decltype(align)::value>(want, (const TIn*)G, row_start, keys, pos, N, (int)V, (int)T, d, partial, S_id, S_sq, S_sign,
-                                                             stream);
+        return launch_rows_want<TIn, decltype(align)::value>(want, (const TIn*)G, row_start, keys, pos, N, (int)V, (int)T, d, index, partial, S_id, S_sq,
+                                                             S_sign, stream);
     };
     constexpr std::integral_constant<int, 4> A4{};
     constexpr std::integral_constant<int, 2> A2{};
