@@ -348,6 +348,41 @@ pex_status pex_moment_track(float *ema_adam, float *ema_micro, const float *S_id
                             size_t workspace_bytes, pex_stream_t stream);
 
 /*
+ * pex_vec_stat_batch -- pex_vec_stat of several vectors of one batch (same B, T and type) together: the same results in one launch
+ * of each pass, where a vector of a few thousand columns is mostly the cost of its launches.  items: host array; C is NULL for
+ * an offset; outputs not in `want` are ignored.  Vectors whose partial sums do not fit the workspace together are done one
+ * group after the other; the query returns what holds all, the largest vector's own pex_vec_stat workspace (rounded up to 256
+ * bytes) is enough.  Checks and error codes as pex_vec_stat, for every item before anything is launched.
+ */
+typedef struct {
+    const void *A, *C;
+    float *s_id, *s_sq, *s_sign;
+    int64_t d;
+} pex_vec_item;
+size_t pex_vec_stat_batch_workspace_bytes(const pex_vec_item *items, int32_t count, int64_t B, int64_t T, pex_dtype dt);
+pex_status pex_vec_stat_batch(const pex_vec_item *items, int32_t count, int64_t B, int64_t T, pex_dtype dt, uint32_t want,
+                              void *workspace, size_t workspace_bytes, pex_stream_t stream);
+
+/*
+ * pex_adam_step -- the end of a training step over all tensors of a model, in three or four launches:
+ *   *sum_sq = sum of S_id^2 over all tensors (fp64, fixed order), then for every tensor pex_adam_update_clipped with it and, if
+ *   `track` is given, pex_moment_track with its two EMAs and sums[2k], sums[2k + 1] for tensor k.
+ * S_id and S_sq are read once for both.  tensors: host array of `count` entries (ema_adam, ema_micro: NULL without `track`; S_sq may be
+ * NULL for PEX_ADAM without `track`); sum_sq: one double, sums: 2 * count doubles, device memory.  Alignments, limits and error
+ * codes as the single calls, checked for every tensor before anything is launched.
+ */
+typedef struct {
+    float *theta, *m, *v;
+    const float *S_id, *S_sq;
+    float *ema_adam, *ema_micro;
+    int64_t n;
+} pex_step_tensor;
+size_t pex_adam_step_workspace_bytes(const pex_step_tensor *tensors, int32_t count);
+pex_status pex_adam_step(const pex_step_tensor *tensors, int32_t count, pex_adam_variant variant, const pex_adam_params *p /* host */,
+                         const pex_moment_params *track /* host or NULL */, float max_norm, double *sum_sq, double *sums,
+                         void *workspace, size_t workspace_bytes, pex_stream_t stream);
+
+/*
  * pex_embed_stat -- per-example gradient statistics of an embedding table E[V, d].  A lookup is a dense layer on
  * one-hot inputs (Sec. 2.3 with X one-hot): row v of the per-example gradient M_b is the sum of G[b,t,:] over the
  * positions t of example b with ids[b,t] == v, and S = sum_b phi(M_b) with phi as in pex_stat (sgn(0) = 0).

@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from array import array as _array
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpex.so")
@@ -37,7 +38,8 @@ EXPORTS = ("pex_status_string", "pex_version", "pex_stat_workspace_bytes", "pex_
            "pex_token_sq_workspace_bytes", "pex_token_sq", "pex_adam_update", "pex_signsgd_update",
            "pex_moment_track_workspace_bytes", "pex_moment_track", "pex_embed_stat_workspace_bytes", "pex_embed_stat",
            "pex_mfma_probe_operand_bytes", "pex_mfma_probe_sink_floats", "pex_mfma_probe",
-           "pex_sum_squares_workspace_bytes", "pex_sum_squares", "pex_adam_update_clipped", "pex_stat_noalloc", "pex_set_option", "pex_get_option", "pex_clip_weights")
+           "pex_sum_squares_workspace_bytes", "pex_sum_squares", "pex_adam_update_clipped", "pex_stat_noalloc", "pex_set_option", "pex_get_option", "pex_clip_weights",
+           "pex_vec_stat_batch_workspace_bytes", "pex_vec_stat_batch", "pex_adam_step_workspace_bytes", "pex_adam_step")
 
 
 class PexError(RuntimeError):
@@ -136,6 +138,14 @@ def lib() -> ctypes.CDLL:
         L.pex_sum_squares.restype = ctypes.c_int
         L.pex_adam_update_clipped.argtypes = [p, p, p, p, p, i64, ctypes.c_int, ctypes.POINTER(AdamParams), p, f, p]
         L.pex_adam_update_clipped.restype = ctypes.c_int
+        L.pex_vec_stat_batch_workspace_bytes.argtypes = [p, i32, i64, i64, ctypes.c_int]
+        L.pex_vec_stat_batch_workspace_bytes.restype = sz
+        L.pex_vec_stat_batch.argtypes = [p, i32, i64, i64, ctypes.c_int, ctypes.c_uint32, p, sz, p]
+        L.pex_vec_stat_batch.restype = ctypes.c_int
+        L.pex_adam_step_workspace_bytes.argtypes = [p, i32]
+        L.pex_adam_step_workspace_bytes.restype = sz
+        L.pex_adam_step.argtypes = [p, i32, ctypes.c_int, ctypes.POINTER(AdamParams), ctypes.POINTER(MomentParams), f, p, p, p, sz, p]
+        L.pex_adam_step.restype = ctypes.c_int
         _lib = L
     return _lib
 
@@ -430,6 +440,59 @@ def pex_vec_stat(A, C=None, want=("identity", "square", "sign"), out=None, works
     return res
 
 
+def _table(rows):
+    """Host array of structures of 64-bit members for a call that takes several tensors: (array to keep alive, address).  The
+    first tensor that is not on the GPU raises here, after the caller's checks of all of them."""
+    for r in rows:
+        if r.__class__ is _NotOnGpu:
+            raise ValueError(f"{r.name} must live in GPU memory (libpex has no CPU path)")
+    a = _array("q", rows)
+    return a, a.buffer_info()[0]
+
+
+def pex_vec_stat_batch_workspace_bytes(widths, B, T, dtype_code) -> int:
+    """For vectors of ``widths`` columns."""
+    a, at = _table([x for d in widths for x in (0, 0, 0, 0, 0, d)])
+    return int(lib().pex_vec_stat_batch_workspace_bytes(at, len(widths), B, T, dtype_code))
+
+
+def pex_vec_stat_batch(items, want=("identity", "square", "sign"), workspace=None, stream=None):
+    """pex_vec_stat of several vectors of one batch in one launch of each pass: ``items`` are (A, C or None, out dict or None) with
+    the same B, T and type.  Returns a list of dicts name -> s[d] fp32."""
+    if _torch is None:
+        _bind_torch()
+    mask = _want_mask(want)
+    A0 = items[0][0]
+    res, rows, widths = [], [], []
+    for A, C, out in items:
+        if A.dim() != 3 or A.shape[:2] != A0.shape[:2] or (C is not None and C.shape != A.shape):
+            raise ValueError("expected A[B,T,d] of one batch and C of the same shape (or None)")
+        if A.dtype != A0.dtype or (C is not None and C.dtype != A.dtype):
+            raise TypeError("A and C of all vectors must share a dtype")
+        d = A.shape[2]
+        rows.append(_dev(A, "A"))
+        rows.append(_dev(C, "C") if C is not None else 0)
+        r = {}
+        for name, bit in WANT.items():
+            if mask & bit:
+                s = (out or {}).get(name)
+                if s is None:
+                    s = _torch.empty(d, dtype=_F32, device=A.device)
+                r[name] = s
+                rows.append(_f32(s, name, numel=d))
+            else:
+                rows.append(0)
+        rows.append(d)
+        widths.append(d)
+        res.append(r)
+    B, T, dt = A0.shape[0], A0.shape[1], _dtype_code(A0)
+    keep, at = _table(rows)
+    query, qargs = pex_vec_stat_batch_workspace_bytes, (widths, B, T, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, A0, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_vec_stat_batch, at, len(items), B, T, dt, mask, wptr, wbytes, _stream(stream))
+    return res
+
+
 def pex_example_norms_workspace_bytes(B, T, din, dout, dtype_code) -> int:
     return int(lib().pex_example_norms_workspace_bytes(B, T, din, dout, dtype_code))
 
@@ -661,3 +724,47 @@ def pex_adam_update_clipped(theta, m, v, S_id, S_sq, variant, params: AdamParams
     _invoke(lib().pex_adam_update_clipped, _f32(theta, "theta"), _f32(m, "m", n), _f32(v, "v", n), _f32(S_id, "S_id", n),
                                          _f32(S_sq, "S_sq", n) if S_sq is not None else None, n, code, ctypes.byref(params),
                                          _f64(sum_sq, "sum_sq", 1), float(max_norm), _stream(stream))
+
+
+def pex_adam_step_workspace_bytes(sizes) -> int:
+    """For tensors of ``sizes`` elements."""
+    a, at = _table([x for n in sizes for x in (0, 0, 0, 0, 0, 0, 0, n)])
+    return int(lib().pex_adam_step_workspace_bytes(at, len(sizes)))
+
+
+_STEP_NAMES = ("theta", "m", "v", "S_id", "S_sq", "ema_adam", "ema_micro")
+
+
+def pex_adam_step(tensors, variant, params: AdamParams, sum_sq, max_norm, moments: MomentParams = None, sums=None, workspace=None, stream=None):
+    """The end of a step over all tensors of a model in a few launches: ``sum_sq`` = sum of S_id^2 over them, the clipped update of
+    each (pex_adam_update_clipped) and, with ``moments``, the moment tracking of each into ``sums`` [len(tensors), 2] (float64;
+    pex_moment_track).  ``tensors`` are tuples (theta, m, v, S_id, S_sq) or, with ``moments``, (.., ema_adam, ema_micro)."""
+    if _torch is None:
+        _bind_torch()
+    width = 5 if moments is None else 7
+    F32, rows, sizes = _F32, [], []
+    for tensor in tensors:
+        if len(tensor) < width:
+            raise ValueError(f"expected {width} tensors per parameter, got {len(tensor)}")
+        n = tensor[0].numel()
+        for t, name in zip(tensor[:width], _STEP_NAMES):
+            if t is None:
+                rows.append(0)
+            elif t.dtype is F32 and t.is_cuda and t.numel() == n and t.is_contiguous():
+                rows.append(t.data_ptr())
+            else:
+                rows.append(_f32(t, name, n))
+        if width == 5:
+            rows += (0, 0)
+        rows.append(n)
+        sizes.append(n)
+    if moments is not None and sums is None:
+        sums = _torch.empty(len(sizes), 2, dtype=_F64, device=sum_sq.device)
+    sums_at = _f64(sums, "sums", 2 * len(sizes)) if moments is not None else None
+    keep, at = _table(rows)
+    query, qargs = pex_adam_step_workspace_bytes, (sizes,)
+    ws, wptr, wbytes = _workspace(query, qargs, tensors[0][0], workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_adam_step, at, len(sizes), VARIANT.get(variant, variant), ctypes.byref(params),
+               ctypes.byref(moments) if moments is not None else None, float(max_norm), _f64(sum_sq, "sum_sq", 1), sums_at, wptr, wbytes,
+               _stream(stream))
+    return sums

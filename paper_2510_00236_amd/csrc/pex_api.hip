@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
+#include <vector>
 
 #include "pex_internal.h"
 
@@ -555,6 +556,25 @@ static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64
     return PEX_OK;
 }
 
+static pex_status check_vec_args(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, uint32_t want, float* s_id,
+                                 float* s_sq, float* s_sign)
+{
+    if (!A) return PEX_ERR_NULL;
+    if (want == 0 || (want & ~7u)) return PEX_ERR_PHI;
+    float* outs[3] = {(want & PEX_WANT_IDENTITY) ? s_id : nullptr, (want & PEX_WANT_SQUARE) ? s_sq : nullptr,
+                      (want & PEX_WANT_SIGN) ? s_sign : nullptr};
+    for (int phi = 0; phi < 3; ++phi)
+        if ((want & (1u << phi)) && !outs[phi]) return PEX_ERR_NULL;
+    if (dt != PEX_F32 && dt != PEX_BF16) return PEX_ERR_DTYPE;
+    const int64_t lim = (int64_t)1 << 31;
+    if (B < 1 || T < 1 || d < 1 || B >= lim || T >= lim || d >= lim || B * T >= lim) return PEX_ERR_SHAPE;
+    const uintptr_t esz = dt == PEX_BF16 ? 2 : 4;
+    if (((uintptr_t)A | (uintptr_t)C) & (esz - 1)) return PEX_ERR_ALIGN;
+    if (((uintptr_t)outs[0] | (uintptr_t)outs[1] | (uintptr_t)outs[2]) & 3u) return PEX_ERR_ALIGN;
+    if (B * plan_vec_stat(B, T, d, dt).nrange >= 65536) return PEX_ERR_SHAPE;      // grid limit of the second launch dimension
+    return PEX_OK;
+}
+
 // the partial sums of a plan without wide columns
 static hipError_t reduce_whole(const ReduceOutputs& io, int count, const StatPlan& plan, hipStream_t stream)
 {
@@ -843,26 +863,66 @@ pex_status pex_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int6
                         float* s_id, float* s_sq, float* s_sign, void* workspace, size_t workspace_bytes,
                         pex_stream_t stream)
 {
-    if (!A) return PEX_ERR_NULL;
-    if (want == 0 || (want & ~7u)) return PEX_ERR_PHI;
+    const pex_status st = check_vec_args(A, C, B, T, d, dt, want, s_id, s_sq, s_sign);
+    if (st != PEX_OK) return st;
     float* outs[3] = {(want & PEX_WANT_IDENTITY) ? s_id : nullptr, (want & PEX_WANT_SQUARE) ? s_sq : nullptr,
                       (want & PEX_WANT_SIGN) ? s_sign : nullptr};
-    for (int phi = 0; phi < 3; ++phi)
-        if ((want & (1u << phi)) && !outs[phi]) return PEX_ERR_NULL;
-    if (dt != PEX_F32 && dt != PEX_BF16) return PEX_ERR_DTYPE;
-    const int64_t lim = (int64_t)1 << 31;
-    if (B < 1 || T < 1 || d < 1 || B >= lim || T >= lim || d >= lim || B * T >= lim) return PEX_ERR_SHAPE;
-    const uintptr_t esz = dt == PEX_BF16 ? 2 : 4;
-    if (((uintptr_t)A | (uintptr_t)C) & (esz - 1)) return PEX_ERR_ALIGN;
-    if (((uintptr_t)outs[0] | (uintptr_t)outs[1] | (uintptr_t)outs[2]) & 3u) return PEX_ERR_ALIGN;
     const VecPlan plan = plan_vec_stat(B, T, d, dt);
-    if (B * plan.nrange >= 65536) return PEX_ERR_SHAPE;      // grid limit of the second launch dimension
     if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     return launch_vec_stat(A, C, B, T, d, dt, plan, (float*)workspace, outs[0], outs[1], outs[2], (hipStream_t)stream) ==
                    hipSuccess
                ? PEX_OK
                : PEX_ERR_HIP;
+}
+
+size_t pex_vec_stat_batch_workspace_bytes(const pex_vec_item* items, int32_t count, int64_t B, int64_t T, pex_dtype dt)
+{
+    if (!items || count < 1 || B < 1 || T < 1 || (dt != PEX_F32 && dt != PEX_BF16)) return 0;
+    size_t total = 0;
+    for (int k = 0; k < count; ++k) {
+        if (items[k].d < 1) return 0;
+        total += vec_batch_bytes(plan_vec_stat(B, T, items[k].d, dt));
+    }
+    return total;
+}
+
+pex_status pex_vec_stat_batch(const pex_vec_item* items, int32_t count, int64_t B, int64_t T, pex_dtype dt, uint32_t want, void* workspace,
+                              size_t workspace_bytes, pex_stream_t stream)
+{
+    if (!items) return PEX_ERR_NULL;
+    if (count < 1) return PEX_ERR_SHAPE;
+    for (int k = 0; k < count; ++k) {
+        const pex_vec_item& it = items[k];
+        const pex_status st = check_vec_args(it.A, it.C, B, T, it.d, dt, want, it.s_id, it.s_sq, it.s_sign);
+        if (st != PEX_OK) return st;
+        if (!workspace || workspace_bytes < vec_batch_bytes(plan_vec_stat(B, T, it.d, dt))) return PEX_ERR_WORKSPACE;
+    }
+    if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
+    for (int k = 0; k < count;) {
+        std::vector<pex_vec_item> group;
+        size_t bytes = 0;
+        int64_t blocks = 0;
+        for (; k < count && (int)group.size() < vec_batch_limit(); ++k) {
+            pex_vec_item it = items[k];
+            const VecPlan plan = plan_vec_stat(B, T, it.d, dt);
+            const int64_t own = (it.d + 63) / 64 * B * plan.nrange;       // at most: a launch holds fewer than 2^32 threads
+            if (!group.empty() && (bytes + vec_batch_bytes(plan) > workspace_bytes || blocks + own >= ((int64_t)1 << 23))) break;
+            bytes += vec_batch_bytes(plan);
+            blocks += own;
+            if (!(want & PEX_WANT_IDENTITY)) it.s_id = nullptr;
+            if (!(want & PEX_WANT_SQUARE)) it.s_sq = nullptr;
+            if (!(want & PEX_WANT_SIGN)) it.s_sign = nullptr;
+            group.push_back(it);
+        }
+        hipError_t e;
+        if (group.size() == 1) {       // alone: as pex_vec_stat, whose grid has two dimensions
+            const pex_vec_item& it = group[0];
+            e = launch_vec_stat(it.A, it.C, B, T, it.d, dt, plan_vec_stat(B, T, it.d, dt), (float*)workspace, it.s_id, it.s_sq, it.s_sign, (hipStream_t)stream);
+        } else e = launch_vec_stat_batch(group.data(), (int)group.size(), B, T, dt, workspace, (hipStream_t)stream);
+        if (e != hipSuccess) return PEX_ERR_HIP;
+    }
+    return PEX_OK;
 }
 
 size_t pex_example_norms_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt)
@@ -1049,6 +1109,40 @@ pex_status pex_adam_update_clipped(float* theta, float* m, float* v, const float
     if (((uintptr_t)theta | (uintptr_t)m | (uintptr_t)v | (uintptr_t)S_id | (uintptr_t)S_sq) & 15u) return PEX_ERR_ALIGN;
     if ((uintptr_t)sum_sq & 7u) return PEX_ERR_ALIGN;
     return launch_adam_update(theta, m, v, S_id, S_sq, n, variant, *p, (hipStream_t)stream, sum_sq, max_norm) == hipSuccess
+               ? PEX_OK
+               : PEX_ERR_HIP;
+}
+
+size_t pex_adam_step_workspace_bytes(const pex_step_tensor* tensors, int32_t count)
+{
+    if (!tensors || count < 1) return 0;
+    for (int k = 0; k < count; ++k)
+        if (tensors[k].n < 1) return 0;
+    return adam_step_workspace(tensors, count);
+}
+
+pex_status pex_adam_step(const pex_step_tensor* tensors, int32_t count, pex_adam_variant variant, const pex_adam_params* p,
+                         const pex_moment_params* track, float max_norm, double* sum_sq, double* sums, void* workspace, size_t workspace_bytes,
+                         pex_stream_t stream)
+{
+    if (!tensors || !p || !sum_sq || (track && !sums)) return PEX_ERR_NULL;
+    if (variant != PEX_ADAM && variant != PEX_MICROADAM && variant != PEX_MICROADAM_VAR && variant != PEX_MICROADAM_MSQ) return PEX_ERR_PHI;
+    if (count < 1 || p->step < 1 || p->B < 1 || !(max_norm > 0.f)) return PEX_ERR_SHAPE;
+    if ((variant == PEX_MICROADAM_VAR || variant == PEX_MICROADAM_MSQ) && p->B < 2) return PEX_ERR_SHAPE;
+    if (track && (track->step < 1 || track->B < 2)) return PEX_ERR_SHAPE;
+    for (int k = 0; k < count; ++k) {
+        const pex_step_tensor& t = tensors[k];
+        if (!t.theta || !t.m || !t.v || !t.S_id || ((variant != PEX_ADAM || track) && !t.S_sq)) return PEX_ERR_NULL;
+        if (track && (!t.ema_adam || !t.ema_micro)) return PEX_ERR_NULL;
+        if (t.n < 1 || t.n >= ((int64_t)1 << 40)) return PEX_ERR_SHAPE;
+        uintptr_t al = (uintptr_t)t.theta | (uintptr_t)t.m | (uintptr_t)t.v | (uintptr_t)t.S_id | (uintptr_t)t.S_sq;
+        if (track) al |= (uintptr_t)t.ema_adam | (uintptr_t)t.ema_micro;
+        if (al & 15u) return PEX_ERR_ALIGN;
+    }
+    if (((uintptr_t)sum_sq | (uintptr_t)sums) & 7u) return PEX_ERR_ALIGN;
+    if (!workspace || workspace_bytes < adam_step_workspace_least(count)) return PEX_ERR_WORKSPACE;
+    if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
+    return launch_adam_step(tensors, count, variant, *p, track, max_norm, sum_sq, sums, workspace, workspace_bytes, (hipStream_t)stream) == hipSuccess
                ? PEX_OK
                : PEX_ERR_HIP;
 }

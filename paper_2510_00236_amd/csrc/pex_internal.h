@@ -135,6 +135,12 @@ VecPlan plan_vec_stat(int64_t B, int64_t T, int64_t d, pex_dtype dt);
 hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, const VecPlan& plan,
                            float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream);
 
+// Several vectors of one batch and type together: at most vec_batch_limit() of them, each with vec_batch_bytes of its plan in
+// the workspace, one after the other (an output that is not wanted is NULL)
+int vec_batch_limit();
+inline size_t vec_batch_bytes(const VecPlan& plan) { return (plan.ws_bytes + 255) & ~(size_t)255; }
+hipError_t launch_vec_stat_batch(const pex_vec_item* items, int count, int64_t B, int64_t T, pex_dtype dt, void* workspace, hipStream_t stream);
+
 // For the first `count` entries: S[i * ld + j] = sum_{k < nsplit} partial[k * group_stride + i * pitch + j], k ascending (fixed
 // order => deterministic), i < rows, j < cols.  leading > 0: where the sum of the first `leading` groups is not finite, it is S.
 struct ReduceOutputs {
@@ -157,6 +163,12 @@ hipError_t launch_sign_update(float* theta, float* m, const float* S, int64_t n,
 size_t moment_track_workspace(int64_t n);
 hipError_t launch_moment_track(float* ema_adam, float* ema_micro, const float* S_id, const float* S_sq, int64_t n,
                                const pex_moment_params& p, double* sums, double* partial, hipStream_t stream);
+
+// The update of all tensors of a model (pex_adam_step): bytes of workspace for workgroups of the smallest chunk, and the least
+size_t adam_step_workspace(const pex_step_tensor* tensors, int count);
+size_t adam_step_workspace_least(int count);
+hipError_t launch_adam_step(const pex_step_tensor* tensors, int count, pex_adam_variant variant, const pex_adam_params& p, const pex_moment_params* track,
+                            float max_norm, double* sum_sq, double* sums, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 size_t embed_workspace(int64_t B, int64_t T, int64_t V, int64_t d);          // for the query
 size_t embed_workspace_least(int64_t B, int64_t T, int64_t V, int64_t d);    // what a call can do with

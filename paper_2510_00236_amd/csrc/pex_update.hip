@@ -3,57 +3,10 @@
 // bandwidth: Adam family 20 B read + 12 B written per parameter (16 + 12 for plain Adam, which never
 // touches S_sq), MicroSignSGD 12 B read + 8 B written.  16-byte accesses, grid-stride, scalar tail.
 #include "pex_internal.h"
+#include "pex_update.h"
 
 namespace pex {
 namespace {
-
-// 16-byte accesses, past the caches where STREAM: a tensor whose buffers exceed the memory-side cache evicts itself on every
-// pass (see `streams`)
-template <bool STREAM>
-__device__ __forceinline__ float4 load4(const float4* p)
-{
-    typedef __attribute__((ext_vector_type(4))) float f4;
-    if constexpr (STREAM) {
-        const f4 q = __builtin_nontemporal_load((const f4*)p);
-        return make_float4(q[0], q[1], q[2], q[3]);
-    } else return *p;
-}
-template <bool STREAM>
-__device__ __forceinline__ void store4(float4* p, const float4& v)
-{
-    typedef __attribute__((ext_vector_type(4))) float f4;
-    if constexpr (STREAM) __builtin_nontemporal_store(f4{v.x, v.y, v.z, v.w}, (f4*)p);
-    else *p = v;
-}
-
-struct AdamConsts {
-    float beta1, one_m_beta1, beta2, one_m_beta2;
-    float inv_bc1, inv_bc2;   // 1/(1-beta1^t), 1/(1-beta2^t)
-    float eps, eps_root, lr, wd, gs, qs;
-    float c_est, inv_B;       // 1/(1-1/B), 1/B
-};
-
-template <int VARIANT>
-__device__ __forceinline__ void adam_one(float& th, float& m, float& v, float sid, float ssq, const AdamConsts& k)
-{
-    const float mu_t = k.gs * sid;
-    const float nu_adam = mu_t * mu_t;
-    float nu_t;
-    if (VARIANT == PEX_ADAM) nu_t = nu_adam;
-    else {
-        const float nu_micro = k.qs * ssq;
-        if (VARIANT == PEX_MICROADAM) nu_t = nu_micro;
-        else if (VARIANT == PEX_MICROADAM_VAR) nu_t = k.c_est * (nu_micro - nu_adam);
-        else nu_t = k.c_est * (nu_adam - nu_micro * k.inv_B);
-    }
-    m = fmaf(k.beta1, m, k.one_m_beta1 * mu_t);
-    v = fmaf(k.beta2, v, k.one_m_beta2 * nu_t);
-    const float mh = m * k.inv_bc1;
-    float vh = v * k.inv_bc2;
-    if (VARIANT == PEX_MICROADAM_VAR || VARIANT == PEX_MICROADAM_MSQ) vh = fmaxf(0.f, vh);
-    const float u = mh / (sqrtf(vh + k.eps_root) + k.eps);
-    th = th - k.lr * u - k.wd * th;
-}
 
 // clip_sumsq != nullptr: gradient clipping by the global norm (Sec. 3.2.3, App. C).  *clip_sumsq is the sum of S_id^2
 // over all parameters of the model (device memory, written by sum_squares_kernel); every per-example gradient is
@@ -65,12 +18,7 @@ __global__ __launch_bounds__(256) void adam_update_kernel(float* __restrict__ th
                                                           const float* __restrict__ S_sq, int64_t n, AdamConsts k,
                                                           const double* __restrict__ clip_sumsq, float max_norm)
 {
-    if (clip_sumsq) {
-        const double norm = fabs((double)k.gs) * sqrt(*clip_sumsq);
-        const float kappa = norm > (double)max_norm ? (float)((double)max_norm / norm) : 1.0f;
-        k.gs *= kappa;
-        k.qs *= kappa * kappa;
-    }
+    if (clip_sumsq) clip(k, *clip_sumsq, max_norm);
     const int64_t n4 = n / 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -136,18 +84,6 @@ __global__ __launch_bounds__(256) void signsgd_update_kernel(float* __restrict__
 // parameters.  The EMAs are fp32 like the optimizer state; the estimators (differences of nearly equal numbers when
 // one moment dominates) and their sums are formed in fp64.  Each workgroup writes one pair of partial sums; the
 // second kernel adds the pairs in a fixed order, so the result does not depend on scheduling.
-struct MomentConsts {
-    float beta2, one_m_beta2, gs, qs;
-    double corr, c_est, inv_B;   // 1/(1-beta2^t) or 1, 1/(1-1/B), 1/B
-};
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 // ONE: a single workgroup of 1024 does the whole tensor and writes the two sums themselves
 template <bool STREAM, bool ONE>
 __global__ __launch_bounds__(ONE ? 1024 : 256) void moment_track_kernel(float* __restrict__ ema_adam, float* __restrict__ ema_micro,
@@ -162,14 +98,7 @@ __global__ __launch_bounds__(ONE ? 1024 : 256) void moment_track_kernel(float* _
     const float4* i4 = reinterpret_cast<const float4*>(S_id);
     const float4* s4 = reinterpret_cast<const float4*>(S_sq);
     double sum_mu2 = 0.0, sum_sigma2 = 0.0;
-    auto one = [&](float& a, float& q, float sid, float ssq) {
-        const float mu_t = k.gs * sid;
-        a = fmaf(k.beta2, a, k.one_m_beta2 * (mu_t * mu_t));
-        q = fmaf(k.beta2, q, k.one_m_beta2 * (k.qs * ssq));
-        const double ah = (double)a * k.corr, qh = (double)q * k.corr;
-        sum_mu2 += k.c_est * (ah - qh * k.inv_B);
-        sum_sigma2 += k.c_est * (qh - ah);
-    };
+    auto one = [&](float& a, float& q, float sid, float ssq) { moment_one(a, q, sid, ssq, k, sum_mu2, sum_sigma2); };
     for (int64_t e = gid; e < n4; e += stride) {
         float4 a = load4<STREAM>(a4 + e), q = load4<STREAM>(q4 + e);
         const float4 si = load4<STREAM>(i4 + e), ss = load4<STREAM>(s4 + e);
@@ -280,12 +209,6 @@ inline unsigned update_grid(int64_t n)
 }
 static_assert(256 * 32 <= 8 * 1024, "the finalizing kernels hold eight partials per lane");
 
-// Buffers of n floats that together exceed the 256 MB memory-side cache by so much that a pass evicts what the next one would have
-// found are accessed past the caches.  Measured on repeated passes (cached / streamed, us), Adam family on five buffers: 320 MiB
-// 84 / 93, 340 91 / 96, 360 104 / 104, 380 114 / 108, 500 159 / 144; on four buffers 360 118 / 113; sign updates 340 100 / 99; moment
-// tracking 340 86 / 92, 360 98 / 98, 400 117 / 108.
-inline bool streams(int64_t n, int buffers) { return n * buffers * 4 > (int64_t)360 << 20; }
-
 // Sums over at most this many values take one workgroup and one launch instead of two (a launch is about 3 us here)
 constexpr int64_t ONE_GROUP = 32768;
 
@@ -295,15 +218,7 @@ hipError_t launch_adam_update(float* theta, float* m, float* v, const float* S_i
                               pex_adam_variant variant, const pex_adam_params& p, hipStream_t stream, const double* clip_sumsq,
                               float max_norm)
 {
-    AdamConsts k;
-    k.beta1 = p.beta1; k.one_m_beta1 = 1.f - p.beta1;
-    k.beta2 = p.beta2; k.one_m_beta2 = 1.f - p.beta2;
-    k.inv_bc1 = (float)(1.0 / (1.0 - pow((double)p.beta1, (double)p.step)));
-    k.inv_bc2 = (float)(1.0 / (1.0 - pow((double)p.beta2, (double)p.step)));
-    k.eps = p.eps; k.eps_root = p.eps_root; k.lr = p.lr; k.wd = p.weight_decay;
-    k.gs = p.grad_scale; k.qs = p.sq_scale;
-    k.inv_B = 1.f / (float)p.B;
-    k.c_est = p.B > 1 ? (float)(1.0 / (1.0 - 1.0 / (double)p.B)) : 0.f;
+    const AdamConsts k = adam_consts(p);
     const dim3 grid(update_grid(n)), block(256);
     auto go = [&](auto cached, auto streamed) {
         (streams(n, variant == PEX_ADAM ? 4 : 5) ? streamed : cached)<<<grid, block, 0, stream>>>(theta, m, v, S_id, S_sq, n, k, clip_sumsq, max_norm);
@@ -361,12 +276,7 @@ size_t moment_track_workspace(int64_t n) { return (size_t)update_grid(n) * 2 * s
 hipError_t launch_moment_track(float* ema_adam, float* ema_micro, const float* S_id, const float* S_sq, int64_t n,
                                const pex_moment_params& p, double* sums, double* partial, hipStream_t stream)
 {
-    MomentConsts k;
-    k.beta2 = p.beta2; k.one_m_beta2 = 1.f - p.beta2;
-    k.gs = p.grad_scale; k.qs = p.sq_scale;
-    k.corr = p.debias ? 1.0 / (1.0 - pow((double)p.beta2, (double)p.step)) : 1.0;
-    k.inv_B = 1.0 / (double)p.B;
-    k.c_est = 1.0 / (1.0 - k.inv_B);
+    const MomentConsts k = moment_consts(p);
     if (n <= ONE_GROUP) {
         moment_track_kernel<false, true><<<dim3(1), dim3(1024), 0, stream>>>(ema_adam, ema_micro, S_id, S_sq, n, k, sums);
         return hipGetLastError();

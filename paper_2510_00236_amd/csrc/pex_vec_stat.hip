@@ -14,6 +14,8 @@
 //                        lanes of a block, combined in a fixed order).
 // The partial sums are B * ranges * d floats: the per-example gradients of a *vector* parameter, which is the one
 // place where holding them is cheap (B*d, not B*din*dout).
+#include <type_traits>
+
 #include "pex_internal.h"
 
 namespace pex {
@@ -48,15 +50,15 @@ __device__ __forceinline__ void load_vec(const TIn* p, float (&v)[VEC])
     }
 }
 
-// partial[(b * nrange + range) * d + j] = sum over the tokens of the range of A[b,t,j] * (HAS_C ? C[b,t,j] : 1)
+// partial[(b * nrange + range) * d + j] = sum over the tokens of the range of A[b,t,j] * (HAS_C ? C[b,t,j] : 1), for the columns
+// of block `colblock`; `row` = b * nrange + range
 template <typename TIn, int VEC, bool HAS_C>
-__global__ __launch_bounds__(CW * RW) void vec_partial_kernel(const TIn* __restrict__ A, const TIn* __restrict__ C, int T, int64_t d,
-                                                              int nrange, int rows_per_range, float* __restrict__ partial)
+__device__ __forceinline__ void partial_sums(const TIn* __restrict__ A, const TIn* __restrict__ C, int T, int64_t d, int nrange, int rows_per_range,
+                                             float* __restrict__ partial, int64_t colblock, int row, float (&red)[RW][CW][VEC])
 {
-    __shared__ float red[RW][CW][VEC];
     const int cl = threadIdx.x % CW, rl = threadIdx.x / CW;
-    const int64_t j = ((int64_t)blockIdx.x * CW + cl) * VEC;
-    const int b = blockIdx.y / nrange, range = blockIdx.y % nrange;
+    const int64_t j = (colblock * CW + cl) * VEC;
+    const int b = row / nrange, range = row % nrange;
     const int t0 = range * rows_per_range;
     const int t1 = (t0 + rows_per_range < T) ? t0 + rows_per_range : T;
     float acc[VEC];
@@ -95,6 +97,14 @@ __global__ __launch_bounds__(CW * RW) void vec_partial_kernel(const TIn* __restr
 #pragma unroll
         for (int e = 0; e < VEC; ++e) dst[e] = ((red[0][cl][e] + red[1][cl][e]) + red[2][cl][e]) + red[3][cl][e];
     }
+}
+
+template <typename TIn, int VEC, bool HAS_C>
+__global__ __launch_bounds__(CW * RW) void vec_partial_kernel(const TIn* __restrict__ A, const TIn* __restrict__ C, int T, int64_t d,
+                                                              int nrange, int rows_per_range, float* __restrict__ partial)
+{
+    __shared__ float red[RW][CW][VEC];
+    partial_sums<TIn, VEC, HAS_C>(A, C, T, d, nrange, rows_per_range, partial, blockIdx.x, blockIdx.y, red);
 }
 
 // Second pass: per column v_b = sum over the ranges, phi, sum over the examples, the partial sums fresh in the caches.
@@ -148,9 +158,8 @@ __global__ __launch_bounds__(CW * RW) void vec_finalize_wide_kernel(const float*
 // d=768 4.4 / 3.8, 32768 4.0 / 5.4; B=2 d=768 2.6 / 3.9, 50256 2.6 / 6.8; B=1 in 128 ranges d=768 7.5 / 4.1; B=3000 d=768 241 / 28;
 // B=2 d=4000001 28 / 810 (VEC = 1).
 template <int VEC, int EL, int RL>
-__global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
-                                                           float* __restrict__ s_id, float* __restrict__ s_sq,
-                                                           float* __restrict__ s_sign)
+__device__ __forceinline__ void finalize_columns(const float* __restrict__ partial, int B, int nrange, int64_t d, float* __restrict__ s_id,
+                                                 float* __restrict__ s_sq, float* __restrict__ s_sign, int64_t colblock)
 {
     static_assert(4 * EL * RL == 256, "one lane per column group, example lane and range lane");
     typedef __attribute__((ext_vector_type(4))) float f4;
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restri
     // first column of a column lane: the row's last chunk ends with the row (the columns it shares with its neighbour come out
     // the same twice)
     auto first_column = [&](int lane) {
-        const int64_t c = ((int64_t)blockIdx.x * 4 + lane) * VEC;
+        const int64_t c = (colblock * 4 + lane) * VEC;
         return c < d && c + VEC > d ? d - VEC : c;
     };
     const int64_t j = first_column(cl);
@@ -246,12 +255,70 @@ __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restri
     if (s_sign) finish(s_sign, a_sg);
 }
 
+template <int VEC, int EL, int RL>
+__global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restrict__ partial, int B, int nrange, int64_t d,
+                                                           float* __restrict__ s_id, float* __restrict__ s_sq,
+                                                           float* __restrict__ s_sign)
+{
+    finalize_columns<VEC, EL, RL>(partial, B, nrange, d, s_id, s_sq, s_sign, blockIdx.x);
+}
+
+// Several vectors of one batch in one launch of each pass: the offsets and scales of a layer are a few thousand columns each, and a
+// launch costs about 4.5 us whatever it does.  The same blocks as one vector's launches, one vector after the other.
+constexpr int BATCH = 16;
+struct VecBatch {
+    int count;
+    unsigned first[BATCH + 1];       // first block of each vector
+    const void *A[BATCH], *C[BATCH];
+    float *partial[BATCH], *s_id[BATCH], *s_sq[BATCH], *s_sign[BATCH];
+    int64_t d[BATCH];
+    int nrange[BATCH], rows_per_range[BATCH], colblocks[BATCH], wide[BATCH];
+    __device__ __forceinline__ int of_block(unsigned b) const
+    {
+        int k = 0;
+        while (k + 1 < count && b >= first[k + 1]) ++k;
+        return k;
+    }
+};
+
+template <typename TIn>
+__global__ __launch_bounds__(CW * RW) void vec_partial_batch_kernel(VecBatch v, int T)
+{
+    constexpr int V = VecOf<TIn>::N;
+    __shared__ float red[RW][CW][V];
+    const int k = v.of_block(blockIdx.x), local = (int)(blockIdx.x - v.first[k]), cb = local % v.colblocks[k], row = local / v.colblocks[k];
+    const TIn *A = (const TIn*)v.A[k], *C = (const TIn*)v.C[k];
+    auto go = [&](auto vec, auto has_c) {
+        constexpr int VEC = decltype(vec)::value;
+        partial_sums<TIn, VEC, decltype(has_c)::value>(A, C, T, v.d[k], v.nrange[k], v.rows_per_range[k], v.partial[k], cb, row,
+                                                       reinterpret_cast<float (&)[RW][CW][VEC]>(red));
+    };
+    constexpr std::integral_constant<int, V> wide{};
+    constexpr std::integral_constant<int, 1> one{};
+    if (v.wide[k]) C ? go(wide, std::true_type{}) : go(wide, std::false_type{});
+    else C ? go(one, std::true_type{}) : go(one, std::false_type{});
+}
+
+template <int EL, int RL>
+__global__ __launch_bounds__(256) void vec_finalize_batch_kernel(VecBatch v, int B)
+{
+    const int k = v.of_block(blockIdx.x);
+    finalize_columns<4, EL, RL>(v.partial[k], B, v.nrange[k], v.d[k], v.s_id[k], v.s_sq[k], v.s_sign[k], blockIdx.x - v.first[k]);
+}
+
+// a dwordx4 load takes whole 16-byte chunks of rows here
+template <typename TIn>
+bool whole_chunks(const void* A, const void* C, int64_t d)
+{
+    return d % VecOf<TIn>::N == 0 && ((((uintptr_t)A | (uintptr_t)C) & 15u) == 0);
+}
+
 template <typename TIn>
 hipError_t launch_typed(const TIn* A, const TIn* C, int64_t B, int64_t T, int64_t d, const VecPlan& plan, float* partial,
                         hipStream_t stream)
 {
     constexpr int V = VecOf<TIn>::N;
-    const bool wide = (d % V == 0) && ((((uintptr_t)A | (uintptr_t)C) & 15u) == 0);
+    const bool wide = whole_chunks<TIn>(A, C, d);
     const int vec = wide ? V : 1;
     const dim3 grid((unsigned)((d + (int64_t)CW * vec - 1) / ((int64_t)CW * vec)), (unsigned)(B * plan.nrange));
     const dim3 block(CW * RW);
@@ -290,27 +357,98 @@ VecPlan plan_vec_stat(int64_t B, int64_t T, int64_t d, pex_dtype dt)
     return p;
 }
 
-hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, const VecPlan& plan,
-                           float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream)
+namespace {
+
+// The narrow blocks' two-stage sum costs about three chain steps of the wide ones; beyond one block per compute unit, every 450
+// blocks of sixteen columns cost another, every 300 where a step is a single load (measurements above the kernels; B=84 d=119314
+// in one range, whole call: wide 72 us, narrow 84).
+bool wide_second_pass(int64_t B, int64_t d, const VecPlan& plan)
 {
-    hipError_t e = dt == PEX_F32 ? launch_typed((const float*)A, (const float*)C, B, T, d, plan, partial, stream)
-                                 : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
-    if (e != hipSuccess) return e;
-    // The narrow blocks' two-stage sum costs about three chain steps of the wide ones; beyond one block per compute unit, every 450
-    // blocks of sixteen columns cost another, every 300 where a step is a single load (measurements above the kernels; B=84 d=119314
-    // in one range, whole call: wide 72 us, narrow 84).
     const int64_t narrow = (d + 15) / 16, chain = ((B + RW - 1) / RW) * ((plan.nrange + 7) / 8);
-    if (chain < 3 + (narrow > 256 ? (narrow - 256) / (plan.nrange == 1 ? 300 : 450) : 0)) {
+    return chain < 3 + (narrow > 256 ? (narrow - 256) / (plan.nrange == 1 ? 300 : 450) : 0);
+}
+
+// four columns a lane (short rows of odd length: more blocks; B=3000 d=77 22 against 27 us)
+bool in_quads(int64_t d) { return d % 4 == 0 || d >= 512; }
+
+hipError_t finalize_one(int64_t B, int64_t d, const VecPlan& plan, const float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream)
+{
+    if (wide_second_pass(B, d, plan)) {
         vec_finalize_wide_kernel<<<dim3((unsigned)((d + CW - 1) / CW)), dim3(CW * RW), 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign);
         return hipGetLastError();
     }
     // example lanes for the batch, the rest of the block to the ranges
-    const bool quads = d % 4 == 0 || d >= 512;      // (short rows of odd length: more blocks; B=3000 d=77 22 against 27 us)
-    const dim3 grid((unsigned)(quads ? narrow : (d + 3) / 4)), block(256);
+    const bool quads = in_quads(d);
+    const dim3 grid((unsigned)(quads ? (d + 15) / 16 : (d + 3) / 4)), block(256);
     auto go = [&](auto kern) { kern<<<grid, block, 0, stream>>>(partial, (int)B, plan.nrange, d, s_id, s_sq, s_sign); };
     if (B > 16) quads ? go(vec_finalize_kernel<4, 64, 1>) : go(vec_finalize_kernel<1, 64, 1>);
     else if (B > 4) quads ? go(vec_finalize_kernel<4, 16, 4>) : go(vec_finalize_kernel<1, 16, 4>);
     else quads ? go(vec_finalize_kernel<4, 4, 16>) : go(vec_finalize_kernel<1, 4, 16>);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, const VecPlan& plan,
+                           float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream)
+{
+    const hipError_t e = dt == PEX_F32 ? launch_typed((const float*)A, (const float*)C, B, T, d, plan, partial, stream)
+                                       : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
+    return e != hipSuccess ? e : finalize_one(B, d, plan, partial, s_id, s_sq, s_sign, stream);
+}
+
+int vec_batch_limit() { return BATCH; }
+
+hipError_t launch_vec_stat_batch(const pex_vec_item* items, int count, int64_t B, int64_t T, pex_dtype dt, void* workspace, hipStream_t stream)
+{
+    VecBatch v{};
+    char* ws = (char*)workspace;
+    unsigned at = 0;
+    for (int k = 0; k < count; ++k) {
+        const pex_vec_item& it = items[k];
+        const VecPlan plan = plan_vec_stat(B, T, it.d, dt);
+        const bool wide = dt == PEX_F32 ? whole_chunks<float>(it.A, it.C, it.d) : whole_chunks<uint16_t>(it.A, it.C, it.d);
+        const int64_t cols = (int64_t)CW * (wide ? (dt == PEX_F32 ? 4 : 8) : 1);
+        v.first[k] = at;
+        v.A[k] = it.A;
+        v.C[k] = it.C;
+        v.partial[k] = (float*)ws;
+        v.d[k] = it.d;
+        v.nrange[k] = plan.nrange;
+        v.rows_per_range[k] = plan.rows_per_range;
+        v.wide[k] = wide;
+        v.colblocks[k] = (int)((it.d + cols - 1) / cols);
+        at += (unsigned)((int64_t)v.colblocks[k] * B * plan.nrange);
+        ws += vec_batch_bytes(plan);
+    }
+    v.count = count;
+    if (dt == PEX_F32) vec_partial_batch_kernel<float><<<dim3(at), dim3(CW * RW), 0, stream>>>(v, (int)T);
+    else vec_partial_batch_kernel<uint16_t><<<dim3(at), dim3(CW * RW), 0, stream>>>(v, (int)T);
+    hipError_t e = hipGetLastError();
+    // second pass: together where it runs on narrow blocks of four columns a lane
+    VecBatch n{};
+    unsigned blocks = 0;
+    for (int k = 0; k < count && e == hipSuccess; ++k) {
+        const pex_vec_item& it = items[k];
+        const VecPlan plan = plan_vec_stat(B, T, it.d, dt);
+        if (wide_second_pass(B, it.d, plan) || !in_quads(it.d)) {
+            e = finalize_one(B, it.d, plan, v.partial[k], it.s_id, it.s_sq, it.s_sign, stream);
+            continue;
+        }
+        const int m = n.count++;
+        n.first[m] = blocks;
+        n.partial[m] = v.partial[k];
+        n.s_id[m] = it.s_id;
+        n.s_sq[m] = it.s_sq;
+        n.s_sign[m] = it.s_sign;
+        n.d[m] = it.d;
+        n.nrange[m] = plan.nrange;
+        blocks += (unsigned)((it.d + 15) / 16);
+    }
+    if (e != hipSuccess || blocks == 0) return e;
+    if (B > 16) vec_finalize_batch_kernel<64, 1><<<dim3(blocks), dim3(256), 0, stream>>>(n, (int)B);
+    else if (B > 4) vec_finalize_batch_kernel<16, 4><<<dim3(blocks), dim3(256), 0, stream>>>(n, (int)B);
+    else vec_finalize_batch_kernel<4, 16><<<dim3(blocks), dim3(256), 0, stream>>>(n, (int)B);
     return hipGetLastError();
 }
 

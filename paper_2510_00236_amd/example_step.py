@@ -9,9 +9,9 @@ and the cotangents of the looked-up vectors.  Per parameter tensor the library r
 S_sq = sum_b g_b^2 without ever storing a per-example gradient; the optimizer kernels consume them in place.
 Order of a step (everything stays on the GPU, nothing synchronises with the host):
   1. statistics of every tensor (one contraction per dense layer gives both S_id and S_sq);
-  2. the squared global norm of the summed gradient, accumulated over the tensors;
+  2. the squared global norm of the summed gradient, over the tensors;
   3. the update of every tensor, which forms the clipping factor from that norm on the device;
-  4. optionally the running mu^2 / sigma^2 measurement of Sec. 3.2.2.
+  4. optionally the running mu^2 / sigma^2 measurement of Sec. 3.2.2 (2 to 4 in one call).
 """
 from __future__ import annotations
 
@@ -62,36 +62,27 @@ def block_inputs(B, T, d, V, dev, seed=0):
 def microadam_step(tensors, inputs, V, step, B, lr=2e-3, max_norm=1e-2, workspace=None, track=True):
     dense, scale = inputs["dense"], inputs["scale"]
     ws = workspace
-    # 1. statistics
+    # 1. statistics: dense layers, then all offsets and scales together, then the embedding
+    vectors = []
     for name, (X, G) in dense.items():
         w, b = tensors[name], tensors[name + ".bias"]
         din, dout = X.shape[2], G.shape[2]
         pex.pex_stat_multi(X, G, ("identity", "square"),
                            out={"identity": w.S_id.view(din, dout), "square": w.S_sq.view(din, dout)}, workspace=ws)
-        pex.pex_vec_stat(G, None, ("identity", "square"), out={"identity": b.S_id, "square": b.S_sq}, workspace=ws)
+        vectors.append((G, None, {"identity": b.S_id, "square": b.S_sq}))
     for name, (A, C) in scale.items():
-        t = tensors[name]
-        pex.pex_vec_stat(A, C, ("identity", "square"), out={"identity": t.S_id, "square": t.S_sq}, workspace=ws)
+        vectors.append((A, C, {"identity": tensors[name].S_id, "square": tensors[name].S_sq}))
+    pex.pex_vec_stat_batch(vectors, ("identity", "square"), workspace=ws)
     e = tensors["embed"]
     d = inputs["embed_cot"].shape[2]
     pex.pex_embed_stat(inputs["ids"], inputs["embed_cot"], V, ("identity", "square"),
                        out={"identity": e.S_id.view(V, d), "square": e.S_sq.view(V, d)}, workspace=ws)
-    # 2. global norm of the summed gradient
-    acc = tensors["_norm"]
-    first = True
-    for t in tensors.values():
-        if isinstance(t, Tensor):
-            pex.pex_sum_squares(t.S_id, acc=acc, accumulate=not first, workspace=ws)
-            first = False
-    # 3. clipped update, 4. moment tracking
+    # 2. global norm of the summed gradient, 3. clipped update, 4. moment tracking: all tensors in one call
     prm = pex.AdamParams(lr=lr, beta1=0.9, beta2=0.95, eps=1e-8, eps_root=0.0, weight_decay=0.0,
                          grad_scale=1.0 / B, sq_scale=1.0 / B, step=step, B=B)
-    mp = pex.MomentParams(beta2=0.95, grad_scale=1.0 / B, sq_scale=1.0 / B, B=B, debias=1, step=step)
-    sums = tensors["_moments"]
-    for k, t in enumerate(x for x in tensors.values() if isinstance(x, Tensor)):
-        if track:
-            pex.pex_moment_track(t.ema_a, t.ema_q, t.S_id, t.S_sq, mp, sums=sums[k], workspace=ws)
-        pex.pex_adam_update_clipped(t.theta, t.m, t.v, t.S_id, t.S_sq, "microadam", prm, acc, max_norm)
+    mp = pex.MomentParams(beta2=0.95, grad_scale=1.0 / B, sq_scale=1.0 / B, B=B, debias=1, step=step) if track else None
+    pex.pex_adam_step([(t.theta, t.m, t.v, t.S_id, t.S_sq, t.ema_a, t.ema_q) for t in tensors.values() if isinstance(t, Tensor)], "microadam",
+                      prm, tensors["_norm"], max_norm, moments=mp, sums=tensors["_moments"], workspace=ws)
 
 
 def build(B, T, d, V, dev):
@@ -109,11 +100,10 @@ def build(B, T, d, V, dev):
     need = [16]
     for X, G in inputs["dense"].values():
         need.append(pex.pex_stat_multi_workspace_bytes(B, T, X.shape[2], G.shape[2], pex.PEX_BF16, 3))
-        need.append(pex.pex_vec_stat_workspace_bytes(B, T, G.shape[2], pex.PEX_BF16))
-    need.append(pex.pex_vec_stat_workspace_bytes(B, T, d, pex.PEX_BF16))
+    widths = [G.shape[2] for _, G in inputs["dense"].values()] + [A.shape[2] for A, _ in inputs["scale"].values()]
+    need.append(pex.pex_vec_stat_batch_workspace_bytes(widths, B, T, pex.PEX_BF16))
     need.append(pex.pex_embed_stat_workspace_bytes(B, T, V, d))
-    biggest = max(t.n for t in tensors.values() if isinstance(t, Tensor))
-    need += [pex.pex_sum_squares_workspace_bytes(biggest), pex.pex_moment_track_workspace_bytes(biggest)]
+    need.append(pex.pex_adam_step_workspace_bytes([t.n for t in tensors.values() if isinstance(t, Tensor)]))
     ws = torch.empty(max(need), dtype=torch.uint8, device=dev)
     return inputs, tensors, ws
 
