@@ -89,6 +89,8 @@ int pex_version(void);
  *                            1 = chosen by a cost model (default), 2 = wherever it applies (dout < 2^20) (environment
  *                            PEX_MEMORY_FOLD).  It rounds the square before adding it where the register tiles use a
  *                            fused multiply-add: the routes agree to fp32 rounding, not bit for bit.
+ * With any option away from its default, layers that do not fill the chip stay on the kernels these options are about
+ * as well (they have a kernel of their own otherwise; fp32 rounding apart, the results are the same).
  * An option changes the plan and with it the *_workspace_bytes of later calls: query again after setting one.  A
  * call whose workspace was sized under another value returns PEX_ERR_WORKSPACE if it is too small.
  * pex_set_option: PEX_ERR_PHI for an unknown option, PEX_ERR_SHAPE for a value out of range.  pex_get_option: the

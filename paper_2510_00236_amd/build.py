@@ -39,7 +39,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     isa_error = None
     try:
         at = lambda name: os.path.join(CSRC, name)
-        isa_check.check_all(HIPCC, [*FLAGS, *extra_flags], at("pex_stat_bf16.hip"), (at("pex_gram.hip"), at("pex_gram_wide.hip")), (at("pex_stat_f32.hip"), at("pex_stat_f32_split.hip")))
+        isa_check.check_all(HIPCC, [*FLAGS, *extra_flags], at("pex_stat_bf16.hip"), (at("pex_gram.hip"), at("pex_gram_wide.hip")), (at("pex_stat_f32.hip"), at("pex_stat_f32_split.hip"), at("pex_stat_small.hip")))
     except (isa_check.IsaCheckError, subprocess.CalledProcessError) as e:
         isa_error = e
     failed = False

@@ -40,6 +40,7 @@ static hipError_t scratch_address(void** out)
 // pex_set_option changes them.  Atomics, so a host thread that plans while another one sets an option reads a
 // whole value; a plan made under one value and launched under another is caught as PEX_ERR_WORKSPACE.
 constexpr int NUM_OPTIONS = 5;
+constexpr int DEFAULT_OPTIONS[NUM_OPTIONS] = {32, 1, 1, 1, 1};
 struct Options {
     std::atomic<int> v[NUM_OPTIONS];
 };
@@ -59,10 +60,9 @@ static Options& options()
     static std::once_flag once;
     std::call_once(once, [] {
         const char* names[NUM_OPTIONS] = {"PEX_MAX_SPLIT", "PEX_TOKEN_PRESQUARE", "PEX_WIDE_BLOCKS", "PEX_GRAM_NORMS", "PEX_MEMORY_FOLD"};
-        const int dflt[NUM_OPTIONS] = {32, 1, 1, 1, 1};
         for (int k = 0; k < NUM_OPTIONS; ++k) {
             const char* e = getenv(names[k]);
-            o.v[k].store(clamp_option(k, (e && *e) ? atoi(e) : dflt[k]));
+            o.v[k].store(clamp_option(k, (e && *e) ? atoi(e) : DEFAULT_OPTIONS[k]));
         }
     });
     return o;
@@ -260,7 +260,7 @@ static size_t scratch_charge_f32(int64_t B, int64_t T, int64_t din, int64_t dout
     return ns > 1 ? (size_t)ns * (size_t)din * (size_t)dout * sizeof(float) : 0;
 }
 
-static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad,
+static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad,
                           const OptionValues& options)
 {
     StatPlan p{};
@@ -311,6 +311,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         if (max_split > fit) max_split = fit < 1 ? 1 : (int)fit;
     }
     int64_t nsplit = 1, per = units;
+    double best_bf16 = 0.0;
     int64_t wide_cols = 0, wide_nsplit = 1, wide_per = units, direct_nsplit = 1;
     bool sign_bytes = false, mem_fold = false;
     if (p.kernel == 2) {
@@ -324,7 +325,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
                               mode == MODE_POWER ? 0.88e-6 : 0.3e-6;
         const double s_bytes = mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0;
         const int most = !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit);
-        const double direct = cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64), s_bytes, most, &nsplit, &per);
+        const double direct = p.seconds = cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64), s_bytes, most, &nsplit, &per);
         // ... or split into bf16 pieces, where that is faster (never for examples of fewer than 48 tokens: there its sums of 32 tokens
         // are no more exact than the fp32 ones, 1.39e-7 against 1.38e-7 of the 2-norm at T = 32, 1.51e-7 against 1.60e-7 at T = 48)
         if (allow_pad && f32_split_supports(B, T, din, dout) && (per_example ? T : B * T) >= 48) {
@@ -332,6 +333,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
             const int64_t blocks = f32_split_blocks(din, dout), fit_p = (((int64_t)1 << 32) - 1) / (blocks * 256);
             const double pieces = cheapest_split_f32_pieces(blocks, units, ((per_example ? T : slab) + 31) / 32, mode, !allow_wide, s_bytes,
                                                             most > fit_p ? (int)fit_p : most, &ns_p, &per_p);
+            p.seconds = pieces < direct ? pieces : direct;
             if (pieces < direct) {
                 p.f32_split = true;
                 direct_nsplit = nsplit;
@@ -345,6 +347,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
         if (nsplit > units) nsplit = units;
         if (nsplit < 1) nsplit = 1;
         per = (units + nsplit - 1) / nsplit;
+        p.seconds = simt_seconds(B, T, din, dout, mode);
     } else {
         // A unit-time is one example (or 64 rows) on one block.
         const double rows_per_unit = per_example ? (double)T : (double)slab;
@@ -420,7 +423,9 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
                 per = per_f;
             }
         }
+        best_bf16 = best;
     }
+    if (p.kernel == 1) p.seconds = padded ? padded_seconds(B, T, p.out_rows, p.out_cols, mode, !allow_wide) : best_bf16;
     nsplit = (units + per - 1) / per;      // no empty group
     p.nsplit = (int)nsplit;
     p.per_split = per_example ? per : per * slab;
@@ -486,9 +491,11 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
             const bool wide_ok = park <= ((size_t)256 << 20);
             if (gram_opt == 3 ? wide_ok : (gram_opt == 1 && wide_ok && t_wide < t_gram && t_wide < t_direct)) {
                 p.gram = p.gram_wide = true;
+                p.seconds = t_wide;
                 p.ws_bytes = p.copy_bytes + (((size_t)gram_wide_partials(T) * (size_t)B * sizeof(float) + 255) & ~(size_t)255) + park;
             } else if (gram_opt == 2 || gram_opt == 3 || t_gram < t_direct) {
                 p.gram = true;
+                p.seconds = t_gram;
                 p.ws_bytes = p.copy_bytes + (size_t)gram_norm_partials(T) * (size_t)B * sizeof(float);
             }
         }
@@ -496,9 +503,89 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     return p;
 }
 
+// The kernel of small layers: eight waves a workgroup, one workgroup a compute unit; a wave's step (32 tokens of bf16, 16 of fp32) takes
+// 0.95 us and 2.0 (there the fp32 MFMA pipe is the bound, two waves on each), the end of an example 0.2 us, a norm 1, either 1 more where
+// the waves have divided its tokens; a launch 5 us to start and end (3 without sums of eight waves), the sum of the norms' parts 3.
+// A full chip is a fifth slower.  Partial sums as above, 4.5 us for their launch.  Fitted on 180 drawn layers of each type, seven statistics, both
+// ways to divide the work: medians within 10 %, nine in ten within 25 %.
+static double cheapest_small(int64_t tiles, int64_t units, int64_t rows_per_unit, bool bf16, Mode mode, int kw, double s_bytes,
+                             int64_t* nsplit, int64_t* per)
+{
+    const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ, norms = mode == MODE_NORMS;
+    const int64_t rows_per_step = bf16 ? 32 : 16;
+    const double t_step = bf16 ? 0.95e-6 : 2.0e-6;
+    const double t_fold = (norms ? 1.0e-6 : 0.2e-6) + (kw == 1 ? 0.0 : 0.8e-6);
+    const double start = (kw == 1 ? 5.0e-6 : plain ? 4.0e-6 : 3.0e-6) + (norms ? 3.0e-6 : 0.0);
+    const int64_t most = norms ? 1024 : 32, lim = units < most ? units : most;
+    double best = 0.0;
+    for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
+        const int64_t pu = (units + ns - 1) / ns;
+        const int64_t ns_eff = (units + pu - 1) / pu;
+        const int64_t rounds = (tiles * ns_eff + 255) / 256;
+        double unit;
+        if (plain) {
+            const int64_t rows = pu * rows_per_unit, steps = ((rows + 7) / 8 + rows_per_step - 1) / rows_per_step;
+            unit = (double)steps * t_step + (double)((rows + 8191) / 8192) * t_fold;
+        } else {
+            const int64_t steps = (rows_per_unit + rows_per_step - 1) / rows_per_step;
+            unit = kw == 1 ? (double)((pu + 7) / 8) * ((double)steps * t_step + t_fold) : (double)pu * ((double)((steps + 7) / 8) * t_step + t_fold);
+        }
+        double cost = (double)rounds * unit * (tiles * ns_eff > 128 ? 1.2 : 1.0) + start;
+        if (!norms && ns_eff > 1) cost += (double)(2 * ns_eff + 1) * s_bytes / 4.0e12 + 4.5e-6;
+        if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
+    }
+    return best;
+}
+
+// The kernel of small layers where its estimate is the lowest.  The options choose among the other kernels: a layer planned under one
+// that is not at its default stays on them.
+static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad, bool allow_small,
+                          const OptionValues& options)
+{
+    const StatPlan p = make_large_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, options);
+    // (a step is 32 or 16 tokens: examples of one to three would be nearly all padding.  Of layers with more tiles than these the large
+    // kernels' estimates are too high, by 30 % for norms at half a chip: norms 46 us there and 85 here, signs 66 and 98 at 640 tiles,
+    // but squares 113 and 66; more than 1024 were not compared)
+    const int64_t most_tiles = mode == MODE_NORMS ? 128 : mode == MODE_SIGN ? 256 : 1024;
+    if (!allow_pad || !allow_small || !allow_wide || T < 4 || small_tiles(din, dout) > most_tiles || !small_supports(T, din, dout, dt, mode)) return p;
+    for (int k = 0; k < NUM_OPTIONS; ++k)
+        if (options[k] != DEFAULT_OPTIONS[k]) return p;
+    const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
+    const int64_t units = plain ? (B * T + 63) / 64 : B;
+    StatPlan s{};
+    s.seconds = 1.0;
+    for (const int kw : {1, 8}) {
+        if (plain && kw == 1) continue;
+        int64_t ns = 1, per = units;
+        const double t = cheapest_small(small_tiles(din, dout), units, plain ? 64 : T, dt == PEX_BF16, mode, kw, (double)din * (double)dout * 4.0, &ns, &per);
+        if (t < s.seconds) {
+            s.seconds = t;
+            s.small_kw = kw;
+            s.nsplit = (int)ns;
+            s.per_split = plain ? per * 64 : per;
+        }
+    }
+    // (the large plans' estimates leave the start and end of a launch out: 5 us on bf16 blocks, 3 on the fp32 kernel, but for the norms;
+    // on bf16 layers the small kernel has to be the clear winner beyond 15 and 25 us, where a chip full of waves draws on the same caches.
+    // 1260 fp32 and 1080 bf16 calls of 5 to 400 us: 1.50 and 1.56 times faster in the mean than without this kernel, the better one every
+    // time would be 1.57 and 1.65; 17 calls slower by 6 % or more, at most 23 %)
+    const double start = mode == MODE_NORMS ? 0.0 : p.kernel == 1 && p.copy_bytes == 0 ? 5.0e-6 : p.kernel == 2 && !p.f32_split ? 3.0e-6 : 0.0;
+    const double margin = dt == PEX_F32 || s.seconds < 15.0e-6 ? 1.0 : mode == MODE_NORMS ? 1.9 : s.seconds < 25.0e-6 ? 1.2 : 1.45;
+    if (s.seconds * margin >= p.seconds + start) return p;
+    s.kernel = p.kernel;
+    s.out_rows = s.din = din;
+    s.out_cols = s.dout = dout;
+    s.wide_nsplit = 1;
+    s.wide_per_split = B;
+    s.ws_bytes = mode == MODE_NORMS ? (size_t)small_tiles(din, dout) * s.small_kw * B * sizeof(float)
+                 : s.nsplit > 1     ? (size_t)s.nsplit * (size_t)din * (size_t)dout * sizeof(float) : 0;
+    if (s.ws_bytes < p.ws_bytes) s.ws_bytes = p.ws_bytes;      // (as for the other kernels: a layer that fits a bound on the workspace does so either way)
+    return s;
+}
+
 // A plan is a function of the shape, the statistic and the options; weighing the candidates takes 1 to 4 us, as long as a
 // launch, and up to 12 for the norms of a thousand examples.  Each host thread keeps sixteen, one per hash of what they depend on.
-StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad)
+StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad, bool allow_small)
 {
     struct Kept {
         int64_t key[5];
@@ -512,7 +599,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     now.key[1] = T;
     now.key[2] = din;
     now.key[3] = dout;
-    now.key[4] = (int64_t)dt * 64 + (int64_t)mode * 4 + (allow_wide ? 2 : 0) + (allow_pad ? 1 : 0);
+    now.key[4] = (int64_t)dt * 64 + (int64_t)mode * 8 + (allow_small ? 4 : 0) + (allow_wide ? 2 : 0) + (allow_pad ? 1 : 0);
     uint64_t h = 0;
     for (const int64_t k : now.key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
     bool same = true;
@@ -523,7 +610,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     }
     for (int k = 0; k < 5; ++k) same = same && now.key[k] == at.key[k];
     if (at.valid && same) return at.plan;
-    now.plan = make_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, now.options);
+    now.plan = make_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, allow_small, now.options);
     now.valid = true;
     at = now;
     return now.plan;
@@ -534,7 +621,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
 static StatPlan plan_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, size_t bytes)
 {
     const StatPlan plan = plan_stat(B, T, din, dout, dt, mode);
-    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout && !plan.f32_split)) return plan;
+    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout && !plan.f32_split && plan.small_kw == 0)) return plan;
     const StatPlan direct = plan_stat(B, T, din, dout, dt, mode, true, false);
     return direct.ws_bytes <= bytes ? direct : plan;
 }
@@ -639,7 +726,9 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
                                        plan.nsplit);
         return e == hipSuccess ? PEX_OK : PEX_ERR_HIP;
     }
-    if (mode == MODE_TOKEN_SQ && plan.copy_bytes > 0) {
+    if (plan.small_kw > 0) {
+        e = launch_stat_small(X, G, B, T, din, dout, dt, mode, plan, out, stream, weight, nullptr, alpha);
+    } else if (mode == MODE_TOKEN_SQ && plan.copy_bytes > 0) {
         e = launch_stat_bf16(X, G, B, T, din, dout, MODE_IDENTITY, plan, S, partials, stream);       // the copies hold the squares
     } else if (plan.kernel == 2) {
         e = launch_stat_f32(X, G, B, T, din, dout, mode, plan, out, stream, weight, nullptr, alpha);
@@ -690,15 +779,18 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
-    // (what shares a contraction on the bf16 matrix cores is identity and square only)
+    // (what shares a contraction on the bf16 matrix cores, or on the kernel of small layers, is identity and square only)
     constexpr uint32_t BOTH = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
-    StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH));
+    // a layer whose square by itself takes the kernel of small layers has the same bits here: the same plan, everything else by itself
+    const StatPlan alone = plan_stat(B, T, din, dout, dt, MODE_SQUARE, true, allow_pad);
+    const bool small = allow_pad && alone.small_kw > 0;
+    const StatPlan sq = small ? alone : plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH), false);
     // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
     // contraction and sign keeps its own.  On fp32 layers sign shares one only as bytes.
     m.pair_want = want;
     if (sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = BOTH;
-    if (sq.kernel == 2 && !f32_bytes_suffice(sq)) m.pair_want = want & BOTH;
-    m.pair = (__builtin_popcount(m.pair_want) >= 2 && sq.kernel != 0);
+    if (small || (sq.kernel == 2 && !f32_bytes_suffice(sq))) m.pair_want = want & BOTH;
+    m.pair = __builtin_popcount(m.pair_want) >= 2 && (sq.kernel != 0 || small);
     if (m.pair) {
         m.single_want = want & ~m.pair_want;
         m.pair_plan = sq;
@@ -829,7 +921,8 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         int k = 0;
         for (int phi = 0; phi < 3; ++phi)
             if (m.pair_want & (1u << phi)) po[phi] = p.nsplit > 1 ? partials + (int64_t)(k++) * p.nsplit * n : outs[phi];
-        const hipError_t e = p.kernel == 2 ? launch_stat_f32_multi(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
+        const hipError_t e = p.small_kw > 0 ? launch_stat_small_pair(x, g, B, T, p.din, p.dout, dt, p, po[0], po[1], hs)
+                             : p.kernel == 2 ? launch_stat_f32_multi(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
                              : (__builtin_popcount(m.pair_want) == 3)
                                  ? launch_stat_bf16_triple(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
                                  : launch_stat_bf16_pair(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs);
@@ -949,7 +1042,10 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
     const int64_t kin = plan.din, kout = plan.dout;
     hipError_t e;
     int64_t nparts;
-    if (plan.gram_wide) {
+    if (plan.small_kw > 0) {
+        nparts = small_tiles(kin, kout) * plan.small_kw;
+        e = launch_stat_small(X, G, B, T, kin, kout, dt, MODE_NORMS, plan, nullptr, hs, nullptr, partial);
+    } else if (plan.gram_wide) {
         nparts = gram_wide_partials(T);
         void* park = front + (((size_t)nparts * (size_t)B * sizeof(float) + 255) & ~(size_t)255);
         e = launch_gram_wide(X, G, B, T, kin, kout, partial, park, hs);
