@@ -3,7 +3,6 @@
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
-#include <vector>
 
 #include "pex_internal.h"
 
@@ -993,26 +992,27 @@ pex_status pex_vec_stat_batch(const pex_vec_item* items, int32_t count, int64_t 
     }
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     for (int k = 0; k < count;) {
-        std::vector<pex_vec_item> group;
+        pex_vec_item group[VEC_BATCH];
+        int n = 0;
         size_t bytes = 0;
         int64_t blocks = 0;
-        for (; k < count && (int)group.size() < vec_batch_limit(); ++k) {
+        for (; k < count && n < VEC_BATCH; ++k) {
             pex_vec_item it = items[k];
             const VecPlan plan = plan_vec_stat(B, T, it.d, dt);
             const int64_t own = (it.d + 63) / 64 * B * plan.nrange;       // at most: a launch holds fewer than 2^32 threads
-            if (!group.empty() && (bytes + vec_batch_bytes(plan) > workspace_bytes || blocks + own >= ((int64_t)1 << 23))) break;
+            if (n > 0 && (bytes + vec_batch_bytes(plan) > workspace_bytes || blocks + own >= ((int64_t)1 << 23))) break;
             bytes += vec_batch_bytes(plan);
             blocks += own;
             if (!(want & PEX_WANT_IDENTITY)) it.s_id = nullptr;
             if (!(want & PEX_WANT_SQUARE)) it.s_sq = nullptr;
             if (!(want & PEX_WANT_SIGN)) it.s_sign = nullptr;
-            group.push_back(it);
+            group[n++] = it;
         }
         hipError_t e;
-        if (group.size() == 1) {       // alone: as pex_vec_stat, whose grid has two dimensions
+        if (n == 1) {       // alone: as pex_vec_stat, whose grid has two dimensions
             const pex_vec_item& it = group[0];
             e = launch_vec_stat(it.A, it.C, B, T, it.d, dt, plan_vec_stat(B, T, it.d, dt), (float*)workspace, it.s_id, it.s_sq, it.s_sign, (hipStream_t)stream);
-        } else e = launch_vec_stat_batch(group.data(), (int)group.size(), B, T, dt, workspace, (hipStream_t)stream);
+        } else e = launch_vec_stat_batch(group, n, B, T, dt, workspace, (hipStream_t)stream);
         if (e != hipSuccess) return PEX_ERR_HIP;
     }
     return PEX_OK;

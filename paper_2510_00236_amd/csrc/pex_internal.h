@@ -146,9 +146,9 @@ VecPlan plan_vec_stat(int64_t B, int64_t T, int64_t d, pex_dtype dt);
 hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int64_t d, pex_dtype dt, const VecPlan& plan,
                            float* partial, float* s_id, float* s_sq, float* s_sign, hipStream_t stream);
 
-// Several vectors of one batch and type together: at most vec_batch_limit() of them, each with vec_batch_bytes of its plan in
+// Several vectors of one batch and type together: at most VEC_BATCH of them, each with vec_batch_bytes of its plan in
 // the workspace, one after the other (an output that is not wanted is NULL)
-int vec_batch_limit();
+constexpr int VEC_BATCH = 16;
 inline size_t vec_batch_bytes(const VecPlan& plan) { return (plan.ws_bytes + 255) & ~(size_t)255; }
 hipError_t launch_vec_stat_batch(const pex_vec_item* items, int count, int64_t B, int64_t T, pex_dtype dt, void* workspace, hipStream_t stream);
 

@@ -265,14 +265,13 @@ __global__ __launch_bounds__(256) void vec_finalize_kernel(const float* __restri
 
 // Several vectors of one batch in one launch of each pass: the offsets and scales of a layer are a few thousand columns each, and a
 // launch costs about 4.5 us whatever it does.  The same blocks as one vector's launches, one vector after the other.
-constexpr int BATCH = 16;
 struct VecBatch {
     int count;
-    unsigned first[BATCH + 1];       // first block of each vector
-    const void *A[BATCH], *C[BATCH];
-    float *partial[BATCH], *s_id[BATCH], *s_sq[BATCH], *s_sign[BATCH];
-    int64_t d[BATCH];
-    int nrange[BATCH], rows_per_range[BATCH], colblocks[BATCH], wide[BATCH];
+    unsigned first[VEC_BATCH + 1];   // first block of each vector
+    const void *A[VEC_BATCH], *C[VEC_BATCH];
+    float *partial[VEC_BATCH], *s_id[VEC_BATCH], *s_sq[VEC_BATCH], *s_sign[VEC_BATCH];
+    int64_t d[VEC_BATCH];
+    int nrange[VEC_BATCH], rows_per_range[VEC_BATCH], colblocks[VEC_BATCH], wide[VEC_BATCH];
     __device__ __forceinline__ int of_block(unsigned b) const
     {
         int k = 0;
@@ -396,8 +395,6 @@ hipError_t launch_vec_stat(const void* A, const void* C, int64_t B, int64_t T, i
                                        : launch_typed((const uint16_t*)A, (const uint16_t*)C, B, T, d, plan, partial, stream);
     return e != hipSuccess ? e : finalize_one(B, d, plan, partial, s_id, s_sq, s_sign, stream);
 }
-
-int vec_batch_limit() { return BATCH; }
 
 hipError_t launch_vec_stat_batch(const pex_vec_item* items, int count, int64_t B, int64_t T, pex_dtype dt, void* workspace, hipStream_t stream)
 {
