@@ -15,9 +15,8 @@
 //   2. row_start: where each token's run begins and, at the next index, ends (RowIndex);
 //   3. each wave owns 16 consecutive sorted positions and every vocabulary row whose run starts among them: cotangent
 //      rows are loaded 16 at a time and added per example, phi is applied whenever the example changes, and the result
-//      is added to the row's sums.  Rows with many positions are done by all waves of the workgroup, each on a
-//      contiguous run of whole examples, and combined in wave order; rows without positions are zero-filled by
-//      further workgroups of the same launch.
+//      is added to the row's sums.  Of a row with many positions every wave does the examples that start at its own 16, and the
+//      waves' sums are combined in wave order; rows without positions are zero-filled by further workgroups of the same launch.
 #include <type_traits>
 
 #include "pex_internal.h"
@@ -609,7 +608,7 @@ __device__ __forceinline__ int64_t chunk_start(int64_t col, int64_t d)
 constexpr int EMB_WAVES = 12;
 constexpr int EMB_ZROWS = 8;     // vocabulary rows a zero-fill wave looks at
 constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent rows a lane keeps in flight
-constexpr int EMB_ALONE = 64;    // a vocabulary row with at most this many positions is done by one wave
+constexpr int EMB_ALONE = 64;    // a vocabulary row with at most this many positions is done by one wave (a lane reads each ahead)
 
 struct RowSums {
     float id[CH], sq[CH], sg[CH];
@@ -619,24 +618,6 @@ struct RowSums {
         for (int e = 0; e < CH; ++e) id[e] = sq[e] = sg[e] = 0.f;
     }
 };
-
-// first index in [lo, hi) whose position is >= limit (positions ascend inside a row's run); the whole wave calls it
-// with the same arguments and looks at 64 positions per step -- an example rarely holds more of one token than that
-__device__ __forceinline__ int first_at_least(const int* __restrict__ pos, int lo, int hi, int limit)
-{
-    const int lane = threadIdx.x & 63;
-    while (lo < hi) {
-        const int k = lo + lane;
-        const bool hit = k >= hi || pos[k] >= limit;
-        const unsigned long long m = __ballot(hit);
-        if (m) {
-            const int r = lo + (int)__builtin_ctzll(m);
-            return r < hi ? r : hi;
-        }
-        lo += 64;
-    }
-    return hi;
-}
 
 // Accumulates the cotangent rows of one vocabulary row, example by example: acc holds the running sum of the current
 // example, phi(acc) goes to the row's sums when the example changes.
@@ -688,9 +669,13 @@ struct RowAccumulator {
 // grid = chunk workgroups of every block of 64 * CH columns, then the zero-fill workgroups: the chunks are the long poles, the
 // zero fill runs under their tail (with the column blocks one after the other, each with its own tail, 149 against 141 us).
 //   chunk workgroup: wave i owns the sorted positions [c0, c0 + EMB_U) and with them every vocabulary row whose run
-//     starts there (a run may continue past the chunk).  It loads EMB_U cotangent rows at a time whatever rows and
-//     examples they belong to, then adds them in order.  Runs longer than EMB_ALONE are only noted; after a barrier
-//     the whole workgroup does each of them, every wave on a contiguous run of whole examples, combined in wave order.
+//     starts there, and, of a run longer than EMB_ALONE, the examples that start there (each may continue past c0 + EMB_U).  It
+//     loads EMB_U cotangent rows at a time whatever rows and examples they belong to, then adds them in order; sums of long runs
+//     go to LDS, where the wave a run starts at combines them after the one barrier.
+//     Small calls are bound by the chain of loads: position -> token -> extent of its run -> cotangent row, about a microsecond
+//     each.  All long runs of a workgroup side by side, the positions behind a wave's own read ahead with the first load and no
+//     search for the bounds of examples make it four loads; one long run after the other by the whole workgroup, each with a chain of
+//     its own, took B=7 T=565 V=7952 d=128 22.4 us (now 12.5), B=21 T=285 V=2759 d=320 22 (16), B=64 T=1024 V=50257 d=768 79 (70).
 //   zero-fill workgroup: wave i looks at EMB_ZROWS vocabulary rows and writes zeros to those without positions.
 template <typename TIn, int ALIGN, int WANT>
 __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* __restrict__ G, const int* __restrict__ row_start,
@@ -738,141 +723,125 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         return;
     }
 
-    __shared__ int heavy_row[EMB_WAVES];   // the long run that starts among wave i's positions, or -1
-    __shared__ float comb[3][64 * CH];
-    if (lane == 0) heavy_row[wave] = -1;
+    constexpr int NSTAT = (WANT & 1) + (WANT >> 1 & 1) + (WANT >> 2 & 1);
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    // sums of the long runs at wave i's positions: slot 0 of the one that goes on from before them, slot 1 of the one that starts there
+    __shared__ f4 comb[EMB_WAVES][2][NSTAT][64];
+    const int64_t c0l = ((int64_t)group * EMB_WAVES + wave) * EMB_U;
+    const int c0 = c0l < N ? (int)c0l : N;
+    const int c1 = c0 + EMB_U < N ? c0 + EMB_U : N;
+
+    // Lane u < EMB_U looks up position c0 + u: its token and the extent of the token's run; the 64 positions behind are read ahead, a
+    // lane each.  Loaded are: positions of runs that start here, and of a long run that goes on from before the examples that start here.
+    const int k = c0 + lane;
+    const bool valid = lane < EMB_U && k < N;
+    int key = V, p = -1, rs = 0, re = 0;
+    if (valid) { key = keys[k]; p = pos[k]; }
+    const int before = c0 > 0 ? pos[c0 - 1] : -1;
+    int behind = c1 + lane < N ? pos[c1 + lane] : -1;
+    key = key < 0 ? V : (key > V ? V : key);
+    if (valid && key < V) { const int r = index.at(key); rs = row_start[r]; re = row_start[r + 1]; }
+    re = re > N ? N : re;
+    const bool is_long = re - rs > EMB_ALONE;
+    const bool mine = rs >= c0 || (is_long && p >= (before / T + 1) * T);
+    const int p_ld = (valid && key < V && mine && p >= 0 && p < N) ? p : -1;
+    const unsigned long long starts = __ballot(valid && key < V && is_long && rs == k);         // at most one among EMB_U positions
+    const int row_before = __builtin_amdgcn_readfirstlane(valid && key < V && is_long && rs < c0 ? key : -1);
+    const int from_before = __builtin_amdgcn_readfirstlane(rs), to_before = __builtin_amdgcn_readfirstlane(re);
+    const int start_lane = starts ? (int)__builtin_ctzll(starts) : 0;
+    const int row_starting = starts ? __builtin_amdgcn_readlane(key, start_lane) : -1, to_starting = __builtin_amdgcn_readlane(re, start_lane);
 
     RowAccumulator<TIn, ALIGN, WANT> ra;
     ra.start(T);
-    {
-        const int64_t c0l = ((int64_t)group * EMB_WAVES + wave) * EMB_U;
-        const int c0 = c0l < N ? (int)c0l : N;
-        const int c1 = c0 + EMB_U < N ? c0 + EMB_U : N;
-        int k0 = c0;
-        int cur_v = -1;      // the row being accumulated
-        int open_end = 0;    // where its run ends
-        while (k0 < (c1 > open_end ? c1 : open_end)) {
-            // lane u < EMB_U looks up position k0 + u: its token, the extent of the token's run, whether the run is ours
-            const int k = k0 + lane;
-            const bool valid = lane < EMB_U && k < N;
-            int key = V, p = -1, rs = 0, re = 0;
-            if (valid) { key = keys[k]; p = pos[k]; }
-            key = key < 0 ? V : (key > V ? V : key);
-            if (valid && key < V) { const int r = index.at(key); rs = row_start[r]; re = row_start[r + 1]; }
-            re = re > N ? N : re;
-            const bool ours = valid && key < V && rs >= c0 && rs < c1;
-            const bool is_heavy = re - rs > EMB_ALONE;
-            if (ours && is_heavy && k == rs) heavy_row[wave] = key;   // at most one such run can start among EMB_U positions
-            const int p_ld = (ours && !is_heavy && p >= 0 && p < N) ? p : -1;
-            int pu[EMB_U], ku[EMB_U], eu[EMB_U];
-            typename Ck::Raw data[EMB_U];
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u) {
-                pu[u] = __builtin_amdgcn_readlane(p_ld, u);
-                ku[u] = __builtin_amdgcn_readlane(key, u);
-                eu[u] = __builtin_amdgcn_readlane(re, u);
-            }
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u) data[u] = (pu[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pu[u] * d, col, d) : Ck::zero();
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u) {
-                if (pu[u] < 0) continue;
-                if (ku[u] != cur_v) {
-                    if (cur_v >= 0) { ra.finish(); store_row(cur_v, ra.sums); ra.sums.clear(); }
-                    cur_v = ku[u];
-                    open_end = eu[u];
-                }
-                ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
-            }
-            // the last position of the batch decides where the next batch starts: inside a run that is loaded the next
-            // batch follows on; a run that is not (another wave's, or a long one) is skipped to its end
-            const int last_ld = pu[EMB_U - 1], last_end = eu[EMB_U - 1];
-            const int next = k0 + EMB_U;
-            k0 = (last_ld >= 0 || last_end < next) ? next : last_end;
-        }
-        if (cur_v >= 0) { ra.finish(); store_row(cur_v, ra.sums); }
-    }
-    __syncthreads();
-    // Long runs: this workgroup does, of every long run that overlaps its EMB_WAVES * EMB_U positions [sc0, sc1), the
-    // examples that start there -- candidate -1 is the run that continues from the positions before sc0, candidate i the
-    // run that starts among wave i's positions.  A run that lies inside [sc0, sc1) is finished here; of any other the
-    // sums go to `partial` (slot 0: continues from before, slot 1: starts here and goes on) for embed_combine_kernel.
-    const int64_t sc0l = (int64_t)group * (EMB_WAVES * EMB_U);
-    const int sc0 = sc0l < N ? (int)sc0l : N;
-    const int sc1 = sc0 + EMB_WAVES * EMB_U < N ? sc0 + EMB_WAVES * EMB_U : N;
-    for (int c = -1; c < EMB_WAVES; ++c) {
-        int hv = -1;
-        if (c >= 0) hv = heavy_row[c];
-        else if (sc0 > 0 && sc0 < N) {
-            const int key = keys[sc0];
-            if (key >= 0 && key < V && row_start[index.at(key)] < sc0 && row_start[index.at(key) + 1] - row_start[index.at(key)] > EMB_ALONE) hv = key;
-        }
-        if (hv < 0 || hv >= V) continue;   // the same for every wave of the workgroup
-        int hs = row_start[index.at(hv)], he = row_start[index.at(hv) + 1];
-        hs = hs < 0 ? 0 : (hs > N ? N : hs);
-        he = he < hs ? hs : (he > N ? N : he);
-        // first position at or after k (hs < k < he) that begins an example
-        auto example_start = [&](int k) {
-            const int limit = (pos[k - 1] / T + 1) * T;
-            return first_at_least(pos, k, he, limit);
-        };
-        const bool from_before = hs < sc0, goes_on = he > sc1;
-        const int plo = from_before ? example_start(sc0) : hs;
-        const int phi = goes_on ? example_start(sc1) : he;
-        // wave i takes the examples that start in [bound(i), bound(i + 1)): an even split of the positions, moved
-        // forward to the next change of example
-        auto bound = [&](int i) {
-            if (i <= 0 || phi <= plo) return plo;
-            if (i >= EMB_WAVES) return phi;
-            const int k = plo + (int)(((int64_t)(phi - plo) * i) / EMB_WAVES);
-            if (k <= plo) return plo;
-            const int b2 = example_start(k);
-            return b2 < phi ? b2 : phi;
-        };
-        const int lo = bound(wave), hi = bound(wave + 1);
-        ra.start(T);
-        for (int k0 = lo; k0 < hi; k0 += EMB_U) {
-            int pp[EMB_U];
-            typename Ck::Raw data[EMB_U];
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u) {
-                pp[u] = (k0 + u < hi) ? pos[k0 + u] : -1;
-                if (pp[u] >= N) pp[u] = -1;   // positions are in [0, N)
-            }
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u) data[u] = (pp[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pp[u] * d, col, d) : Ck::zero();
-#pragma unroll
-            for (int u = 0; u < EMB_U; ++u)
-                if (pp[u] >= 0) ra.add(pp[u], data[u], ((pp[u] + (int)col) & 1) != 0);
-        }
+    int cur_v = -1;      // the row being accumulated
+    auto keep = [&](int slot) {
+        int n = 0;
+        if (WANT & 1) comb[wave][slot][n++][lane] = f4{ra.sums.id[0], ra.sums.id[1], ra.sums.id[2], ra.sums.id[3]};
+        if (WANT & 2) comb[wave][slot][n++][lane] = f4{ra.sums.sq[0], ra.sums.sq[1], ra.sums.sq[2], ra.sums.sq[3]};
+        if (WANT & 4) comb[wave][slot][n++][lane] = f4{ra.sums.sg[0], ra.sums.sg[1], ra.sums.sg[2], ra.sums.sg[3]};
+    };
+    auto close = [&]() {
+        if (cur_v < 0) return;
         ra.finish();
-        for (int i = 0; i < EMB_WAVES; ++i) {
-            if (wave == i) {
+        if (cur_v == row_before) keep(0);
+        else if (cur_v == row_starting) keep(1);
+        else store_row(cur_v, ra.sums);
+        ra.sums.clear();
+    };
+    if (row_before >= 0) keep(0);      // zeros, where no example of it starts here
+    int pu[EMB_U];
+    typename Ck::Raw data[EMB_U];
+    auto load_rows = [&]() {
 #pragma unroll
-                for (int e2 = 0; e2 < CH; ++e2) {
-                    const int o = lane * CH + e2;
-                    if (i == 0) { comb[0][o] = ra.sums.id[e2]; comb[1][o] = ra.sums.sq[e2]; comb[2][o] = ra.sums.sg[e2]; }
-                    else { comb[0][o] += ra.sums.id[e2]; comb[1][o] += ra.sums.sq[e2]; comb[2][o] += ra.sums.sg[e2]; }
-                }
-            }
-            __syncthreads();
-        }
-        if (wave == 0) {
+        for (int u = 0; u < EMB_U; ++u) data[u] = (pu[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pu[u] * d, col, d) : Ck::zero();
+    };
+    int ku[EMB_U];
 #pragma unroll
-            for (int e2 = 0; e2 < CH; ++e2) {
-                const int o = lane * CH + e2;
-                ra.sums.id[e2] = comb[0][o]; ra.sums.sq[e2] = comb[1][o]; ra.sums.sg[e2] = comb[2][o];
-            }
-            if (!from_before && !goes_on) store_row(hv, ra.sums);
-            else if (col_ok) {
-                float* pr = partial + (((int64_t)group * 2 + (from_before ? 0 : 1)) * 3) * d + col;
-                if (WANT & 1) store_chunk<ALIGN, false>(pr, ra.sums.id, d);
-                if (WANT & 2) store_chunk<ALIGN, false>(pr + d, ra.sums.sq, d);
-                if (WANT & 4) store_chunk<ALIGN, false>(pr + 2 * d, ra.sums.sg, d);
-            }
-        }
-        __syncthreads();
+    for (int u = 0; u < EMB_U; ++u) {
+        pu[u] = __builtin_amdgcn_readlane(p_ld, u);
+        ku[u] = __builtin_amdgcn_readlane(key, u);
     }
+    load_rows();
+#pragma unroll
+    for (int u = 0; u < EMB_U; ++u) {
+        if (pu[u] < 0) continue;
+        if (ku[u] != cur_v) {
+            close();
+            cur_v = ku[u];
+        }
+        ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
+    }
+    // what is left of the last position's run: all of it, or of a long one the rest of the example
+    if (pu[EMB_U - 1] >= 0) {
+        const int run_end = __builtin_amdgcn_readlane(re, EMB_U - 1);
+        const bool whole = __builtin_amdgcn_readlane((int)is_long, EMB_U - 1) == 0;
+        for (int k0 = c1;; k0 += 64) {
+            const unsigned long long rest = ~__ballot(k0 + lane < run_end && (whole || behind < ra.limit));
+            const int n = rest ? (int)__builtin_ctzll(rest) : 64;
+            for (int u0 = 0; u0 < n; u0 += EMB_U) {
+#pragma unroll
+                for (int u = 0; u < EMB_U; ++u) {
+                    const int q = __builtin_amdgcn_readlane(behind, u0 + u);
+                    pu[u] = u0 + u < n && q < N ? q : -1;
+                }
+                load_rows();
+#pragma unroll
+                for (int u = 0; u < EMB_U; ++u)
+                    if (pu[u] >= 0) ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
+            }
+            if (n < 64) break;
+            behind = k0 + 64 + lane < N ? pos[k0 + 64 + lane] : -1;
+        }
+    }
+    close();
+    __syncthreads();
+
+    // A long run's sums of the waves it covers, in wave order, by the wave it starts at (by the first one if it goes on from before the
+    // workgroup's positions [sc0, sc1)).  A run that lies inside these is finished here; of any other the sums go to `partial`
+    // (slot 0: goes on from before, slot 1: starts here and goes on) for embed_combine_kernel.
+    const int64_t sc0 = (int64_t)group * (EMB_WAVES * EMB_U);
+    const int64_t sc1 = sc0 + EMB_WAVES * EMB_U < N ? sc0 + EMB_WAVES * EMB_U : N;
+    auto combine = [&](int v, int slot, bool goes_on_from, int end) {
+        if (!col_ok) return;
+        f4 sum[NSTAT];
+#pragma unroll
+        for (int n = 0; n < NSTAT; ++n) sum[n] = comb[wave][slot][n][lane];
+        for (int w = wave + 1; w < EMB_WAVES && sc0 + w * EMB_U < end; ++w)
+#pragma unroll
+            for (int n = 0; n < NSTAT; ++n) sum[n] += comb[w][0][n][lane];
+        const bool inside = !goes_on_from && end <= sc1;
+        int n = 0;
+#pragma unroll
+        for (int stat = 0; stat < 3; ++stat) {
+            if (!(WANT & (1 << stat))) continue;
+            const float x[CH] = {sum[n][0], sum[n][1], sum[n][2], sum[n][3]};
+            ++n;
+            if (inside) store_chunk<ALIGN>((stat == 0 ? S_id : stat == 1 ? S_sq : S_sg) + (int64_t)v * d + col, x, d);
+            else store_chunk<ALIGN, false>(partial + (((int64_t)group * 2 + (goes_on_from ? 0 : 1)) * 3 + stat) * d + col, x, d);
+        }
+    };
+    if (wave == 0 && row_before >= 0 && from_before < sc0) combine(row_before, 0, true, to_before);
+    if (row_starting >= 0) combine(row_starting, 1, false, to_starting);
 }
 
 // Finishes the long runs that span several workgroups of embed_rows_kernel: the workgroup-sized slice s in which such a
