@@ -350,6 +350,22 @@ pex_status pex_moment_track(float *ema_adam, float *ema_micro, const float *S_id
                             size_t workspace_bytes, pex_stream_t stream);
 
 /*
+ * pex_stat_pair_batch -- identity and square (pex_stat_multi) of several layers of one batch: same B, T and type, widths of their own.
+ * bf16 layers on 256 x 128 blocks share launches and are cut into fewer groups of examples; the sums are those of pex_stat_multi in
+ * another order of the groups (fp32 rounding).  All other layers are done one by one.  items: host array.  The query returns what the
+ * shared launches need; a workspace that is enough for each layer's pex_stat_multi is accepted.  Checks and error codes as
+ * pex_stat_multi, for every item before anything is launched.
+ */
+typedef struct {
+    const void *X, *G;
+    float *S_id, *S_sq;
+    int64_t din, dout;
+} pex_pair_item;
+size_t pex_stat_pair_batch_workspace_bytes(const pex_pair_item *items, int32_t count, int64_t B, int64_t T, pex_dtype dt);
+pex_status pex_stat_pair_batch(const pex_pair_item *items, int32_t count, int64_t B, int64_t T, pex_dtype dt, void *workspace,
+                               size_t workspace_bytes, pex_stream_t stream);
+
+/*
  * pex_vec_stat_batch -- pex_vec_stat of several vectors of one batch (same B, T and type) together: the same results in one launch
  * of each pass, where a vector of a few thousand columns is mostly the cost of its launches.  items: host array; C is NULL for
  * an offset; outputs not in `want` are ignored.  Vectors whose partial sums do not fit the workspace together are done one

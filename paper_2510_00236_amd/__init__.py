@@ -39,7 +39,7 @@ EXPORTS = ("pex_status_string", "pex_version", "pex_stat_workspace_bytes", "pex_
            "pex_moment_track_workspace_bytes", "pex_moment_track", "pex_embed_stat_workspace_bytes", "pex_embed_stat",
            "pex_mfma_probe_operand_bytes", "pex_mfma_probe_sink_floats", "pex_mfma_probe",
            "pex_sum_squares_workspace_bytes", "pex_sum_squares", "pex_adam_update_clipped", "pex_stat_noalloc", "pex_set_option", "pex_get_option", "pex_clip_weights",
-           "pex_vec_stat_batch_workspace_bytes", "pex_vec_stat_batch", "pex_adam_step_workspace_bytes", "pex_adam_step")
+           "pex_stat_pair_batch_workspace_bytes", "pex_stat_pair_batch", "pex_vec_stat_batch_workspace_bytes", "pex_vec_stat_batch", "pex_adam_step_workspace_bytes", "pex_adam_step")
 
 
 class PexError(RuntimeError):
@@ -138,6 +138,10 @@ def lib() -> ctypes.CDLL:
         L.pex_sum_squares.restype = ctypes.c_int
         L.pex_adam_update_clipped.argtypes = [p, p, p, p, p, i64, ctypes.c_int, ctypes.POINTER(AdamParams), p, f, p]
         L.pex_adam_update_clipped.restype = ctypes.c_int
+        L.pex_stat_pair_batch_workspace_bytes.argtypes = [p, i32, i64, i64, ctypes.c_int]
+        L.pex_stat_pair_batch_workspace_bytes.restype = sz
+        L.pex_stat_pair_batch.argtypes = [p, i32, i64, i64, ctypes.c_int, p, sz, p]
+        L.pex_stat_pair_batch.restype = ctypes.c_int
         L.pex_vec_stat_batch_workspace_bytes.argtypes = [p, i32, i64, i64, ctypes.c_int]
         L.pex_vec_stat_batch_workspace_bytes.restype = sz
         L.pex_vec_stat_batch.argtypes = [p, i32, i64, i64, ctypes.c_int, ctypes.c_uint32, p, sz, p]
@@ -448,6 +452,44 @@ def _table(rows):
             raise ValueError(f"{r.name} must live in GPU memory (libpex has no CPU path)")
     a = _array("q", rows)
     return a, a.buffer_info()[0]
+
+
+def pex_stat_pair_batch_workspace_bytes(widths, B, T, dtype_code) -> int:
+    """For layers of ``widths`` (din, dout)."""
+    a, at = _table([x for din, dout in widths for x in (0, 0, 0, 0, din, dout)])
+    return int(lib().pex_stat_pair_batch_workspace_bytes(at, len(widths), B, T, dtype_code))
+
+
+def pex_stat_pair_batch(layers, workspace=None, stream=None):
+    """pex_stat_multi(identity, square) of several layers of one batch, as few launches as their sizes allow: ``layers`` are
+    (X, G, out dict or None) with the same B, T and type.  Returns a list of dicts name -> S[din,dout] fp32."""
+    if _torch is None:
+        _bind_torch()
+    X0 = layers[0][0]
+    res, rows, widths = [], [], []
+    for X, G, out in layers:
+        _, _, din, dout = _shapes(X, G)
+        if X.shape[:2] != X0.shape[:2]:
+            raise ValueError("expected layers of one batch: the same B and T")
+        if X.dtype != X0.dtype:
+            raise TypeError("all layers must share a dtype")
+        rows += (_dev(X, "X"), _dev(G, "G"))
+        r = {}
+        for name in ("identity", "square"):
+            S = (out or {}).get(name)
+            if S is None:
+                S = _torch.empty(din, dout, dtype=_F32, device=X.device)
+            r[name] = S
+            rows.append(_f32(S, name, shape=(din, dout)))
+        rows += (din, dout)
+        widths.append((din, dout))
+        res.append(r)
+    B, T, dt = X0.shape[0], X0.shape[1], _dtype_code(X0)
+    keep, at = _table(rows)
+    query, qargs = pex_stat_pair_batch_workspace_bytes, (widths, B, T, dt)
+    ws, wptr, wbytes = _workspace(query, qargs, X0, workspace, stream)
+    _invoke_ws(query, qargs, ws, lib().pex_stat_pair_batch, at, len(layers), B, T, dt, wptr, wbytes, _stream(stream))
+    return res
 
 
 def pex_vec_stat_batch_workspace_bytes(widths, B, T, dtype_code) -> int:

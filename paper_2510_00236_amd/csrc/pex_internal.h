@@ -93,6 +93,16 @@ hipError_t launch_stat_bf16_pair(const void* X, const void* G, int64_t B, int64_
 bool bf16_triple_supported(const StatPlan& plan);
 hipError_t launch_stat_bf16_triple(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
                                    const StatPlan& plan, float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
+// Identity and square of up to PAIR_BATCH layers of one batch in one launch: nsplit groups of per_split examples each; the outputs are S
+// where nsplit == 1, else [nsplit][din][dout] partial sums
+constexpr int PAIR_BATCH = 6;
+struct PairItem {
+    const void *X, *G;
+    float *out_id, *out_sq;
+    int64_t din, dout;
+};
+int64_t bf16_pair_blocks(int64_t din, int64_t dout);
+hipError_t launch_stat_bf16_pair_batch(const PairItem* items, int count, int64_t B, int64_t T, int64_t nsplit, int64_t per_split, hipStream_t stream);
 bool bf16_supports(int64_t B, int64_t T, int64_t din, int64_t dout);
 bool f32_mfma_supports(int64_t B, int64_t T, int64_t din, int64_t dout);
 void f32_tile_shape(int64_t din, int64_t dout, int* bm, int* bn);
@@ -160,6 +170,16 @@ struct ReduceOutputs {
 };
 hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
                                   int64_t ld, hipStream_t stream, int leading = 0);
+
+// The same of up to 2 * PAIR_BATCH outputs of n[k] floats (a multiple of four) in one launch, nsplit groups each, n[k] apart
+struct ReduceBatch {
+    int count;
+    unsigned first[2 * PAIR_BATCH + 1];
+    const float* partial[2 * PAIR_BATCH];
+    float* S[2 * PAIR_BATCH];
+    int64_t n[2 * PAIR_BATCH];
+};
+hipError_t launch_reduce_batch(ReduceBatch b, int nsplit, hipStream_t stream);       // `first` is set here
 
 hipError_t launch_adam_update(float* theta, float* m, float* v, const float* S_id, const float* S_sq, int64_t n,
                               pex_adam_variant variant, const pex_adam_params& p, hipStream_t stream,

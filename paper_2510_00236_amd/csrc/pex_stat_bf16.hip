@@ -214,15 +214,16 @@ __device__ __forceinline__ int chunk_at_position(int pos, int r)
     else return (pos + ROW_BYTES / 16 - 4 * ((r >> 1) & 1)) % (ROW_BYTES / 16);
 }
 
+// One workgroup: block (tm, tn) of S for the examples (or rows) of group `split`.
 template <typename TL, int OUTS>
-__global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ G,
-                                                              int64_t rows_total, int seg_len, int din, int dout, int ldg, int ldo,
-                                                              int store_rows, int store_cols,
-                                                              int64_t rows_per_split, int tiles_m, int tiles_n,
-                                                              float* __restrict__ out_id, float* __restrict__ out_sq,
-                                                              float* __restrict__ out_sg, const float* __restrict__ weight,
-                                                              float* __restrict__ norm_partial, int examples_total, float alpha,
-                                                              int byte_partials)
+__device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, const uint16_t* __restrict__ G,
+                                                int64_t rows_total, int seg_len, int din, int dout, int ldg, int ldo,
+                                                int store_rows, int store_cols,
+                                                int64_t rows_per_split, int tiles_m, int tiles_n,
+                                                float* __restrict__ out_id, float* __restrict__ out_sq,
+                                                float* __restrict__ out_sg, const float* __restrict__ weight,
+                                                float* __restrict__ norm_partial, int examples_total, float alpha,
+                                                int byte_partials, int split, int tm, int tn)
 {
     constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, NS = TL::NS, FM = TL::FM, FN = TL::FN, KS = TL::KS;
     constexpr int XROW = TL::XROW, GROW = TL::GROW, NXI = TL::NXI, NGI0 = TL::NGI0, NGI1 = TL::NGI1, RX = TL::RX;
@@ -244,8 +245,6 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
     static_assert(!(HAS_POW && ((OUTS & OUT_SQ) || HAS_W)), "the power statistic uses the square's register tile and the weight slot");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
-    int split, tm, tn;
-    map_workgroup(tiles_m, tiles_n, split, tm, tn);
     const int i0 = tm * BM, j0 = tn * BN;
     const int64_t row_begin = (int64_t)split * rows_per_split;
     int64_t row_end = row_begin + rows_per_split;
@@ -668,6 +667,22 @@ __global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __
         }
 }
 
+template <typename TL, int OUTS>
+__global__ __launch_bounds__(TL::NT, 1) void stat_bf16_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ G,
+                                                              int64_t rows_total, int seg_len, int din, int dout, int ldg, int ldo,
+                                                              int store_rows, int store_cols,
+                                                              int64_t rows_per_split, int tiles_m, int tiles_n,
+                                                              float* __restrict__ out_id, float* __restrict__ out_sq,
+                                                              float* __restrict__ out_sg, const float* __restrict__ weight,
+                                                              float* __restrict__ norm_partial, int examples_total, float alpha,
+                                                              int byte_partials)
+{
+    int split, tm, tn;
+    map_workgroup(tiles_m, tiles_n, split, tm, tn);
+    stat_bf16_block<TL, OUTS>(X, G, rows_total, seg_len, din, dout, ldg, ldo, store_rows, store_cols, rows_per_split, tiles_m, tiles_n, out_id, out_sq,
+                              out_sg, weight, norm_partial, examples_total, alpha, byte_partials, split, tm, tn);
+}
+
 // out = bf16(in^2), 8 values per lane per step
 __global__ __launch_bounds__(256) void square_bf16_kernel(const uint4_t* __restrict__ in, uint4_t* __restrict__ out, int64_t n16)
 {
@@ -738,6 +753,31 @@ hipError_t launch_one(const uint16_t* X, const uint16_t* G, int64_t B, int64_t T
     kern<<<grid, block, TL::LDS_BYTES, stream>>>(X, G, B * T, (int)T, (int)din, (int)dout, (int)ldg, (int)ldo, (int)store_rows,
                                                  (int)store_cols, rows_per_split, tiles_m, tiles_n, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, byte_partials ? 1 : 0);
     return hipGetLastError();
+}
+
+// Identity and square of several layers of one batch in one launch, the layers' workgroups one after the other.  A layer by itself is cut
+// into as many groups of examples as fill the chip, whose partial sums are written and read again; layers that fill it together need fewer,
+// and one start and end.  Four layers of a block, us, by themselves -> together: GPT-2-small, B=64 T=1024 (54 + 18 + 72 + 72 blocks;
+// 4, 13, 7 and 7 groups -> 8: 7 rounds of 8 examples for 8) 1162 -> 1114; d=320, B=21 T=285 (8, 21, 11, 11 -> 4) 105 -> 52; d=128, B=12
+// T=94 (12 -> 6) 58 -> 18.
+struct PairLayers {
+    int count;
+    unsigned first[PAIR_BATCH + 1];
+    const uint16_t *X[PAIR_BATCH], *G[PAIR_BATCH];
+    float *out_id[PAIR_BATCH], *out_sq[PAIR_BATCH];
+    int din[PAIR_BATCH], dout[PAIR_BATCH], tiles_m[PAIR_BATCH], tiles_n[PAIR_BATCH];
+};
+
+__global__ __launch_bounds__(TilePhi::NT, 1) void stat_pair_batch_kernel(PairLayers l, int64_t rows_total, int seg_len, int64_t rows_per_split,
+                                                                         int examples_total)
+{
+    int k = 0;
+    while (k + 1 < l.count && blockIdx.x >= l.first[k + 1]) ++k;
+    const int din = l.din[k], dout = l.dout[k], tiles_m = l.tiles_m[k], tiles_n = l.tiles_n[k];
+    int split, tm, tn;
+    map_workgroup((int)(l.first[k + 1] - l.first[k]), (int)(blockIdx.x - l.first[k]), tiles_m, tiles_n, split, tm, tn);
+    stat_bf16_block<TilePhi, OUT_ID | OUT_SQ>(l.X[k], l.G[k], rows_total, seg_len, din, dout, dout, dout, din, dout, rows_per_split, tiles_m,
+                                              tiles_n, l.out_id[k], l.out_sq[k], nullptr, nullptr, nullptr, examples_total, 0.f, 0, split, tm, tn);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1210,6 +1250,36 @@ hipError_t launch_stat_bf16_pair(const void* X, const void* G, int64_t B, int64_
         return launch_one<TilePhi, OUT_SQ | OUT_SIGN_F32>(x, g, B, T, din, dout, plan, nullptr, out_sq, out_sg, stream);
     }
     return hipErrorInvalidValue;
+}
+
+int64_t bf16_pair_blocks(int64_t din, int64_t dout) { return ((din + TilePhi::BM - 1) / TilePhi::BM) * ((dout + TilePhi::BN - 1) / TilePhi::BN); }
+
+hipError_t launch_stat_bf16_pair_batch(const PairItem* items, int count, int64_t B, int64_t T, int64_t nsplit, int64_t per_split, hipStream_t stream)
+{
+    if (count < 1 || count > PAIR_BATCH) return hipErrorInvalidValue;
+    PairLayers l{};
+    l.count = count;
+    unsigned at = 0;
+    for (int k = 0; k < count; ++k) {
+        const PairItem& it = items[k];
+        l.first[k] = at;
+        l.X[k] = (const uint16_t*)it.X;
+        l.G[k] = (const uint16_t*)it.G;
+        l.out_id[k] = it.out_id;
+        l.out_sq[k] = it.out_sq;
+        l.din[k] = (int)it.din;
+        l.dout[k] = (int)it.dout;
+        l.tiles_m[k] = (int)((it.din + TilePhi::BM - 1) / TilePhi::BM);
+        l.tiles_n[k] = (int)((it.dout + TilePhi::BN - 1) / TilePhi::BN);
+        at += (unsigned)((int64_t)l.tiles_m[k] * l.tiles_n[k] * nsplit);
+    }
+    l.first[count] = at;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [] { attr_err = hipFuncSetAttribute((const void*)stat_pair_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TilePhi::LDS_BYTES); });
+    if (attr_err != hipSuccess) return attr_err;
+    stat_pair_batch_kernel<<<dim3(at), dim3(TilePhi::NT), TilePhi::LDS_BYTES, stream>>>(l, B * T, (int)T, per_split * T, (int)B);
+    return hipGetLastError();
 }
 
 }  // namespace pex

@@ -230,6 +230,30 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, 
     }
 }
 
+// Several outputs of the same number of groups, the blocks of one after the other
+__global__ __launch_bounds__(256) void reduce_batch_kernel(ReduceBatch b, int nsplit)
+{
+    int k = 0;
+    while (k + 1 < b.count && blockIdx.x >= b.first[k + 1]) ++k;
+    const float* __restrict__ partial = b.partial[k];
+    float* __restrict__ S = b.S[k];
+    const int64_t n = b.n[k], stride = (int64_t)(b.first[k + 1] - b.first[k]) * 1024;
+    for (int64_t e = (int64_t)(blockIdx.x - b.first[k]) * 1024 + 4 * threadIdx.x; e < n; e += stride) {
+        const float* p = partial + e;
+        float4_v s = *(const float4_v*)p;
+        int g = 1;
+        for (; g + 4 <= nsplit; g += 4) {
+            float4_v v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = *(const float4_v*)(p + (g + u) * n);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s += v[u];
+        }
+        for (; g < nsplit; ++g) s += *(const float4_v*)(p + g * n);
+        *(float4_v*)(S + e) = s;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_stat_generic(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
@@ -336,6 +360,19 @@ hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit
     int64_t blocks = (rows * ((cols + 3) / 4) + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     reduce_partials_kernel<<<dim3((unsigned)blocks, (unsigned)count), dim3(256), 0, stream>>>(io, nsplit, group_stride, rows, cols, pitch, ld, leading);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce_batch(ReduceBatch b, int nsplit, hipStream_t stream)
+{
+    unsigned at = 0;
+    for (int k = 0; k < b.count; ++k) {
+        b.first[k] = at;
+        const int64_t blocks = (b.n[k] + 1023) / 1024;
+        at += (unsigned)(blocks < 4096 ? blocks : 4096);
+    }
+    b.first[b.count] = at;
+    reduce_batch_kernel<<<dim3(at), dim3(256), 0, stream>>>(b, nsplit);
     return hipGetLastError();
 }
 

@@ -62,14 +62,14 @@ def block_inputs(B, T, d, V, dev, seed=0):
 def microadam_step(tensors, inputs, V, step, B, lr=2e-3, max_norm=1e-2, workspace=None, track=True):
     dense, scale = inputs["dense"], inputs["scale"]
     ws = workspace
-    # 1. statistics: dense layers, then all offsets and scales together, then the embedding
-    vectors = []
+    # 1. statistics: all dense layers together, all offsets and scales together, then the embedding
+    layers, vectors = [], []
     for name, (X, G) in dense.items():
         w, b = tensors[name], tensors[name + ".bias"]
         din, dout = X.shape[2], G.shape[2]
-        pex.pex_stat_multi(X, G, ("identity", "square"),
-                           out={"identity": w.S_id.view(din, dout), "square": w.S_sq.view(din, dout)}, workspace=ws)
+        layers.append((X, G, {"identity": w.S_id.view(din, dout), "square": w.S_sq.view(din, dout)}))
         vectors.append((G, None, {"identity": b.S_id, "square": b.S_sq}))
+    pex.pex_stat_pair_batch(layers, workspace=ws)
     for name, (A, C) in scale.items():
         vectors.append((A, C, {"identity": tensors[name].S_id, "square": tensors[name].S_sq}))
     pex.pex_vec_stat_batch(vectors, ("identity", "square"), workspace=ws)
@@ -98,8 +98,7 @@ def build(B, T, d, V, dev):
     tensors["_norm"] = torch.zeros(1, dtype=torch.float64, device=dev)
     tensors["_moments"] = torch.zeros(n_t, 2, dtype=torch.float64, device=dev)
     need = [16]
-    for X, G in inputs["dense"].values():
-        need.append(pex.pex_stat_multi_workspace_bytes(B, T, X.shape[2], G.shape[2], pex.PEX_BF16, 3))
+    need.append(pex.pex_stat_pair_batch_workspace_bytes([(X.shape[2], G.shape[2]) for X, G in inputs["dense"].values()], B, T, pex.PEX_BF16))
     widths = [G.shape[2] for _, G in inputs["dense"].values()] + [A.shape[2] for A, _ in inputs["scale"].values()]
     need.append(pex.pex_vec_stat_batch_workspace_bytes(widths, B, T, pex.PEX_BF16))
     need.append(pex.pex_embed_stat_workspace_bytes(B, T, V, d))
