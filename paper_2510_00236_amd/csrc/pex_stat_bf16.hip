@@ -314,7 +314,7 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
     // stays zero -- and is written to LDS once.  Squaring it in place in LDS (a read and a write of every byte on top of the
     // load's own write) cost 60 % over the plain contraction; this way the LDS sees one write per byte, as it does
     // from a direct load.  Two register sets: slab s uses set s mod 2, its loads are issued two slabs before it is
-    // written to the ring, which happens one slab before its first reader; the compiler tracks these loads itself.
+    // written to the ring (and squared between the MFMAs of the slab before that), which happens one slab before its first reader; the compiler tracks these loads itself.
     // (load_slab repeats the slab bookkeeping of issue_slab on purpose: sharing it through a helper changed the code
     // generated for every other flavour -- about 50 more instructions per kernel, phi = square 4 % slower.)
     [[maybe_unused]] uint4_t stage[2][TOKEN ? LPS : 1];
@@ -336,14 +336,17 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
         if (iss_off >= slen) iss_off = 0;
         ++iss_slab;
     };
-    auto square_store = [&](auto SETC, int buf) {
+    auto square_set = [&](auto SETC) {
         constexpr int S = decltype(SETC)::value;
-        unsigned char* bx = lds + buf * TL::STAGE;
-        unsigned char* bg = bx + TL::X_BYTES;
 #pragma unroll
         for (int n = 0; n < (TOKEN ? LPS : 1); ++n)
 #pragma unroll
             for (int e = 0; e < 4; ++e) stage[S][n][e] = square_pair_rne(stage[S][n][e]);
+    };
+    auto store_set = [&](auto SETC, int buf) {
+        constexpr int S = decltype(SETC)::value;
+        unsigned char* bx = lds + buf * TL::STAGE;
+        unsigned char* bg = bx + TL::X_BYTES;
 #pragma unroll
         for (int n = 0; n < NXI; ++n) *(lds_u4)(bx + (wave * NXI + n) * 1024 + lane * 16) = stage[S][n];
 #pragma unroll
@@ -434,7 +437,7 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
                 if (ks < KS - 1 || f < FPK - RC) read_frag(ks, f);
         issue_slab(GROUPC);   // after the reads: a wave that stalls on the memory pipeline here has its reads in flight
     };
-    // per-token square: after the reads of slab g, this wave's part of slab g+1 is squared and written to the ring (a
+    // per-token square: after the reads of slab g, this wave's part of slab g+1, squared by then, is written to the ring (a
     // phase or more ahead of its first reader), and the registers it leaves take the loads of slab g+3
     auto read_phase_staged = [&](auto SETC) {
         rd_bx = lds + rd_buf * TL::STAGE;
@@ -444,14 +447,20 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
 #pragma unroll
             for (int f = 0; f < FPK; ++f)
                 if (ks < KS - 1 || f < FPK - RC) read_frag(ks, f);
-        square_store(SETC, rd_buf);
+        store_set(SETC, rd_buf);
         load_slab(SETC);
     };
     // Multiply phase: MFMA number i is followed by fragment read i of the last k-step (while i < RC).  The
     // scheduling fences pin this order; the compiler adds the LDS waits the MFMAs need.  The G fragment index runs
     // back and forth ("snake"), so consecutive MFMAs share an operand register wherever they can: measured +2 % on an
     // MFMA-only loop (less switching on the operand reads, and the chip's clock is set by power).
-    auto multiply_phase = [&]() {
+    // SQUARE >= 0 (per-token square): the part of slab g+2 in that register set is squared between the last MFMAs, five vector
+    // instructions to a pair of values, two pairs after every three MFMAs -- under the 16 cycles of each, where in the read phase they
+    // made that phase the longer one.
+    auto multiply_phase = [&](auto SQUAREC) {
+        constexpr int SQUARE = decltype(SQUAREC)::value;
+        constexpr int PAIRS = TOKEN ? 4 * LPS : 0, MFMAS = KS * FM * FN, FIRST = MFMAS - 3 * PAIRS / 2;
+        static_assert(!TOKEN || FIRST >= RC, "the squares follow the late reads");
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -468,6 +477,13 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
                     if (late >= 0) {
                         read_frag(KS - 1, FPK - RC + late);
                         __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (SQUARE >= 0) {
+                        if (i >= FIRST && (i - FIRST) % 3 != 2) {
+                            const int w = (i - FIRST) / 3 * 2 + (i - FIRST) % 3;
+                            stage[SQUARE][w / 4][w % 4] = square_pair_rne(stage[SQUARE][w / 4][w % 4]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
                 }
         __builtin_amdgcn_s_setprio(0);
@@ -560,15 +576,17 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
         if (total > 0) {
             load_slab(S0);
             load_slab(S1);
-            square_store(S0, 0);
+            square_set(S0);
+            store_set(S0, 0);
             load_slab(S0);                        // slab 2
+            square_set(S1);
             wait_lds_and_barrier();               // slab 0 is visible to every wave
             // iteration g writes slab g+1 from set (g+1) mod 2: two iterations per trip, so that the set is fixed in the code
             auto iteration = [&](auto SETC) {
                 read_phase_staged(SETC);
                 __builtin_amdgcn_sched_barrier(0);
                 wait_lds_and_barrier();
-                multiply_phase();
+                multiply_phase(std::integral_constant<int, 1 - decltype(SETC)::value>{});
                 __builtin_amdgcn_sched_barrier(0);
                 plain_barrier();
             };
@@ -583,6 +601,7 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
         }
     } else
     if (total > 0) {
+        constexpr std::integral_constant<int, -1> NONE{};
         if (group == 0) {
 #pragma unroll
             for (int s = 0; s < AHEAD0; ++s) issue_slab(G0);
@@ -599,7 +618,7 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
                 read_phase(G0);
                 __builtin_amdgcn_sched_barrier(0);
                 wait_lds_and_barrier();       // ends phase 2g
-                multiply_phase();
+                multiply_phase(NONE);
                 __builtin_amdgcn_sched_barrier(0);
                 wait_vmcnt<INFLIGHT0>();   // this wave's part of slab g+1 has landed
                 plain_barrier();              // ends phase 2g+1
@@ -613,7 +632,7 @@ __device__ __forceinline__ void stat_bf16_block(const uint16_t* __restrict__ X, 
                 __builtin_amdgcn_sched_barrier(0);
                 wait_vmcnt<INFLIGHT1>();   // this wave's part of slab g+1 has landed
                 wait_lds_and_barrier();       // ends phase 2g+1
-                multiply_phase();
+                multiply_phase(NONE);
                 __builtin_amdgcn_sched_barrier(0);
                 plain_barrier();              // ends phase 2g+2
                 if (PER_EXAMPLE && ++st_in_seg == nst) { st_in_seg = 0; fold_all(); }
