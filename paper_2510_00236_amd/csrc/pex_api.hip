@@ -429,14 +429,15 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
     p.nsplit = (int)nsplit;
     p.per_split = per_example ? per : per * slab;
     // Per-token square on the MFMA kernel: squaring the operands inside the kernel (global -> registers -> LDS instead
-    // of direct-to-LDS loads, plus the arithmetic) costs about +50 % time; squaring them once into bf16 copies costs one
+    // of direct-to-LDS loads) costs about +42 % time; squaring them once into bf16 copies costs one
     // pass over X and G at HBM speed (~5.5 TB/s, 4 bytes moved per element).  The copies win when din*dout/(din+dout)
-    // is large.
+    // is large.  Measured, inside and by copies, us: 32 x 1024 tokens, 1280x5120 464, 503; 16 x 1024, 1536x6144 348, 344;
+    // 16 x 1024, 2048x4096 270, 261; 16 x 2048, 2048x8192 963, 925.
     const int presquare = options[PEX_OPT_TOKEN_PRESQUARE];
     if (mode == MODE_TOKEN_SQ && p.kernel == 1 && presquare != 0 && !p.square_halves) {
         const double elems = (double)B * (double)T * (double)(din + dout);
         const double t_pre = 4.0 * elems / 5.5e12 + 6.0e-6;
-        const double t_fused_extra = 0.5 * 2.0 * (double)B * (double)T * (double)din * (double)dout / 1.3e15;
+        const double t_fused_extra = 0.42 * 2.0 * (double)B * (double)T * (double)din * (double)dout / 1.3e15;
         if (t_pre < t_fused_extra || presquare == 2) p.copy_x = p.copy_g = true;
     }
     const size_t copied = (p.copy_x ? (size_t)din : 0) + (p.copy_g ? (size_t)dout : 0);
