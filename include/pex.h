@@ -107,7 +107,7 @@ int32_t pex_get_option(pex_option opt);
  * phi = sign is B * (avg o sign) of Sec. 3.1).
  *
  *   X  [B,T,din], G [B,T,dout]  device, dtype `dt` (bf16 payloads are multiplied exactly and summed in
- *                               fp32; fp32 payloads use true fp32 products), read-only.
+ *                               fp32; products of fp32 payloads are good to 2^-24 and summed in fp32), read-only.
  *   S  [din,dout] fp32 device, overwritten.  For phi = sign the entries are integers in [-B, B]
  *                               (sgn(0) = 0) stored as fp32, exact for B < 2^24.
  *   workspace / workspace_bytes device scratch of at least pex_stat_workspace_bytes(...) bytes with the

@@ -134,18 +134,19 @@ static double cheapest_split_f32(int64_t tiles, int64_t units, int64_t rows_per_
     return best;
 }
 
-// fp32 layers on the bf16 matrix cores: blocks of 128 x 128, two of them on a compute unit.  A slab of 32 tokens takes 1.75 us when
-// a block has its unit to itself, two slabs 2.45 us when two blocks share one; the fold of an example 0.5 us (signs and norms 0.9);
-// a launch 5 us to start and end, norms another 2 us with every round of blocks (their partial sums leave after every example).
-// Identity and square together also add S_id up in memory: 64 KiB per block and example, read and written at 3.9 TB/s, of which a fifth of
-// the contraction's time is hidden (2048 x 2048, B=32 T=64: 21 us an example; 2048 x 4096, B=8 T=1024: 6 us).  Fitted on 150 drawn
-// layers of 8 to 700 us and eight statistics: the estimates are within 16 % for nine in ten.
+// fp32 layers on the bf16 matrix cores: blocks of 128 x 128, two of them on a compute unit.  A slab of 32 tokens takes 1.9 us when
+// a block has its unit to itself, two slabs 2.5 us when two blocks share one; the fold of an example 0.6 us (signs and powers 1.3, norms 3.5);
+// a launch 8.6 us to start and end (norms 3.8, and 0.3 with every round of blocks).  Partial sums at 6.3 TB/s, 2.4 us for their launch.
+// Identity and square together also add S_id up in memory: 64 KiB per block and example, read and written at 4.3 TB/s, of which a seventh of
+// the contraction's time is hidden (2048 x 2048, B=32 T=64: 21 us an example; 2048 x 4096, B=8 T=1024: 6 us).  Fitted on 140 drawn
+// layers of 8 to 700 us and six statistics: the estimates are within 8 % for four in five, of the pair within 12 %.
 static double cheapest_split_f32_pieces(int64_t blocks, int64_t units, int64_t slabs_per_unit, Mode mode, bool pair, double s_bytes, int max_split,
                                         int64_t* nsplit, int64_t* per)
 {
-    constexpr double SLAB_ALONE = 1.75e-6, SLABS_SHARED = 2.45e-6;
+    constexpr double SLAB_ALONE = 1.93e-6, SLABS_SHARED = 2.46e-6;
+    const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
     const double slabs = (double)slabs_per_unit;
-    const double t_fold = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ ? 0.0 : mode == MODE_SIGN || mode == MODE_NORMS ? 0.9e-6 : 0.5e-6;
+    const double t_fold = plain ? 0.1e-6 : mode == MODE_SIGN || mode == MODE_POWER ? 1.33e-6 : mode == MODE_NORMS ? 3.5e-6 : 0.59e-6;
     double best = 0.0;
     const int64_t lim = units < max_split ? units : max_split;
     for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
@@ -154,12 +155,12 @@ static double cheapest_split_f32_pieces(int64_t blocks, int64_t units, int64_t s
         const int64_t wgs = blocks * ns_eff, per_cu = (wgs + 255) / 256;
         double t_unit = t_fold;
         if (pair) {
-            const double memory = 1.25 * 2.0 * 65536.0 * (double)(wgs < 512 ? wgs : 512) / 3.9e12 - 0.2 * slabs * SLABS_SHARED;
+            const double memory = 0.9 * 2.0 * 65536.0 * (double)(wgs < 512 ? wgs : 512) / 3.9e12 - 0.14 * slabs * SLABS_SHARED;
             if (memory > 0.0) t_unit += memory;
         }
-        double cost = (double)pu * ((double)(per_cu / 2) * (slabs * SLABS_SHARED + t_unit) + (double)(per_cu % 2) * (slabs * SLAB_ALONE + t_unit)) + 5.0e-6;
-        if (mode == MODE_NORMS) cost += (double)((per_cu + 1) / 2) * 2.0e-6;
-        else if (ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes * (pair ? 2.0 : 1.0) / 4.0e12 + 2.5e-6;
+        double cost = (double)pu * ((double)(per_cu / 2) * (slabs * SLABS_SHARED + t_unit) + (double)(per_cu % 2) * (slabs * SLAB_ALONE + t_unit));
+        cost += mode == MODE_NORMS ? 3.75e-6 + (double)((per_cu + 1) / 2) * 0.3e-6 : 8.6e-6;
+        if (mode != MODE_NORMS && ns_eff > 1) cost += (2 * ns_eff + 1) * s_bytes * (pair ? 2.0 : 1.0) / 6.3e12 + 2.35e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -325,8 +326,7 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
         const double s_bytes = mode == MODE_NORMS ? 0.0 : (double)din * (double)dout * 4.0;
         const int most = !held || fit > max_split ? max_split : (fit < 1 ? 1 : (int)fit);
         const double direct = p.seconds = cheapest_split_f32(tiles, units, per_example ? T : slab, t_fold, (bm / 64) * (bn / 64), s_bytes, most, &nsplit, &per);
-        // ... or split into bf16 pieces, where that is faster (never for examples of fewer than 48 tokens: there its sums of 32 tokens
-        // are no more exact than the fp32 ones, 1.39e-7 against 1.38e-7 of the 2-norm at T = 32, 1.51e-7 against 1.60e-7 at T = 48)
+        // ... or split into bf16 pieces, where that is faster (never for examples of fewer than 48 tokens, a slab and a half: not compared)
         if (allow_pad && f32_split_supports(B, T, din, dout) && (per_example ? T : B * T) >= 48) {
             int64_t ns_p = 1, per_p = units;
             const int64_t blocks = f32_split_blocks(din, dout), fit_p = (((int64_t)1 << 32) - 1) / (blocks * 256);
