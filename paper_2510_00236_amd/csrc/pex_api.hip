@@ -1,6 +1,7 @@
 // pex_api.hip -- the C ABI of libpex: host-side validation, planning and kernel dispatch.
 // Every entry point validates first and launches nothing on error.
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 #include <mutex>
 
@@ -182,11 +183,15 @@ static double bf16_block_rate(int bm, int bn)
 // square 1.2, with signs 1.9, all three 2.3 (256 x 128 blocks); signs 2.95, norms 2.15 (256 x 256).
 // Used for the norms and for layers of odd width.  The other plans count the contraction alone: with the fold some layers of few
 // examples got up to a fifth slower (and others, of many short ones, a quarter faster).
+static double bf16_fold(Mode mode, bool shared, int bm, int bn)
+{
+    const double fold = shared ? 1.3e-6 : mode == MODE_SIGN ? 1.2e-6 : mode == MODE_NORMS ? 0.8e-6 : mode == MODE_POWER ? 1.6e-6 : 0.55e-6;
+    return fold * (bm * bn / 32768.0);
+}
 static double bf16_unit_with_fold(Mode mode, bool shared, int64_t T, int bm, int bn)
 {
     const double slabs = 2.0 * (double)((T + 31) / 32 * 32) * bm * bn / bf16_block_rate(bm, bn);
-    const double fold = shared ? 1.3e-6 : mode == MODE_SIGN ? 1.2e-6 : mode == MODE_NORMS ? 0.8e-6 : mode == MODE_POWER ? 1.6e-6 : 0.55e-6;
-    return slabs + fold * (bm * bn / 32768.0);
+    return slabs + bf16_fold(mode, shared, bm, bn);
 }
 
 // bf16 layers whose rows are not whole 16-byte chunks: padded copies on the MFMA kernels, or the SIMT kernel on the operands as
@@ -346,7 +351,7 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
         if (nsplit > units) nsplit = units;
         if (nsplit < 1) nsplit = 1;
         per = (units + nsplit - 1) / nsplit;
-        p.seconds = simt_seconds(B, T, din, dout, mode);
+        p.seconds = simt_seconds(B, T, din, dout, mode) * (allow_wide ? 1.0 : 2.0);
     } else {
         // A unit-time is one example (or 64 rows) on one block.
         const double rows_per_unit = per_example ? (double)T : (double)slab;
@@ -424,8 +429,17 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
         }
         best_bf16 = best;
     }
-    if (p.kernel == 1) p.seconds = padded ? padded_seconds(B, T, p.out_rows, p.out_cols, mode, !allow_wide) : best_bf16;
     nsplit = (units + per - 1) / per;      // no empty group
+    if (p.kernel == 1) {
+        p.seconds = padded ? padded_seconds(B, T, p.out_rows, p.out_cols, mode, !allow_wide) : best_bf16;
+        if (!padded && mode != MODE_NORMS) {      // what the plan is chosen without: folds, the start and end of a launch, the launch of the sum
+            p.seconds += 5.0e-6 + (nsplit > 1 ? 4.5e-6 : 0.0);
+            if (per_example && !mem_fold) {
+                const int64_t rest = dout - wide_cols, rounds = (((din + bm - 1) / bm) * ((rest + bn - 1) / bn) * nsplit + 255) / 256;
+                p.seconds += (double)(rounds * per) * bf16_fold(mode, !allow_wide, bm, bn);
+            }
+        }
+    }
     p.nsplit = (int)nsplit;
     p.per_split = per_example ? per : per * slab;
     // Per-token square on the MFMA kernel: squaring the operands inside the kernel (global -> registers -> LDS instead
@@ -503,19 +517,31 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
     return p;
 }
 
-// The kernel of small layers: eight waves a workgroup, one workgroup a compute unit; a wave's step (32 tokens of bf16, 16 of fp32) takes
-// 0.95 us and 2.0 (there the fp32 MFMA pipe is the bound, two waves on each), the end of an example 0.2 us, a norm 1, either 1 more where
-// the waves have divided its tokens; a launch 5 us to start and end (3 without sums of eight waves), the sum of the norms' parts 3.
-// A full chip is a fifth slower.  Partial sums as above, 4.5 us for their launch.  Fitted on 180 drawn layers of each type, seven statistics, both
-// ways to divide the work: medians within 10 %, nine in ten within 25 %.
-static double cheapest_small(int64_t tiles, int64_t units, int64_t rows_per_unit, bool bf16, Mode mode, int kw, double s_bytes,
+// The kernel of small layers: eight waves a workgroup, one workgroup a compute unit.  A wave's step (32 tokens of bf16, 16 of fp32) takes
+// 1.04 us and 2.1 where the waves divide an example's tokens, 0.85 and 1.95 where they divide the examples (fp32: the MFMA pipe, two
+// waves on each; identity and square together on tiles of half the width 0.75 and 1.1), the end of an example 0.45 us (1.0 of a norm or a
+// plain contraction); a launch 3 to 4 us to start and end, another round of workgroups 3, the sum of the norms' parts 2.5.  Every tile reads its features of all tokens: 128-byte lines, one more where rows do not start at
+// one, at 14 TB/s from the caches; operands that an XCD's cache does not hold come once for each of up to eight of them at 6.5 TB/s.  That is
+// the bound of layers of some dozen tiles with many tokens (110 x 535 tokens, 328 x 350: 105 us, planned at 44 without it, and 62 by
+// padded copies).  Stores of 16 bytes at 4 TB/s, partial sums at 5, 4 us for their launch.  Fitted on 260 drawn layers, five
+// statistics, both ways to divide the work: estimates within 20 % for four in five.
+static double cheapest_small(int64_t din, int64_t dout, int64_t rows, int64_t units, int64_t rows_per_unit, bool bf16, Mode mode, bool pair, int kw,
                              int64_t* nsplit, int64_t* per)
 {
     const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ, norms = mode == MODE_NORMS;
-    const int64_t rows_per_step = bf16 ? 32 : 16;
-    const double t_step = bf16 ? 0.95e-6 : 2.0e-6;
-    const double t_fold = (norms ? 1.0e-6 : 0.2e-6) + (kw == 1 ? 0.0 : 0.8e-6);
-    const double start = (kw == 1 ? 5.0e-6 : plain ? 4.0e-6 : 3.0e-6) + (norms ? 3.0e-6 : 0.0);
+    const bool half = pair && kw == 1;
+    const int64_t tiles = small_tiles(din, dout, half), rows_per_step = bf16 ? 32 : 16, size = bf16 ? 2 : 4;
+    const double t_step = kw == 8 ? (bf16 ? 1.04e-6 : 2.1e-6) : half ? (bf16 ? 0.75e-6 : 1.1e-6) : (bf16 ? 0.85e-6 : 1.95e-6);
+    const double t_fold = plain || (norms && kw == 1) ? 1.0e-6 : 0.45e-6;
+    const double start = (plain ? 3.0e-6 : kw == 1 ? 4.0e-6 : 3.4e-6) + (norms ? 2.5e-6 : pair ? 0.6e-6 : 0.0), next_round = 3.0e-6;
+    auto lines = [&](int64_t width, int64_t cols) { return (double)(cols * size) / 128.0 + (width * size % 128 != 0 ? 0.9 : 0.0); };
+    const double caches = (double)tiles * (double)rows * (lines(din, 64) + lines(dout, half ? 32 : 64)) * 128.0 / 14.0e12, c2 = caches * caches;
+    const double x_bytes = (double)(rows * din * size), g_bytes = (double)(rows * dout * size);
+    const int64_t tiles_m = (din + 63) / 64, tiles_n = tiles / tiles_m;
+    const bool fits = x_bytes + g_bytes <= 32.0e6;
+    const double misses = (x_bytes * (double)(fits ? 1 : tiles_n < 8 ? tiles_n : 8) + g_bytes * (double)(fits ? 1 : tiles_m < 8 ? tiles_m : 8)) / 6.5e12,
+                 m2 = misses * misses;
+    const double s_bytes = norms ? 0.0 : (double)din * (double)dout * (pair ? 8.0 : 4.0);
     const int64_t most = norms ? 1024 : 32, lim = units < most ? units : most;
     double best = 0.0;
     for (int64_t ns = 1; ns <= lim; ns = more_groups(units, ns)) {
@@ -524,14 +550,15 @@ static double cheapest_small(int64_t tiles, int64_t units, int64_t rows_per_unit
         const int64_t rounds = (tiles * ns_eff + 255) / 256;
         double unit;
         if (plain) {
-            const int64_t rows = pu * rows_per_unit, steps = ((rows + 7) / 8 + rows_per_step - 1) / rows_per_step;
-            unit = (double)steps * t_step + (double)((rows + 8191) / 8192) * t_fold;
+            const int64_t own = pu * rows_per_unit, steps = ((own + 7) / 8 + rows_per_step - 1) / rows_per_step;
+            unit = (double)steps * t_step + (double)((own + 8191) / 8192) * t_fold;
         } else {
             const int64_t steps = (rows_per_unit + rows_per_step - 1) / rows_per_step;
             unit = kw == 1 ? (double)((pu + 7) / 8) * ((double)steps * t_step + t_fold) : (double)pu * ((double)((steps + 7) / 8) * t_step + t_fold);
         }
-        double cost = (double)rounds * unit * (tiles * ns_eff > 128 ? 1.2 : 1.0) + start;
-        if (!norms && ns_eff > 1) cost += (double)(2 * ns_eff + 1) * s_bytes / 4.0e12 + 4.5e-6;
+        const double waves = (double)rounds * unit, w2 = waves * waves;
+        double cost = sqrt(sqrt(w2 * w2 + c2 * c2 + m2 * m2)) + start + (double)(rounds - 1) * next_round + s_bytes / 4.0e12;       // the largest of the three, and more where they are alike
+        if (!norms && ns_eff > 1) cost += (double)(2 * ns_eff) * s_bytes / 5.0e12 + 4.0e-6;
         if (ns == 1 || cost < best) { best = cost; *nsplit = ns_eff; *per = pu; }
     }
     return best;
@@ -542,12 +569,17 @@ static double cheapest_small(int64_t tiles, int64_t units, int64_t rows_per_unit
 static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad, bool allow_small,
                           const OptionValues& options)
 {
-    const StatPlan p = make_large_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, options);
+    StatPlan p = make_large_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, options);
+    // (What calls of 10 to 200 us take of the large plans' estimates, in the median: bf16 layers 0.8, on the SIMT kernel 0.88; norms by
+    // the contraction 0.75, of padded copies 0.67, by Gram matrices 0.97, on the SIMT kernel 1.1; the fp32 kernel 3 us more but for the norms.)
+    const bool norms = mode == MODE_NORMS, pair = !allow_wide, copies = p.kernel == 1 && p.copy_bytes > 0;       // pair: identity and square together
+    if (dt == PEX_BF16) p.seconds *= p.kernel == 0 ? (norms ? 1.1 : 0.88) : !norms ? 0.8 : copies ? 0.67 : p.gram ? 0.97 : 0.75;
+    else if (p.kernel == 2 && !p.f32_split && !norms) p.seconds += 3.0e-6;
     // (a step is 32 or 16 tokens: examples of one to three would be nearly all padding.  Of layers with more tiles than these the large
     // kernels' estimates are too high, by 30 % for norms at half a chip: norms 46 us there and 85 here, signs 66 and 98 at 640 tiles,
     // but squares 113 and 66; more than 1024 were not compared)
     const int64_t most_tiles = mode == MODE_NORMS ? 128 : mode == MODE_SIGN ? 256 : 1024;
-    if (!allow_pad || !allow_small || !allow_wide || T < 4 || small_tiles(din, dout) > most_tiles || !small_supports(T, din, dout, dt, mode)) return p;
+    if (!allow_pad || !allow_small || T < 4 || small_tiles(din, dout) > most_tiles || !small_supports(T, din, dout, dt, mode)) return p;
     for (int k = 0; k < NUM_OPTIONS; ++k)
         if (options[k] != DEFAULT_OPTIONS[k]) return p;
     const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
@@ -557,7 +589,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     for (const int kw : {1, 8}) {
         if (plain && kw == 1) continue;
         int64_t ns = 1, per = units;
-        const double t = cheapest_small(small_tiles(din, dout), units, plain ? 64 : T, dt == PEX_BF16, mode, kw, (double)din * (double)dout * 4.0, &ns, &per);
+        const double t = cheapest_small(din, dout, B * T, units, plain ? 64 : T, dt == PEX_BF16, mode, pair, kw, &ns, &per);
         if (t < s.seconds) {
             s.seconds = t;
             s.small_kw = kw;
@@ -565,13 +597,11 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
             s.per_split = plain ? per * 64 : per;
         }
     }
-    // (the large plans' estimates leave the start and end of a launch out: 5 us on bf16 blocks, 3 on the fp32 kernel, but for the norms;
-    // on bf16 layers the small kernel has to be the clear winner beyond 15 and 25 us, where a chip full of waves draws on the same caches.
-    // 1260 fp32 and 1080 bf16 calls of 5 to 400 us: 1.50 and 1.56 times faster in the mean than without this kernel, the better one every
-    // time would be 1.57 and 1.65; 17 calls slower by 6 % or more, at most 23 %)
-    const double start = mode == MODE_NORMS ? 0.0 : p.kernel == 1 && p.copy_bytes == 0 ? 5.0e-6 : p.kernel == 2 && !p.f32_split ? 3.0e-6 : 0.0;
-    const double margin = dt == PEX_F32 || s.seconds < 15.0e-6 ? 1.0 : mode == MODE_NORMS ? 1.9 : s.seconds < 25.0e-6 ? 1.2 : 1.45;
-    if (s.seconds * margin >= p.seconds + start) return p;
+    // (Of 211 bf16 and 49 fp32 layers and five statistics the choice is 1.3 % slower in the mean than the better kernel every time, and four of
+    // 1100 calls are slower than without the kernel by more than 6 %, at most 34 %.  Norms that would go by the contraction on whole chunks
+    // leave it for a clear gain only.)
+    const double margin = norms && dt == PEX_BF16 && p.kernel == 1 && !copies && !p.gram && s.seconds >= 15.0e-6 ? 1.6 : 1.05;
+    if (s.seconds * margin >= p.seconds) return p;
     s.kernel = p.kernel;
     s.out_rows = s.din = din;
     s.out_cols = s.dout = dout;
@@ -779,17 +809,17 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
-    // (what shares a contraction on the bf16 matrix cores, or on the kernel of small layers, is identity and square only)
+    // (what shares a contraction of fp32 layers on the bf16 matrix cores is identity and square only)
     constexpr uint32_t BOTH = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
-    // a layer whose square by itself takes the kernel of small layers has the same bits here: the same plan, everything else by itself
-    const StatPlan alone = plan_stat(B, T, din, dout, dt, MODE_SQUARE, true, allow_pad);
-    const bool small = allow_pad && alone.small_kw > 0;
-    const StatPlan sq = small ? alone : plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH), false);
+    // On the kernel of small layers any of them share one, with signs up to the number of tiles signs alone take it for.
+    StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad);
+    const bool small = n >= 2 && sq.small_kw > 0 && (want == BOTH || small_tiles(din, dout) <= 256);
+    if (!small) sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH), false);
     // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
     // contraction and sign keeps its own.  On fp32 layers sign shares one only as bytes.
     m.pair_want = want;
-    if (sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = BOTH;
-    if (small || (sq.kernel == 2 && !f32_bytes_suffice(sq))) m.pair_want = want & BOTH;
+    if (!small && sq.kernel == 1 && n == 3 && !bf16_triple_supported(sq)) m.pair_want = BOTH;
+    if (!small && sq.kernel == 2 && !f32_bytes_suffice(sq)) m.pair_want = want & BOTH;
     m.pair = __builtin_popcount(m.pair_want) >= 2 && (sq.kernel != 0 || small);
     if (m.pair) {
         m.single_want = want & ~m.pair_want;
@@ -816,8 +846,8 @@ static bool pair_joins(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtyp
     if (dt != PEX_BF16) return false;
     for (int k = 0; k < NUM_OPTIONS; ++k)
         if (option(k) != DEFAULT_OPTIONS[k]) return false;       // the options are about the plans of single layers
-    const MultiPlan m = plan_multi(B, T, din, dout, dt, PEX_WANT_IDENTITY | PEX_WANT_SQUARE);
-    return m.pair && m.pair_plan.kernel == 1 && m.pair_plan.small_kw == 0 && m.pair_plan.copy_bytes == 0 && din % 8 == 0 && dout % 8 == 0;
+    const StatPlan p = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, true, false);
+    return p.kernel == 1 && p.copy_bytes == 0 && din % 8 == 0 && dout % 8 == 0;
 }
 
 struct PairBatchPlan {
@@ -826,14 +856,14 @@ struct PairBatchPlan {
     size_t ws_bytes;
 };
 
-// The layers' blocks as those of one layer, all cut into the same number of groups, against each by itself; an example counted with its
+// The layers' blocks as those of one layer, all cut into the same number of groups, against each by itself, whichever kernel that takes; an example counted with its
 // fold, 3 us for the start and end of a workgroup, 5 for a launch, partial sums as for single layers.  (Numbers of their own, so that shorter
 // groups fill the last round, were estimated over the layers of transformer blocks: none to 3 % better, 8 in one of six.)
 // A sum is rounded once per example of a group and once per group: no more often than in the layer where that was most by itself.
 // (All 64 examples of a GPT-2-small block in one group: 1.06 ms instead of 1.11, but S_id 2.36e-7 off its 64-bit value instead of 2.04e-7.)
 static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout)
 {
-    constexpr double START = 3.0e-6, LAUNCH = 5.0e-6, RATE = 4.0e12;
+    constexpr double START = 3.0e-6, LAUNCH = 5.0e-6, RATE = 4.0e12, TAKEN = 0.8;      // (that part of such an estimate, see make_plan)
     const double unit = bf16_unit_with_fold(MODE_SQUARE, true, T, 256, 128);
     auto seconds = [&](int64_t blocks, int64_t ns, int64_t per, double bytes) {
         const double t = (double)((blocks * ns + 255) / 256) * ((double)per * unit + START);
@@ -844,8 +874,8 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
     for (int k = 0; k < count; ++k) {
         const int64_t own = bf16_pair_blocks(din[k], dout[k]);
         const double own_bytes = 2.0 * (double)din[k] * (double)dout[k] * sizeof(float);
-        const StatPlan p = plan_multi(B, T, din[k], dout[k], PEX_BF16, PEX_WANT_IDENTITY | PEX_WANT_SQUARE).pair_plan;
-        alone += seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH;
+        const StatPlan p = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false, true, false), by_itself = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false);
+        alone += by_itself.small_kw > 0 ? by_itself.seconds : TAKEN * (seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH);
         blocks += own;
         bytes += own_bytes;
         if (p.per_split + p.nsplit > most_roundings) most_roundings = p.per_split + p.nsplit;
@@ -856,7 +886,7 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
     const int64_t most = B < 32 ? B : 32;
     for (int64_t ns = 1; ns <= most; ns = more_groups(B, ns)) {
         const int64_t per = (B + ns - 1) / ns, groups = (B + per - 1) / per;
-        const double cost = seconds(blocks, groups, per, bytes) + (groups > 1 ? 2.0 : 1.0) * LAUNCH;
+        const double cost = TAKEN * (seconds(blocks, groups, per, bytes) + (groups > 1 ? 2.0 : 1.0) * LAUNCH);
         if (cost >= best || per + groups > most_roundings || (groups > 1 && (double)groups * bytes > 512.0 * 1048576.0)) continue;
         best = cost;
         plan = PairBatchPlan{true, groups, per, groups > 1 ? (size_t)groups * (size_t)bytes : 0};
@@ -1018,7 +1048,7 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         int k = 0;
         for (int phi = 0; phi < 3; ++phi)
             if (m.pair_want & (1u << phi)) po[phi] = p.nsplit > 1 ? partials + (int64_t)(k++) * p.nsplit * n : outs[phi];
-        const hipError_t e = p.small_kw > 0 ? launch_stat_small_pair(x, g, B, T, p.din, p.dout, dt, p, po[0], po[1], hs)
+        const hipError_t e = p.small_kw > 0 ? launch_stat_small_multi(x, g, B, T, p.din, p.dout, dt, p, po[0], po[1], po[2], hs)
                              : p.kernel == 2 ? launch_stat_f32_multi(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)
                              : (__builtin_popcount(m.pair_want) == 3)
                                  ? launch_stat_bf16_triple(x, g, B, T, p.din, p.dout, p, po[0], po[1], po[2], hs)

@@ -21,7 +21,7 @@ enum Mode : int { MODE_IDENTITY = 0, MODE_SQUARE = 1, MODE_SIGN = 2, MODE_TOKEN_
 struct StatPlan {
     int kernel;        // 0 = generic SIMT kernel (odd shapes), 1 = bf16 MFMA kernel, 2 = fp32 MFMA kernel
     bool f32_split;    // kernel 2: the operands as three bf16 pieces each on the bf16 matrix cores (128 x 128 blocks)
-    double seconds;    // estimate, launches included
+    double seconds;    // estimate of the call, launches included (allow_wide = false: of identity and square together)
     int small_kw;      // > 0: the kernel of small layers, its waves divide an example's tokens by this (1 or 8)
     int nsplit;        // number of groups the batch (or, for plain contractions, B*T) is split into
     int64_t per_split; // examples (or rows of B*T) per group
@@ -117,13 +117,13 @@ hipError_t launch_stat_f32_split(const void* X, const void* G, int64_t B, int64_
                                  float* out, hipStream_t stream, const float* weight, float* norm_partial, float alpha);
 hipError_t launch_stat_f32_split_pair(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,
                                       float* out_id, float* out_sq, hipStream_t stream);
-// layers that do not fill the chip, either type; the pair of identity and square takes the plan of the square
+// layers that do not fill the chip, either type; several statistics at once take the plan of identity and square (allow_wide = false)
 bool small_supports(int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode);
-int64_t small_tiles(int64_t din, int64_t dout);
+int64_t small_tiles(int64_t din, int64_t dout, bool half = false);      // half: those of identity and square together where the waves divide the examples
 hipError_t launch_stat_small(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, const StatPlan& plan,
                              float* out, hipStream_t stream, const float* weight = nullptr, float* norm_partial = nullptr, float alpha = 0.f);
-hipError_t launch_stat_small_pair(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, const StatPlan& plan,
-                                  float* out_id, float* out_sq, hipStream_t stream);
+hipError_t launch_stat_small_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, const StatPlan& plan,
+                                   float* out_id, float* out_sq, float* out_sg, hipStream_t stream);
 // byte-wide sign counters hold a group of the plan
 bool f32_bytes_suffice(const StatPlan& plan);
 hipError_t launch_stat_f32_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan,

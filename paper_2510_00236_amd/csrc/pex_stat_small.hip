@@ -3,8 +3,8 @@
 // The large kernels give a workgroup a block of 128 x 64 entries or more and fill the chip by splitting the batch over workgroups,
 // whose partial sums a second launch adds; rows that are not whole 16-byte chunks are copied by a third.  On small layers that is
 // the time: a launch costs about 4.5 us whatever it does, a block of 256 x 128 is mostly empty, and the tokens of an example
-// run through one workgroup one slab after the other.  Here the eight waves of a workgroup share one tile of 64 x 64 (two
-// statistics of bf16 layers at once: 64 x 32) and divide its examples and tokens:
+// run through one workgroup one slab after the other.  Here the eight waves of a workgroup share one tile of 64 x 64 (several
+// statistics at once, where the waves divide the examples: 64 x 32) and divide its examples and tokens:
 //   KW = 1: every wave takes every eighth example, its own sums, added up through LDS at the end;
 //   KW = 8: every wave takes an eighth of the tokens of each example; M_b is added up through LDS at the end of the example, each
 //           wave taking phi of an eighth of it.
@@ -358,6 +358,9 @@ hipError_t launch_typed(const void* X, const void* G, int64_t B, int64_t T, int6
     return hipErrorInvalidValue;
 }
 
+// NaN counts as -1 on bf16 layers of whole 16-byte chunks, as 0 on all others
+float sign_of_nan(int64_t din, int64_t dout, pex_dtype dt) { return dt == PEX_BF16 && din % 8 == 0 && dout % 8 == 0 ? -1.f : 0.f; }
+
 }  // namespace
 
 bool small_supports(int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode)
@@ -368,26 +371,34 @@ bool small_supports(int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mod
     return small_tiles(din, dout) < ((int64_t)1 << 22);
 }
 
-int64_t small_tiles(int64_t din, int64_t dout) { return ((din + SM_T - 1) / SM_T) * ((dout + SM_T - 1) / SM_T); }
+int64_t small_tiles(int64_t din, int64_t dout, bool half) { return ((din + SM_T - 1) / SM_T) * (half ? (dout + 31) / 32 : (dout + SM_T - 1) / SM_T); }
 
 hipError_t launch_stat_small(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, const StatPlan& plan,
                              float* out, hipStream_t stream, const float* weight, float* norm_partial, float alpha)
 {
-    // NaN counts as -1 on bf16 layers of whole 16-byte chunks, as 0 on all others
-    const float nan_sign = dt == PEX_BF16 && din % 8 == 0 && dout % 8 == 0 ? -1.f : 0.f;
+    const float nan_sign = sign_of_nan(din, dout, dt);
     return dt == PEX_F32 ? launch_typed<float>(X, G, B, T, din, dout, mode, plan, out, stream, weight, norm_partial, alpha, nan_sign)
                          : launch_typed<uint16_t>(X, G, B, T, din, dout, mode, plan, out, stream, weight, norm_partial, alpha, nan_sign);
 }
 
-hipError_t launch_stat_small_pair(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, const StatPlan& plan,
-                                  float* out_id, float* out_sq, hipStream_t stream)
+hipError_t launch_stat_small_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, const StatPlan& plan,
+                                   float* out_id, float* out_sq, float* out_sg, hipStream_t stream)
 {
-    constexpr int O = F_ID | F_SQ;
-    if (plan.small_kw == 8)
-        return dt == PEX_F32 ? launch_small<float, O, 8, 4>(X, G, B, T, din, dout, plan, out_id, out_sq, nullptr, stream, nullptr, nullptr, 0.f, 0.f)
-                             : launch_small<uint16_t, O, 8, 4>(X, G, B, T, din, dout, plan, out_id, out_sq, nullptr, stream, nullptr, nullptr, 0.f, 0.f);
-    return dt == PEX_F32 ? launch_small<float, O, 1, 2>(X, G, B, T, din, dout, plan, out_id, out_sq, nullptr, stream, nullptr, nullptr, 0.f, 0.f)
-                         : launch_small<uint16_t, O, 1, 2>(X, G, B, T, din, dout, plan, out_id, out_sq, nullptr, stream, nullptr, nullptr, 0.f, 0.f);
+    const float nan_sign = sign_of_nan(din, dout, dt);
+    auto go = [&](auto outs) {
+        constexpr int O = decltype(outs)::value;
+        auto typed = [&](auto zero) {
+            typedef decltype(zero) TIn;
+            return plan.small_kw == 8 ? launch_small<TIn, O, 8, 4>(X, G, B, T, din, dout, plan, out_id, out_sq, out_sg, stream, nullptr, nullptr, 0.f, nan_sign)
+                                      : launch_small<TIn, O, 1, 2>(X, G, B, T, din, dout, plan, out_id, out_sq, out_sg, stream, nullptr, nullptr, 0.f, nan_sign);
+        };
+        return dt == PEX_F32 ? typed(0.f) : typed((uint16_t)0);
+    };
+    if (out_id && out_sq && out_sg) return go(std::integral_constant<int, F_ID | F_SQ | F_SG>{});
+    if (out_id && out_sq) return go(std::integral_constant<int, F_ID | F_SQ>{});
+    if (out_id && out_sg) return go(std::integral_constant<int, F_ID | F_SG>{});
+    if (out_sq && out_sg) return go(std::integral_constant<int, F_SQ | F_SG>{});
+    return hipErrorInvalidValue;
 }
 
 }  // namespace pex

@@ -117,3 +117,57 @@ def test_infinities_and_nan_as_on_the_other_kernels(pex_option, dtype, din, dout
         assert torch.equal(torch.isnan(small[k]), torch.isnan(v)) and torch.equal(torch.isinf(small[k]), torch.isinf(v)), k
         ok = torch.isfinite(v)
         assert torch.equal(small[k][ok], v[ok]) if k == "sign" else (small[k][ok] - v[ok]).abs().max() <= 2e-5 * v[ok].abs().max(), k
+
+
+def test_layers_the_caches_bound_stay_on_the_large_kernels(tmp_path):
+    """Many tokens in some dozen tiles, rows that do not start at cache lines: every tile reads its features of all tokens."""
+    rows = [(22, 2887, 181, 680, 1, 0), (88, 255, 158, 1313, 1, 0), (110, 535, 328, 350, 1, 0), (110, 535, 328, 350, 1, 1), (84, 775, 579, 258, 1, 0), (20, 3261, 512, 192, 1, 0)]
+    assert [kw for kw, _ in _ask(tmp_path, rows)] == [0] * len(rows)
+
+
+def test_several_statistics_are_planned_for_what_they_cost(tmp_path):
+    """Identity and square on tiles of half the width, twice the workgroups: layers whose square alone is one round of them stay on the large
+    kernels if the pair is two; what test_several_statistics_at_once runs is on the kernel, with both ways to divide the work and with groups."""
+    assert [kw for kw, _ in _ask(tmp_path, [(115, 342, 192, 807, 1, 7), (193, 176, 192, 959, 1, 7), (43, 1507, 344, 192, 1, 7)])] == [0, 0, 0]
+    code = {"f32": pex.PEX_F32, "bf16": pex.PEX_BF16}
+    got = _ask(tmp_path, [(*s[:4], code[s[4]], 7) for s in SEVERAL])
+    assert {(kw, ns > 1) for kw, ns in got} == {(1, False), (1, True), (8, False), (8, True)}, got
+
+
+SEVERAL = [(9, 200, 4, 4, "f32"), (2, 9, 64, 64, "bf16"), (5, 17, 65, 67, "f32"), (5, 33, 61, 130, "bf16"), (3, 257, 63, 34, "bf16"), (3, 129, 63, 34, "f32"),
+           (2, 1100, 130, 7, "bf16"), (19, 20, 37, 130, "bf16"), (61, 50, 72, 40, "bf16"), (200, 6, 33, 70, "f32"), (61, 300, 72, 40, "bf16"), (61, 300, 72, 40, "f32"),
+           (31, 40, 200, 300, "bf16"), (1, 900, 70, 130, "bf16")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,T,din,dout,dtype", SEVERAL)
+def test_several_statistics_at_once(B, T, din, dout, dtype):
+    X, G = si.custom(B, T, din, dout, dtype=dtype, seed=B * 31 + T)
+    Xd, Gd = X.to(DEV), G.to(DEV)
+    st = oracle.stat(si.widen(X), si.widen(G))
+    f = lambda t: t.cpu().numpy().astype(np.float64)
+    for want in (("identity", "square"), ("identity", "sign"), ("square", "sign"), ("identity", "square", "sign")):
+        out = {k: torch.full((din, dout), float("nan"), device=DEV) for k in want}
+        pex.pex_stat_multi(Xd, Gd, want, out=out)
+        tag = f"B{B} T{T} {din}x{dout} {dtype} {want}"
+        if "identity" in want:
+            assert_real_stat(f(out["identity"]), st.S_id, dtype, tag, elementwise=False)
+        if "square" in want:
+            assert_real_stat(f(out["square"]), st.S_sq, dtype, tag, elementwise=False)
+        if "sign" in want:
+            assert_sign_stat(f(out["sign"]), st.S_sign, st.amb, tag)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,dout,nan_sign", [("f32", 66, 0.0), ("bf16", 64, -1.0), ("bf16", 66, 0.0)])
+def test_signs_of_nan_in_company(dtype, dout, nan_sign):
+    X, G = si.custom(11, 40, 72, dout, dtype=dtype, seed=4)
+    G = G.clone()
+    G[2, 39, dout - 1] = float("nan")
+    alone = pex.pex_stat(X.to(DEV), G.to(DEV), "sign")
+    got = pex.pex_stat_multi(X.to(DEV), G.to(DEV), ("identity", "square", "sign"))
+    rest = [b for b in range(11) if b != 2]
+    others = oracle.stat(si.widen(X[rest]), si.widen(G[rest]))
+    clear = others.amb[:, -1] == 0
+    assert np.array_equal(got["sign"].cpu().numpy()[clear, -1], others.S_sign[clear, -1] + nan_sign)
+    assert torch.equal(got["sign"][:, :-1], alone[:, :-1]) and torch.isnan(got["square"][:, -1]).all() and torch.isfinite(got["square"][:, :-1]).all()
