@@ -464,8 +464,6 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
     p.wide_ws_bytes = (wide_cols > 0 && wide_nsplit > 1) ? (size_t)wide_nsplit * (size_t)din * (size_t)wide_cols * sizeof(float) : 0;
     p.ws_bytes = p.copy_bytes + p.wide_ws_bytes +
                  ((nsplit > 1 && dout > wide_cols) ? (size_t)nsplit * (size_t)din * (size_t)(dout - wide_cols) * sizeof(float) : 0);
-    // (a layer that fits a bound on the workspace, or does not, is the same layer whichever way it is multiplied)
-    if (p.f32_split && direct_nsplit > nsplit) p.ws_bytes = (size_t)direct_nsplit * (size_t)din * (size_t)dout * sizeof(float);
     if (p.square_halves) p.ws_bytes = p.copy_bytes + (size_t)4 * (size_t)nsplit * (size_t)din * (size_t)dout * sizeof(float);
     if (p.sign_bytes) p.ws_bytes = p.copy_bytes + (size_t)nsplit * sign_byte_partial_bytes(din, dout);
     if (mode == MODE_NORMS) {   // no S at all: one partial of ||M_b||^2 per tile (and wave) and example
@@ -514,6 +512,8 @@ static StatPlan make_large_plan(int64_t B, int64_t T, int64_t din, int64_t dout,
             }
         }
     }
+    p.query_bytes = p.ws_bytes;
+    if (p.f32_split && mode != MODE_NORMS && direct_nsplit > nsplit) p.query_bytes = (size_t)direct_nsplit * (size_t)din * (size_t)dout * sizeof(float);
     return p;
 }
 
@@ -609,7 +609,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     s.wide_per_split = B;
     s.ws_bytes = mode == MODE_NORMS ? (size_t)small_tiles(din, dout) * s.small_kw * B * sizeof(float)
                  : s.nsplit > 1     ? (size_t)s.nsplit * (size_t)din * (size_t)dout * sizeof(float) : 0;
-    if (s.ws_bytes < p.ws_bytes) s.ws_bytes = p.ws_bytes;      // (as for the other kernels: a layer that fits a bound on the workspace does so either way)
+    s.query_bytes = s.ws_bytes > p.query_bytes ? s.ws_bytes : p.query_bytes;
     return s;
 }
 
@@ -646,14 +646,15 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     return now.plan;
 }
 
-// The plan of a call that has `bytes` of workspace: a layer of odd width whose padded copies do not fit runs on the SIMT kernel if
-// that plan does.
+// The plan of a call that has `bytes` of workspace: a layer that does not fit with the kernel of small layers goes without it, one whose
+// padded copies do not fit, or that does not with bf16 pieces, runs on the operands as they are.  A call that fits none gets the first plan.
 static StatPlan plan_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, size_t bytes)
 {
-    const StatPlan plan = plan_stat(B, T, din, dout, dt, mode);
-    if (plan.ws_bytes <= bytes || (plan.din == din && plan.dout == dout && !plan.f32_split && plan.small_kw == 0)) return plan;
-    const StatPlan direct = plan_stat(B, T, din, dout, dt, mode, true, false);
-    return direct.ws_bytes <= bytes ? direct : plan;
+    const StatPlan first = plan_stat(B, T, din, dout, dt, mode);
+    StatPlan plan = first;
+    if (plan.query_bytes > bytes && plan.small_kw > 0) plan = plan_stat(B, T, din, dout, dt, mode, true, true, false);
+    if (plan.query_bytes > bytes && (plan.din != din || plan.dout != dout || plan.f32_split)) plan = plan_stat(B, T, din, dout, dt, mode, true, false);
+    return plan.query_bytes <= bytes ? plan : first;
 }
 
 static pex_status check_stat_args(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout,
@@ -732,8 +733,8 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
 {
     const StatPlan plan = plan_within(B, T, din, dout, dt, mode, workspace ? workspace_bytes : 0);
     float* out = S;
-    if (plan.ws_bytes > 0) {
-        if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
+    if (plan.query_bytes > 0) {
+        if (!workspace || workspace_bytes < plan.query_bytes) return PEX_ERR_WORKSPACE;
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     }
     float* partials = (float*)((char*)workspace + plan.copy_bytes);
@@ -802,17 +803,17 @@ struct MultiPlan {
     uint32_t pair_want;   // for which statistics
     uint32_t single_want; // served by separate pex_stat passes
     StatPlan pair_plan;
-    size_t ws_bytes;
+    size_t query_bytes;   // what the call asks for: at least what it would without the kernel of small layers
 };
 
-static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true)
+static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true)
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
     // (what shares a contraction of fp32 layers on the bf16 matrix cores is identity and square only)
     constexpr uint32_t BOTH = PEX_WANT_IDENTITY | PEX_WANT_SQUARE;
     // On the kernel of small layers any of them share one, with signs up to the number of tiles signs alone take it for.
-    StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad);
+    StatPlan sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad, allow_small);
     const bool small = n >= 2 && sq.small_kw > 0 && (want == BOTH || small_tiles(din, dout) <= 256);
     if (!small) sq = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, allow_pad && (dt != PEX_F32 || want == BOTH), false);
     // Three wanted: all from one contraction while the sign counts fit bytes; otherwise identity and square share a
@@ -824,18 +825,33 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
     if (m.pair) {
         m.single_want = want & ~m.pair_want;
         m.pair_plan = sq;
-        m.pair_plan.ws_bytes = sq.copy_bytes + __builtin_popcount(m.pair_want) * (sq.ws_bytes - sq.copy_bytes);
-        m.ws_bytes = m.pair_plan.ws_bytes;
+        m.query_bytes = small ? __builtin_popcount(m.pair_want) * sq.ws_bytes : sq.copy_bytes + __builtin_popcount(m.pair_want) * (sq.query_bytes - sq.copy_bytes);
     } else {
         m.pair_want = 0;
         m.single_want = want;
     }
     for (int phi = 0; phi < 3; ++phi)
         if (m.single_want & (1u << phi)) {
-            const size_t w = plan_stat(B, T, din, dout, dt, (Mode)phi, true, allow_pad).ws_bytes;
-            if (w > m.ws_bytes) m.ws_bytes = w;     // passes run one after the other on the stream and reuse it
+            const size_t w = plan_stat(B, T, din, dout, dt, (Mode)phi, true, allow_pad, allow_small).query_bytes;
+            if (w > m.query_bytes) m.query_bytes = w;     // passes run one after the other on the stream and reuse it
         }
+    if (small) {
+        const size_t without = plan_multi(B, T, din, dout, dt, want, allow_pad, false).query_bytes;
+        if (without > m.query_bytes) m.query_bytes = without;
+    }
     return m;
+}
+
+// The plan of a call that has `bytes` of workspace, as plan_within
+static MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes)
+{
+    const MultiPlan first = plan_multi(B, T, din, dout, dt, want);
+    if (first.query_bytes <= bytes) return first;
+    for (const bool allow_pad : {true, false}) {
+        const MultiPlan m = plan_multi(B, T, din, dout, dt, want, allow_pad, false);
+        if (m.query_bytes <= bytes) return m;
+    }
+    return first;
 }
 
 // ---- identity and square of several bf16 layers of one batch in one launch (pex_stat_pair_batch)
@@ -978,7 +994,7 @@ size_t pex_stat_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t dout,
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return 0;
-    return plan_stat(B, T, din, dout, dt, (Mode)phi).ws_bytes;
+    return plan_stat(B, T, din, dout, dt, (Mode)phi).query_bytes;
 }
 
 pex_status pex_stat(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
@@ -997,7 +1013,7 @@ pex_status pex_stat_noalloc(const void* X, const void* G, int64_t B, int64_t T, 
     if (st != PEX_OK) return st;
     if (phi != PEX_PHI_IDENTITY && phi != PEX_PHI_SQUARE && phi != PEX_PHI_SIGN) return PEX_ERR_PHI;
     const size_t limit = (size_t)PEX_NOALLOC_SCRATCH_BYTES;
-    const size_t need = plan_within(B, T, din, dout, dt, (Mode)phi, limit).ws_bytes;
+    const size_t need = plan_within(B, T, din, dout, dt, (Mode)phi, limit).query_bytes;
     if (need > limit) return PEX_ERR_TOO_LARGE;
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return PEX_ERR_HIP;
@@ -1011,7 +1027,7 @@ size_t pex_stat_multi_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
     if (want == 0 || (want & ~7u)) return 0;
-    return plan_multi(B, T, din, dout, dt, want).ws_bytes;
+    return plan_multi(B, T, din, dout, dt, want).query_bytes;
 }
 
 pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
@@ -1027,13 +1043,9 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         if (st != PEX_OK) return st;
     }
     const size_t given = workspace ? workspace_bytes : 0;
-    MultiPlan m = plan_multi(B, T, din, dout, dt, want);
-    if (m.ws_bytes > given) {        // without padded copies?
-        const MultiPlan simt = plan_multi(B, T, din, dout, dt, want, false);
-        if (simt.ws_bytes <= given) m = simt;
-    }
-    if (m.ws_bytes > 0) {
-        if (!workspace || workspace_bytes < m.ws_bytes) return PEX_ERR_WORKSPACE;
+    const MultiPlan m = plan_multi_within(B, T, din, dout, dt, want, given);
+    if (m.query_bytes > 0) {
+        if (!workspace || workspace_bytes < m.query_bytes) return PEX_ERR_WORKSPACE;
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     }
     hipStream_t hs = (hipStream_t)stream;
@@ -1102,7 +1114,7 @@ size_t pex_stat_pair_batch_workspace_bytes(const pex_pair_item* items, int32_t c
     size_t need = 0;
     for (int k = 0; k < count; ++k) {
         if (items[k].din < 1 || items[k].dout < 1) return 0;
-        const size_t own = plan_multi(B, T, items[k].din, items[k].dout, dt, PEX_WANT_IDENTITY | PEX_WANT_SQUARE).ws_bytes;
+        const size_t own = plan_multi(B, T, items[k].din, items[k].dout, dt, PEX_WANT_IDENTITY | PEX_WANT_SQUARE).query_bytes;
         if (own > need) need = own;
     }
     PairBatchPlan plan;
@@ -1127,8 +1139,7 @@ pex_status pex_stat_pair_batch(const pex_pair_item* items, int32_t count, int64_
             const pex_status st = check_stat_args(it.X, it.G, B, T, it.din, it.dout, dt, S);
             if (st != PEX_OK) return st;
         }
-        size_t need = plan_multi(B, T, it.din, it.dout, dt, BOTH).ws_bytes;
-        if (need > given) need = plan_multi(B, T, it.din, it.dout, dt, BOTH, false).ws_bytes;
+        const size_t need = plan_multi_within(B, T, it.din, it.dout, dt, BOTH, given).query_bytes;
         if (need > given) return PEX_ERR_WORKSPACE;
         uses_workspace = uses_workspace || need > 0;
     }
@@ -1221,7 +1232,7 @@ size_t pex_example_norms_workspace_bytes(int64_t B, int64_t T, int64_t din, int6
 {
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
-    return plan_stat(B, T, din, dout, dt, MODE_NORMS).ws_bytes;
+    return plan_stat(B, T, din, dout, dt, MODE_NORMS).query_bytes;
 }
 
 pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
@@ -1232,7 +1243,7 @@ pex_status pex_example_norms(const void* X, const void* G, int64_t B, int64_t T,
     if (!N) return PEX_ERR_NULL;
     if ((uintptr_t)N & 3u) return PEX_ERR_ALIGN;
     const StatPlan plan = plan_within(B, T, din, dout, dt, MODE_NORMS, workspace ? workspace_bytes : 0);
-    if (!workspace || workspace_bytes < plan.ws_bytes) return PEX_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < plan.query_bytes) return PEX_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
     hipStream_t hs = (hipStream_t)stream;
     char* front = (char*)workspace + plan.copy_bytes;
@@ -1269,7 +1280,7 @@ size_t pex_weighted_sum_workspace_bytes(int64_t B, int64_t T, int64_t din, int64
 {
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
-    return plan_stat(B, T, din, dout, dt, MODE_WEIGHTED).ws_bytes;
+    return plan_stat(B, T, din, dout, dt, MODE_WEIGHTED).query_bytes;
 }
 
 pex_status pex_weighted_sum(const void* X, const void* G, const float* w, int64_t B, int64_t T, int64_t din, int64_t dout,
@@ -1294,7 +1305,7 @@ size_t pex_stat_power_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t
 {
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
-    return plan_stat(B, T, din, dout, dt, MODE_POWER).ws_bytes;
+    return plan_stat(B, T, din, dout, dt, MODE_POWER).query_bytes;
 }
 
 pex_status pex_stat_power(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,
@@ -1320,7 +1331,7 @@ size_t pex_token_sq_workspace_bytes(int64_t B, int64_t T, int64_t din, int64_t d
 {
     if (B < 1 || T < 1 || din < 1 || dout < 1) return 0;
     if (dt != PEX_F32 && dt != PEX_BF16) return 0;
-    return plan_stat(B, T, din, dout, dt, MODE_TOKEN_SQ).ws_bytes;
+    return plan_stat(B, T, din, dout, dt, MODE_TOKEN_SQ).query_bytes;
 }
 
 pex_status pex_token_sq(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt,

@@ -43,6 +43,8 @@ struct StatPlan {
     bool gram;         // MODE_NORMS on bf16 layers: through the T x T Gram matrices instead of the contraction
     bool gram_wide;    // ... on 256 x 256 blocks whose X X^T part waits in the workspace (after the partials, 256-byte aligned)
     size_t ws_bytes;   // copy_bytes + wide_ws_bytes + (nsplit > 1 ? nsplit * din * (dout - wide_cols) * 4 : 0)
+    size_t query_bytes; // what a call asks for: that, or what the layer needs by fp32 products and without the kernel of small layers if that is
+                        // more (a layer that fits a bound on the workspace, or does not, is the same layer whichever kernel takes it)
 };
 
 // allow_wide = false keeps the plan on one block shape (the launches that produce several statistics at once need it);

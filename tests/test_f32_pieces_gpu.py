@@ -226,8 +226,8 @@ def test_the_other_statistics_where_pieces_do_not_hold(large, kind):
         for rows in (slice(0, 200), slice(200, 201), slice(201, din)):
             ok = finite[rows]
             if ok.any():
-                assert (np.abs(S[rows] - r[rows])[ok].max() <= 2e-5 * np.abs(r[rows])[ok].max()), (kind, name, rows)
+                assert np.abs(S[rows][ok] - r[rows][ok]).max() <= 2e-5 * np.abs(r[rows][ok]).max(), (kind, name, rows)
     N = pex.pex_example_norms(Xd, Gd).cpu().double().numpy()
     finite = norms < 3.4e38
     assert np.array_equal(np.isfinite(N), finite) and np.array_equal(np.isnan(N), np.isnan(norms)), kind
-    assert (np.abs(N - norms)[finite] <= 2e-5 * norms[finite]).all(), kind
+    assert (np.abs(N[finite] - norms[finite]) <= 2e-5 * norms[finite]).all(), kind

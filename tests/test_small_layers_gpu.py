@@ -171,3 +171,56 @@ def test_signs_of_nan_in_company(dtype, dout, nan_sign):
     clear = others.amb[:, -1] == 0
     assert np.array_equal(got["sign"].cpu().numpy()[clear, -1], others.S_sign[clear, -1] + nan_sign)
     assert torch.equal(got["sign"][:, :-1], alone[:, :-1]) and torch.isnan(got["square"][:, -1]).all() and torch.isfinite(got["square"][:, :-1]).all()
+
+
+def test_workspace_is_what_the_layer_needs_either_way(tmp_path, pex_option):
+    """The query holds the partial sums of the plan and whatever the layer asks for without the kernel, not copies that it does not make
+    for each of several statistics (an option that is about neither statistic keeps the kernel out)."""
+    code = {"f32": pex.PEX_F32, "bf16": pex.PEX_BF16}
+    shapes = SEVERAL + [(2, 1050, 1934, 128, "bf16"), (8, 700, 300, 333, "bf16")]
+    plans = _ask(tmp_path, [(*s[:4], code[s[4]], 7) for s in shapes])
+    wants = (("identity", "square"), ("square", "sign"), ("identity", "square", "sign"))
+    query = lambda s: [pex.pex_stat_multi_workspace_bytes(*s[:4], code[s[4]], w) for w in wants]
+    got = [query(s) for s in shapes]
+    pex_option("gram_norms", 0)
+    for s, (kw, ns), now in zip(shapes, plans, got):
+        assert kw > 0, s
+        for w, bytes_now, without in zip(wants, now, query(s)):
+            assert bytes_now == max(without, len(w) * ns * s[2] * s[3] * 4 if ns > 1 else 0), (s, w)
+
+
+@pytest.mark.gpu
+def test_workspaces_of_every_size_that_was_enough(pex_option):
+    """Less than the query, but enough without the kernel or without copies: the same statistics; less than that is refused."""
+    for B, T, din, dout, dtype in [(61, 300, 72, 40, "bf16"), (61, 300, 72, 40, "f32"), (200, 6, 33, 70, "f32"), (24, 700, 100, 131, "bf16"), (40, 300, 200, 201, "bf16")]:
+        code = pex.PEX_F32 if dtype == "f32" else pex.PEX_BF16
+        X, G = si.custom(B, T, din, dout, dtype=dtype, seed=B + T)
+        Xd, Gd = X.to(DEV), G.to(DEV)
+        st = oracle.stat(si.widen(X), si.widen(G))
+        sizes = set()
+        for option in (1, 0):
+            pex_option("gram_norms", option)
+            sizes.add(pex.pex_stat_multi_workspace_bytes(B, T, din, dout, code, ("identity", "square")))
+            sizes.add(pex.pex_stat_workspace_bytes(B, T, din, dout, code, "square"))
+        pex_option("gram_norms", 1)
+        done = set()
+        S = {k: torch.empty(din, dout, device=DEV) for k in ("identity", "square")}
+        for size in sorted(sizes | {max(sizes) * 2}):
+            ws = torch.full((size + 4096,), 77, dtype=torch.uint8, device=DEV)
+            for pair in (True, False):
+                for t in S.values():
+                    t.fill_(float("nan"))
+                if pair:
+                    rc = pex.lib().pex_stat_multi(Xd.data_ptr(), Gd.data_ptr(), B, T, din, dout, code, 3, S["identity"].data_ptr(), S["square"].data_ptr(), None, ws.data_ptr(), size, None)
+                else:
+                    rc = pex.lib().pex_stat(Xd.data_ptr(), Gd.data_ptr(), B, T, din, dout, code, pex.PEX_PHI_SQUARE, S["square"].data_ptr(), ws.data_ptr(), size, None)
+                torch.cuda.synchronize()
+                assert (ws[size:] == 77).all() and rc in (0, 6)
+                if rc == 0:
+                    done.add(pair)
+                    assert_real_stat(S["square"].cpu().double().numpy(), st.S_sq, dtype, f"{size} bytes", elementwise=False)
+                    if pair:
+                        assert_real_stat(S["identity"].cpu().double().numpy(), st.S_id, dtype, f"{size} bytes", elementwise=False)
+                else:
+                    assert torch.isnan(S["square"]).all()
+        assert done == {True, False}
