@@ -73,7 +73,8 @@ int pex_version(void);
  *                            only, 1 = the first columns of S on the wide shape where a cost model says so
  *                            (default: layers whose wide blocks fill whole rounds of the 256 compute units),
  *                            2 = as many columns as fit on the wide shape, always (environment PEX_WIDE_BLOCKS).
- *                            The result is the same bits under every value.
+ *                            Either shape folds the same per-example tiles; the groups of examples, and with them the
+ *                            rounding of the sum over examples in fp32, may differ.
  *   PEX_OPT_GRAM_NORMS       pex_example_norms on bf16 layers has two routes: the per-example contraction, and the T x T
  *                            Gram matrices of the "ghost" norm (Sec. 2.3), N_b = <X_b X_b^T, G_b G_b^T>, on blocks of
  *                            128 x 128 or, with 256 KiB of workspace per block and example, of 256 x 256.  0 = the
@@ -89,8 +90,9 @@ int pex_version(void);
  *                            1 = chosen by a cost model (default), 2 = wherever it applies (dout < 2^20) (environment
  *                            PEX_MEMORY_FOLD).  It rounds the square before adding it where the register tiles use a
  *                            fused multiply-add: the routes agree to fp32 rounding, not bit for bit.
- * With any option away from its default, layers that do not fill the chip stay on the kernels these options are about
- * as well (they have a kernel of their own otherwise; fp32 rounding apart, the results are the same).
+ * Layers that do not fill the chip have a kernel of their own while every option has its default (per-example norms: also
+ * under any PEX_OPT_MAX_SPLIT); with another one away from it they are on the kernels these options are about.  The
+ * results agree to fp32 rounding.
  * An option changes the plan and with it the *_workspace_bytes of later calls: query again after setting one.  A
  * call whose workspace was sized under another value returns PEX_ERR_WORKSPACE if it is too small.
  * pex_set_option: PEX_ERR_PHI for an unknown option, PEX_ERR_SHAPE for a value out of range.  pex_get_option: the

@@ -569,6 +569,18 @@ static double cheapest_small(int64_t din, int64_t dout, int64_t rows, int64_t un
 static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide, bool allow_pad, bool allow_small,
                           const OptionValues& options)
 {
+    if (mode == MODE_NORMS && options[PEX_OPT_MAX_SPLIT] < 32) {
+        // the same bits under every bound on the groups: by the same route and kernel, in no more groups
+        OptionValues unbound = options;
+        unbound.v[PEX_OPT_MAX_SPLIT] = 32;
+        StatPlan p = make_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, allow_small, unbound);
+        const int64_t most = options[PEX_OPT_MAX_SPLIT];
+        if (!p.gram && p.nsplit > most) {
+            p.per_split = (B + most - 1) / most;
+            p.nsplit = (int)((B + p.per_split - 1) / p.per_split);
+        }
+        return p;
+    }
     StatPlan p = make_large_plan(B, T, din, dout, dt, mode, allow_wide, allow_pad, options);
     // (What calls of 10 to 200 us take of the large plans' estimates, in the median: bf16 layers 0.8, on the SIMT kernel 0.88; norms by
     // the contraction 0.75, of padded copies 0.67, by Gram matrices 0.97, on the SIMT kernel 1.1; the fp32 kernel 3 us more but for the norms.)
