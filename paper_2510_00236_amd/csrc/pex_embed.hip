@@ -175,9 +175,9 @@ __global__ __launch_bounds__(256) void row_start_kernel(const int* __restrict__ 
 
 // Few positions of a vocabulary too large for buckets: the whole radix sort and row_start in one launch of one workgroup, keys
 // and positions in LDS.  Same digits, same order: wave i owns a contiguous segment of the positions; counters per (wave, digit) give every key its place.  Bound by the
-// latency of its few dozen steps, 15 - 18 us for 1500 - 2040 positions, against the five or seven launches of the kernels above,
-// which take about 4.5 us each whatever they do (whole call, 345 / 630 / 2040 positions: 45 / 104 / 58 -> 27 / 45 / 38 us; at 3700
-// and 8192 positions the one workgroup is the slower one by 4 and 7 us).
+// latency of its few dozen steps and of writing row_start alone, against the five or seven launches of the kernels above, which take about
+// 4.5 us each whatever they do.  Whole calls of 100 / 345 / 630 / 1500 / 2048 positions, by those kernels and by this one, us: V=300000 126 / 70 / 59 /
+// 54 / 52, 98 / 56 / 46 / 52 / 54; V=2000000 712 / 289 / 212 / 164 / 150, 556 / 274 / 206 / 184 / 174.
 constexpr int SMALL_N = 2048, SMALL_WAVES = 16;
 
 template <typename TId>
@@ -276,11 +276,12 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void sort_small_kernel(const TId*
 //     of smaller buckets it meets.  Bound by the instructions of 256 workgroups reading everything: 12 us for 8192 positions, 66
 //     for 65536, so it ends at 4096, where two launches take as long.
 //   tile_buckets_kernel, bucket_sort_kernel<.., true>: tiles of 1024 positions are first put in bucket order, each by a
-//     workgroup of its own; a bucket's workgroup then reads its segment of every tile.  4.8 + 7 us for 65536 positions; 50 where half
+//     workgroup of its own; a bucket's workgroup then reads its segment of every tile.  4.8 + 12 us for 65536 positions of Zipf frequencies; 50 where half
 //     of them are one token, which one workgroup then places alone.
-// (Before: a radix sort with five launches for two 8-bit digits, 30 us.  Whole calls, identity and square, before / now: B=64 T=1024
-// V=50257 d=768 115 / 96 us, uniform tokens 94 / 80, half of them one token 190 / 169; B=8 T=512 d=256 56 / 38; B=9 T=152 V=2515 d=384,
-// by one workgroup before, 25.7 / 19.1; B=128 T=2048 d=256 126 / 101.)
+// (Before: a radix sort with five launches for two 8-bit digits, 30 us.  Whole calls with the rows, identity and square, by that sort and the rows
+// kernel of its time / now: B=64 T=1024 V=50257 d=768 115 / 91 us, uniform tokens 93 / 78, half of them one token 175 / 160; B=8 T=512 d=256 59 / 31;
+// B=9 T=152 V=2515 d=384 30 / 18; B=128 T=2048 d=256 128 / 84.  A dominant token, which one workgroup places: B=256 T=1024 d=256 with
+// 25 / 50 / 90 / 100 % of the positions 215 / 348 / 586 / 864, now 184 / 314 / 542 / 792.)
 constexpr int BUCKETS = 256, BUCKET_WAVES = 16, BUCKET_TILE = BUCKET_WAVES * 64, BUCKET_MAX_TILES = 256;
 constexpr int BUCKET_MAX_V = BUCKETS * 1024;               // 64 KiB of counters
 constexpr int BUCKET_ONE_LAUNCH_N = 4096, BUCKET_MAX_N = BUCKET_MAX_TILES * BUCKET_TILE;

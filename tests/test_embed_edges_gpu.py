@@ -1,5 +1,4 @@
-"""Embedding statistics at the edges: batches on both sides of what one workgroup sorts (2048 positions), one slice of positions
-and several, one to four sort passes, rows of every alignment (lengths that are multiples of 4, 2 and 1, shorter than a lane's
+"""Embedding statistics at the edges: one slice of positions and several (the sorts: test_embed_sorts_gpu.py), rows of every alignment (lengths that are multiples of 4, 2 and 1, shorter than a lane's
 four columns), gaps in the vocabulary of every length.  Outputs sit inside a larger buffer."""
 import numpy as np
 import pytest
@@ -15,15 +14,15 @@ DEV = "cuda:0"
 
 CASES = [
     # B, T, V, d, dtype, ids dtype, Zipf exponent, padding
-    (8, 256, 300, 12, "bf16", torch.int64, 1.0, 0.05),       # exactly 2048 positions
-    (64, 32, 66000, 6, "bf16", torch.int32, 0.3, 0.0),       # the same, three passes, mostly single positions
-    (3, 683, 300, 9, "bf16", torch.int32, 1.0, 0.0),         # 2049: the sort of many workgroups
+    (8, 256, 300, 12, "bf16", torch.int64, 1.0, 0.05),       # every token in a bucket of one or two
+    (64, 32, 66000, 6, "bf16", torch.int32, 0.3, 0.0),       # mostly single positions, 258 tokens to a bucket
+    (3, 683, 300, 9, "bf16", torch.int32, 1.0, 0.0),         # a last batch of one position
     (1, 64, 5000, 3, "f32", torch.int64, 0.0, 0.5),          # rows shorter than four columns, long gaps
     (2, 96, 17, 5, "bf16", torch.int64, 1.0, 0.0),           # one slice of 192 positions, frequent tokens only
     (2, 97, 17, 258, "bf16", torch.int32, 1.0, 0.0),         # one position more; two column blocks, the second of two columns
     (5, 333, 40, 261, "f32", torch.int64, 1.2, 0.1),
     (4, 500, 7, 103, "bf16", torch.int32, 1.0, 0.0),         # runs over several slices, odd rows
-    (3, 20, 17000000, 2, "f32", torch.int64, 0.0, 0.0),      # four passes
+    (3, 20, 17000000, 2, "f32", torch.int64, 0.0, 0.0),      # a radix sort of four passes by one wave
     (1, 1, 9, 1, "bf16", torch.int64, 0.0, 0.0),
 ]
 

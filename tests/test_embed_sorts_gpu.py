@@ -55,6 +55,18 @@ def test_sorts(B, T, V, d, exponent, pad):
     _check(ids, B, T, V, d)
 
 
+@pytest.mark.parametrize("B,T,exponent,pad", [
+    (8, 256, 1.0, 0.0),      # exactly 2048 positions, frequent tokens: every wave's segment holds keys, counters of the same digit in all of them
+    (3, 500, 1.0, 0.2),      # 1500: segments of several batches of 64, the last ones partly and wholly empty; padding
+    (5, 26, 0.5, 0.0),       # 130: three waves, the last of two positions
+    (2, 32, 0.0, 0.9),       # one batch of one wave
+    (3, 683, 1.0, 0.1),      # 2049: the sort of many workgroups
+])
+def test_radix_sorts_of_a_vocabulary_too_large_for_buckets(B, T, exponent, pad):
+    V = 300000
+    _check(si.token_ids(B, T, V, seed=B + T, exponent=exponent, pad_fraction=pad), B, T, V, 3)
+
+
 def test_half_of_the_positions_one_token():
     """A bucket whose workgroup meets batches of one token, of a few tokens and of many."""
     B, T, V = 12, 1000, 700
