@@ -167,6 +167,8 @@ pex_status pex_stat_noalloc(const void *X, const void *G, int64_t B, int64_t T, 
  *   On the layers the MFMA kernels take, all wanted statistics come from one contraction (for all three, and on fp32
  *   layers for sign with any other, this needs at most 127 examples per group of the batch; beyond that identity and
  *   square share one and sign runs alone); other inputs are served one statistic at a time.  Workspace as for pex_stat, sized by the query below.
+ *   For identity and square of few long bf16 examples the query has room for every M_b where that is the faster way (at most 512 MiB); a
+ *   workspace that holds the partial sums alone is enough and gives the same bits.
  */
 #define PEX_WANT_IDENTITY 1u
 #define PEX_WANT_SQUARE 2u

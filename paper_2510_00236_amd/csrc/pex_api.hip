@@ -811,6 +811,7 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
 // How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (on the layers the
 // MFMA kernels take), the rest one at a time.
 struct MultiPlan {
+    bool examples;        // identity and square from the M_b themselves, in the workspace (pair_plan: whose groups their sums have)
     bool pair;            // a fused launch is used
     uint32_t pair_want;   // for which statistics
     uint32_t single_want; // served by separate pex_stat passes
@@ -818,7 +819,31 @@ struct MultiPlan {
     size_t query_bytes;   // what the call asks for: at least what it would without the kernel of small layers
 };
 
-static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true)
+// Identity and square of few long examples of a bf16 layer: M_b of every example by the kernel of plain contractions -- one register tile
+// on 256 x 256 blocks at 6.1e12 FLOP/s a compute unit, where both statistics beside it leave 256 x 128 at 4.4e12 -- into the workspace, and
+// the sums over b, in the groups of `pair` and with the same bits, in a second pass.  What that moves, written and read, takes 0.3 us a MB and
+// 0.55 beyond 200 MB, which the memory-side cache does not hold.  Measured, together in one launch -> so, us: 4 x 8192 tokens, 4096 x 4096
+// 992 -> 860; 16 x 4096, 768 x 3072 411 -> 313; 16 x 4092, 1024 x 1024 155 -> 121; 7 x 3000, 3000 x 1000 231 -> 151; but 12 x 1500,
+// 2048 x 2048 157 -> 176 and 5 x 1200, 4096 x 4096 202 -> 287.  The pair's estimate is 20 % low on such layers (0 to 27), more where its groups
+// are single examples, both of whose statistics it writes and reads: there this is taken for any gain, elsewhere for a clear one.
+// Returns how much of the pair's time that is, 1 where it is not taken.
+static double examples_share(int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& pair)
+{
+    if (pair.kernel != 1 || pair.copy_bytes > 0 || T < 1024) return 1.0;
+    const double bytes = (double)din * (double)dout * 4.0, mb = (double)B * bytes * 1.0e-6;
+    if ((double)B * bytes > 512.0 * 1048576.0) return 1.0;
+    for (int k = 0; k < NUM_OPTIONS; ++k)
+        if (option(k) != DEFAULT_OPTIONS[k]) return 1.0;       // the options are about the other plans
+    int bm, bn;
+    bf16_tile_shape(MODE_IDENTITY, B, &bm, &bn);
+    const int64_t wgs = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn) * B;
+    const double t = (double)((wgs + 255) / 256) * 2.0 * (double)T * bm * bn / 6.1e12 + 2.0 * bytes / 5.0e12 + 8.0e-6 +
+                     1.0e-6 * (mb < 200.0 ? 0.3 * mb : 60.0 + 0.55 * (mb - 200.0));
+    return t < pair.seconds * (pair.per_split == 1 ? 1.2 : 1.04) ? t / (1.2 * pair.seconds) : 1.0;
+}
+
+static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true,
+                            bool allow_examples = true)
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
@@ -842,6 +867,11 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
         m.pair_want = 0;
         m.single_want = want;
     }
+    if (allow_examples && want == BOTH && m.pair && !small && examples_share(B, T, din, dout, sq) < 1.0) {
+        m.examples = true;
+        const size_t need = (size_t)B * (size_t)din * (size_t)dout * sizeof(float);
+        if (need > m.query_bytes) m.query_bytes = need;
+    }
     for (int phi = 0; phi < 3; ++phi)
         if (m.single_want & (1u << phi)) {
             const size_t w = plan_stat(B, T, din, dout, dt, (Mode)phi, true, allow_pad, allow_small).query_bytes;
@@ -859,6 +889,10 @@ static MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t do
 {
     const MultiPlan first = plan_multi(B, T, din, dout, dt, want);
     if (first.query_bytes <= bytes) return first;
+    if (first.examples) {
+        const MultiPlan m = plan_multi(B, T, din, dout, dt, want, true, true, false);
+        if (m.query_bytes <= bytes) return m;
+    }
     for (const bool allow_pad : {true, false}) {
         const MultiPlan m = plan_multi(B, T, din, dout, dt, want, allow_pad, false);
         if (m.query_bytes <= bytes) return m;
@@ -906,7 +940,8 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
         const int64_t own = bf16_pair_blocks(din[k], dout[k]);
         const double own_bytes = 2.0 * (double)din[k] * (double)dout[k] * sizeof(float);
         const StatPlan p = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false, true, false), by_itself = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false);
-        alone += by_itself.small_kw > 0 ? by_itself.seconds : TAKEN * (seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH);
+        alone += by_itself.small_kw > 0 ? by_itself.seconds
+                                        : TAKEN * examples_share(B, T, din[k], dout[k], p) * (seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH);
         blocks += own;
         bytes += own_bytes;
         if (p.per_split + p.nsplit < fewest_roundings) fewest_roundings = p.per_split + p.nsplit;
@@ -1065,6 +1100,14 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
     }
     hipStream_t hs = (hipStream_t)stream;
     StatPlan front{};       // whose copies the workspace begins with
+    if (m.examples) {
+        StatPlan each = m.pair_plan;       // one example a group
+        each.nsplit = (int)B;
+        each.per_split = T;
+        float* M = (float*)workspace;
+        if (launch_stat_bf16(X, G, B, T, din, dout, MODE_IDENTITY, each, M, M, hs) != hipSuccess) return PEX_ERR_HIP;
+        return launch_fold_examples(M, B, m.pair_plan.per_split, din * dout, outs[0], outs[1], hs) == hipSuccess ? PEX_OK : PEX_ERR_HIP;
+    }
     if (m.pair) {
         const StatPlan& p = front = m.pair_plan;
         const int64_t n = p.din * p.dout;

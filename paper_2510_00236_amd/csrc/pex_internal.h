@@ -173,6 +173,8 @@ struct ReduceOutputs {
 hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit, int64_t group_stride, int64_t rows, int64_t cols, int64_t pitch,
                                   int64_t ld, hipStream_t stream, int leading = 0);
 
+// S_id = sum_b M[b], S_sq = sum_b M[b]^2 over M [B][n] (n a multiple of four), in groups of per_group examples whose sums are then added
+hipError_t launch_fold_examples(const float* M, int64_t B, int64_t per_group, int64_t n, float* S_id, float* S_sq, hipStream_t stream);
 // The same of up to 2 * PAIR_BATCH outputs of n[k] floats (a multiple of four) in one launch, nsplit groups each, n[k] apart
 struct ReduceBatch {
     int count;

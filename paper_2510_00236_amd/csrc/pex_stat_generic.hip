@@ -230,6 +230,45 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceOutputs io, 
     }
 }
 
+// S_id = sum_b M_b and S_sq = sum_b M_b^2 of n entries, a multiple of four, from the M_b themselves [B][n]: within groups of per_group
+// examples and then over the groups, both ascending, as the contraction kernels and the reduction of their partial sums add them.
+// Bound by memory, four examples in flight per lane (4 x 67 MB read and 134 written, after the contraction that wrote them: see profiles).
+__global__ __launch_bounds__(256) void fold_examples_kernel(const float* __restrict__ M, int64_t B, int64_t per_group, int64_t n,
+                                                            float* __restrict__ S_id, float* __restrict__ S_sq)
+{
+    const int64_t stride = (int64_t)gridDim.x * 1024;
+    for (int64_t e = (int64_t)blockIdx.x * 1024 + 4 * threadIdx.x; e < n; e += stride) {
+        const float* p = M + e;
+        const float4_v zero = {0.f, 0.f, 0.f, 0.f};
+        float4_v id = zero, sq = zero, sum_id, sum_sq;
+        int64_t begun = 0, next = per_group;      // groups added to the sums; the first example of the next one
+        auto end_group = [&]() {
+            sum_id = begun == 0 ? id : sum_id + id;
+            sum_sq = begun == 0 ? sq : sum_sq + sq;
+            id = sq = zero;
+            ++begun;
+            next += per_group;
+        };
+        for (int64_t b = 0; b < B; b += 4) {
+            float4_v v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b + u < B) v[u] = *(const float4_v*)(p + (b + u) * n);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (b + u >= B) break;
+                if (b + u == next) end_group();
+                id += v[u];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sq[c] = fmaf(v[u][c], v[u][c], sq[c]);
+            }
+        }
+        end_group();
+        *(float4_v*)(S_id + e) = sum_id;
+        *(float4_v*)(S_sq + e) = sum_sq;
+    }
+}
+
 // Several outputs of the same number of groups, the blocks of one after the other
 __global__ __launch_bounds__(256) void reduce_batch_kernel(ReduceBatch b, int nsplit)
 {
@@ -360,6 +399,13 @@ hipError_t launch_reduce_partials(const ReduceOutputs& io, int count, int nsplit
     int64_t blocks = (rows * ((cols + 3) / 4) + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     reduce_partials_kernel<<<dim3((unsigned)blocks, (unsigned)count), dim3(256), 0, stream>>>(io, nsplit, group_stride, rows, cols, pitch, ld, leading);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_examples(const float* M, int64_t B, int64_t per_group, int64_t n, float* S_id, float* S_sq, hipStream_t stream)
+{
+    const int64_t blocks = (n + 1023) / 1024;
+    fold_examples_kernel<<<dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, stream>>>(M, B, per_group, n, S_id, S_sq);
     return hipGetLastError();
 }
 
