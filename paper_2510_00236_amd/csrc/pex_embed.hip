@@ -518,22 +518,19 @@ __global__ __launch_bounds__(BUCKET_TILE) void bucket_sort_kernel(const TId* __r
 // writing half of each 32 bytes.
 // ALIGN = the largest of 4, 2, 1 that divides the row length, 0 for rows shorter than four columns.  Rows of any length from
 // four on are whole chunks: the last lane takes the row's last four columns, whoever else has some of them (the same sums in
-// the same order).  fp32 chunks are one load whatever their address (a dwordx4 asks for no more than a float's); bf16 rows of
-// even length start at dwords; in rows of odd length a chunk is the two dwords that hold its first three columns and its
-// last column by itself, told apart when they are added.  (Element by element, one column per lane, before: V=50257, d=767,
-// B=64 T=1024 288 us, 161 this way; V=40529, d=206, B=6 T=105 108 us, 43 together with the sort of one launch.)
+// the same order).  A chunk is one load whatever its address.  (Element by element, one column per lane, before: V=50257, d=767,
+// B=64 T=1024 288 us, 161 with two aligned loads; V=40529, d=206, B=6 T=105 108 us, 43 together with the sort of one launch.)
 constexpr int CH = 4;
 
 template <typename TIn, int ALIGN>
 struct Chunk {
     typedef __attribute__((ext_vector_type(4))) unsigned int u4;
-    typedef __attribute__((ext_vector_type(3))) unsigned int u3;
     typedef __attribute__((ext_vector_type(2))) unsigned int u2;
     typedef u4 __attribute__((aligned(4))) u4_u;
-    typedef u2 __attribute__((aligned(4))) u2_u;
+    typedef u2 __attribute__((aligned(2))) u2_u;
     static constexpr bool BF16 = sizeof(TIn) == 2;
-    typedef typename std::conditional<!BF16 || ALIGN == 0, u4, typename std::conditional<ALIGN == 1, u3, u2>::type>::type Raw;
-    static __device__ __forceinline__ Raw zero() { return (Raw)(0u); }
+    static constexpr int WORDS = !BF16 || ALIGN == 0 ? 4 : 2;
+    typedef typename std::conditional<WORDS == 4, u4, u2>::type Raw;
     // columns col .. col+3 of `row` (of length d)
     static __device__ __forceinline__ Raw load(const TIn* row, int64_t col, int64_t d)
     {
@@ -548,28 +545,13 @@ struct Chunk {
             return z;
         } else if constexpr (!BF16) return *(const u4_u*)p;
         else if constexpr (ALIGN == 4) return *(const u2*)p;
-        else if constexpr (ALIGN == 2) return *(const u2_u*)p;
-        else {
-            const u2 q = *(const u2_u*)((uintptr_t)p & ~(uintptr_t)3);
-            Raw z;
-            z[0] = q[0];
-            z[1] = q[1];
-            z[2] = p[3];
-            return z;
-        }
+        else return *(const u2_u*)p;
     }
-    // odd: the chunk starts in the second half of a dword
-    static __device__ __forceinline__ void add_to(float (&acc)[CH], const Raw& raw, bool odd)
+    static __device__ __forceinline__ void add_to(float (&acc)[CH], const Raw& raw)
     {
-        if constexpr (ALIGN == 0 || !BF16) {
+        if constexpr (WORDS == 4) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(BF16 ? raw[e] << 16 : raw[e]);
-        } else if constexpr (ALIGN == 1) {
-            const unsigned int lo0 = raw[0] << 16, hi0 = raw[0] & 0xffff0000u, lo1 = raw[1] << 16, hi1 = raw[1] & 0xffff0000u;
-            acc[0] += __uint_as_float(odd ? hi0 : lo0);
-            acc[1] += __uint_as_float(odd ? lo1 : hi0);
-            acc[2] += __uint_as_float(odd ? hi1 : lo1);
-            acc[3] += __uint_as_float(raw[2] << 16);
         } else {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
@@ -609,7 +591,12 @@ __device__ __forceinline__ int64_t chunk_start(int64_t col, int64_t d)
 constexpr int EMB_WAVES = 12;
 constexpr int EMB_ZROWS = 8;     // vocabulary rows a zero-fill wave looks at
 constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent rows a lane keeps in flight
-constexpr int EMB_ALONE = 64;    // a vocabulary row with at most this many positions is done by one wave (a lane reads each ahead)
+// A vocabulary row with at most so many positions is done by the wave it starts at; of a longer one each wave does its own examples.  Few
+// workgroups wait for the longest chain of such rows, sixteen at a time, of a wave: EMB_U (no less: two long runs must not start at one wave's
+// positions).  A full chip does not, and every row done together costs a pass through LDS: 64, whose positions a lane each reads ahead.
+// Whole calls with 64 and with 16: B=64 T=1000 V=2000 d=200 (334
+// workgroups) 37.9 and 33.8 us, B=40 T=600 V=9000 d=512 (250) 30.0 and 27.1; B=64 T=700 V=40000 d=768 (702) 71.7 and 72.5.
+inline int embed_alone(int64_t workgroups) { return workgroups > 2 * 256 ? 64 : EMB_U; }
 
 struct RowSums {
     float id[CH], sq[CH], sg[CH];
@@ -626,17 +613,13 @@ template <typename TIn, int ALIGN, int WANT>
 struct RowAccumulator {
     RowSums sums;
     float acc[CH];
-    int limit;     // first position of the next example
-    bool open;     // acc holds something
-    int T;
-    __device__ __forceinline__ void start(int T_)
+    int example;     // whose sum acc holds, -1: none
+    __device__ __forceinline__ void start()
     {
-        T = T_;
         sums.clear();
 #pragma unroll
         for (int e = 0; e < CH; ++e) acc[e] = 0.f;
-        limit = 0;
-        open = false;
+        example = -1;
     }
     __device__ __forceinline__ void fold()
     {
@@ -648,21 +631,17 @@ struct RowAccumulator {
             acc[e] = 0.f;
         }
     }
-    // p is uniform over the wave
-    __device__ __forceinline__ void add(int p, const typename Chunk<TIn, ALIGN>::Raw& raw, bool odd)
+    // `of` is uniform over the wave
+    __device__ __forceinline__ void add(int of, const typename Chunk<TIn, ALIGN>::Raw& raw)
     {
-        if (p >= limit) {
-            if (open) fold();
-            open = true;
-            limit = (p / T + 1) * T;
-        }
-        Chunk<TIn, ALIGN>::add_to(acc, raw, odd);
+        if (of != example) finish();
+        example = of;
+        Chunk<TIn, ALIGN>::add_to(acc, raw);
     }
     __device__ __forceinline__ void finish()
     {
-        if (open) fold();
-        open = false;
-        limit = 0;
+        if (example >= 0) fold();
+        example = -1;
     }
 };
 
@@ -670,18 +649,17 @@ struct RowAccumulator {
 // grid = chunk workgroups of every block of 64 * CH columns, then the zero-fill workgroups: the chunks are the long poles, the
 // zero fill runs under their tail (with the column blocks one after the other, each with its own tail, 149 against 141 us).
 //   chunk workgroup: wave i owns the sorted positions [c0, c0 + EMB_U) and with them every vocabulary row whose run
-//     starts there, and, of a run longer than EMB_ALONE, the examples that start there (each may continue past c0 + EMB_U).  It
+//     starts there, and, of a run longer than `alone`, the examples that start there (each may continue past c0 + EMB_U).  It
 //     loads EMB_U cotangent rows at a time whatever rows and examples they belong to, then adds them in order; sums of long runs
 //     go to LDS, where the wave a run starts at combines them after the one barrier.
-//     Small calls are bound by the chain of loads: position -> token -> extent of its run -> cotangent row, about a microsecond
-//     each.  All long runs of a workgroup side by side, the positions behind a wave's own read ahead with the first load and no
-//     search for the bounds of examples make it four loads; one long run after the other by the whole workgroup, each with a chain of
-//     its own, took B=7 T=565 V=7952 d=128 22.4 us (now 12.5), B=21 T=285 V=2759 d=320 22 (16), B=64 T=1024 V=50257 d=768 79 (70).
+//     Small calls are bound by one wave's instructions: its lookups take 1.3 us, its own sixteen rows 3.6 (at most 6), sixteen more of the
+//     run it is in 2 to 3 (measured inside the kernel).  All long runs of a workgroup are done side by side, the positions behind a
+//     wave's own are read ahead with the first load, nothing searches for the bounds of examples, one copy of the code adds a row.
 //   zero-fill workgroup: wave i looks at EMB_ZROWS vocabulary rows and writes zeros to those without positions.
 template <typename TIn, int ALIGN, int WANT>
 __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* __restrict__ G, const int* __restrict__ row_start,
                                                                     const int* __restrict__ keys, const int* __restrict__ pos,
-                                                                    int N, int V, int T, int64_t d, RowIndex index, int chunk_groups,
+                                                                    int N, int V, int T, int64_t d, RowIndex index, int alone, int chunk_groups,
                                                                     int colblocks, float* __restrict__ partial, float* __restrict__ S_id,
                                                                     float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
@@ -743,8 +721,9 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
     key = key < 0 ? V : (key > V ? V : key);
     if (valid && key < V) { const int r = index.at(key); rs = row_start[r]; re = row_start[r + 1]; }
     re = re > N ? N : re;
-    const bool is_long = re - rs > EMB_ALONE;
-    const bool mine = rs >= c0 || (is_long && p >= (before / T + 1) * T);
+    const bool is_long = re - rs > alone;
+    const int of = p / T;
+    const bool mine = rs >= c0 || (is_long && (before < 0 || of > before / T));
     const int p_ld = (valid && key < V && mine && p >= 0 && p < N) ? p : -1;
     const unsigned long long starts = __ballot(valid && key < V && is_long && rs == k);         // at most one among EMB_U positions
     const int row_before = __builtin_amdgcn_readfirstlane(valid && key < V && is_long && rs < c0 ? key : -1);
@@ -753,7 +732,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
     const int row_starting = starts ? __builtin_amdgcn_readlane(key, start_lane) : -1, to_starting = __builtin_amdgcn_readlane(re, start_lane);
 
     RowAccumulator<TIn, ALIGN, WANT> ra;
-    ra.start(T);
+    ra.start();
     int cur_v = -1;      // the row being accumulated
     auto keep = [&](int slot) {
         int n = 0;
@@ -770,45 +749,56 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
         ra.sums.clear();
     };
     if (row_before >= 0) keep(0);      // zeros, where no example of it starts here
-    int pu[EMB_U];
-    typename Ck::Raw data[EMB_U];
-    auto load_rows = [&]() {
+    // EMB_U cotangent rows, loaded at once whatever rows and examples they belong to, then added one after the other by one copy of the
+    // code, whose index into the registers is uniform over the wave: of 16 copies, each with the ends of examples and rows, a wave runs
+    // through cold code once (own sixteen rows of the slowest wave 6 us instead of 9; B=17 T=38 V=3662 d=192 16.0 -> 15.0 us).
+    constexpr int WORDS = Ck::WORDS, PER = 32 / WORDS, PARTS = EMB_U / PER;
+    typedef __attribute__((ext_vector_type(32))) unsigned int u32;
+    u32 data[PARTS];
+    const int64_t col_ld = col_ok ? col : 0;
+    auto load_rows = [&](int p_of_lane, int first) {       // rows of the positions that lanes first .. first + EMB_U - 1 hold (negative: none, row 0)
 #pragma unroll
-        for (int u = 0; u < EMB_U; ++u) data[u] = (pu[u] >= 0 && col_ok) ? Ck::load(G + (int64_t)pu[u] * d, col, d) : Ck::zero();
-    };
-    int ku[EMB_U];
+        for (int u = 0; u < EMB_U; ++u) {
+            const int q = __builtin_amdgcn_readlane(p_of_lane, first + u);
+            if (q < 0) continue;
+            const typename Ck::Raw raw = Ck::load(G + (int64_t)q * d, col_ld, d);
 #pragma unroll
-    for (int u = 0; u < EMB_U; ++u) {
-        pu[u] = __builtin_amdgcn_readlane(p_ld, u);
-        ku[u] = __builtin_amdgcn_readlane(key, u);
-    }
-    load_rows();
-#pragma unroll
-    for (int u = 0; u < EMB_U; ++u) {
-        if (pu[u] < 0) continue;
-        if (ku[u] != cur_v) {
-            close();
-            cur_v = ku[u];
+            for (int e = 0; e < WORDS; ++e) data[u / PER][u % PER * WORDS + e] = raw[e];
         }
-        ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
-    }
+    };
+    auto row = [&](const u32& part, int which) {
+        typename Ck::Raw raw;
+#pragma unroll
+        for (int e = 0; e < WORDS; ++e) raw[e] = part[which * WORDS + e];
+        return raw;
+    };
+    load_rows(p_ld, 0);
+#pragma unroll
+    for (int part = 0; part < PARTS; ++part)
+#pragma unroll 1
+        for (int i = 0; i < PER; ++i) {
+            const int q = __builtin_amdgcn_readlane(p_ld, part * PER + i), v = __builtin_amdgcn_readlane(key, part * PER + i);
+            if (q < 0) continue;
+            if (v != cur_v) {
+                close();
+                cur_v = v;
+            }
+            ra.add(__builtin_amdgcn_readlane(of, part * PER + i), row(data[part], i));
+        }
     // what is left of the last position's run: all of it, or of a long one the rest of the example
-    if (pu[EMB_U - 1] >= 0) {
-        const int run_end = __builtin_amdgcn_readlane(re, EMB_U - 1);
+    if (__builtin_amdgcn_readlane(p_ld, EMB_U - 1) >= 0) {
+        const int run_end = __builtin_amdgcn_readlane(re, EMB_U - 1), last_of = __builtin_amdgcn_readlane(of, EMB_U - 1);
         const bool whole = __builtin_amdgcn_readlane((int)is_long, EMB_U - 1) == 0;
         for (int k0 = c1;; k0 += 64) {
-            const unsigned long long rest = ~__ballot(k0 + lane < run_end && (whole || behind < ra.limit));
+            const int behind_of = behind / T;
+            const unsigned long long rest = ~__ballot(k0 + lane < run_end && (whole || behind_of == last_of));
             const int n = rest ? (int)__builtin_ctzll(rest) : 64;
             for (int u0 = 0; u0 < n; u0 += EMB_U) {
+                load_rows(lane < n ? behind : -1, u0);
 #pragma unroll
-                for (int u = 0; u < EMB_U; ++u) {
-                    const int q = __builtin_amdgcn_readlane(behind, u0 + u);
-                    pu[u] = u0 + u < n && q < N ? q : -1;
-                }
-                load_rows();
-#pragma unroll
-                for (int u = 0; u < EMB_U; ++u)
-                    if (pu[u] >= 0) ra.add(pu[u], data[u], ((pu[u] + (int)col) & 1) != 0);
+                for (int u = 0; u < EMB_U; ++u)      // (one row's, short: 16 copies)
+                    if (u0 + u < n)
+                        ra.add(__builtin_amdgcn_readlane(behind_of, u0 + u), row(data[u / PER], u % PER));
             }
             if (n < 64) break;
             behind = k0 + 64 + lane < N ? pos[k0 + 64 + lane] : -1;
@@ -850,7 +840,7 @@ __global__ __launch_bounds__(EMB_WAVES * 64) void embed_rows_kernel(const TIn* _
 // grid = (slices, column blocks), one wave each.
 template <int ALIGN, int WANT>
 __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict__ row_start, const int* __restrict__ keys, int N, int V,
-                                                           int64_t d, RowIndex index, const float* __restrict__ partial,
+                                                           int64_t d, RowIndex index, int alone, const float* __restrict__ partial,
                                                            float* __restrict__ S_id, float* __restrict__ S_sq, float* __restrict__ S_sg)
 {
     constexpr int SLICE = EMB_WAVES * EMB_U;
@@ -859,7 +849,7 @@ __global__ __launch_bounds__(64) void embed_combine_kernel(const int* __restrict
     const int key = keys[sc1 - 1];
     if (key < 0 || key >= V) return;
     const int rs = row_start[index.at(key)], re = row_start[index.at(key) + 1];
-    if (!(rs >= sc0 && re > sc1 && re <= N && re - rs > EMB_ALONE)) return;
+    if (!(rs >= sc0 && re > sc1 && re <= N && re - rs > alone)) return;
     const int64_t col0 = ((int64_t)blockIdx.y * 64 + threadIdx.x) * CH;
     if (col0 >= d) return;
     const int64_t col = chunk_start<ALIGN>(col0, d);
@@ -1002,11 +992,12 @@ hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, cons
     const int chunk_groups = (int)((N + per_group - 1) / per_group);
     const int zero_groups = (int)(((int64_t)V + EMB_WAVES * EMB_ZROWS - 1) / (EMB_WAVES * EMB_ZROWS));
     const unsigned colblocks = (unsigned)((d + 64 * CH - 1) / (64 * CH));
+    const int alone = embed_alone((int64_t)chunk_groups * colblocks);
     embed_rows_kernel<TIn, ALIGN, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
-        G, row_start, keys, pos, N, V, T, d, index, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
+        G, row_start, keys, pos, N, V, T, d, index, alone, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || chunk_groups == 1) return e;       // no run leaves a single slice
-    embed_combine_kernel<ALIGN, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, index, partial,
+    embed_combine_kernel<ALIGN, WANT><<<dim3((unsigned)chunk_groups, colblocks), dim3(64), 0, stream>>>(row_start, keys, N, V, d, index, alone, partial,
                                                                                                    S_id, S_sq, S_sg);
     return hipGetLastError();
 }
