@@ -18,7 +18,10 @@
 // Measured, in us, before -> now: square of 8 x 367 tokens, 64 x 128 fp32: 31.0 -> 15.2; sign, 36 x 32, 832 x 896 bf16: 33 -> 20 (182 tiles,
 // no groups); square, 117 x 322, 58 x 184 bf16 (no copies of odd rows): 36 -> 20; weighted sum and norms, 56 x 1154, 64 x 48 bf16: 84 -> 34;
 // plain, 1 x 9000, 20 x 31: one launch of 2 shares.  Rates stay low -- 8 x 827, 832 x 113 fp32 has 28 us for 2.4 GFLOP and 25 MB --
-// because a wave waits for a step of loads (about 1 us of bf16) and there are two on a SIMD.
+// because a wave waits for a step of loads (about 1 us of bf16) and there are two on a SIMD.  Of a small call the start (to the first two
+// steps' loads) is 1.3 to 2.4 us and the end 1 to 2 (clock stamps inside the kernel), most of it code that runs once: so nothing is divided that the grid
+// can hold, addresses are a scalar and one 32-bit offset, and a wave's sums leave as two stores.  Square, 3 x 20 tokens, 2669 x 504 bf16 10.1 -> 7.6 us;
+// 17 x 24, 3712 x 369 15.8 -> 12.8; pair, 2 x 546, 1920 x 64 10.8 -> 9.5; 26 x 2428, 176 x 64 20.9 -> 19.9.
 #include <type_traits>
 
 #include "pex_f32.h"
@@ -44,8 +47,7 @@ __device__ __forceinline__ void load_words(const void* p, uint32_t (&v)[N])
 
 template <typename TIn, int OUTS, int KW, int FN>
 __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void stat_small_kernel(
-    const TIn* __restrict__ X, const TIn* __restrict__ G, int64_t rows_total, int seg_len, int din, int dout, int64_t rows_per_split, int tiles_n, int tiles,
-    int64_t out_stride, float* __restrict__ out_id, float* __restrict__ out_sq, float* __restrict__ out_sg, const float* __restrict__ weight,
+    const TIn* __restrict__ X, const TIn* __restrict__ G, int rows_total, int seg_len, int din, int dout, int per_split, int64_t out_stride, float* __restrict__ out_id, float* __restrict__ out_sq, float* __restrict__ out_sg, const float* __restrict__ weight,
     float* __restrict__ norm_partial, int examples_total, float alpha, float nan_sign)
 {
     constexpr bool BF16 = sizeof(TIn) == 2;
@@ -55,28 +57,37 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     constexpr int R = BF16 ? 32 : 16, NR = BF16 ? 8 : 4;       // tokens of a step, of a lane
     constexpr int XW = BF16 ? 2 : 4, GW = BF16 ? FN / 2 : FN;  // words a lane loads of a token
     constexpr int ALIGN = (int)sizeof(TIn);
-    constexpr int TILES = FM * FN, SL = TILES / KW, FS = TILES / W;    // 16 x 16 tiles of a wave: all, after an example, at the end
-    __shared__ float4_t red[W * TILES * 64];
+    constexpr int TILES = FM * FN, SL = KW == 1 ? TILES : FN / 2;      // 16 x 16 tiles of a wave, what it keeps of them after an example (fours of entries)
+    static_assert(FM * 2 == W && (KW == 1 || KW == W), "a wave finishes two of the four rows of one feature");
+    // What the waves add up goes through LDS in halves: entries 2h, 2h + 1 of every lane's four of a tile.  Wave w finishes those of h = w % 2 of
+    // the tiles of row feature w / 2: of each of two rows FN columns side by side, one store (four of four bytes each took 2 us of a
+    // launch of 5.4: sign, 8 x 21, 960 x 384).
+    typedef __attribute__((ext_vector_type(2))) float float2_t;
+    __shared__ float2_t red[2][W * TILES][64];
     const int lane = threadIdx.x & 63, q = lane >> 4, p = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), ew = wave / KW, kw = wave % KW;
-    const int split = (int)(blockIdx.x / (unsigned)tiles), tile = (int)(blockIdx.x % (unsigned)tiles);
-    const int i0 = tile / tiles_n * SM_T, j0 = tile % tiles_n * (16 * FN);
+    // grid = (column tiles, row tiles, groups): the start of a workgroup is a part of a small call's time, so it divides nothing
+    const int split = (int)blockIdx.z, tile = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int i0 = (int)blockIdx.y * SM_T, j0 = (int)blockIdx.x * (16 * FN);
 
-    const int64_t row_begin = (int64_t)split * rows_per_split;
-    int64_t row_end = row_begin + rows_per_split;
-    if (row_end > rows_total) row_end = rows_total;
     // segment: one example; of a plain contraction an equal share of the rows (the last one may be shorter)
-    const int64_t rows = row_end - row_begin, shares = (rows + SM_CHUNK - 1) / SM_CHUNK;
-    const int slen = PER_EXAMPLE ? seg_len : (int)((rows + shares - 1) / shares);
-    const int nex = (int)((rows + slen - 1) / slen);
+    const int first_example = PER_EXAMPLE ? split * per_split : 0;
+    const int64_t row_begin = PER_EXAMPLE ? (int64_t)first_example * seg_len : (int64_t)split * per_split;
+    int slen = seg_len, nex = per_split < examples_total - first_example ? per_split : examples_total - first_example, rows = 0;
+    if constexpr (!PER_EXAMPLE) {
+        rows = per_split < rows_total - (int)row_begin ? per_split : rows_total - (int)row_begin;
+        const unsigned shares = ((unsigned)rows + SM_CHUNK - 1) / SM_CHUNK;
+        slen = (int)(((unsigned)rows + shares - 1) / shares);
+        nex = (int)(((unsigned)rows + (unsigned)slen - 1) / (unsigned)slen);
+    }
     // this wave: tokens [t_begin, t_end) of examples ew, ew + EW, ...
     const int per = ((slen + R - 1) / R + KW - 1) / KW * R;
     const int t_begin = kw * per;
     auto t_end = [&](int ex) {
         int end = t_begin + per < slen ? t_begin + per : slen;
         if (!PER_EXAMPLE) {
-            const int64_t left = rows - (int64_t)ex * slen;
-            if (end > left) end = (int)left;
+            const int left = rows - ex * slen;
+            if (end > left) end = left;
         }
         return end;
     };
@@ -85,6 +96,11 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // first of the features this lane loads: the last ones of the width where there are fewer
     const int cx = i0 + 4 * p + 4 <= din ? i0 + 4 * p : din - 4, cg = j0 + FN * p + FN <= dout ? j0 + FN * p : dout - FN;
     auto row_of = [&](int r) { return BF16 ? 8 * q + r : 4 * r + q; };
+    // byte offsets inside a step: of this lane's first token, and from one token to the next
+    const uint32_t x_row = (uint32_t)din * (uint32_t)sizeof(TIn), g_row = (uint32_t)dout * (uint32_t)sizeof(TIn);
+    const uint32_t x_col = (uint32_t)cx * (uint32_t)sizeof(TIn), g_col = (uint32_t)cg * (uint32_t)sizeof(TIn);
+    const uint32_t x_lane = (uint32_t)row_of(0) * x_row + x_col, g_lane = (uint32_t)row_of(0) * g_row + g_col;
+    constexpr uint32_t ROWS_ON = BF16 ? 1 : 4;
     uint32_t xr[2][NR][XW], gr[2][NR][GW];
     int left[2];       // tokens of a slot's step that exist
     int ld_ex = ew, ld_t = t_begin;
@@ -93,17 +109,19 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         while (ld_ex < nex && ld_t >= t_end(ld_ex)) { ld_ex += EW; ld_t = t_begin; }
         left[s] = 0;
         if (ld_ex >= nex) return;
-        const int n = t_end(ld_ex) - ld_t;
+        const int n = __builtin_amdgcn_readfirstlane(t_end(ld_ex) - ld_t);
         left[s] = n;
-        const int64_t row = row_begin + (int64_t)ld_ex * slen + ld_t;
+        // (every lane of the wave is at the same token, which the compiler does not see: addresses in scalar registers)
+        const int64_t row = row_begin + (int64_t)__builtin_amdgcn_readfirstlane(ld_ex) * slen + __builtin_amdgcn_readfirstlane(ld_t);
         const char* xb = (const char*)(X + row * din);
         const char* gb = (const char*)(G + row * dout);
+        // the last token there is stands in for those past it
+        const uint32_t rows_on = (uint32_t)((n < R ? n : R) - 1), x_last = rows_on * x_row + x_col, g_last = rows_on * g_row + g_col;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            int t = row_of(r);
-            if (n < R) t = t < n ? t : n - 1;
-            load_words<XW, ALIGN>(xb + ((uint32_t)t * (uint32_t)din + (uint32_t)cx) * (uint32_t)sizeof(TIn), xr[s][r]);
-            load_words<GW, ALIGN>(gb + ((uint32_t)t * (uint32_t)dout + (uint32_t)cg) * (uint32_t)sizeof(TIn), gr[s][r]);
+            const uint32_t xo = x_lane + r * ROWS_ON * x_row, go = g_lane + r * ROWS_ON * g_row;
+            load_words<XW, ALIGN>(xb + (xo < x_last ? xo : x_last), xr[s][r]);
+            load_words<GW, ALIGN>(gb + (go < g_last ? go : g_last), gr[s][r]);
         }
         ld_t += R;
     };
@@ -173,15 +191,20 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
 
     // 16 x 16 tile t = m FN + n: entry r of a lane is feature `m` of the four of row lane 4q + r, feature n of column lane p
-    auto row_feature = [&](int t, int r, bool& own) {
-        const int c = i0 + 4 * (4 * q + r), f = (c + 4 <= din ? c : din - 4) + t / FN;
+    auto row_feature = [&](int m, int r, bool& own) {
+        const int c = i0 + 4 * (4 * q + r), f = (c + 4 <= din ? c : din - 4) + m;
         own = f >= c && c < din;
         return f;
     };
-    auto col_feature = [&](int t, bool& own) {
-        const int c = j0 + FN * p, f = (c + FN <= dout ? c : dout - FN) + t % FN;
-        own = f >= c && c < dout;
-        return f;
+    auto col_feature = [&](int n, bool& own) {
+        const int c = j0 + FN * p;
+        own = cg + n >= c && c < dout;
+    };
+    // (KW = W: entry 2 (n % 2) + i of four n / 2 is row i of this wave's two, column n)
+    const int mine_m = wave / 2, mine_h = wave % 2;
+    auto share = [&](int w, int t, const float4_t& v) __attribute__((always_inline)) {
+        red[0][w * TILES + t][lane] = float2_t{v[0], v[1]};
+        red[1][w * TILES + t][lane] = float2_t{v[2], v[3]};
     };
     float4_t s_id[HAS_ID ? SL : 1], s_sq[HAS_SQ ? SL : 1], s_sg[HAS_SG ? SL : 1];
 #pragma unroll
@@ -213,21 +236,28 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                     v += run[t];
                     run[t] = float4_t{0.f, 0.f, 0.f, 0.f};
                 }
-                red[(wave * TILES + t) * 64 + lane] = v;
+                share(wave, t, v);
             }
             __syncthreads();
         }
-        const int example = (int)(row_begin / seg_len) + ex;
+        const int example = first_example + ex;
         const float w = (OUTS & F_IDW) && ex < nex ? weight[example] : 1.f;
-        float norm = 0.f;
+        float part[4] = {0.f, 0.f, 0.f, 0.f};        // of a norm: four short chains of additions
         if (ex < nex) {
 #pragma unroll
             for (int t = 0; t < SL; ++t) {
-                const int tt = kw * SL + t;
-                float4_t v = KW == 1 ? acc[t / FN][t % FN] : red[(ew * KW * TILES + tt) * 64 + lane];
-                if constexpr (KW > 1) {
+                float4_t v;
+                if constexpr (KW == 1) v = acc[t / FN][t % FN];
+                else {
 #pragma unroll
-                    for (int k = 1; k < KW; ++k) v += red[((ew * KW + k) * TILES + tt) * 64 + lane];
+                    for (int half = 0; half < 2; ++half) {
+                        const int tt = mine_m * FN + 2 * t + half;
+                        float2_t u = red[mine_h][tt][lane];
+#pragma unroll
+                        for (int k = 1; k < KW; ++k) u += red[mine_h][k * TILES + tt][lane];
+                        v[2 * half] = u[0];
+                        v[2 * half + 1] = u[1];
+                    }
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -242,14 +272,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                     }
                     if (OUTS & F_NORM) {
                         bool mine_i, mine_j;
-                        row_feature(tt, r, mine_i);
-                        col_feature(tt, mine_j);
+                        row_feature(KW == 1 ? t / FN : mine_m, KW == 1 ? r : 2 * mine_h + r % 2, mine_i);
+                        col_feature(KW == 1 ? t % FN : 2 * t + r / 2, mine_j);
                         const float u = mine_i && mine_j ? x : 0.f;      // (on both factors: an infinity that is not ours times zero is NaN)
-                        norm = fmaf(u, u, norm);
+                        part[r] = fmaf(u, u, part[r]);
                     }
                 }
             }
             if (OUTS & F_NORM) {
+                float norm = (part[0] + part[1]) + (part[2] + part[3]);
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) norm += __shfl_xor(norm, off);
                 if (lane == 0) norm_partial[((int64_t)tile * KW + kw) * examples_total + example] = norm;
@@ -289,49 +320,54 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     if (OUTS & F_NORM) return;
 
-    // the groups' sums, each wave an eighth of the tile
-    auto finish = [&](const float4_t* sums, float* __restrict__ out) __attribute__((always_inline)) {
-        float4_t v[FS];
+    // the groups' sums, each wave an eighth of the tile.  (The last columns of a width may be another lane's or tile's too, who stores the same.)
+    auto finish = [&](const float4_t* sums, float* __restrict__ out, bool first) __attribute__((always_inline)) {
+        float v[2][FN];
         if constexpr (EW > 1) {
-            __syncthreads();
+            if (!first) __syncthreads();
 #pragma unroll
-            for (int t = 0; t < SL; ++t) red[(wave * SL + t) * 64 + lane] = sums[t];
+            for (int t = 0; t < TILES; ++t) share(wave, t, sums[t]);
             __syncthreads();
         }
 #pragma unroll
-        for (int f = 0; f < FS; ++f) {
-            const int t = ew * FS + f;             // of this kw's SL tiles
-            if constexpr (EW == 1) v[f] = sums[f];
-            else {
-                v[f] = red[(kw * SL + t) * 64 + lane];
+        for (int n = 0; n < FN; ++n) {
+            if constexpr (EW == 1) {
+                v[0][n] = sums[n / 2][2 * (n % 2)];
+                v[1][n] = sums[n / 2][2 * (n % 2) + 1];
+            } else {
+                const int t = mine_m * FN + n;
+                float2_t u = red[mine_h][t][lane];
 #pragma unroll
-                for (int e = 1; e < EW; ++e) v[f] += red[((e * KW + kw) * SL + t) * 64 + lane];
+                for (int e = 1; e < EW; ++e) u += red[mine_h][e * TILES + t][lane];
+                v[0][n] = u[0];
+                v[1][n] = u[1];
             }
-            const int tt = kw * SL + t;
-            bool mine_j;
-            const int j = col_feature(tt, mine_j);
+        }
+        typedef __attribute__((ext_vector_type(FN))) float row_t;
+        typedef row_t __attribute__((aligned(4))) row_u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                bool mine_i;
-                const int i = row_feature(tt, r, mine_i);
-                if (mine_i && mine_j) out[(int64_t)split * out_stride + (int64_t)i * dout + j] = v[f][r];
-            }
+        for (int r = 0; r < 2; ++r) {
+            bool mine_i;
+            const int i = row_feature(mine_m, 2 * mine_h + r, mine_i);
+            row_t x;
+#pragma unroll
+            for (int n = 0; n < FN; ++n) x[n] = v[r][n];
+            if (mine_i && j0 + FN * p < dout) *(row_u*)(out + (int64_t)split * out_stride + (int64_t)i * dout + cg) = x;
         }
     };
-    if constexpr (HAS_ID) finish(s_id, out_id);
-    if constexpr (HAS_SQ) finish(s_sq, out_sq);
-    if constexpr (HAS_SG) finish(s_sg, out_sg);
+    if constexpr (HAS_ID) finish(s_id, out_id, true);
+    if constexpr (HAS_SQ) finish(s_sq, out_sq, !HAS_ID);
+    if constexpr (HAS_SG) finish(s_sg, out_sg, !HAS_ID && !HAS_SQ);
 }
 
 template <typename TIn, int OUTS, int KW, int FN>
 hipError_t launch_small(const void* X, const void* G, int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& plan, float* out_id, float* out_sq,
                         float* out_sg, hipStream_t stream, const float* weight, float* norm_partial, float alpha, float nan_sign)
 {
-    constexpr bool PER_EXAMPLE = !(OUTS == F_PLAIN || OUTS == F_TOKEN);
-    const int64_t tiles_n = (dout + 16 * FN - 1) / (16 * FN), tiles = (din + SM_T - 1) / SM_T * tiles_n;
-    stat_small_kernel<TIn, OUTS, KW, FN><<<dim3((unsigned)(tiles * plan.nsplit)), dim3(W * 64), 0, stream>>>(
-        (const TIn*)X, (const TIn*)G, B * T, (int)T, (int)din, (int)dout, PER_EXAMPLE ? plan.per_split * T : plan.per_split, (int)tiles_n, (int)tiles,
-        din * dout, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, nan_sign);
+    const int64_t tiles_n = (dout + 16 * FN - 1) / (16 * FN), tiles_m = (din + SM_T - 1) / SM_T;
+    if (tiles_m > 65535 || plan.nsplit > 65535) return hipErrorInvalidValue;       // (more tiles by far than layers that are planned here have)
+    stat_small_kernel<TIn, OUTS, KW, FN><<<dim3((unsigned)tiles_n, (unsigned)tiles_m, (unsigned)plan.nsplit), dim3(W * 64), 0, stream>>>(
+        (const TIn*)X, (const TIn*)G, (int)(B * T), (int)T, (int)din, (int)dout, (int)plan.per_split, din * dout, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, nan_sign);
     return hipGetLastError();
 }
 
