@@ -182,11 +182,28 @@ _torch = _F32 = _F64 = _U8 = None
 _DTYPE_CODES = {}
 
 
+# The checks and calls of a training loop in native code (host/pex_host.cpp), from the second call on: a function of it takes a call or
+# returns False, and then the Python code below makes the checks one by one.  Without the module everything goes that way.
+_host = None
+
+
 def _bind_torch():
-    global _torch, _F32, _F64, _U8
+    global _torch, _F32, _F64, _U8, _host
     import torch
     _DTYPE_CODES.update({torch.float32: PEX_F32, torch.bfloat16: PEX_BF16})
     _F32, _F64, _U8, _torch = torch.float32, torch.float64, torch.uint8, torch
+    if os.path.exists(LIB_PATH):
+        try:
+            from . import _pex_host
+            _pex_host.setup(AdamParams, MomentParams, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+            _host = _pex_host
+        except (ImportError, AttributeError):      # not built, or a torch without a GPU runtime
+            pass
+
+
+def _refused(code):
+    """The HIP runtime refused a launch of a native call."""
+    raise PexError(code, status_string(code))
 
 
 def _dtype_code(t) -> int:
@@ -359,6 +376,10 @@ def _invoke_ws(query, qargs, workspace, fn, *args):
 
 def pex_stat(X, G, phi, S=None, workspace=None, stream=None):
     """S[din,dout] = sum_b phi(X_b^T G_b), fp32.  ``phi`` is 'identity' | 'square' | 'sign' (or its code)."""
+    if _host is not None and stream is None:
+        r = _host.stat(X, G, PHI.get(phi, phi), S, workspace)
+        if r:
+            return S if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
@@ -388,6 +409,10 @@ def pex_stat_noalloc(X, G, phi, S, stream=None):
 def pex_stat_multi(X, G, want, out=None, workspace=None, stream=None):
     """Several statistics from one pass.  ``want`` is an iterable of 'identity' | 'square' | 'sign' (or the bit
     set); returns a dict name -> S[din,dout] fp32.  ``out`` may supply the output tensors by name."""
+    if _host is not None and stream is None:
+        r = _host.stat_multi(X, G, _want_mask(want), out, workspace)
+        if r:
+            return r if r.__class__ is dict else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
@@ -463,6 +488,10 @@ def pex_stat_pair_batch_workspace_bytes(widths, B, T, dtype_code) -> int:
 def pex_stat_pair_batch(layers, workspace=None, stream=None):
     """pex_stat_multi(identity, square) of several layers of one batch, as few launches as their sizes allow: ``layers`` are
     (X, G, out dict or None) with the same B, T and type.  Returns a list of dicts name -> S[din,dout] fp32."""
+    if _host is not None and stream is None:
+        r = _host.stat_pair_batch(layers, workspace)
+        if r:
+            return r if r.__class__ is list else _refused(r)
     if _torch is None:
         _bind_torch()
     X0 = layers[0][0]
@@ -501,6 +530,10 @@ def pex_vec_stat_batch_workspace_bytes(widths, B, T, dtype_code) -> int:
 def pex_vec_stat_batch(items, want=("identity", "square", "sign"), workspace=None, stream=None):
     """pex_vec_stat of several vectors of one batch in one launch of each pass: ``items`` are (A, C or None, out dict or None) with
     the same B, T and type.  Returns a list of dicts name -> s[d] fp32."""
+    if _host is not None and stream is None:
+        r = _host.vec_stat_batch(items, _want_mask(want), workspace)
+        if r:
+            return r if r.__class__ is list else _refused(r)
     if _torch is None:
         _bind_torch()
     mask = _want_mask(want)
@@ -549,6 +582,10 @@ def pex_stat_power_workspace_bytes(B, T, din, dout, dtype_code) -> int:
 
 def pex_example_norms(X, G, N=None, workspace=None, stream=None):
     """N[B] = ||X_b^T G_b||_F^2, fp32."""
+    if _host is not None and stream is None:
+        r = _host.example_norms(X, G, N, workspace)
+        if r:
+            return N if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
@@ -564,6 +601,10 @@ def pex_example_norms(X, G, N=None, workspace=None, stream=None):
 
 def pex_weighted_sum(X, G, w, S=None, workspace=None, stream=None):
     """S[din,dout] = sum_b w[b] X_b^T G_b, fp32 (``w`` fp32 [B] on the GPU)."""
+    if _host is not None and stream is None:
+        r = _host.weighted_sum(X, G, w, S, workspace)
+        if r:
+            return S if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
@@ -580,6 +621,10 @@ def pex_weighted_sum(X, G, w, S=None, workspace=None, stream=None):
 def pex_clip_weights(N, max_norm, w=None, stream=None):
     """w[B] = min(1, max_norm / sqrt(sum over layers of N)), ``N`` fp32 [layers, B] (or [B]) of per-layer squared
     per-example gradient norms on the GPU."""
+    if _host is not None and stream is None:
+        r = _host.clip_weights(N, max_norm, w)
+        if r:
+            return w if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     if N.dim() not in (1, 2):
@@ -620,6 +665,10 @@ def pex_token_norms(X, G, N_tok=None, stream=None):
 
 def pex_token_sq(X, G, S=None, workspace=None, stream=None):
     """S_tok[din,dout] = (X o X)^T (G o G), fp32."""
+    if _host is not None and stream is None:
+        r = _host.token_sq(X, G, S, workspace)
+        if r:
+            return S if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
@@ -636,6 +685,10 @@ def pex_token_sq(X, G, S=None, workspace=None, stream=None):
 def pex_adam_update(theta, m, v, S_id, S_sq, variant, params: AdamParams, stream=None):
     """One in-place step of the Adam family (Algorithm 1).  ``S_sq`` may be None for plain Adam."""
     code = VARIANT.get(variant, variant)
+    if _host is not None and stream is None:
+        r = _host.adam_update(theta, m, v, S_id, S_sq, code, params)
+        if r:
+            return None if r is True else _refused(r)
     n = theta.numel()
     _invoke(lib().pex_adam_update, _f32(theta, "theta"), _f32(m, "m", n), _f32(v, "v", n), _f32(S_id, "S_id", n),
                                  _f32(S_sq, "S_sq", n) if S_sq is not None else None, n, code,
@@ -644,6 +697,10 @@ def pex_adam_update(theta, m, v, S_id, S_sq, variant, params: AdamParams, stream
 
 def pex_signsgd_update(theta, m, S_sign, lr, beta, weight_decay, B, debias=False, step=1, stream=None):
     """One in-place MicroSignSGD step (EMA o avg o sign)."""
+    if _host is not None and stream is None:
+        r = _host.signsgd_update(theta, m, S_sign, lr, beta, weight_decay, B, debias, step)
+        if r:
+            return None if r is True else _refused(r)
     n = theta.numel()
     _invoke(lib().pex_signsgd_update, _f32(theta, "theta"), _f32(m, "m", n), _f32(S_sign, "S_sign", n), n, lr, beta,
                                     weight_decay, int(B), int(bool(debias)), int(step), _stream(stream))
@@ -684,6 +741,10 @@ def pex_embed_stat_workspace_bytes(B, T, V, d) -> int:
 def pex_embed_stat(ids, G, V, want, out=None, workspace=None, stream=None):
     """Per-example gradient statistics of an embedding table: ``ids`` [B,T] int32/int64, ``G`` [B,T,d] cotangents of
     the looked-up vectors; returns a dict name -> S[V,d] fp32 for the names in ``want``.  Ids outside [0,V) are padding."""
+    if _host is not None and stream is None:
+        r = _host.embed_stat(ids, G, V, _want_mask(want), out, workspace)
+        if r:
+            return r if r.__class__ is dict else _refused(r)
     if _torch is None:
         _bind_torch()
     if ids.dim() != 2 or G.dim() != 3 or tuple(G.shape[:2]) != tuple(ids.shape):
@@ -781,6 +842,10 @@ def pex_adam_step(tensors, variant, params: AdamParams, sum_sq, max_norm, moment
     """The end of a step over all tensors of a model in a few launches: ``sum_sq`` = sum of S_id^2 over them, the clipped update of
     each (pex_adam_update_clipped) and, with ``moments``, the moment tracking of each into ``sums`` [len(tensors), 2] (float64;
     pex_moment_track).  ``tensors`` are tuples (theta, m, v, S_id, S_sq) or, with ``moments``, (.., ema_adam, ema_micro)."""
+    if _host is not None and stream is None:
+        r = _host.adam_step(tensors, VARIANT.get(variant, variant), params, sum_sq, max_norm, moments, sums, workspace)
+        if r:
+            return sums if r is True else _refused(r)
     if _torch is None:
         _bind_torch()
     width = 5 if moments is None else 7

@@ -1,10 +1,11 @@
-"""Build libpex.so (HIP, gfx950) in-tree with hipcc.  Run as ``python -m paper_2510_00236_amd.build``."""
+"""Build libpex.so (HIP, gfx950) in-tree with hipcc, and the binding's native calls with g++.  Run as ``python -m paper_2510_00236_amd.build``."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
@@ -18,12 +19,27 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextr
          "-I", os.path.join(_ROOT, "include"), "-I", CSRC]
 
 
+HOST_SOURCE = os.path.join(_HERE, "host", "pex_host.cpp")
+HOST_MODULE = os.path.join(_HERE, "_pex_host.so")
+
+
+def host_command():
+    """Compiles the binding's native calls against the headers of the installed torch and links them to libpex.so beside them."""
+    import importlib.util
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    include = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"],
+               os.path.join(_ROOT, "include"), "/opt/rocm/include"]
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", *["-I" + d for d in include],
+            HOST_SOURCE, "-o", HOST_MODULE, "-L" + os.path.join(torch_dir, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python", "-L" + _HERE, "-l:libpex.so",
+            "-Wl,-rpath,$ORIGIN", "-Wl,--allow-shlib-undefined"]
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every translation unit and link libpex.so.  Always recompiles."""
+    """Compile every translation unit, link libpex.so and the module beside it.  Always recompiles."""
     os.makedirs(_OBJ, exist_ok=True)
     objs = []
     procs = []
@@ -58,6 +74,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         raise RuntimeError(f"libpex build failed: {isa_error}")
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    subprocess.run(host_command(), check=True)
     return LIB
 
 
