@@ -593,10 +593,11 @@ constexpr int EMB_ZROWS = 8;     // vocabulary rows a zero-fill wave looks at
 constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent rows a lane keeps in flight
 // A vocabulary row with at most so many positions is done by the wave it starts at; of a longer one each wave does its own examples.  Few
 // workgroups wait for the longest chain of such rows, sixteen at a time, of a wave: EMB_U (no less: two long runs must not start at one wave's
-// positions).  A full chip does not, and every row done together costs a pass through LDS: 64, whose positions a lane each reads ahead.
-// Whole calls with 64 and with 16: B=64 T=1000 V=2000 d=200 (334
-// workgroups) 37.9 and 33.8 us, B=40 T=600 V=9000 d=512 (250) 30.0 and 27.1; B=64 T=700 V=40000 d=768 (702) 71.7 and 72.5.
-inline int embed_alone(int64_t workgroups) { return workgroups > 2 * 256 ? 64 : EMB_U; }
+// positions).  A full chip does not, nor does one with a workgroup a unit that mostly writes a large table, and every row done together costs a
+// pass through LDS: 64, whose positions a lane each reads ahead.  Whole calls with 64 and with 16: B=64 T=1000 V=2000 d=200 (334 workgroups) 37.9
+// and 33.8 us, B=40 T=600 V=9000 d=512 (250) 30.0 and 27.1, B=30 T=500 V=50257 d=768 (237) 74.8 and 74.1; B=64 T=700 V=40000 d=768 (702) 71.7 and
+// 72.5, B=56 T=300 V=25000 d=1000 (352) 65.2 and 66.6.
+inline int embed_alone(int64_t workgroups, int64_t entries) { return workgroups > 2 * 256 || (workgroups > 256 && entries > ((int64_t)1 << 24)) ? 64 : EMB_U; }
 
 struct RowSums {
     float id[CH], sq[CH], sg[CH];
@@ -992,7 +993,7 @@ hipError_t launch_rows(const TIn* G, const int* row_start, const int* keys, cons
     const int chunk_groups = (int)((N + per_group - 1) / per_group);
     const int zero_groups = (int)(((int64_t)V + EMB_WAVES * EMB_ZROWS - 1) / (EMB_WAVES * EMB_ZROWS));
     const unsigned colblocks = (unsigned)((d + 64 * CH - 1) / (64 * CH));
-    const int alone = embed_alone((int64_t)chunk_groups * colblocks);
+    const int alone = embed_alone((int64_t)chunk_groups * colblocks, (int64_t)V * d);
     embed_rows_kernel<TIn, ALIGN, WANT><<<dim3((unsigned)chunk_groups * colblocks + (unsigned)zero_groups), dim3(EMB_WAVES * 64), 0, stream>>>(
         G, row_start, keys, pos, N, V, T, d, index, alone, chunk_groups, (int)colblocks, partial, S_id, S_sq, S_sg);
     hipError_t e = hipGetLastError();

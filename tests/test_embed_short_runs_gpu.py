@@ -42,7 +42,7 @@ def test_runs_about_a_waves_positions(d, dtype, B, each):
     _check(ids, torch.randn(B, T, d, device=DEV, generator=g).to(dtype), V)
 
 
-@pytest.mark.parametrize("B,T,V,d", [(24, 1000, 900, 1024), (24, 1100, 900, 1024), (30, 1000, 700, 1021)])       # 500, 552 and 628 workgroups
+@pytest.mark.parametrize("B,T,V,d", [(24, 1000, 900, 1024), (24, 1100, 900, 1024), (30, 1000, 700, 1021), (14, 1000, 17000, 1024)])       # 500, 552 and 628 workgroups; 292 and 17 M entries
 def test_on_both_sides_of_a_full_chip(B, T, V, d):
     g = torch.Generator(device=DEV).manual_seed(T)
     ids = (torch.rand(B, T, device=DEV, generator=g) ** 2 * V).long()
