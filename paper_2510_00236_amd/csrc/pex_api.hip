@@ -826,20 +826,22 @@ struct MultiPlan {
 // 992 -> 860; 16 x 4096, 768 x 3072 411 -> 313; 16 x 4092, 1024 x 1024 155 -> 121; 7 x 3000, 3000 x 1000 231 -> 151; but 12 x 1500,
 // 2048 x 2048 157 -> 176 and 5 x 1200, 4096 x 4096 202 -> 287.  The pair's estimate is 20 % low on such layers (0 to 27), more where its groups
 // are single examples, both of whose statistics it writes and reads: there this is taken for any gain, elsewhere for a clear one.
+// Of examples of 256 tokens on the layers that are cut into groups of two gain: 8 x 684, 1280 x 1152 39.6 -> 33.8; 12 x 521, 576 x 1792 36.4 -> 31.9.
 // Returns how much of the pair's time that is, 1 where it is not taken.
 static double examples_share(int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& pair)
 {
-    if (pair.kernel != 1 || pair.copy_bytes > 0 || T < 1024) return 1.0;
+    if (pair.kernel != 1 || pair.copy_bytes > 0 || T < 256) return 1.0;
     const double bytes = (double)din * (double)dout * 4.0, mb = (double)B * bytes * 1.0e-6;
     if ((double)B * bytes > 512.0 * 1048576.0) return 1.0;
     for (int k = 0; k < NUM_OPTIONS; ++k)
         if (option(k) != DEFAULT_OPTIONS[k]) return 1.0;       // the options are about the other plans
     int bm, bn;
     bf16_tile_shape(MODE_IDENTITY, B, &bm, &bn);
+    const bool long_ones = T >= 1024;       // (the four-wave kernel; the eight-wave one below)
     const int64_t wgs = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn) * B;
-    const double t = (double)((wgs + 255) / 256) * 2.0 * (double)T * bm * bn / 6.1e12 + 2.0 * bytes / 5.0e12 + 8.0e-6 +
+    const double t = (double)((wgs + 255) / 256) * 2.0 * (double)T * bm * bn / (long_ones ? 6.1e12 : 5.2e12) + 2.0 * bytes / 5.0e12 + 8.0e-6 +
                      1.0e-6 * (mb < 200.0 ? 0.3 * mb : 60.0 + 0.55 * (mb - 200.0));
-    return t < pair.seconds * (pair.per_split == 1 ? 1.2 : 1.04) ? t / (1.2 * pair.seconds) : 1.0;
+    return t < pair.seconds * (!long_ones ? 1.1 : pair.per_split == 1 ? 1.2 : 1.04) ? t / (1.2 * pair.seconds) : 1.0;
 }
 
 static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true,

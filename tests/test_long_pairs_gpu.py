@@ -14,6 +14,8 @@ CASES = [
     (3, 5000, 1000, 3000),       # blocks and slabs that are not whole; groups of two examples and of one
     (5, 2049, 2048, 2056),       # one token past a slab, one chunk past a block
     (16, 4092, 1024, 1024),      # eight groups of two
+    (6, 429, 968, 1856),         # shorter examples, on the eight-wave kernel: groups of two
+    (20, 261, 768, 640),
 ]
 
 
