@@ -808,17 +808,6 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
     return PEX_OK;
 }
 
-// How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (on the layers the
-// MFMA kernels take), the rest one at a time.
-struct MultiPlan {
-    bool examples;        // identity and square from the M_b themselves, in the workspace (pair_plan: whose groups their sums have)
-    bool pair;            // a fused launch is used
-    uint32_t pair_want;   // for which statistics
-    uint32_t single_want; // served by separate pex_stat passes
-    StatPlan pair_plan;
-    size_t query_bytes;   // what the call asks for: at least what it would without the kernel of small layers
-};
-
 // Identity and square of few long examples of a bf16 layer: M_b of every example by the kernel of plain contractions -- one register tile
 // on 256 x 256 blocks at 6.1e12 FLOP/s a compute unit, where both statistics beside it leave 256 x 128 at 4.4e12 -- into the workspace, and
 // the sums over b, in the groups of `pair` and with the same bits, in a second pass.  What that moves, written and read, takes 0.3 us a MB and
@@ -844,8 +833,7 @@ static double examples_share(int64_t B, int64_t T, int64_t din, int64_t dout, co
     return t < pair.seconds * (!long_ones ? 1.1 : pair.per_split == 1 ? 1.2 : 1.04) ? t / (1.2 * pair.seconds) : 1.0;
 }
 
-static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true,
-                            bool allow_examples = true)
+MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad, bool allow_small, bool allow_examples)
 {
     MultiPlan m{};
     const int n = __builtin_popcount(want);
@@ -880,23 +868,19 @@ static MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex
             if (w > m.query_bytes) m.query_bytes = w;     // passes run one after the other on the stream and reuse it
         }
     if (small) {
-        const size_t without = plan_multi(B, T, din, dout, dt, want, allow_pad, false).query_bytes;
+        const size_t without = plan_multi(B, T, din, dout, dt, want, allow_pad, false, false).query_bytes;
         if (without > m.query_bytes) m.query_bytes = without;
     }
     return m;
 }
 
-// The plan of a call that has `bytes` of workspace, as plan_within
-static MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes)
+// The plan of a call that has `bytes` of workspace, as plan_within; what a layer needs at least has no room for its M_b
+MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes)
 {
     const MultiPlan first = plan_multi(B, T, din, dout, dt, want);
     if (first.query_bytes <= bytes) return first;
-    if (first.examples) {
-        const MultiPlan m = plan_multi(B, T, din, dout, dt, want, true, true, false);
-        if (m.query_bytes <= bytes) return m;
-    }
     for (const bool allow_pad : {true, false}) {
-        const MultiPlan m = plan_multi(B, T, din, dout, dt, want, allow_pad, false);
+        const MultiPlan m = plan_multi(B, T, din, dout, dt, want, allow_pad, false, false);
         if (m.query_bytes <= bytes) return m;
     }
     return first;

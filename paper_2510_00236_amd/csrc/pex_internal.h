@@ -53,6 +53,22 @@ struct StatPlan {
 StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mode, bool allow_wide = true, bool allow_pad = true,
                    bool allow_small = true);
 
+// How pex_stat_multi is carried out: `pair` = two or three of the statistics from one MFMA contraction (on the layers the
+// MFMA kernels take), the rest one at a time.
+struct MultiPlan {
+    bool examples;        // identity and square from the M_b themselves, in the workspace (pair_plan: whose groups their sums have)
+    bool pair;            // a fused launch is used
+    uint32_t pair_want;   // for which statistics
+    uint32_t single_want; // served by separate pex_stat passes
+    StatPlan pair_plan;
+    size_t query_bytes;   // what the call asks for: at least what it would without the kernel of small layers
+};
+// allow_pad and allow_small as for plan_stat; allow_examples = false keeps the M_b out of the workspace
+MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true,
+                     bool allow_examples = true);
+// The plan of a call that has `bytes` of workspace
+MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes);
+
 // Launchers.  `out` is S when plan.nsplit == 1, else the workspace holding [nsplit][din][dout] partials.
 // MODE_WEIGHTED reads one weight per example from `weight`; MODE_NORMS writes no S but one partial of ||M_b||^2 per
 // tile (generic kernel) into norm_partial[tile][B].

@@ -1,0 +1,43 @@
+"""Plans of several statistics at once (host only): the M_b of few long examples through the workspace, and what the calls ask for where that is not
+the way they go (multi_probe.cpp, linked to the library)."""
+import subprocess
+
+import pytest
+
+import paper_2510_00236_amd as pex
+from test_plan_host import _compile
+
+BF, MIB = pex.PEX_BF16, 1 << 20
+
+
+@pytest.fixture(scope="module")
+def multi(tmp_path_factory):
+    exe = _compile("multi_probe.cpp", str(tmp_path_factory.mktemp("multi") / "probe"))
+
+    def ask(shapes):
+        """[(B, T, din, dout)] -> [(examples, nsplit, per_split, query, plain, small, within)] of identity and square, bf16"""
+        text = "".join(f"{B} {T} {i} {o} {BF} 3\n" for B, T, i, o in shapes)
+        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        return [tuple(int(v) for v in l.split()) for l in out.splitlines()]
+
+    return ask
+
+
+# On the kernel of small layers, with the workspace the layer needs without it (bytes).
+SMALL = [((224, 292, 128, 256), 8 * MIB), ((66, 881, 128, 320), 7208960), ((72, 898, 64, 128), 1572864), ((110, 593, 768, 64), 11010048)]
+
+
+def test_small_layers_ask_for_no_room_for_their_examples(multi):
+    for (shape, needs), (examples, _, _, query, plain, small, within) in zip(SMALL, multi([s for s, _ in SMALL])):
+        assert small and not examples, shape
+        assert query == plain == needs, (shape, query, plain)
+        assert within <= needs, (shape, within)
+
+
+def test_partial_sums_alone_are_enough(multi):
+    """Whatever way a layer goes, a workspace for its partial sums alone is accepted."""
+    shapes = [(B, T, i, o) for B in (2, 3, 5, 17, 72, 224) for T in (24, 292, 898, 2048) for i in (64, 128, 768, 2304) for o in (64, 256, 1408, 4096)]
+    plans = multi(shapes)
+    assert any(p[0] for p in plans) and any(p[5] for p in plans)
+    for shape, (_, _, _, query, plain, _, within) in zip(shapes, plans):
+        assert within <= plain <= query, (shape, query, plain, within)
