@@ -1155,16 +1155,18 @@ pex_status pex_vec_stat(const void* A, const void* C, int64_t B, int64_t T, int6
 size_t pex_stat_pair_batch_workspace_bytes(const pex_pair_item* items, int32_t count, int64_t B, int64_t T, pex_dtype dt)
 {
     if (!items || count < 1 || B < 1 || T < 1 || (dt != PEX_F32 && dt != PEX_BF16)) return 0;
-    size_t need = 0;
-    for (int k = 0; k < count; ++k) {
+    for (int k = 0; k < count; ++k)
         if (items[k].din < 1 || items[k].dout < 1) return 0;
-        const size_t own = plan_multi(B, T, items[k].din, items[k].dout, dt, PEX_WANT_IDENTITY | PEX_WANT_SQUARE).query_bytes;
-        if (own > need) need = own;
-    }
+    size_t need = 0;
     PairBatchPlan plan;
-    for (int k = 0; k < count; k += next_pair_group(items, count, k, B, T, dt, &plan)) {
-        next_pair_group(items, count, k, B, T, dt, &plan);
+    for (int k = 0; k < count;) {
+        const int end = k + next_pair_group(items, count, k, B, T, dt, &plan);
         if (plan.ws_bytes > need) need = plan.ws_bytes;
+        for (; k < end; ++k) {
+            // what each would need by itself, and room for its M_b only where it goes by itself
+            const size_t own = plan_multi(B, T, items[k].din, items[k].dout, dt, PEX_WANT_IDENTITY | PEX_WANT_SQUARE, true, true, !plan.joint).query_bytes;
+            if (own > need) need = own;
+        }
     }
     return need;
 }

@@ -41,3 +41,12 @@ def test_partial_sums_alone_are_enough(multi):
     assert any(p[0] for p in plans) and any(p[5] for p in plans)
     for shape, (_, _, _, query, plain, _, within) in zip(shapes, plans):
         assert within <= plain <= query, (shape, query, plain, within)
+
+
+@pytest.mark.parametrize("B,T,d,needs", [(3, 1508, 1536, 56623104), (37, 1755, 768, 169869312), (83, 526, 256, 62914560)])
+def test_layers_in_one_launch_ask_for_no_room_for_their_examples(multi, B, T, d, needs):
+    """A block whose four layers share a launch, although one of them by itself would have its M_b in the workspace."""
+    widths = [(d, 3 * d), (d, d), (d, 4 * d), (4 * d, d)]
+    alone = multi([(B, T, i, o) for i, o in widths])
+    assert any(p[0] and p[3] > needs for p in alone)
+    assert pex.pex_stat_pair_batch_workspace_bytes(widths, B, T, BF) == needs
