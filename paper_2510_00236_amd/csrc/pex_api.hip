@@ -874,10 +874,12 @@ MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype 
     return m;
 }
 
-// The plan of a call that has `bytes` of workspace, as plan_within; what a layer needs at least has no room for its M_b
-MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes)
+// The plan of a call that has `bytes` of workspace at `workspace`, as plan_within; what a layer needs at least has no room for its M_b.
+// (A layer that needs none runs beside a workspace at any address.)
+MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, const void* workspace, size_t bytes)
 {
-    const MultiPlan first = plan_multi(B, T, din, dout, dt, want);
+    if (!workspace) bytes = 0;
+    const MultiPlan first = plan_multi(B, T, din, dout, dt, want, true, true, ((uintptr_t)workspace & 15u) == 0);
     if (first.query_bytes <= bytes) return first;
     for (const bool allow_pad : {true, false}) {
         const MultiPlan m = plan_multi(B, T, din, dout, dt, want, allow_pad, false, false);
@@ -1079,7 +1081,7 @@ pex_status pex_stat_multi(const void* X, const void* G, int64_t B, int64_t T, in
         if (st != PEX_OK) return st;
     }
     const size_t given = workspace ? workspace_bytes : 0;
-    const MultiPlan m = plan_multi_within(B, T, din, dout, dt, want, given);
+    const MultiPlan m = plan_multi_within(B, T, din, dout, dt, want, workspace, workspace_bytes);
     if (m.query_bytes > 0) {
         if (!workspace || workspace_bytes < m.query_bytes) return PEX_ERR_WORKSPACE;
         if ((uintptr_t)workspace & 15u) return PEX_ERR_ALIGN;
@@ -1185,7 +1187,7 @@ pex_status pex_stat_pair_batch(const pex_pair_item* items, int32_t count, int64_
             const pex_status st = check_stat_args(it.X, it.G, B, T, it.din, it.dout, dt, S);
             if (st != PEX_OK) return st;
         }
-        const size_t need = plan_multi_within(B, T, it.din, it.dout, dt, BOTH, given).query_bytes;
+        const size_t need = plan_multi_within(B, T, it.din, it.dout, dt, BOTH, workspace, workspace_bytes).query_bytes;
         if (need > given) return PEX_ERR_WORKSPACE;
         uses_workspace = uses_workspace || need > 0;
     }

@@ -66,8 +66,8 @@ struct MultiPlan {
 // allow_pad and allow_small as for plan_stat; allow_examples = false keeps the M_b out of the workspace
 MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad = true, bool allow_small = true,
                      bool allow_examples = true);
-// The plan of a call that has `bytes` of workspace
-MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, size_t bytes);
+// The plan of a call that has `bytes` of workspace at `workspace`
+MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, const void* workspace, size_t bytes);
 
 // Launchers.  `out` is S when plan.nsplit == 1, else the workspace holding [nsplit][din][dout] partials.
 // MODE_WEIGHTED reads one weight per example from `weight`; MODE_NORMS writes no S but one partial of ||M_b||^2 per

@@ -15,7 +15,7 @@ def multi(tmp_path_factory):
     exe = _compile("multi_probe.cpp", str(tmp_path_factory.mktemp("multi") / "probe"))
 
     def ask(shapes):
-        """[(B, T, din, dout)] -> [(examples, nsplit, per_split, query, plain, small, within)] of identity and square, bf16"""
+        """[(B, T, din, dout)] -> [(examples, nsplit, per_split, query, plain, small, within, odd)] of identity and square, bf16"""
         text = "".join(f"{B} {T} {i} {o} {BF} 3\n" for B, T, i, o in shapes)
         out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
         return [tuple(int(v) for v in l.split()) for l in out.splitlines()]
@@ -28,7 +28,7 @@ SMALL = [((224, 292, 128, 256), 8 * MIB), ((66, 881, 128, 320), 7208960), ((72, 
 
 
 def test_small_layers_ask_for_no_room_for_their_examples(multi):
-    for (shape, needs), (examples, _, _, query, plain, small, within) in zip(SMALL, multi([s for s, _ in SMALL])):
+    for (shape, needs), (examples, _, _, query, plain, small, within, _) in zip(SMALL, multi([s for s, _ in SMALL])):
         assert small and not examples, shape
         assert query == plain == needs, (shape, query, plain)
         assert within <= needs, (shape, within)
@@ -39,8 +39,15 @@ def test_partial_sums_alone_are_enough(multi):
     shapes = [(B, T, i, o) for B in (2, 3, 5, 17, 72, 224) for T in (24, 292, 898, 2048) for i in (64, 128, 768, 2304) for o in (64, 256, 1408, 4096)]
     plans = multi(shapes)
     assert any(p[0] for p in plans) and any(p[5] for p in plans)
-    for shape, (_, _, _, query, plain, _, within) in zip(shapes, plans):
+    for shape, (_, _, _, query, plain, _, within, _) in zip(shapes, plans):
         assert within <= plain <= query, (shape, query, plain, within)
+
+
+def test_layers_that_need_no_workspace_take_one_at_any_address(multi):
+    shapes = [(4, 8192, 4096, 4096), (1, 8192, 4096, 4096), (7, 2864, 2944, 2304)]
+    for shape, (examples, nsplit, _, query, plain, _, _, odd) in zip(shapes, multi(shapes)):
+        assert examples and nsplit == 1 and query == 4 * shape[0] * shape[2] * shape[3] and plain == 0, shape
+        assert odd == 0, (shape, odd)
 
 
 @pytest.mark.parametrize("B,T,d,needs", [(3, 1508, 1536, 56623104), (37, 1755, 768, 169869312), (83, 526, 256, 62914560)])
