@@ -409,15 +409,15 @@ def pex_stat_noalloc(X, G, phi, S, stream=None):
 def pex_stat_multi(X, G, want, out=None, workspace=None, stream=None):
     """Several statistics from one pass.  ``want`` is an iterable of 'identity' | 'square' | 'sign' (or the bit
     set); returns a dict name -> S[din,dout] fp32.  ``out`` may supply the output tensors by name."""
+    mask = _want_mask(want)
     if _host is not None and stream is None:
-        r = _host.stat_multi(X, G, _want_mask(want), out, workspace)
+        r = _host.stat_multi(X, G, mask, out, workspace)
         if r:
             return r if r.__class__ is dict else _refused(r)
     if _torch is None:
         _bind_torch()
     B, T, din, dout = _shapes(X, G)
     dt = _dtype_code(X)
-    mask = _want_mask(want)
     res = {}
     ptrs = []
     for name, bit in WANT.items():
@@ -530,13 +530,13 @@ def pex_vec_stat_batch_workspace_bytes(widths, B, T, dtype_code) -> int:
 def pex_vec_stat_batch(items, want=("identity", "square", "sign"), workspace=None, stream=None):
     """pex_vec_stat of several vectors of one batch in one launch of each pass: ``items`` are (A, C or None, out dict or None) with
     the same B, T and type.  Returns a list of dicts name -> s[d] fp32."""
+    mask = _want_mask(want)
     if _host is not None and stream is None:
-        r = _host.vec_stat_batch(items, _want_mask(want), workspace)
+        r = _host.vec_stat_batch(items, mask, workspace)
         if r:
             return r if r.__class__ is list else _refused(r)
     if _torch is None:
         _bind_torch()
-    mask = _want_mask(want)
     A0 = items[0][0]
     res, rows, widths = [], [], []
     for A, C, out in items:
@@ -741,8 +741,9 @@ def pex_embed_stat_workspace_bytes(B, T, V, d) -> int:
 def pex_embed_stat(ids, G, V, want, out=None, workspace=None, stream=None):
     """Per-example gradient statistics of an embedding table: ``ids`` [B,T] int32/int64, ``G`` [B,T,d] cotangents of
     the looked-up vectors; returns a dict name -> S[V,d] fp32 for the names in ``want``.  Ids outside [0,V) are padding."""
+    mask = _want_mask(want)
     if _host is not None and stream is None:
-        r = _host.embed_stat(ids, G, V, _want_mask(want), out, workspace)
+        r = _host.embed_stat(ids, G, V, mask, out, workspace)
         if r:
             return r if r.__class__ is dict else _refused(r)
     if _torch is None:
@@ -752,7 +753,6 @@ def pex_embed_stat(ids, G, V, want, out=None, workspace=None, stream=None):
     if ids.dtype not in (_torch.int32, _torch.int64):
         raise TypeError(f"ids must be int32 or int64, got {ids.dtype}")
     B, T, d = G.shape
-    mask = _want_mask(want)
     res, ptrs = {}, []
     for name, bit in WANT.items():
         if mask & bit:

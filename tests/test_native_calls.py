@@ -32,6 +32,23 @@ def test_calls_that_are_not_taken(host):
                 assert fn(*args[:k], odd, *args[k + 1:]) is False, (fn, k, odd)
 
 
+def test_names_from_an_iterator(monkeypatch):
+    """`want` is read once, also where the native call leaves a call to the Python checks (no outputs given here)."""
+    class Declines:
+        def __getattr__(self, name):
+            return lambda *args: False
+
+    masks = []
+    pex._bind_torch()
+    monkeypatch.setattr(pex, "_host", Declines())
+    monkeypatch.setattr(pex, "_dev", lambda *a, **k: 0)
+    monkeypatch.setattr(pex, "_invoke_ws", lambda query, qargs, ws, fn, *args: masks.append(args))
+    X, ids = torch.zeros(2, 3, 8), torch.zeros(2, 3, dtype=torch.int64)
+    assert list(pex.pex_stat_multi(X, X, iter(BOTH))) == list(BOTH) and masks[-1][7] == 3
+    assert list(pex.pex_embed_stat(ids, X, 9, (n for n in ("sign", "square")))) == ["square", "sign"] and masks[-1][8] == 6
+    assert [list(d) for d in pex.pex_vec_stat_batch([(X, None, None)] * 2, iter(("identity",)))] == [["identity"]] * 2 and masks[-1][5] == 1
+
+
 def _inputs(g):
     B, T, a, b, V = 5, 37, 72, 40, 90
     r = lambda *s: torch.randn(*s, device=DEV, generator=g)  # noqa: E731
