@@ -1,5 +1,9 @@
 """The binding's calls in native code: the same results as through the Python checks, and whatever a call does not want left to those (wrong types, sizes and
 places raise what they raise there, and nothing is launched first)."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -30,6 +34,53 @@ def test_calls_that_are_not_taken(host):
         for k in range(len(args)):
             for odd in (None, "x", object(), 2**70, -1, [], X.to(torch.float16)):
                 assert fn(*args[:k], odd, *args[k + 1:]) is False, (fn, k, odd)
+
+
+# Tensors that say they are on a GPU, at addresses nobody reads: in every call one of them throws when asked for its address, so that none reaches the library.
+THROWING = """
+import sys
+import torch
+import paper_2510_00236_amd as pex
+
+def tensor(*shape, dtype=torch.float32, throws=False):
+    storage = torch._C._construct_storage_from_data_pointer(4096, torch.device("cuda", 0), 1 << 20)
+    meta = dict(device=torch.device("cuda", 0), dtype=dtype, size=shape, stride=torch.empty(shape, device="meta").stride(), storage_offset=0)
+    t = torch._C._construct_CUDA_Tensor_From_Storage_And_Metadata(meta, storage)
+    if throws:
+        torch._C._set_throw_on_mutable_data_ptr(t)
+    return t
+
+pex._bind_torch()
+host = pex._host
+host.setup(pex.AdamParams, pex.MomentParams, lambda: 0, lambda device: 0)
+X, S, v, ids = tensor(2, 4, 64), tensor(64, 64), tensor(64), tensor(2, 4, dtype=torch.int64)
+ws, one, N = tensor(1 << 18, dtype=torch.uint8), tensor(1, dtype=torch.float64), tensor(2)
+bad = dict(X=tensor(2, 4, 64, throws=True), S=tensor(64, 64, throws=True), v=tensor(64, throws=True), ids=tensor(2, 4, dtype=torch.int64, throws=True),
+           ws=tensor(1 << 18, dtype=torch.uint8, throws=True), one=tensor(1, dtype=torch.float64, throws=True), N=tensor(2, throws=True))
+good, prm = dict(X=X, S=S, v=v, ids=ids, ws=ws, one=one, N=N), pex.AdamParams()
+both, vec = lambda g: {"identity": S, "square": g["S"]}, lambda g: {"identity": v, "square": g["v"]}
+calls = [("X S ws", lambda g: host.stat(g["X"], X, 1, g["S"], g["ws"])), ("X S ws", lambda g: host.stat_multi(g["X"], X, 3, both(g), g["ws"])),
+         ("X S ws", lambda g: host.token_sq(X, g["X"], g["S"], g["ws"])), ("X N ws", lambda g: host.example_norms(X, g["X"], g["N"], g["ws"])),
+         ("X N S ws", lambda g: host.weighted_sum(X, g["X"], g["N"], g["S"], g["ws"])), ("N", lambda g: host.clip_weights(N, 1.0, g["N"])),
+         ("ids X S ws", lambda g: host.embed_stat(g["ids"], g["X"], 64, 3, both(g), g["ws"])), ("S", lambda g: host.adam_update(S, S, S, S, g["S"], 1, prm)),
+         ("S", lambda g: host.signsgd_update(S, S, g["S"], 0.1, 0.9, 0.0, 2, False, 1)),
+         ("S one ws", lambda g: host.adam_step([(S, S, S, S, g["S"])] * 2, 1, prm, g["one"], 1.0, None, None, g["ws"])),
+         ("X S ws", lambda g: host.stat_pair_batch([(X, X, both(good)), (X, g["X"], both(g))], g["ws"])),
+         ("X v ws", lambda g: host.vec_stat_batch([(X, None, vec(good)), (X, g["X"], vec(g))], 3, g["ws"]))]
+held = [sys.getrefcount(t) for t in (X, S, v, ws)]
+for which, call in calls:
+    for name in which.split():
+        assert call({**good, name: bad[name]}) is False, (which, name)
+assert held == [sys.getrefcount(t) for t in (X, S, v, ws)]
+print("all left to the Python checks")
+"""
+
+
+def test_addresses_that_throw(host):
+    """A tensor whose address cannot be had leaves the call to the Python checks, with the interpreter's lock held."""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1")
+    r = subprocess.run([sys.executable, "-c", THROWING], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "all left" in r.stdout, (r.returncode, r.stdout, r.stderr[-2000:])
 
 
 def test_names_from_an_iterator(monkeypatch):
