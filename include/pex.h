@@ -52,7 +52,8 @@ typedef void *pex_stream_t; /* a hipStream_t */
 /* Human-readable name of a status code (static storage, never NULL). */
 const char *pex_status_string(pex_status s);
 
-/* Library version, major*10000 + minor*100 + patch. */
+/* Library version, major*10000 + minor*100 + patch: PEX_VERSION of the header the library was built with. */
+#define PEX_VERSION 200
 int pex_version(void);
 
 /*

@@ -195,9 +195,10 @@ def _bind_torch():
     if os.path.exists(LIB_PATH):
         try:
             from . import _pex_host
-            _pex_host.setup(AdamParams, MomentParams, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-            _host = _pex_host
-        except (ImportError, AttributeError):      # not built, or a torch without a GPU runtime
+            if _pex_host.PEX_VERSION == lib().pex_version():
+                _pex_host.setup(AdamParams, MomentParams, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+                _host = _pex_host
+        except (ImportError, AttributeError, OSError):      # not built, of an older header, or a torch without a GPU runtime
             pass
 
 

@@ -1011,7 +1011,7 @@ const char* pex_status_string(pex_status s)
     return "PEX: unknown status";
 }
 
-int pex_version(void) { return 200; }
+int pex_version(void) { return PEX_VERSION; }
 
 pex_status pex_set_option(pex_option opt, int32_t value)
 {

@@ -469,5 +469,7 @@ extern "C" __attribute__((visibility("default"))) PyObject* PyInit__pex_host(voi
     const char* text[3] = {"identity", "square", "sign"};
     for (int k = 0; k < 3; ++k)
         if (!(names[k] = PyUnicode_InternFromString(text[k]))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddIntConstant(m, "PEX_VERSION", PEX_VERSION) != 0) Py_CLEAR(m);
+    return m;
 }

@@ -83,6 +83,36 @@ def test_addresses_that_throw(host):
     assert r.returncode == 0 and "all left" in r.stdout, (r.returncode, r.stdout, r.stderr[-2000:])
 
 
+@pytest.mark.parametrize("command", [["false"], ["no such compiler"], None])
+def test_library_without_the_native_calls(command, monkeypatch, tmp_path, capfd):
+    """Where they cannot be compiled the build goes on, without those of an earlier one."""
+    from paper_2510_00236_amd import build
+
+    def no_torch():
+        raise ImportError("no torch")
+
+    old = tmp_path / "_pex_host.so"
+    old.write_bytes(b"of an earlier header")
+    monkeypatch.setattr(build, "HOST_MODULE", str(old))
+    monkeypatch.setattr(build, "host_command", no_torch if command is None else lambda: command)
+    assert build.build_host() is False and not old.exists()
+    assert "not built" in capfd.readouterr().err
+
+
+def test_native_calls_of_another_header_are_not_used(monkeypatch):
+    class Old:
+        PEX_VERSION = -1
+
+        @staticmethod
+        def setup(*args):
+            raise AssertionError("used")
+
+    monkeypatch.setattr(pex, "_pex_host", Old, raising=False)
+    monkeypatch.setattr(pex, "_host", None)
+    pex._bind_torch()
+    assert pex._host is None
+
+
 def test_names_from_an_iterator(monkeypatch):
     """`want` is read once, also where the native call leaves a call to the Python checks (no outputs given here)."""
     class Declines:
