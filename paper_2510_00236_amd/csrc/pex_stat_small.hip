@@ -35,6 +35,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 
 constexpr int W = 8;                       // waves of a workgroup
 constexpr int SM_T = 64;                   // rows of a tile; columns: 16 FN
+constexpr int64_t SM_ROW_TILES = 65535;    // a dimension of the grid
 constexpr int SM_CHUNK = 8192;             // at most so many rows of a plain contraction are folded into its sum together (1024 a wave) ...
 constexpr int SM_SHORT = 4;                // ... of which a wave adds up this many steps at a time
 
@@ -365,7 +366,7 @@ hipError_t launch_small(const void* X, const void* G, int64_t B, int64_t T, int6
                         float* out_sg, hipStream_t stream, const float* weight, float* norm_partial, float alpha, float nan_sign)
 {
     const int64_t tiles_n = (dout + 16 * FN - 1) / (16 * FN), tiles_m = (din + SM_T - 1) / SM_T;
-    if (tiles_m > 65535 || plan.nsplit > 65535) return hipErrorInvalidValue;       // (more tiles by far than layers that are planned here have)
+    if (tiles_m > SM_ROW_TILES || plan.nsplit > 65535) return hipErrorInvalidValue;       // (small_supports asks for the first; plans have at most 1024 groups)
     stat_small_kernel<TIn, OUTS, KW, FN><<<dim3((unsigned)tiles_n, (unsigned)tiles_m, (unsigned)plan.nsplit), dim3(W * 64), 0, stream>>>(
         (const TIn*)X, (const TIn*)G, (int)(B * T), (int)T, (int)din, (int)dout, (int)plan.per_split, din * dout, out_id, out_sq, out_sg, weight, norm_partial, (int)B, alpha, nan_sign);
     return hipGetLastError();
@@ -404,7 +405,8 @@ bool small_supports(int64_t T, int64_t din, int64_t dout, pex_dtype dt, Mode mod
     // a lane reads four features of a row; 32-bit byte offsets inside a step; the tokens of an example are counted in 32 bits
     if (din < 4 || dout < 4 || din > ((int64_t)1 << 24) || dout > ((int64_t)1 << 24) || T > ((int64_t)1 << 30)) return false;
     if (dt == PEX_BF16 && mode == MODE_TOKEN_SQ) return false;
-    return small_tiles(din, dout) < ((int64_t)1 << 22);
+    // row tiles are a grid dimension of at most 65535
+    return small_tiles(din, dout) < ((int64_t)1 << 22) && (din + SM_T - 1) / SM_T <= SM_ROW_TILES;
 }
 
 int64_t small_tiles(int64_t din, int64_t dout, bool half) { return ((din + SM_T - 1) / SM_T) * (half ? (dout + 31) / 32 : (dout + SM_T - 1) / SM_T); }

@@ -57,3 +57,11 @@ def test_layers_in_one_launch_ask_for_no_room_for_their_examples(multi, B, T, d,
     alone = multi([(B, T, i, o) for i, o in widths])
     assert any(p[0] and p[3] > needs for p in alone)
     assert pex.pex_stat_pair_batch_workspace_bytes(widths, B, T, BF) == needs
+
+
+def test_small_layers_have_no_more_row_tiles_than_a_grid_dimension(tmp_path):
+    """65535 tiles of 64 rows, whatever the limits of the plan."""
+    exe = _compile("supports_probe.cpp", str(tmp_path / "supports"))
+    text = "".join(f"16 {din} {dout} {dt} 1\n" for dt in (0, 1) for din, dout in ((65535 * 64, 8), (65535 * 64 + 1, 8), (8, 65535 * 64 + 1), (64, 64)))
+    out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.split()
+    assert out == ["1", "0", "1", "1"] * 2
