@@ -6,7 +6,7 @@
  * H -> X, Lambda -> G, L -> T, D -> din, F -> dout):
  *     X[B,T,din]  activations entering the layer,
  *     G[B,T,dout] cotangents (d loss / d layer output),
- *     M_b = X_b^T G_b   the per-example weight gradient (din x dout), never stored,
+ *     M_b = X_b^T G_b   the per-example weight gradient (din x dout), never stored (but see PEX_OPT_STORED_EXAMPLES),
  *     S   = sum_b phi(M_b),  phi in {identity, elementwise square, sign}.
  *
  * Conventions common to every entry point
@@ -53,7 +53,7 @@ typedef void *pex_stream_t; /* a hipStream_t */
 const char *pex_status_string(pex_status s);
 
 /* Library version, major*10000 + minor*100 + patch: PEX_VERSION of the header the library was built with. */
-#define PEX_VERSION 200
+#define PEX_VERSION 201
 int pex_version(void);
 
 /*
@@ -91,7 +91,13 @@ int pex_version(void);
  *                            1 = chosen by a cost model (default), 2 = wherever it applies (dout < 2^20) (environment
  *                            PEX_MEMORY_FOLD).  It rounds the square before adding it where the register tiles use a
  *                            fused multiply-add: the routes agree to fp32 rounding, not bit for bit.
- * Layers that do not fill the chip have a kernel of their own while every option has its default (per-example norms: also
+ *   PEX_OPT_STORED_EXAMPLES  identity and square together (pex_stat_multi, and the layers of pex_stat_pair_batch that do not share a
+ *                            launch) of few long examples of a bf16 layer may have every M_b in the workspace, at most 512 MiB of
+ *                            them, and sum them in a second pass.  0 = never: a workspace holds sums over groups of examples only,
+ *                            1 = where a cost model says so and the workspace has the room (default) (environment
+ *                            PEX_STORED_EXAMPLES).  Both ways give the same bits; with it weighs whether the layers of a batch share a
+ *                            launch, whose groups of examples differ from theirs.  No other plan depends on it.
+ * Layers that do not fill the chip have a kernel of their own while every option but the last has its default (per-example norms: also
  * under any PEX_OPT_MAX_SPLIT); with another one away from it they are on the kernels these options are about.  The
  * results agree to fp32 rounding.
  * An option changes the plan and with it the *_workspace_bytes of later calls: query again after setting one.  A
@@ -100,7 +106,7 @@ int pex_version(void);
  * current value, -1 for an unknown option.
  */
 typedef enum { PEX_OPT_MAX_SPLIT = 0, PEX_OPT_TOKEN_PRESQUARE = 1, PEX_OPT_WIDE_BLOCKS = 2, PEX_OPT_GRAM_NORMS = 3,
-               PEX_OPT_MEMORY_FOLD = 4 } pex_option;
+               PEX_OPT_MEMORY_FOLD = 4, PEX_OPT_STORED_EXAMPLES = 5 } pex_option;
 pex_status pex_set_option(pex_option opt, int32_t value);
 int32_t pex_get_option(pex_option opt);
 
@@ -168,8 +174,8 @@ pex_status pex_stat_noalloc(const void *X, const void *G, int64_t B, int64_t T, 
  *   On the layers the MFMA kernels take, all wanted statistics come from one contraction (for all three, and on fp32
  *   layers for sign with any other, this needs at most 127 examples per group of the batch; beyond that identity and
  *   square share one and sign runs alone); other inputs are served one statistic at a time.  Workspace as for pex_stat, sized by the query below.
- *   For identity and square of few long bf16 examples the query has room for every M_b where that is the faster way (at most 512 MiB); a
- *   workspace that holds the partial sums alone is enough and gives the same bits.
+ *   For identity and square of few long bf16 examples the query has room for every M_b where that is the faster way (at most 512 MiB,
+ *   PEX_OPT_STORED_EXAMPLES); a workspace that holds the partial sums alone is enough and gives the same bits.
  */
 #define PEX_WANT_IDENTITY 1u
 #define PEX_WANT_SQUARE 2u

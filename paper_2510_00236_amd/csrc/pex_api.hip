@@ -39,8 +39,8 @@ static hipError_t scratch_address(void** out)
 // Planner options.  Their first values come from the environment, read once per process; afterwards only
 // pex_set_option changes them.  Atomics, so a host thread that plans while another one sets an option reads a
 // whole value; a plan made under one value and launched under another is caught as PEX_ERR_WORKSPACE.
-constexpr int NUM_OPTIONS = 5;
-constexpr int DEFAULT_OPTIONS[NUM_OPTIONS] = {32, 1, 1, 1, 1};
+constexpr int NUM_OPTIONS = 6, PLAN_OPTIONS = 5;       // all; those the plan of a single statistic depends on
+constexpr int DEFAULT_OPTIONS[NUM_OPTIONS] = {32, 1, 1, 1, 1, 1};
 struct Options {
     std::atomic<int> v[NUM_OPTIONS];
 };
@@ -51,6 +51,7 @@ static int clamp_option(int opt, int value)
 {
     if (opt == PEX_OPT_MAX_SPLIT) return value < 1 ? 1 : (value > 32 ? 32 : value);
     if (opt == PEX_OPT_GRAM_NORMS) return value < 0 ? 0 : (value > 3 ? 3 : value);   // 2, 3: forced, on small / large blocks
+    if (opt == PEX_OPT_STORED_EXAMPLES) return value < 0 ? 0 : (value > 1 ? 1 : value);
     return value < 0 ? 0 : (value > 2 ? 2 : value);      // every other option: 0 = off, 1 = cost model, 2 = forced
 }
 
@@ -59,7 +60,7 @@ static Options& options()
     static Options o;
     static std::once_flag once;
     std::call_once(once, [] {
-        const char* names[NUM_OPTIONS] = {"PEX_MAX_SPLIT", "PEX_TOKEN_PRESQUARE", "PEX_WIDE_BLOCKS", "PEX_GRAM_NORMS", "PEX_MEMORY_FOLD"};
+        const char* names[NUM_OPTIONS] = {"PEX_MAX_SPLIT", "PEX_TOKEN_PRESQUARE", "PEX_WIDE_BLOCKS", "PEX_GRAM_NORMS", "PEX_MEMORY_FOLD", "PEX_STORED_EXAMPLES"};
         for (int k = 0; k < NUM_OPTIONS; ++k) {
             const char* e = getenv(names[k]);
             o.v[k].store(clamp_option(k, (e && *e) ? atoi(e) : DEFAULT_OPTIONS[k]));
@@ -72,9 +73,11 @@ static int option(int opt) { return options().v[opt].load(); }
 
 // The options one plan is made with: read once, so that a plan is never a mixture.
 struct OptionValues {
-    int v[NUM_OPTIONS];
+    int v[PLAN_OPTIONS];
     int operator[](int opt) const { return v[opt]; }
 };
+
+static bool stored_examples() { return option(PEX_OPT_STORED_EXAMPLES) != 0; }
 
 // The next number of groups with a smaller largest group (the numbers between share the same plan), past every bound if there is none.
 static int64_t more_groups(int64_t units, int64_t ns)
@@ -592,7 +595,7 @@ static StatPlan make_plan(int64_t B, int64_t T, int64_t din, int64_t dout, pex_d
     // but squares 113 and 66; more than 1024 were not compared)
     const int64_t most_tiles = mode == MODE_NORMS ? 128 : mode == MODE_SIGN ? 256 : 1024;
     if (!allow_pad || !allow_small || T < 4 || small_tiles(din, dout) > most_tiles || !small_supports(T, din, dout, dt, mode)) return p;
-    for (int k = 0; k < NUM_OPTIONS; ++k)
+    for (int k = 0; k < PLAN_OPTIONS; ++k)
         if (options[k] != DEFAULT_OPTIONS[k]) return p;
     const bool plain = mode == MODE_IDENTITY || mode == MODE_TOKEN_SQ;
     const int64_t units = plain ? (B * T + 63) / 64 : B;
@@ -646,7 +649,7 @@ StatPlan plan_stat(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt
     for (const int64_t k : now.key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
     bool same = true;
     Kept& at = kept[h >> 60];
-    for (int k = 0; k < NUM_OPTIONS; ++k) {
+    for (int k = 0; k < PLAN_OPTIONS; ++k) {
         now.options.v[k] = option(k);
         same = same && now.options[k] == at.options[k];
     }
@@ -822,7 +825,7 @@ static double examples_share(int64_t B, int64_t T, int64_t din, int64_t dout, co
     if (pair.kernel != 1 || pair.copy_bytes > 0 || T < 256) return 1.0;
     const double bytes = (double)din * (double)dout * 4.0, mb = (double)B * bytes * 1.0e-6;
     if ((double)B * bytes > 512.0 * 1048576.0) return 1.0;
-    for (int k = 0; k < NUM_OPTIONS; ++k)
+    for (int k = 0; k < PLAN_OPTIONS; ++k)
         if (option(k) != DEFAULT_OPTIONS[k]) return 1.0;       // the options are about the other plans
     int bm, bn;
     bf16_tile_shape(MODE_IDENTITY, B, &bm, &bn);
@@ -857,7 +860,7 @@ MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype 
         m.pair_want = 0;
         m.single_want = want;
     }
-    if (allow_examples && want == BOTH && m.pair && !small && examples_share(B, T, din, dout, sq) < 1.0) {
+    if (allow_examples && stored_examples() && want == BOTH && m.pair && !small && examples_share(B, T, din, dout, sq) < 1.0) {
         m.examples = true;
         const size_t need = (size_t)B * (size_t)din * (size_t)dout * sizeof(float);
         if (need > m.query_bytes) m.query_bytes = need;
@@ -894,7 +897,7 @@ MultiPlan plan_multi_within(int64_t B, int64_t T, int64_t din, int64_t dout, pex
 static bool pair_joins(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt)
 {
     if (dt != PEX_BF16) return false;
-    for (int k = 0; k < NUM_OPTIONS; ++k)
+    for (int k = 0; k < PLAN_OPTIONS; ++k)
         if (option(k) != DEFAULT_OPTIONS[k]) return false;       // the options are about the plans of single layers
     const StatPlan p = plan_stat(B, T, din, dout, dt, MODE_SQUARE, false, true, false);
     return p.kernel == 1 && p.copy_bytes == 0 && din % 8 == 0 && dout % 8 == 0;
@@ -913,7 +916,7 @@ struct PairBatchPlan {
 // 64-bit sums are, in 1e-16 of the 2-norm squared, 10 T/32 + 3.5 (examples of a group + groups) of S_id, (0.5 + 81/B) T/32 + 1.9 (..) of S_sq, within
 // 2 and 5 %.  The groups are such that neither grows by more than 2.5 % over any layer by itself on these blocks.  (Bounded by the layer that
 // is rounded most often, B=22, T=70, d=768: the whole step 374 us instead of 461, but S_id of the projection 7.8e-8 off instead of 5.5e-8.)
-static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout)
+static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout, bool stored)
 {
     constexpr double START = 3.0e-6, LAUNCH = 5.0e-6, RATE = 4.0e12, TAKEN = 0.8;      // (that part of such an estimate, see make_plan)
     const double unit = bf16_unit_with_fold(MODE_SQUARE, true, T, 256, 128);
@@ -929,7 +932,7 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
         const double own_bytes = 2.0 * (double)din[k] * (double)dout[k] * sizeof(float);
         const StatPlan p = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false, true, false), by_itself = plan_stat(B, T, din[k], dout[k], PEX_BF16, MODE_SQUARE, false);
         alone += by_itself.small_kw > 0 ? by_itself.seconds
-                                        : TAKEN * examples_share(B, T, din[k], dout[k], p) * (seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH);
+                                        : TAKEN * (stored ? examples_share(B, T, din[k], dout[k], p) : 1.0) * (seconds(own, p.nsplit, p.per_split, own_bytes) + (p.nsplit > 1 ? 2.0 : 1.0) * LAUNCH);
         blocks += own;
         bytes += own_bytes;
         if (p.per_split + p.nsplit < fewest_roundings) fewest_roundings = p.per_split + p.nsplit;
@@ -952,24 +955,25 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
 static PairBatchPlan plan_pair_batch(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout)
 {
     struct Kept {
-        int64_t key[3 + 2 * PAIR_BATCH];
+        int64_t key[4 + 2 * PAIR_BATCH];
         PairBatchPlan plan;
         bool valid;
     };
     static thread_local Kept kept[8];
-    int64_t key[3 + 2 * PAIR_BATCH] = {B, T, count};
+    const bool stored = stored_examples();
+    int64_t key[4 + 2 * PAIR_BATCH] = {B, T, count, stored};
     uint64_t h = 0;
     for (int k = 0; k < count; ++k) {
-        key[3 + 2 * k] = din[k];
-        key[4 + 2 * k] = dout[k];
+        key[4 + 2 * k] = din[k];
+        key[5 + 2 * k] = dout[k];
     }
     for (const int64_t x : key) h = (h ^ (uint64_t)x) * 0x9e3779b97f4a7c15ull;
     Kept& at = kept[h >> 61];
     bool same = at.valid;
-    for (int k = 0; k < 3 + 2 * PAIR_BATCH; ++k) same = same && key[k] == at.key[k];
+    for (int k = 0; k < 4 + 2 * PAIR_BATCH; ++k) same = same && key[k] == at.key[k];
     if (same) return at.plan;
-    at.plan = make_pair_batch_plan(B, T, count, din, dout);
-    for (int k = 0; k < 3 + 2 * PAIR_BATCH; ++k) at.key[k] = key[k];
+    at.plan = make_pair_batch_plan(B, T, count, din, dout, stored);
+    for (int k = 0; k < 4 + 2 * PAIR_BATCH; ++k) at.key[k] = key[k];
     at.valid = true;
     return at.plan;
 }

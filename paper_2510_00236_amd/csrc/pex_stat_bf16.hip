@@ -2,7 +2,7 @@
 //
 // Mathematics (Sec. 2.3, dense layers in sequence models): contract over the sequence, M_b = X_b^T G_b, apply phi
 // to the complete per-example tile while it is still in registers, sum over the batch.  The per-example gradient
-// never leaves the register file.  The per-token square (X o X)^T (G o G) is one plain contraction over all
+// leaves the register file only where a group is one example: as the M_b that identity and square of few long ones may be summed from.  The per-token square (X o X)^T (G o G) is one plain contraction over all
 // B*T rows whose operands are squared on the way.
 //
 // Data path

@@ -6,7 +6,8 @@ What a training loop hands over per step: for every dense layer its input activa
 G[B,T,dout] of its outputs (the backward pass already has both), for an offset the cotangents of the sum it was
 added to, for an elementwise scale those cotangents and the activation it multiplied, for the embedding the token ids
 and the cotangents of the looked-up vectors.  Per parameter tensor the library returns S_id = sum_b g_b and
-S_sq = sum_b g_b^2 without ever storing a per-example gradient; the optimizer kernels consume them in place.
+S_sq = sum_b g_b^2; the optimizer kernels consume them in place.  (No per-example gradient of a matrix is stored, but for layers of few long examples
+that share no launch, where that is faster; never with the planner option 'stored_examples' at 0.)
 Order of a step (everything stays on the GPU, nothing synchronises with the host):
   1. statistics of every tensor (one contraction per dense layer gives both S_id and S_sq);
   2. the squared global norm of the summed gradient, over the tensors;

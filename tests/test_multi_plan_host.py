@@ -1,5 +1,6 @@
 """Plans of several statistics at once (host only): the M_b of few long examples through the workspace, and what the calls ask for where that is not
 the way they go (multi_probe.cpp, linked to the library)."""
+import os
 import subprocess
 
 import pytest
@@ -14,10 +15,10 @@ BF, MIB = pex.PEX_BF16, 1 << 20
 def multi(tmp_path_factory):
     exe = _compile("multi_probe.cpp", str(tmp_path_factory.mktemp("multi") / "probe"))
 
-    def ask(shapes):
+    def ask(shapes, **env):
         """[(B, T, din, dout)] -> [(examples, nsplit, per_split, query, plain, small, within, odd)] of identity and square, bf16"""
         text = "".join(f"{B} {T} {i} {o} {BF} 3\n" for B, T, i, o in shapes)
-        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True, env=dict(os.environ, **env)).stdout
         return [tuple(int(v) for v in l.split()) for l in out.splitlines()]
 
     return ask
@@ -57,6 +58,22 @@ def test_layers_in_one_launch_ask_for_no_room_for_their_examples(multi, B, T, d,
     alone = multi([(B, T, i, o) for i, o in widths])
     assert any(p[0] and p[3] > needs for p in alone)
     assert pex.pex_stat_pair_batch_workspace_bytes(widths, B, T, BF) == needs
+
+
+def test_the_option_that_keeps_examples_out_of_the_workspace(multi, pex_option):
+    shapes = [(4, 8192, 4096, 4096), (6, 429, 968, 1856), (224, 292, 128, 256), (16, 2048, 2048, 8192)]
+    on, off = multi(shapes), multi(shapes, PEX_STORED_EXAMPLES="0")
+    assert [p[0] for p in on] == [1, 1, 0, 0] and [p[0] for p in off] == [0, 0, 0, 0]
+    for a, b in zip(on, off):
+        assert b[3] == b[4] == a[4] and a[1:3] == b[1:3] and a[5] == b[5]        # no room for them, the same groups, the same kernel
+    # a block of layers goes together again, and by itself again
+    block = ([(832, 3 * 832), (832, 832), (832, 4 * 832), (4 * 832, 832)], 9, 2370, BF)
+    one = (*shapes[0], BF, ("identity", "square"))
+    for value, together, alone in ((1, 110755840, 1 << 28), (0, 199360512, 0), (1, 110755840, 1 << 28)):
+        pex_option("stored_examples", value)
+        assert pex.pex_get_option("stored_examples") == value
+        assert pex.pex_stat_pair_batch_workspace_bytes(*block) == together and pex.pex_stat_multi_workspace_bytes(*one) == alone
+    assert pex.lib().pex_set_option(pex.PEX_OPT_STORED_EXAMPLES, 2) == 2
 
 
 def test_small_layers_have_no_more_row_tiles_than_a_grid_dimension(tmp_path):
