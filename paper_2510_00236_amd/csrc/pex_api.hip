@@ -812,28 +812,35 @@ static pex_status run_stat(const void* X, const void* G, int64_t B, int64_t T, i
 }
 
 // Identity and square of few long examples of a bf16 layer: M_b of every example by the kernel of plain contractions -- one register tile
-// on 256 x 256 blocks at 6.1e12 FLOP/s a compute unit, where both statistics beside it leave 256 x 128 at 4.4e12 -- into the workspace, and
-// the sums over b, in the groups of `pair` and with the same bits, in a second pass.  What that moves, written and read, takes 0.3 us a MB and
-// 0.55 beyond 200 MB, which the memory-side cache does not hold.  Measured, together in one launch -> so, us: 4 x 8192 tokens, 4096 x 4096
-// 992 -> 860; 16 x 4096, 768 x 3072 411 -> 313; 16 x 4092, 1024 x 1024 155 -> 121; 7 x 3000, 3000 x 1000 231 -> 151; but 12 x 1500,
-// 2048 x 2048 157 -> 176 and 5 x 1200, 4096 x 4096 202 -> 287.  The pair's estimate is 20 % low on such layers (0 to 27), more where its groups
-// are single examples, both of whose statistics it writes and reads: there this is taken for any gain, elsewhere for a clear one.
-// Of examples of 256 tokens on the layers that are cut into groups of two gain: 8 x 684, 1280 x 1152 39.6 -> 33.8; 12 x 521, 576 x 1792 36.4 -> 31.9.
-// Returns how much of the pair's time that is, 1 where it is not taken.
+// on 256 x 256 blocks, where both statistics beside it leave 256 x 128 -- into the workspace, and the sums over b, in the groups of `pair`
+// and with the same bits, in a second pass.  A round of blocks takes 12 us (16 after another) and an example's multiply-adds, at 6.25e12 FLOP/s
+// a compute unit on a full chip and up to 8.5 where few are busy (the eight-wave kernel, of examples below 1024 tokens, 7.6); the second pass 2.5 us
+// and its bytes at 7 TB/s, or 0.6 us for every four examples where its few workgroups wait for their chains of loads (218 examples of 300 tokens,
+// 208 x 416: 85 workgroups, 32 us for 75 MB); what the memory-side cache does not hold 0.2 us a MB.  Of 929 layers of 1 to 256 examples estimates
+// within 10 % for four in five.  The pair's estimate is right where its blocks are one round, 5 % low for long examples, else 10 to 25 % low: so much more
+// this may be.  687 of the layers are taken and 1.19 times faster in the mean, the least 0.97; of the others, 0.93 in the mean, three would gain more than
+// 10 %, at most 16.  Together in one launch -> so, us: 4 x 8192 tokens, 4096 x 4096 992 -> 860; 16 x 4096, 768 x 3072 411 -> 313; 16 x 4092,
+// 1024 x 1024 155 -> 121; 7 x 3000, 3000 x 1000 231 -> 151; 8 x 684, 1280 x 1152 39.6 -> 33.8; but 12 x 1500, 2048 x 2048 157 -> 176; 211 x 289,
+// 528 x 152 47 -> 73; 25 x 1302, 576 x 384 36 -> 43; 23 x 969, 2688 x 1536 271 -> 297.
+// Returns how much of the pair's time that is, 1 where it is not taken, beside estimates of many rounds of pairs (of 45 blocks of layers that change
+// with it 44 are on the faster way, 30 if this is divided by what the layer's own estimate is low).
 static double examples_share(int64_t B, int64_t T, int64_t din, int64_t dout, const StatPlan& pair)
 {
     if (pair.kernel != 1 || pair.copy_bytes > 0 || T < 256) return 1.0;
-    const double bytes = (double)din * (double)dout * 4.0, mb = (double)B * bytes * 1.0e-6;
-    if ((double)B * bytes > 512.0 * 1048576.0) return 1.0;
+    const double bytes = (double)din * (double)dout * 4.0, stored = (double)B * bytes;
+    if (stored > 512.0 * 1048576.0) return 1.0;
     for (int k = 0; k < PLAN_OPTIONS; ++k)
         if (option(k) != DEFAULT_OPTIONS[k]) return 1.0;       // the options are about the other plans
     int bm, bn;
     bf16_tile_shape(MODE_IDENTITY, B, &bm, &bn);
-    const bool long_ones = T >= 1024;       // (the four-wave kernel; the eight-wave one below)
-    const int64_t wgs = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn) * B;
-    const double t = (double)((wgs + 255) / 256) * 2.0 * (double)T * bm * bn / (long_ones ? 6.1e12 : 5.2e12) + 2.0 * bytes / 5.0e12 + 8.0e-6 +
-                     1.0e-6 * (mb < 200.0 ? 0.3 * mb : 60.0 + 0.55 * (mb - 200.0));
-    return t < pair.seconds * (!long_ones ? 1.1 : pair.per_split == 1 ? 1.2 : 1.04) ? t / (1.2 * pair.seconds) : 1.0;
+    const int64_t wgs = ((din + bm - 1) / bm) * ((dout + bn - 1) / bn) * B, rounds = (wgs + 255) / 256;
+    const double rate = T >= 1024 ? 8.5e12 - 2.25e12 * (double)wgs / (double)(256 * rounds) : 7.6e12;
+    const double moved = (stored + 2.0 * bytes) / 7.0e12, chain = 0.6e-6 * (double)((B + 3) / 4);
+    double t = (double)rounds * (16.0e-6 + 2.0 * (double)T * bm * bn / rate) - 4.0e-6 + 2.5e-6 + (moved > chain ? moved : chain);
+    if (stored > 200.0e6) t += 0.2e-12 * (stored - 200.0e6);
+    const bool several_rounds = bf16_pair_blocks(din, dout) * pair.nsplit > 256, long_ones = T >= 1536;
+    const double most = several_rounds ? (long_ones ? 1.2 : 1.1) : (long_ones ? 1.05 : 1.0);
+    return t < most * pair.seconds ? t / (1.25 * pair.seconds) : 1.0;
 }
 
 MultiPlan plan_multi(int64_t B, int64_t T, int64_t din, int64_t dout, pex_dtype dt, uint32_t want, bool allow_pad, bool allow_small, bool allow_examples)
