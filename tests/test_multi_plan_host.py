@@ -69,6 +69,15 @@ def test_examples_go_through_the_workspace_where_that_is_the_faster_way(multi):
     assert [p[0] for p in multi(faster)] == [1] * 7
 
 
+def test_the_layers_of_the_gpu_tests_go_that_way(multi):
+    from test_long_pairs_gpu import CASES
+    shapes, per, groups = zip(*CASES)
+    plans = multi(shapes)
+    assert [p[:3] for p in plans] == [(1, n, k) for k, n in zip(per, groups)]
+    more_room = [p[3] > p[4] for p in plans]
+    assert more_room == [False] * 6 + [True] * 6
+
+
 def test_the_option_that_keeps_examples_out_of_the_workspace(multi, pex_option):
     shapes = [(4, 8192, 4096, 4096), (6, 429, 968, 1856), (224, 292, 128, 256), (16, 2048, 2048, 8192)]
     on, off = multi(shapes), multi(shapes, PEX_STORED_EXAMPLES="0")
