@@ -594,9 +594,10 @@ constexpr int EMB_U = 16;        // sorted positions a wave owns = cotangent row
 // A vocabulary row with at most so many positions is done by the wave it starts at; of a longer one each wave does its own examples.  Few
 // workgroups wait for the longest chain of such rows, sixteen at a time, of a wave: EMB_U (no less: two long runs must not start at one wave's
 // positions).  A full chip does not, nor does one with a workgroup a unit that mostly writes a large table, and every row done together costs a
-// pass through LDS: 64, whose positions a lane each reads ahead.  Whole calls with 64 and with 16: B=64 T=1000 V=2000 d=200 (334 workgroups) 37.9
-// and 33.8 us, B=40 T=600 V=9000 d=512 (250) 30.0 and 27.1, B=30 T=500 V=50257 d=768 (237) 74.8 and 74.1; B=64 T=700 V=40000 d=768 (702) 71.7 and
-// 72.5, B=56 T=300 V=25000 d=1000 (352) 65.2 and 66.6.
+// pass through LDS: 64, whose positions a lane each reads ahead.  The time of whole calls with 64 over that with 16, 125 drawn ones of 129 to 912
+// workgroups, in the mean: at most 256 workgroups 1.08 up to 2^24 entries of the table, 1.00 (1.00 to 1.02) beyond; 257 to 512 1.05 up to 2^23, 1.00
+// (0.97 to 1.05) up to 2^24 and 0.99 (0.98 to 1.00) beyond; more 1.02 up to 2^23, which this leaves, and 0.99 (0.97 to 1.02) beyond.  B=64 T=1000
+// V=2000 d=200 (334 workgroups) 37.9 and 34.3 us, B=40 T=600 V=9000 d=512 (250) 30.7 and 28.3; B=64 T=700 V=40000 d=768 (702) 71.7 and 72.1.
 inline int embed_alone(int64_t workgroups, int64_t entries) { return workgroups > 2 * 256 || (workgroups > 256 && entries > ((int64_t)1 << 24)) ? 64 : EMB_U; }
 
 struct RowSums {
