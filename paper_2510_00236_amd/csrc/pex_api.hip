@@ -959,7 +959,7 @@ static PairBatchPlan make_pair_batch_plan(int64_t B, int64_t T, int count, const
 }
 
 // Kept like the plans of plan_stat, eight a thread.
-static PairBatchPlan plan_pair_batch(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout)
+static PairBatchPlan plan_pair_batch(int64_t B, int64_t T, int count, const int64_t* din, const int64_t* dout, bool stored)
 {
     struct Kept {
         int64_t key[4 + 2 * PAIR_BATCH];
@@ -967,7 +967,6 @@ static PairBatchPlan plan_pair_batch(int64_t B, int64_t T, int count, const int6
         bool valid;
     };
     static thread_local Kept kept[8];
-    const bool stored = stored_examples();
     int64_t key[4 + 2 * PAIR_BATCH] = {B, T, count, stored};
     uint64_t h = 0;
     for (int k = 0; k < count; ++k) {
@@ -985,8 +984,9 @@ static PairBatchPlan plan_pair_batch(int64_t B, int64_t T, int count, const int6
     return at.plan;
 }
 
-// The items from `from` on that go together: how many items this step covers, and the plan if they share a launch
-static int next_pair_group(const pex_pair_item* items, int32_t count, int32_t from, int64_t B, int64_t T, pex_dtype dt, PairBatchPlan* plan)
+// The items from `from` on that go together: how many items this step covers, and the plan if they share a launch.  stored = false: against each
+// by itself without its M_b in the workspace.
+static int next_pair_group(const pex_pair_item* items, int32_t count, int32_t from, int64_t B, int64_t T, pex_dtype dt, bool stored, PairBatchPlan* plan)
 {
     int64_t din[PAIR_BATCH], dout[PAIR_BATCH];
     int n = 0;
@@ -996,7 +996,7 @@ static int next_pair_group(const pex_pair_item* items, int32_t count, int32_t fr
         ++n;
     }
     *plan = PairBatchPlan{};
-    if (n >= 2) *plan = plan_pair_batch(B, T, n, din, dout);
+    if (n >= 2) *plan = plan_pair_batch(B, T, n, din, dout, stored);
     return n > 0 ? n : 1;
 }
 
@@ -1173,7 +1173,7 @@ size_t pex_stat_pair_batch_workspace_bytes(const pex_pair_item* items, int32_t c
     size_t need = 0;
     PairBatchPlan plan;
     for (int k = 0; k < count;) {
-        const int end = k + next_pair_group(items, count, k, B, T, dt, &plan);
+        const int end = k + next_pair_group(items, count, k, B, T, dt, stored_examples(), &plan);
         if (plan.ws_bytes > need) need = plan.ws_bytes;
         for (; k < end; ++k) {
             // what each would need by itself, and room for its M_b only where it goes by itself
@@ -1206,7 +1206,13 @@ pex_status pex_stat_pair_batch(const pex_pair_item* items, int32_t count, int64_
     hipStream_t hs = (hipStream_t)stream;
     for (int k = 0; k < count;) {
         PairBatchPlan plan;
-        const int n = next_pair_group(items, count, k, B, T, dt, &plan);
+        const int n = next_pair_group(items, count, k, B, T, dt, stored_examples(), &plan);
+        if (n >= 2 && !plan.joint) {
+            // each by itself only with the room that counts on
+            bool room = true;
+            for (int o = k; o < k + n; ++o) room = room && (plan_multi(B, T, items[o].din, items[o].dout, dt, BOTH).query_bytes <= given);
+            if (!room || ((uintptr_t)workspace & 15u)) next_pair_group(items, count, k, B, T, dt, false, &plan);
+        }
         if (!plan.joint || plan.ws_bytes > given || (plan.ws_bytes > 0 && ((uintptr_t)workspace & 15u))) {
             for (const int end = k + n; k < end; ++k) {
                 const pex_pair_item& it = items[k];

@@ -95,3 +95,26 @@ def test_together_as_exact_as_alone(B, T, d):
         for k, ref in (("identity", M.sum(0)), ("square", (M * M).sum(0))):
             err = lambda S: float((S.double() - ref).norm() / ref.norm())
             assert err(out[k]) <= 1.05 * err(alone[k]), (k, X.shape, G.shape)
+
+
+@pytest.mark.parametrize("B,T,d", [(15, 897, 704), (13, 1550, 832)])
+def test_together_where_a_workspace_has_no_room_for_their_examples(B, T, d, pex_option):
+    """Layers that go each by itself, with the M_b of some in the workspace, go together in a workspace of the size they ask for without."""
+    g = torch.Generator(device=DEV).manual_seed(T)
+    widths = [(d, 3 * d), (d, d), (d, 4 * d), (4 * d, d)]
+    layers = [tuple(torch.randn(B, T, n, device=DEV, generator=g).bfloat16() for n in w) for w in widths]
+
+    def run(size):
+        out = [{k: torch.full(w, float("nan"), device=DEV) for k in ("identity", "square")} for w in widths]
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        pex.pex_stat_pair_batch([(X, G, o) for (X, G), o in zip(layers, out)], workspace=ws)
+        return [S for o in out for S in o.values()]
+
+    room = pex.pex_stat_pair_batch_workspace_bytes(widths, B, T, pex.PEX_BF16)
+    alone = run(room)
+    pex_option("stored_examples", 0)
+    size = pex.pex_stat_pair_batch_workspace_bytes(widths, B, T, pex.PEX_BF16)
+    together = run(size)
+    pex_option("stored_examples", 1)
+    assert size < room and not all(torch.equal(a, b) for a, b in zip(alone, together))       # (other groups of examples, other roundings)
+    assert all(torch.equal(a, b) for a, b in zip(run(size), together))
