@@ -24,7 +24,9 @@ HOST_MODULE = os.path.join(_HERE, "_pex_host.so")
 
 
 def host_command():
-    """Compiles the binding's native calls against the headers of the installed torch and links them to libpex.so beside them."""
+    """Compiles the binding's native calls against the headers of the installed torch and links them to libpex.so beside them.  As torch itself
+    without assertions: those of its headers bring a thread-local counter, and with glibc before 2.39 a library with thread-local storage that
+    nobody touches puts every look-up of torch's own on the slow path (an allocation 1.11 -> 1.36 us, a random fill 4.4 -> 5.5)."""
     import importlib.util
     spec = importlib.util.find_spec("torch")
     if spec is None:
@@ -32,7 +34,7 @@ def host_command():
     torch_dir = spec.submodule_search_locations[0]
     include = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"],
                os.path.join(_ROOT, "include"), "/opt/rocm/include"]
-    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", *["-I" + d for d in include],
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-w", "-DNDEBUG", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", *["-I" + d for d in include],
             HOST_SOURCE, "-o", HOST_MODULE, "-L" + os.path.join(torch_dir, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python", "-L" + _HERE, "-l:libpex.so",
             "-Wl,-rpath,$ORIGIN", "-Wl,--allow-shlib-undefined"]
 

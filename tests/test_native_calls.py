@@ -1,6 +1,7 @@
 """The binding's calls in native code: the same results as through the Python checks, and whatever a call does not want left to those (wrong types, sizes and
 places raise what they raise there, and nothing is launched first)."""
 import os
+import struct
 import subprocess
 import sys
 
@@ -97,6 +98,16 @@ def test_library_without_the_native_calls(command, monkeypatch, tmp_path, capfd)
     monkeypatch.setattr(build, "host_command", no_torch if command is None else lambda: command)
     assert build.build_host() is False and not old.exists()
     assert "not built" in capfd.readouterr().err
+
+
+def test_no_thread_local_storage(host):
+    """The module brings none (ELF program header PT_TLS): loading it would slow down every call of torch."""
+    with open(host.__file__, "rb") as f:
+        head = f.read(64)
+        at, size, count = struct.unpack_from("<Q", head, 32)[0], *struct.unpack_from("<HH", head, 54)
+        f.seek(at)
+        kinds = [struct.unpack_from("<I", f.read(size))[0] for _ in range(count)]
+    assert 1 in kinds and 7 not in kinds, kinds
 
 
 def test_native_calls_of_another_header_are_not_used(monkeypatch):
